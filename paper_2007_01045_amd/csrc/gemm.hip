@@ -115,7 +115,11 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
-template <int R, bool KS, int NW, int BK>
+// KT: the last k-tile of a K segment may be short (a multiple of 8).  A k-strided operand needs nothing for that:
+// its rows beyond the segment lie beyond the buffer's record count and read as zero.  A k-contiguous one would
+// read on into its next row; there the lanes whose 16-byte chunk lies beyond the segment are given an offset
+// outside the buffer for that one tile (a select per load and k-tile, in the shadow of the MFMAs).
+template <int R, bool KS, int NW, int BK, bool KT = false>
 struct OperandTile {
   static_assert(BK == 64 || BK == 32, "k-tiles of 64 or 32");
   static constexpr int CH = BK / 8;                   // 16-byte chunks per row of a k-contiguous tile
@@ -124,6 +128,9 @@ struct OperandTile {
   static constexpr int LDS_BYTES = LDS_ELEMS * 2;
   static_assert(R * CH % (64 * NW) == 0, "tile rows must split evenly over the waves");
   int voff[NI];  // per-lane byte offset of each load inside the k-tile's slab
+  static constexpr bool MASKED = KT && !KS;
+  int vfull[MASKED ? NI : 1];  // the offsets of a whole k-tile, and which of them a short one leaves out
+  unsigned over;
 
   // chunk swizzle of row `row` of a k-contiguous tile
   static __device__ __forceinline__ int rswz(int row) { return BK == 64 ? (row >> 1) & 7 : (row >> 2) & 3; }
@@ -140,18 +147,28 @@ struct OperandTile {
   static constexpr int BIAS = 3072;
   static constexpr int GROUP = NI < 4 ? NI : 4;
   static_assert(NI % GROUP == 0 && (GROUP == 2 || GROUP == 4), "a wave loads 2, 4 or 8 chunks per operand");
-  __device__ __forceinline__ void init(int ld, int r0, int wave, int lane) {
+  __device__ __forceinline__ void init(int ld, int r0, int wave, int lane, int last_chunks) {
+    over = 0;
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
       int pos = (wave * NI + j) * 64 + lane;
       if (!KS) {
         int row = pos / CH, kc = (pos % CH) ^ rswz(row);
         voff[j] = ((r0 + row) * ld + kc * 8) * 2;
+        if (MASKED && kc >= last_chunks) over |= 1u << j;
       } else {
         int krow = pos / (R / 8), c = (pos % (R / 8)) ^ kswz(krow);
         voff[j] = (krow * ld + r0 + c * 8) * 2;
       }
       voff[j] += BIAS - (j % GROUP) * 1024;
+      if (MASKED) vfull[j] = voff[j];
+    }
+  }
+  // the next k-tile to be requested is (or is not) the short one at the end of a segment
+  __device__ __forceinline__ void set_short(bool is_short) {
+    if constexpr (MASKED) {
+#pragma unroll
+      for (int j = 0; j < NI; ++j) voff[j] = is_short && ((over >> j) & 1) ? (int)0x80000000 : vfull[j];
     }
   }
   // Request one k-step's slab.  rs: buffer resource whose base is the slab's first element minus
@@ -252,12 +269,12 @@ __device__ __forceinline__ float sum8(float v) {
   return v;
 }
 
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK>
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool KT = false>
 struct GemmTile {
   static constexpr int NW = WGM * WGN, NT = 64 * NW;
   static constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
-  typedef OperandTile<BM, AKS, NW, BK> TA;
-  typedef OperandTile<BN, BKS, NW, BK> TB;
+  typedef OperandTile<BM, AKS, NW, BK, KT> TA;
+  typedef OperandTile<BN, BKS, NW, BK, KT> TB;
   static constexpr int STAGE_ELEMS = TA::LDS_ELEMS + TB::LDS_ELEMS;
   static constexpr int EPI_LD = WN + 4;  // fp32 staging row
   static constexpr size_t MAIN_BYTES = NS * (size_t)STAGE_ELEMS * sizeof(bf16);
@@ -266,10 +283,11 @@ struct GemmTile {
   static constexpr size_t LDS_BYTES = MAIN_BYTES > EPI_BYTES ? MAIN_BYTES : EPI_BYTES;
 };
 
-// CS: the variant that can also sum B over k (EPI_BSUM)
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS>
+// CS: the variant that can also sum B over k (EPI_BSUM); KT: the variant for K segments that are no multiple of 64
+// when an operand is k-contiguous (see OperandTile)
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-  typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK> CFG;
+  typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT> CFG;
   typedef typename CFG::TA TA;
   typedef typename CFG::TB TB;
   constexpr int MI = CFG::MI, NI = CFG::NI;
@@ -316,18 +334,22 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, i
   const bf16* Ab = g.Az[0] ? (const bf16*)pick(g.Az) : (const bf16*)g.A + z * g.sA;
   const bf16* Bb = g.Bz[0] ? (const bf16*)pick(g.Bz) : (const bf16*)g.B + z * g.sB;
   void* const Cb = g.Cz[0] ? pick(g.Cz) : g.C;
-  const int nk = g.K / BK;
-  const int tiles_per_seg = g.kseg_len / BK;
+  const int tiles_per_seg = (g.kseg_len + BK - 1) / BK;
+  const int nk = g.K / g.kseg_len * tiles_per_seg;
+  const int k_rows = g.K > g.kseg_len ? g.kseg_len : g.k_valid;   // rows of one segment of a k-strided operand
   // bytes of one segment of each operand that may be read (beyond: zero)
   const long a_ext =
-      AKS ? ((long)(g.k_valid - 1) * g.lda + g.m_valid) * 2 : ((long)(g.m_valid - 1) * g.lda + g.kseg_len) * 2;
+      AKS ? ((long)(k_rows - 1) * g.lda + g.m_valid) * 2 : ((long)(g.m_valid - 1) * g.lda + g.kseg_len) * 2;
   const long b_ext =
-      BKS ? ((long)(g.k_valid - 1) * g.ldb + g.n_valid) * 2 : ((long)(g.n_valid - 1) * g.ldb + g.kseg_len) * 2;
+      BKS ? ((long)(k_rows - 1) * g.ldb + g.n_valid) * 2 : ((long)(g.n_valid - 1) * g.ldb + g.kseg_len) * 2;
 
   TA ta;
   TB tb;
-  ta.init(g.lda, m0, wave, lane);
-  tb.init(g.ldb, n0, wave, lane);
+  const int last_chunks = (g.kseg_len - (tiles_per_seg - 1) * BK) / 8;   // 16-byte chunks of a segment's last k-tile
+  ta.init(g.lda, m0, wave, lane, last_chunks);
+  tb.init(g.ldb, n0, wave, lane, last_chunks);
+  ta.set_short(tiles_per_seg == 1);
+  tb.set_short(tiles_per_seg == 1);
   FragAddr<BM, AKS, MI, BK> fa;
   FragAddr<BN, BKS, NI, BK> fb;
   fa.init(wm0, lane);
@@ -371,6 +393,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, i
     ars[2] = more ? (cross ? a_rec0 : max(ars[2] - a_step, (int)TA::BIAS)) : (int)TA::BIAS;
     brs[2] = more ? (cross ? b_rec0 : max(brs[2] - b_step, (int)TB::BIAS)) : (int)TB::BIAS;
     seg_left = cross ? tiles_per_seg : seg_left;
+    ta.set_short(seg_left == 1);
+    tb.set_short(seg_left == 1);
   };
   // request the next k-tile into ring slot S
   auto issue_loads = [&](auto S) {
@@ -728,13 +752,20 @@ template __global__ void gemm_mfma_kernel<128, 128, 2, 2, 2, true, true, 64, tru
 template __global__ void gemm_mfma_kernel<128, 64, 2, 2, 3, true, true, 64, true>(GemmArgs, int, int);
 template __global__ void gemm_mfma_kernel<128, 128, 2, 2, 4, true, true, 32, true>(GemmArgs, int, int);
 template __global__ void gemm_mfma_kernel<128, 128, 2, 2, 4, true, true, 32, false>(GemmArgs, int, int);
+#define DAPPLE_GEMM_INST_KT(BM, BN, WGM, WGN, NS, BK)                                                                  \
+  template __global__ void gemm_mfma_kernel<BM, BN, WGM, WGN, NS, false, false, BK, false, true>(GemmArgs, int, int); \
+  template __global__ void gemm_mfma_kernel<BM, BN, WGM, WGN, NS, false, true, BK, false, true>(GemmArgs, int, int);  \
+  template __global__ void gemm_mfma_kernel<BM, BN, WGM, WGN, NS, true, false, BK, false, true>(GemmArgs, int, int);
+DAPPLE_GEMM_INST_KT(128, 128, 2, 2, 2, 64)
+DAPPLE_GEMM_INST_KT(128, 64, 2, 2, 3, 64)
+#undef DAPPLE_GEMM_INST_KT
 #undef DAPPLE_GEMM_INST
 
 // ------------------------------------------------------------------ host side
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS = false>
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS = false, bool KT = false>
 static hipError_t launch_mfma(const GemmArgs& g, hipStream_t st) {
-  typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK> CFG;
-  auto kern = gemm_mfma_kernel<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS>;
+  typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT> CFG;
+  auto kern = gemm_mfma_kernel<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT>;
   // once per instantiation, whichever host thread comes first (initialisation of a function-local static is
   // thread-safe)
   static const hipError_t attr_rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -756,12 +787,26 @@ static hipError_t launch_mfma_layout(const GemmArgs& g, hipStream_t st) {
                       : launch_mfma<BM, BN, WGM, WGN, NS, false, false, BK>(g, st);
 }
 
+// K segments that are no multiple of 64; with both operands k-strided the ordinary kernels serve (see OperandTile)
+template <int BM, int BN, int WGM, int WGN, int NS, int BK = 64>
+static hipError_t launch_mfma_short_k(const GemmArgs& g, hipStream_t st) {
+  if (g.a_kstrided) {
+    return g.b_kstrided ? launch_mfma<BM, BN, WGM, WGN, NS, true, true, BK>(g, st)
+                        : launch_mfma<BM, BN, WGM, WGN, NS, true, false, BK, false, true>(g, st);
+  }
+  return g.b_kstrided ? launch_mfma<BM, BN, WGM, WGN, NS, false, true, BK, false, true>(g, st)
+                      : launch_mfma<BM, BN, WGM, WGN, NS, false, false, BK, false, true>(g, st);
+}
+
 static bool aligned_to(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
   if (dt != DT_BF16) return false;
-  constexpr int BK = 64;  // every tile configuration takes K and the K segments in multiples of 64
-  if (g.K < BK || g.K % BK || g.kseg_len % BK || g.K % g.kseg_len) return false;
+  constexpr int BK = 64;  // the widest k-tile
+  if (g.K < 1 || g.kseg_len < 1 || g.K % g.kseg_len) return false;
+  // a k-contiguous operand is read in chunks of 8 elements, so a segment's end must fall between two chunks; with
+  // both operands k-strided K may be anything
+  if (g.kseg_len % 8 && !(g.a_kstrided && g.b_kstrided)) return false;
   if (g.lda % 8 || g.ldb % 8 || g.ldc % 4 || g.N % 4) return false;
   if (g.sA % 8 || g.sB % 8 || g.sC % 4 || g.sBias % 4 || g.segA % 8 || g.segB % 8) return false;
   if (!aligned_to(g.A, 16) || !aligned_to(g.B, 16) || !aligned_to(g.C, 16)) return false;
@@ -780,7 +825,7 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
     if ((long)BK * g.lda * 2 > 0x7fffffffL || (long)BK * g.ldb * 2 > 0x7fffffffL) return false;
   }
   if ((g.epi & (EPI_ADD | EPI_MUL | EPI_ROWDOT)) && (g.ldaux % 4 || !aligned_to(g.aux, 16))) return false;
-  if ((g.epi & EPI_ROWDOT) && ((g.epi & (EPI_ADD | EPI_MUL | EPI_GELU | EPI_ACC32 | EPI_OUT32)) || g.batch != 1 ||
+  if ((g.epi & EPI_ROWDOT) && (g.kseg_len % BK || (g.epi & (EPI_ADD | EPI_MUL | EPI_GELU | EPI_ACC32 | EPI_OUT32)) || g.batch != 1 ||
                                !g.rowdot || !g.aux || !aligned_to(g.rowdot, 4)))
     return false;
   if ((g.epi & EPI_BIAS) && !aligned_to(g.bias, 8)) return false;
@@ -798,6 +843,7 @@ hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st) {
     const long t256 = (long)((g.M + 255) / 256) * ((g.N + 255) / 256) * g.batch;
     const bool tt = g.a_kstrided && g.b_kstrided;   // the weight-gradient layout
     const bool bsum = (g.epi & EPI_BSUM) != 0;      // (offered for that layout only: checked above)
+    const bool short_k = g.kseg_len % 64 != 0 && !tt;
     // Tile choice.  Every k-tile goes global -> LDS through the compute unit's vector cache at 64 bytes per
     // clock, and from LDS to the waves at 128 bytes per clock, against 4096 MFMA flops per clock.  A 128x128
     // tile (64x64 per wave) needs the vector cache's whole rate and 1.5 times what LDS can do (fragment reads
@@ -824,6 +870,13 @@ hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st) {
     int tile = g.tile;
     if (tile == 5 && !tt) tile = 3;
     if (bsum && (tile == 1 || tile == 2 || tile == 6)) tile = 0;
+    // K segments that are no multiple of 64 with a k-contiguous operand: the masked variants of 3 and 4.  (Such
+    // products, and the weight gradients of a micro-batch whose token count is no multiple of 64, used to take the
+    // plain kernel: a stage of 768 x 3072 with 3 x 200 tokens spent 380 ms per iteration of 6 micro-batches mostly
+    // there and in the plain attention kernels; 3.7 ms with the MFMA kernels.)
+    if (short_k)
+      return (tile == 4 || (tile != 3 && t128 < 192)) ? launch_mfma_short_k<128, 64, 2, 2, 3>(g, st)
+                                                      : launch_mfma_short_k<128, 128, 2, 2, 2>(g, st);
     if (tile == 0) {
       if (tt && t128 >= 192) tile = 5;
       else if (!tt && t128 >= 384 && t256 < 512 && !(g.epi & (EPI_ADD | EPI_MUL))) tile = 6;
