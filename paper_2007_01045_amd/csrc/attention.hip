@@ -6,7 +6,7 @@
 //              delta = rowsum(dctx o ctx),
 //              dv = P^T dctx,  dq = dS k / sqrt(d),  dk = dS^T q / sqrt(d)
 //
-// MFMA kernels (bf16, d = 64, s % 64 == 0): a workgroup of 4 waves; each wave owns
+// MFMA kernels (bf16, d % 8 == 0, d <= 128, any s): a workgroup of 4 waves; each wave owns
 // 32 query rows (forward, dq) or 32 key rows (dk/dv) whose fragments stay in
 // registers, and streams 64-row blocks of the other side through LDS.  The
 // products are oriented so that the accumulator's lane index is the row the wave
@@ -20,6 +20,8 @@
 // workgroup share a compute unit: each is a chain MFMA -> softmax arithmetic ->
 // MFMA with one wave per SIMD, and two of them on a SIMD fill each other's waits
 // (b=4, s=512, A=16: 39 us as two launches one after the other, 29 us as one).
+// Head widths other than 64 and ragged lengths were on the plain kernels before (2 layers of 1024 with heads of 128,
+// 2 x 256 tokens, 4 micro-batches: 242 ms per iteration, 1.8 ms now).
 // delta = rowsum(dctx o ctx) must exist before either starts: the stage takes it
 // from the epilogue of the product that makes dctx (delta_blocks), a caller
 // without that product gets it from a small kernel of its own first.
@@ -118,82 +120,119 @@ __global__ void attn_bwd_plain(AttnArgs a, float scale2, float scale, int which)
 }
 
 // ------------------------------------------------------------------ MFMA kernels
-constexpr int AD = 64;  // head dimension
+// D: width of a head's block in LDS and registers (32, 64 or 128; a head of d <= D columns is padded with zeros).
+// RAG: some edge is ragged -- s is no multiple of 64 or d is smaller than D: rows and columns outside are read as
+//      zeros, their probabilities are zero, and nothing outside is stored.
+// HL:  the probabilities and dS enter their products as a sum of two bf16 values (high and low half), so that they
+//      count with 16 significant bits; otherwise they are rounded to bf16 once.  (D = 64 with s % 64 == 0 rounds
+//      once; every other shape was served by fp32 arithmetic before it had MFMA kernels and keeps that accuracy.
+//      The extra MFMAs ride in the shadow of the exponentials: the matrix pipe is busy 13% of these kernels.)
 
-// A 64 x 64 bf16 block sits in LDS as 64 rows of 128 bytes with the 16-byte chunks of row
-// r XOR-swizzled by aswz(r).  The same block is read two ways -- 128-bit reads along a
-// row (16 lanes = 16 rows at a time) and transpose reads down the rows (32 lanes = 4 rows
-// x 64 bytes at a time) -- and LDS has 64 four-byte banks, so either group must cover 256
-// distinct bytes modulo 256: rows of equal parity need distinct chunks (a bijection of
-// (r>>1)&7), and rows r and r+2 must land in different 64-byte halves (bit 2 of the
-// swizzle = bit 1 of r).  Rotating the three bits of (r>>1)&7 right by one gives both.
+// A 64 x D bf16 block sits in LDS as 64 rows of D/8 16-byte chunks, the chunks of row r XOR-swizzled by aswz(r).
+// The same block is read two ways -- 128-bit reads along a row (16 lanes = 16 rows at a time) and transpose reads
+// down the rows (32 lanes = 4 rows x 64 bytes at a time) -- and LDS has 64 four-byte banks, so either group must
+// cover 256 distinct bytes modulo 256.
+//   D = 64:  rows of equal parity need distinct chunks (a bijection of (r>>1)&7), and rows r and r+2 must land in
+//            different 64-byte halves (bit 2 of the swizzle = bit 1 of r): (r>>1)&7 rotated right by one gives both.
+//   D = 128: 16 rows need 16 distinct chunks and 4 neighbouring rows four distinct 64-byte quarters: the two halves
+//            of r & 15 swapped.
+//   D = 32:  four rows fill 256 bytes; rows r, r+4, r+8, r+12 need distinct chunks: (r>>2)&3.
+template <int D>
 __device__ __forceinline__ int aswz(int r) {
-  int x = (r >> 1) & 7;
-  return ((x & 1) << 2) | (x >> 1);
+  if (D == 64) {
+    int x = (r >> 1) & 7;
+    return ((x & 1) << 2) | (x >> 1);
+  }
+  if (D == 128) return ((r & 3) << 2) | ((r >> 2) & 3);
+  return (r >> 2) & 3;
 }
 
-// a 64 x 64 block in flight from global memory: 2 chunks of 16 bytes per thread (256 threads)
+// a 64 x D block in flight from global memory: D/32 chunks of 16 bytes per thread (256 threads)
 typedef int i32x4 __attribute__((ext_vector_type(4)));
-struct Block64 {
-  // native vectors in named members: with the runtime's uint4 (a struct around a union) the
-  // compiler kept the block in scratch memory and waited for the loads at once
-  i32x4 c0, c1;
-  __device__ __forceinline__ void load(const bf16* g, int ldg, int tid) {
-    c0 = *(const i32x4*)(g + (long)(tid >> 3) * ldg + (tid & 7) * 8);
-    c1 = *(const i32x4*)(g + (long)((tid + 256) >> 3) * ldg + (tid & 7) * 8);
+template <int D, bool RAG>
+struct BlockD {
+  static constexpr int N = D / 32, CPR = D / 8;
+  // native vectors: with the runtime's uint4 (a struct around a union) the compiler kept the block in scratch
+  // memory and waited for the loads at once
+  i32x4 c[N];
+  // rows: how many of the 64 rows exist; d: columns that exist
+  __device__ __forceinline__ void load(const bf16* g, int ldg, int tid, int rows, int d) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int r = (tid + 256 * i) / CPR, kc = tid % CPR;
+      if (RAG) {
+        c[i] = i32x4{0, 0, 0, 0};
+        if (r < rows && kc * 8 < d) c[i] = *(const i32x4*)(g + (long)r * ldg + kc * 8);
+      } else {
+        c[i] = *(const i32x4*)(g + (long)r * ldg + kc * 8);
+      }
+    }
   }
   __device__ __forceinline__ void store(bf16* S, int tid) const {
-    int r = tid >> 3, kc = tid & 7;
-    *(i32x4*)(S + r * AD + ((kc ^ aswz(r)) << 3)) = c0;
-    r += 32;
-    *(i32x4*)(S + r * AD + ((kc ^ aswz(r)) << 3)) = c1;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int r = (tid + 256 * i) / CPR, kc = tid % CPR;
+      *(i32x4*)(S + r * D + ((kc ^ aswz<D>(r)) << 3)) = c[i];
+    }
   }
 };
 // operand fragment, contraction index contiguous in LDS: rows r0 + (lane&31), k = 16 kk + 8 (lane>>5) + e
+template <int D>
 __device__ __forceinline__ bf16x8 frag_rows(const bf16* S, int r0, int kk, int lane) {
   int r = r0 + (lane & 31), kc = kk * 2 + (lane >> 5);
-  return *(const bf16x8*)(S + r * AD + ((kc ^ aswz(r)) << 3));
+  return *(const bf16x8*)(S + r * D + ((kc ^ aswz<D>(r)) << 3));
 }
 // operand fragment, contraction index along LDS rows: column c0 + (lane&31); element e < 4 is
 // LDS row k0 + 4 (lane>>5) + e, element 4 + e is LDS row k0 + 8 + 4 (lane>>5) + e -- the order
 // in which a 32x32 accumulator hands its rows to a lane
+template <int D>
 __device__ __forceinline__ bf16x8 frag_cols(const bf16* S, int c0, int k0, int lane) {
   int i16 = lane & 15, g16 = (lane >> 4) & 1, h = lane >> 5;
   int r = k0 + 4 * h + (i16 >> 2);
   int col = c0 + 16 * g16 + 4 * (i16 & 3);
-  const bf16* p0 = S + r * AD + (((col >> 3) ^ aswz(r)) << 3) + (col & 7);
-  const bf16* p1 = S + (r + 8) * AD + (((col >> 3) ^ aswz(r + 8)) << 3) + (col & 7);
+  const bf16* p0 = S + r * D + (((col >> 3) ^ aswz<D>(r)) << 3) + (col & 7);
+  const bf16* p1 = S + (r + 8) * D + (((col >> 3) ^ aswz<D>(r + 8)) << 3) + (col & 7);
   return join8(lds_read_tr16(p0), lds_read_tr16(p1));
 }
 // global fragment of a row the wave owns: row r (or zeros), k = 16 kk + 8 (lane>>5) + e
-__device__ __forceinline__ bf16x8 frag_global(const bf16* base, long row, bool ok, int ld, int kk, int lane) {
-  if (!ok) {
+template <bool RAG>
+__device__ __forceinline__ bf16x8 frag_global(const bf16* base, long row, bool ok, int ld, int kk, int lane, int d) {
+  const int k = kk * 16 + 8 * (lane >> 5);
+  if (!ok || (RAG && k >= d)) {
     bf16x8 z;
 #pragma unroll
     for (int e = 0; e < 8; ++e) z[e] = (bf16)0.f;
     return z;
   }
-  return *(const bf16x8*)(base + row * ld + kk * 16 + 8 * (lane >> 5));
+  return *(const bf16x8*)(base + row * ld + k);
 }
 // accumulator rows 16 ks .. 16 ks + 15 of a 32-row block, as the k-permuted operand
 __device__ __forceinline__ bf16x8 acc_to_operand(const float (&p)[16], int ks) {
   bf16x8 f;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    f[e] = (bf16)p[8 * ks + e];
-    f[4 + e] = (bf16)p[8 * ks + 4 + e];
-  }
+  for (int e = 0; e < 8; ++e) f[e] = (bf16)p[8 * ks + e];
+  return f;
+}
+// what rounding to bf16 left of them
+__device__ __forceinline__ bf16x8 acc_to_operand_low(const float (&p)[16], bf16x8 hi, int ks) {
+  bf16x8 f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) f[e] = (bf16)(p[8 * ks + e] - (float)hi[e]);
   return f;
 }
 
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0)
 
-// delta of query row qi of sequence bi, head hh: from [b, A, s], or the head's two blocks of 32 columns
+// delta of query row qi of sequence bi, head hh: from [b, A, s], or the head's d/32 blocks of 32 columns
 // out of [H/32][b*s]
+template <int D>
 __device__ __forceinline__ float delta_at(const AttnArgs& a, int bi, int hh, int qi) {
-  if (a.delta_blocks) {
+  if (a.delta_blocks) {   // only where d == D
     const long T = (long)a.b * a.s, row = (long)bi * a.s + qi;
-    return a.delta_blocks[(2 * hh) * T + row] + a.delta_blocks[(2 * hh + 1) * T + row];
+    float t = a.delta_blocks[(D / 32 * hh) * T + row];
+#pragma unroll
+    for (int j = 1; j < D / 32; ++j) t += a.delta_blocks[(D / 32 * hh + j) * T + row];
+    return t;
   }
   return a.delta[((long)bi * a.A + hh) * a.s + qi];
 }
@@ -212,26 +251,31 @@ __device__ __forceinline__ f32x16 zero16() {
 // (Forward with the key blocks split over two waves per SIMD, merged at the end: 12.9 instead of 14.7 us alone, but
 // the iteration gets 0.7% slower: the workgroup then fills both wave slots of its SIMDs and keeps the other streams'
 // kernels off the compute unit.  One wave per SIMD it stays.)
+template <int D, bool RAG, bool HL>
 __global__ __launch_bounds__(256) void attn_fwd_mfma(AttnArgs a, float scale2) {
-  __shared__ __attribute__((aligned(16))) bf16 Ks[64 * AD];
-  __shared__ __attribute__((aligned(16))) bf16 Vs[64 * AD];
+  constexpr int NKK = D / 16, NDB = D / 32;
+  __shared__ __attribute__((aligned(16))) bf16 Ks[64 * D];
+  __shared__ __attribute__((aligned(16))) bf16 Vs[64 * D];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
   const int bi = blockIdx.y / a.A, hh = blockIdx.y % a.A;
-  const long hb = (long)bi * a.s * a.H + hh * AD;
+  const int d = RAG ? a.d : D;
+  const long hb = (long)bi * a.s * a.H + hh * d;
   const bf16 *Q = (const bf16*)a.q + hb, *K = (const bf16*)a.k + hb, *V = (const bf16*)a.v + hb;
   const int qrow = blockIdx.x * 128 + wave * 32 + (lane & 31);
   const bool qok = qrow < a.s;
-  const int nkb = a.s / 64;
-  Block64 kblk, vblk;  // the next key/value block, in flight while the current one is used
-  kblk.load(K, a.H, tid);
-  vblk.load(V, a.H, tid);
+  const int nkb = RAG ? (a.s + 63) / 64 : a.s / 64;
+  BlockD<D, RAG> kblk, vblk;  // the next key/value block, in flight while the current one is used
+  kblk.load(K, a.H, tid, a.s, d);
+  vblk.load(V, a.H, tid, a.s, d);
 
-  bf16x8 qf[4];
+  bf16x8 qf[NKK];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) qf[kk] = frag_global(Q, qrow, qok, a.H, kk, lane);
+  for (int kk = 0; kk < NKK; ++kk) qf[kk] = frag_global<RAG>(Q, qrow, qok, a.H, kk, lane, d);
 
   float m = -INFINITY, l = 0.f;
-  f32x16 o[2] = {zero16(), zero16()};  // rows d = 32 dblk + 8 blk + 4 h + e, column = the lane's query
+  f32x16 o[NDB];  // rows d = 32 dblk + 8 blk + 4 h + e, column = the lane's query
+#pragma unroll
+  for (int db = 0; db < NDB; ++db) o[db] = zero16();
 
   for (int kb = 0; kb < nkb; ++kb) {
     __syncthreads();
@@ -241,36 +285,47 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(AttnArgs a, float scale2) {
     {  // unconditional: the last iteration fetches its own block again (harmless, and it keeps
        // the in-flight block in registers instead of scratch)
       const int nb = kb + 1 < nkb ? kb + 1 : kb;
-      kblk.load(K + (long)nb * 64 * a.H, a.H, tid);
-      vblk.load(V + (long)nb * 64 * a.H, a.H, tid);
+      kblk.load(K + (long)nb * 64 * a.H, a.H, tid, a.s - nb * 64, d);
+      vblk.load(V + (long)nb * 64 * a.H, a.H, tid, a.s - nb * 64, d);
     }
     float p[2][16];
     float mx = -INFINITY;
     // All LDS reads of a phase are issued before its first MFMA (left to itself the compiler
-    // reuses one register set and waits for every read in turn): the 8 key fragments, then the
-    // 8 value fragments, which land while the softmax arithmetic runs.
-    bf16x8 kf[2][4], vf[4][2];
+    // reuses one register set and waits for every read in turn): the key fragments, then the
+    // value fragments, which land while the softmax arithmetic runs.  (D = 128: by halves, for registers.)
+    bf16x8 kf[2][NKK], vf[4][NDB];
+    constexpr bool ALL = D <= 64;
+    if (ALL) {
 #pragma unroll
-    for (int kb2 = 0; kb2 < 2; ++kb2)
+      for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) kf[kb2][kk] = frag_rows(Ks, kb2 * 32, kk, lane);
-    __builtin_amdgcn_sched_barrier(0);
+        for (int kk = 0; kk < NKK; ++kk) kf[kb2][kk] = frag_rows<D>(Ks, kb2 * 32, kk, lane);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int kb2 = 0; kb2 < 2; ++kb2) {
+      if (!ALL) {
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk) kf[kb2][kk] = frag_rows<D>(Ks, kb2 * 32, kk, lane);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       f32x16 sa = zero16();  // rows: key 32 kb2 + 8 blk + 4 h + e, column: query
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) sa = MFMA(kf[kb2][kk], qf[kk], sa);
+      for (int kk = 0; kk < NKK; ++kk) sa = MFMA(kf[kb2][kk], qf[kk], sa);
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         p[kb2][v] = sa[v] * scale2;
+        if (RAG && kb * 64 + kb2 * 32 + 8 * (v >> 2) + 4 * h + (v & 3) >= a.s) p[kb2][v] = -INFINITY;
         mx = fmaxf(mx, p[kb2][v]);
       }
     }
+    if (ALL) {
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
+      for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-      for (int db = 0; db < 2; ++db) vf[ks][db] = frag_cols(Vs, db * 32, ks * 16, lane);
-    __builtin_amdgcn_sched_barrier(0);
+        for (int db = 0; db < NDB; ++db) vf[ks][db] = frag_cols<D>(Vs, db * 32, ks * 16, lane);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     float mn = fmaxf(m, mx);
     float alpha = exp2_neg(m - mn);
@@ -286,66 +341,85 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(AttnArgs a, float scale2) {
     l = l * alpha + rs;
     m = mn;
     // the running maximum of most rows settles after the first key blocks: skip the rescale of
-    // the 32 accumulator registers when no lane of the wave needs it (alpha == 1 exactly)
+    // the accumulator registers when no lane of the wave needs it (alpha == 1 exactly)
     if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {
 #pragma unroll
-      for (int db = 0; db < 2; ++db)
+      for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
     }
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       bf16x8 pf = acc_to_operand(p[ks >> 1], ks & 1);
+      if (!ALL) {
 #pragma unroll
-      for (int db = 0; db < 2; ++db) o[db] = MFMA(vf[ks][db], pf, o[db]);
+        for (int db = 0; db < NDB; ++db) vf[ks][db] = frag_cols<D>(Vs, db * 32, ks * 16, lane);
+      }
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) o[db] = MFMA(vf[ks][db], pf, o[db]);
+      if (HL) {
+        const bf16x8 pl = acc_to_operand_low(p[ks >> 1], pf, ks & 1);
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) o[db] = MFMA(vf[ks][db], pl, o[db]);
+      }
     }
   }
   if (qok) {
     float inv = 1.0f / l;
     bf16* C = (bf16*)a.ctx + hb + (long)qrow * a.H;
 #pragma unroll
-    for (int db = 0; db < 2; ++db)
+    for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk) {
+        const int col = db * 32 + 8 * blk + 4 * h;
+        if (RAG && col >= d) continue;
         bf16x4 ov;
 #pragma unroll
         for (int e = 0; e < 4; ++e) ov[e] = (bf16)(o[db][4 * blk + e] * inv);
-        *(bf16x4*)(C + db * 32 + 8 * blk + 4 * h) = ov;
+        *(bf16x4*)(C + col) = ov;
         if (a.ctx32)
-          *(float4*)(a.ctx32 + hb + (long)qrow * a.H + db * 32 + 8 * blk + 4 * h) =
+          *(float4*)(a.ctx32 + hb + (long)qrow * a.H + col) =
               make_float4(o[db][4 * blk] * inv, o[db][4 * blk + 1] * inv, o[db][4 * blk + 2] * inv, o[db][4 * blk + 3] * inv);
       }
     if (h == 0) a.lse[((long)bi * a.A + hh) * a.s + qrow] = m + log2f(l);
   }
 }
 
-// dk, dv: the wave owns 32 key rows; query blocks of 64 stream through LDS
-__device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, float scale) {
-  __shared__ __attribute__((aligned(16))) bf16 Qs[64 * AD];
-  __shared__ __attribute__((aligned(16))) bf16 Gs[64 * AD];
-  __shared__ __attribute__((aligned(16))) float Ls[64];
-  __shared__ __attribute__((aligned(16))) float Ds[64];
+// dk, dv: the wave owns 32 key rows; query blocks of 64 stream through LDS (Qs, Gs; Ls, Ds: their lse and delta)
+template <int D, bool RAG, bool HL>
+__device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, float scale, bf16* Qs, bf16* Gs, float* Ls,
+                                               float* Ds) {
+  constexpr int NKK = D / 16, NDB = D / 32;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
   const int bi = blockIdx.y / a.A, hh = blockIdx.y % a.A;
-  const long hb = (long)bi * a.s * a.H + hh * AD;
+  const int d = RAG ? a.d : D;
+  const long hb = (long)bi * a.s * a.H + hh * d;
   const bf16 *Q = (const bf16*)a.q + hb, *K = (const bf16*)a.k + hb, *V = (const bf16*)a.v + hb,
              *G = (const bf16*)a.dctx + hb;
   const float* lse = a.lse + ((long)bi * a.A + hh) * a.s;
   const int krow = blockIdx.x * 128 + wave * 32 + (lane & 31);
   const bool kok = krow < a.s;
 
-  bf16x8 kf[4], vf[4];
+  bf16x8 kf[NKK], vf[NKK];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    kf[kk] = frag_global(K, krow, kok, a.H, kk, lane);
-    vf[kk] = frag_global(V, krow, kok, a.H, kk, lane);
+  for (int kk = 0; kk < NKK; ++kk) {
+    kf[kk] = frag_global<RAG>(K, krow, kok, a.H, kk, lane, d);
+    vf[kk] = frag_global<RAG>(V, krow, kok, a.H, kk, lane, d);
   }
-  f32x16 dv[2] = {zero16(), zero16()}, dk[2] = {zero16(), zero16()};  // rows d, column = the lane's key
-  const int nqb = a.s / 64;
-  Block64 qblk, gblk;  // the next query / dctx block, in flight while the current one is used
-  qblk.load(Q, a.H, tid);
-  gblk.load(G, a.H, tid);
-  float stat = tid < 64 ? lse[tid] : (tid < 128 ? delta_at(a, bi, hh, tid - 64) : 0.f);
+  f32x16 dv[NDB], dk[NDB];  // rows d, column = the lane's key
+#pragma unroll
+  for (int db = 0; db < NDB; ++db) dv[db] = dk[db] = zero16();
+  const int nqb = RAG ? (a.s + 63) / 64 : a.s / 64;
+  BlockD<D, RAG> qblk, gblk;  // the next query / dctx block, in flight while the current one is used
+  // a query beyond the last has zero rows, lse 0 and delta 0: probability 1 times a zero row, dS = 0
+  auto load_stat = [&](int qb) {
+    const int q = qb * 64 + (tid & 63);
+    if (tid >= 128 || (RAG && q >= a.s)) return 0.f;
+    return tid < 64 ? lse[q] : delta_at<D>(a, bi, hh, q);
+  };
+  qblk.load(Q, a.H, tid, a.s, d);
+  gblk.load(G, a.H, tid, a.s, d);
+  float stat = load_stat(0);
 
   for (int qb = 0; qb < nqb; ++qb) {
     __syncthreads();
@@ -356,19 +430,19 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
     __syncthreads();
     {  // unconditional (the last iteration fetches its own block again): keeps the block in registers
       const int nb = qb + 1 < nqb ? qb + 1 : qb;
-      qblk.load(Q + (long)nb * 64 * a.H, a.H, tid);
-      gblk.load(G + (long)nb * 64 * a.H, a.H, tid);
-      stat = tid < 64 ? lse[nb * 64 + tid] : (tid < 128 ? delta_at(a, bi, hh, nb * 64 + tid - 64) : 0.f);
+      qblk.load(Q + (long)nb * 64 * a.H, a.H, tid, a.s - nb * 64, d);
+      gblk.load(G + (long)nb * 64 * a.H, a.H, tid, a.s - nb * 64, d);
+      stat = load_stat(nb);
     }
 #pragma unroll
     for (int qb2 = 0; qb2 < 2; ++qb2) {
       // every LDS read of a phase before its first MFMA (see attn_fwd_mfma)
-      bf16x8 qf[4], gf[4], gc[2][2], qc[2][2];
+      bf16x8 qf[NKK], gf[NKK], gc[2][NDB], qc[2][NDB];
       float4 L4s[4], D4s[4];
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        qf[kk] = frag_rows(Qs, qb2 * 32, kk, lane);
-        gf[kk] = frag_rows(Gs, qb2 * 32, kk, lane);
+      for (int kk = 0; kk < NKK; ++kk) {
+        qf[kk] = frag_rows<D>(Qs, qb2 * 32, kk, lane);
+        gf[kk] = frag_rows<D>(Gs, qb2 * 32, kk, lane);
       }
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk) {
@@ -378,16 +452,16 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
       __builtin_amdgcn_sched_barrier(0);
       f32x16 sa = zero16(), dp = zero16();  // rows: query 32 qb2 + 8 blk + 4 h + e, column: key
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
+      for (int kk = 0; kk < NKK; ++kk) {
         sa = MFMA(qf[kk], kf[kk], sa);
         dp = MFMA(gf[kk], vf[kk], dp);
       }
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-        for (int db = 0; db < 2; ++db) {
-          gc[ks][db] = frag_cols(Gs, db * 32, qb2 * 32 + ks * 16, lane);
-          qc[ks][db] = frag_cols(Qs, db * 32, qb2 * 32 + ks * 16, lane);
+        for (int db = 0; db < NDB; ++db) {
+          gc[ks][db] = frag_cols<D>(Gs, db * 32, qb2 * 32 + ks * 16, lane);
+          qc[ks][db] = frag_cols<D>(Qs, db * 32, qb2 * 32 + ks * 16, lane);
         }
       __builtin_amdgcn_sched_barrier(0);
       float p[16], ds[16];
@@ -406,9 +480,17 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
       for (int ks = 0; ks < 2; ++ks) {
         bf16x8 pf = acc_to_operand(p, ks), dsf = acc_to_operand(ds, ks);
 #pragma unroll
-        for (int db = 0; db < 2; ++db) {
+        for (int db = 0; db < NDB; ++db) {
           dv[db] = MFMA(gc[ks][db], pf, dv[db]);
           dk[db] = MFMA(qc[ks][db], dsf, dk[db]);
+        }
+        if (HL) {
+          const bf16x8 pl = acc_to_operand_low(p, pf, ks), dsl = acc_to_operand_low(ds, dsf, ks);
+#pragma unroll
+          for (int db = 0; db < NDB; ++db) {
+            dv[db] = MFMA(gc[ks][db], pl, dv[db]);
+            dk[db] = MFMA(qc[ks][db], dsl, dk[db]);
+          }
         }
       }
     }
@@ -417,46 +499,51 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
     bf16* DK = (bf16*)a.dk + hb + (long)krow * a.H;
     bf16* DV = (bf16*)a.dv + hb + (long)krow * a.H;
 #pragma unroll
-    for (int db = 0; db < 2; ++db)
+    for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk) {
+        const int col = db * 32 + 8 * blk + 4 * h;
+        if (RAG && col >= d) continue;
         bf16x4 o1, o2;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           o1[e] = (bf16)(dk[db][4 * blk + e] * scale);
           o2[e] = (bf16)dv[db][4 * blk + e];
         }
-        *(bf16x4*)(DK + db * 32 + 8 * blk + 4 * h) = o1;
-        *(bf16x4*)(DV + db * 32 + 8 * blk + 4 * h) = o2;
+        *(bf16x4*)(DK + col) = o1;
+        *(bf16x4*)(DV + col) = o2;
       }
   }
 }
 
 // dq: the wave owns 32 query rows; key blocks of 64 stream through LDS
-__device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, float scale) {
-  __shared__ __attribute__((aligned(16))) bf16 Ks[64 * AD];
-  __shared__ __attribute__((aligned(16))) bf16 Vs[64 * AD];
+template <int D, bool RAG, bool HL>
+__device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, float scale, bf16* Ks, bf16* Vs) {
+  constexpr int NKK = D / 16, NDB = D / 32;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
   const int bi = blockIdx.y / a.A, hh = blockIdx.y % a.A;
-  const long hb = (long)bi * a.s * a.H + hh * AD;
+  const int d = RAG ? a.d : D;
+  const long hb = (long)bi * a.s * a.H + hh * d;
   const bf16 *Q = (const bf16*)a.q + hb, *K = (const bf16*)a.k + hb, *V = (const bf16*)a.v + hb,
              *G = (const bf16*)a.dctx + hb;
   const int qrow = blockIdx.x * 128 + wave * 32 + (lane & 31);
   const bool qok = qrow < a.s;
   const float Lq = qok ? a.lse[((long)bi * a.A + hh) * a.s + qrow] : 0.f;
 
-  const float Dq = qok ? delta_at(a, bi, hh, qrow) : 0.f;
-  bf16x8 qf[4], gf[4];
+  const float Dq = qok ? delta_at<D>(a, bi, hh, qrow) : 0.f;
+  bf16x8 qf[NKK], gf[NKK];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    qf[kk] = frag_global(Q, qrow, qok, a.H, kk, lane);
-    gf[kk] = frag_global(G, qrow, qok, a.H, kk, lane);
+  for (int kk = 0; kk < NKK; ++kk) {
+    qf[kk] = frag_global<RAG>(Q, qrow, qok, a.H, kk, lane, d);
+    gf[kk] = frag_global<RAG>(G, qrow, qok, a.H, kk, lane, d);
   }
-  f32x16 dq[2] = {zero16(), zero16()};  // rows d, column = the lane's query
-  const int nkb = a.s / 64;
-  Block64 kblk, vblk;
-  kblk.load(K, a.H, tid);
-  vblk.load(V, a.H, tid);
+  f32x16 dq[NDB];  // rows d, column = the lane's query
+#pragma unroll
+  for (int db = 0; db < NDB; ++db) dq[db] = zero16();
+  const int nkb = RAG ? (a.s + 63) / 64 : a.s / 64;
+  BlockD<D, RAG> kblk, vblk;
+  kblk.load(K, a.H, tid, a.s, d);
+  vblk.load(V, a.H, tid, a.s, d);
 
   for (int kb = 0; kb < nkb; ++kb) {
     __syncthreads();
@@ -466,57 +553,69 @@ __device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, fl
     {  // unconditional: the last iteration fetches its own block again (harmless, and it keeps
        // the in-flight block in registers instead of scratch)
       const int nb = kb + 1 < nkb ? kb + 1 : kb;
-      kblk.load(K + (long)nb * 64 * a.H, a.H, tid);
-      vblk.load(V + (long)nb * 64 * a.H, a.H, tid);
+      kblk.load(K + (long)nb * 64 * a.H, a.H, tid, a.s - nb * 64, d);
+      vblk.load(V + (long)nb * 64 * a.H, a.H, tid, a.s - nb * 64, d);
     }
 #pragma unroll
     for (int kb2 = 0; kb2 < 2; ++kb2) {
       // every LDS read of a phase before its first MFMA (see attn_fwd_mfma)
-      bf16x8 kr[4], vr[4], kc[2][2];
+      bf16x8 kr[NKK], vr[NKK], kc[2][NDB];
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        kr[kk] = frag_rows(Ks, kb2 * 32, kk, lane);
-        vr[kk] = frag_rows(Vs, kb2 * 32, kk, lane);
+      for (int kk = 0; kk < NKK; ++kk) {
+        kr[kk] = frag_rows<D>(Ks, kb2 * 32, kk, lane);
+        vr[kk] = frag_rows<D>(Vs, kb2 * 32, kk, lane);
       }
       __builtin_amdgcn_sched_barrier(0);
       f32x16 sa = zero16(), dp = zero16();  // rows: key 32 kb2 + 8 blk + 4 h + e, column: query
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
+      for (int kk = 0; kk < NKK; ++kk) {
         sa = MFMA(kr[kk], qf[kk], sa);
         dp = MFMA(vr[kk], gf[kk], dp);
       }
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-        for (int db = 0; db < 2; ++db) kc[ks][db] = frag_cols(Ks, db * 32, kb2 * 32 + ks * 16, lane);
+        for (int db = 0; db < NDB; ++db) kc[ks][db] = frag_cols<D>(Ks, db * 32, kb2 * 32 + ks * 16, lane);
       __builtin_amdgcn_sched_barrier(0);
       float ds[16];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) ds[v] = exp2_neg(sa[v] * scale2 - Lq) * (dp[v] - Dq);
+      for (int v = 0; v < 16; ++v) {
+        ds[v] = exp2_neg(sa[v] * scale2 - Lq) * (dp[v] - Dq);
+        // a key beyond the last: its logit 0 may lie far above the row's logsumexp, so it is masked, not multiplied away
+        if (RAG && kb * 64 + kb2 * 32 + 8 * (v >> 2) + 4 * h + (v & 3) >= a.s) ds[v] = 0.f;
+      }
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         bf16x8 dsf = acc_to_operand(ds, ks);
 #pragma unroll
-        for (int db = 0; db < 2; ++db) dq[db] = MFMA(kc[ks][db], dsf, dq[db]);
+        for (int db = 0; db < NDB; ++db) dq[db] = MFMA(kc[ks][db], dsf, dq[db]);
+        if (HL) {
+          const bf16x8 dsl = acc_to_operand_low(ds, dsf, ks);
+#pragma unroll
+          for (int db = 0; db < NDB; ++db) dq[db] = MFMA(kc[ks][db], dsl, dq[db]);
+        }
       }
     }
   }
   if (qok) {
     bf16* DQ = (bf16*)a.dq + hb + (long)qrow * a.H;
 #pragma unroll
-    for (int db = 0; db < 2; ++db)
+    for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk) {
+        const int col = db * 32 + 8 * blk + 4 * h;
+        if (RAG && col >= d) continue;
         bf16x4 ov;
 #pragma unroll
         for (int e = 0; e < 4; ++e) ov[e] = (bf16)(dq[db][4 * blk + e] * scale);
-        *(bf16x4*)(DQ + db * 32 + 8 * blk + 4 * h) = ov;
+        *(bf16x4*)(DQ + col) = ov;
       }
   }
 }
 
 // delta [b, A, s] for the MFMA backward of a caller that has no product in front to leave it: one wave per row
-// of dctx / ctx, a lane takes 8 consecutive columns, a head (64 columns) is 8 consecutive lanes
+// of dctx / ctx, a lane takes 8 consecutive columns, a head (d = 32, 64 or 128 columns) is d/8 consecutive lanes
+template <int D>
 __global__ __launch_bounds__(256) void attn_delta_rows(AttnArgs a) {
   const int lane = threadIdx.x & 63;
   const long row = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -538,32 +637,62 @@ __global__ __launch_bounds__(256) void attn_delta_rows(AttnArgs a) {
         for (int e = 0; e < 8; ++e) t = fmaf((float)g[e], (float)o[e], t);
       }
     }
-    t += __shfl_xor(t, 1, 64);
-    t += __shfl_xor(t, 2, 64);
-    t += __shfl_xor(t, 4, 64);
-    if (col < a.H && (lane & 7) == 0) a.delta[((long)bi * a.A + col / AD) * a.s + qi] = t;
+#pragma unroll
+    for (int x = 1; x < D / 8; x <<= 1) t += __shfl_xor(t, x, 64);
+    if (col < a.H && lane % (D / 8) == 0) a.delta[((long)bi * a.A + col / D) * a.s + qi] = t;
   }
 }
 
-// both roles in one launch: grid.z = 0 the dq workgroups, 1 the dk/dv workgroups
-__global__ __launch_bounds__(256, 2) void attn_bwd_mfma(AttnArgs a, float scale2, float scale) {
-  if (blockIdx.z == 0) attn_dq_body(a, scale2, scale);
-  else attn_dkdv_body(a, scale2, scale);
+// both roles in one launch: grid.z = 0 the dq workgroups, 1 the dk/dv workgroups.  At most 256 registers per lane up
+// to D = 64, so that a workgroup of each role shares a compute unit; D = 128 keeps twice the accumulators.
+template <int D, bool RAG, bool HL>
+__global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_mfma(AttnArgs a, float scale2, float scale) {
+  __shared__ __attribute__((aligned(16))) bf16 X[64 * D];
+  __shared__ __attribute__((aligned(16))) bf16 Y[64 * D];
+  __shared__ __attribute__((aligned(16))) float Ls[64];
+  __shared__ __attribute__((aligned(16))) float Ds[64];
+  if (blockIdx.z == 0) attn_dq_body<D, RAG, HL>(a, scale2, scale, X, Y);
+  else attn_dkdv_body<D, RAG, HL>(a, scale2, scale, X, Y, Ls, Ds);
 }
 
 // ------------------------------------------------------------------ launchers
 static bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
+// Every bf16 head of up to 128 columns in whole 16-byte chunks, at any sequence length
 bool attn_uses_mfma(Dtype dt, const AttnArgs& a) {
-  return dt == DT_BF16 && a.d == AD && a.s % 64 == 0 && a.H % 8 == 0 && al16(a.q) && al16(a.k) && al16(a.v) &&
+  return dt == DT_BF16 && a.d % 8 == 0 && a.d <= 128 && a.H % 8 == 0 && al16(a.q) && al16(a.k) && al16(a.v) &&
          al16(a.ctx) && (a.dctx == nullptr || (al16(a.dctx) && al16(a.dq) && al16(a.dk) && al16(a.dv)));
+}
+bool attn_takes_delta_blocks(Dtype dt, const AttnArgs& a) {
+  return attn_uses_mfma(dt, a) && (a.d == 32 || a.d == 64 || a.d == 128);
+}
+
+// f(D, RAG, HL) as constants for the shape: the narrowest block that holds a head
+template <typename F>
+static void pick_variant(const AttnArgs& a, F&& f) {
+  typedef std::true_type T;
+  typedef std::false_type N;
+  const bool rag = a.s % 64 != 0;
+  if (a.d <= 32) {
+    if (rag || a.d != 32) f(std::integral_constant<int, 32>{}, T{}, T{});
+    else f(std::integral_constant<int, 32>{}, N{}, T{});
+  } else if (a.d <= 64) {
+    if (rag || a.d != 64) f(std::integral_constant<int, 64>{}, T{}, T{});
+    else f(std::integral_constant<int, 64>{}, N{}, N{});
+  } else {
+    if (rag || a.d != 128) f(std::integral_constant<int, 128>{}, T{}, T{});
+    else f(std::integral_constant<int, 128>{}, N{}, T{});
+  }
 }
 
 hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
   float scale2 = LOG2E / sqrtf((float)a.d);
   if (attn_uses_mfma(dt, a)) {
     dim3 grid((a.s + 127) / 128, a.b * a.A);
-    hipLaunchKernelGGL(attn_fwd_mfma, grid, dim3(256), 0, st, a, scale2);
+    pick_variant(a, [&](auto D, auto RAG, auto HL) {
+      auto kern = attn_fwd_mfma<decltype(D)::value, decltype(RAG)::value, decltype(HL)::value>;
+      hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a, scale2);
+    });
     return hipGetLastError();
   }
   long total = (long)a.b * a.A * a.s * a.d;
@@ -575,20 +704,26 @@ hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
 
 hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
   float scale = 1.0f / sqrtf((float)a.d), scale2 = LOG2E * scale;
+  const long nd = (long)a.b * a.s * a.A;
+  const dim3 gd((unsigned)((nd + 255) / 256));
   hipError_t e;
   if (attn_uses_mfma(dt, a)) {
     if (!a.delta_blocks) {  // no product in front that left delta behind
-      const long rows = (long)a.b * a.s;
-      hipLaunchKernelGGL(attn_delta_rows, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, a);
+      const dim3 gr((unsigned)(((long)a.b * a.s + 3) / 4));
+      if (a.d == 32) hipLaunchKernelGGL(attn_delta_rows<32>, gr, dim3(256), 0, st, a);
+      else if (a.d == 64) hipLaunchKernelGGL(attn_delta_rows<64>, gr, dim3(256), 0, st, a);
+      else if (a.d == 128) hipLaunchKernelGGL(attn_delta_rows<128>, gr, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL(attn_delta_kernel<bf16>, gd, dim3(256), 0, st, a);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
     dim3 grid((a.s + 127) / 128, a.b * a.A, 2);
-    hipLaunchKernelGGL(attn_bwd_mfma, grid, dim3(256), 0, st, a, scale2, scale);
+    pick_variant(a, [&](auto D, auto RAG, auto HL) {
+      auto kern = attn_bwd_mfma<decltype(D)::value, decltype(RAG)::value, decltype(HL)::value>;
+      hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a, scale2, scale);
+    });
     return hipGetLastError();
   }
-  long nd = (long)a.b * a.s * a.A;
-  dim3 gd((unsigned)((nd + 255) / 256));
   if (dt == DT_BF16) hipLaunchKernelGGL(attn_delta_kernel<bf16>, gd, dim3(256), 0, st, a);
   else hipLaunchKernelGGL(attn_delta_kernel<float>, gd, dim3(256), 0, st, a);
   e = hipGetLastError();

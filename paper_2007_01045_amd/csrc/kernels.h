@@ -88,6 +88,8 @@ struct AttnArgs {
 hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st);
 hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& a, hipStream_t st);
 bool attn_uses_mfma(Dtype dt, const AttnArgs& a);
+// true when its backward can take delta_blocks (a head is a whole number of 32-column blocks)
+bool attn_takes_delta_blocks(Dtype dt, const AttnArgs& a);
 
 // ---------------------------------------------------------------- row kernels
 // y = LN(z) over the last dim (H), stats[2*r] = mean, stats[2*r+1] = rstd.  z_f32: z is fp32

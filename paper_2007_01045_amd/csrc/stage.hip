@@ -564,7 +564,7 @@ int dapple_stage::backward(char* sl, const void* dy, void* dx) {
        // 32 columns, the delta of the attention backward
       GemmArgs ga{};
       ga.A = dz1; ga.lda = H; ga.B = w(p.Wo); ga.ldb = H; ga.C = dctx; ga.ldc = H; ga.M = T; ga.N = H; ga.K = H;
-      if (aa.ctx32 && attn_uses_mfma(dt, aa)) {
+      if (aa.ctx32 && attn_takes_delta_blocks(dt, aa)) {
         GemmArgs probe = ga;
         probe.epi = EPI_ROWDOT | EPI_AUX32; probe.aux = aa.ctx32; probe.ldaux = H; probe.rowdot = delta;
         probe.batch = 1; probe.kseg_len = ga.K; probe.k_valid = ga.K; probe.m_valid = ga.M; probe.n_valid = ga.N;

@@ -171,6 +171,16 @@ def test_gemm_mfma_segments_and_batch():
     gemm_case(B.DTYPE_BF16, 136, 128, 64, False, True, B.EPI_BIAS, batch=3, expect_mfma=True)
 
 
+@pytest.mark.parametrize("tile", [0, 3, 4])
+@pytest.mark.parametrize("K", [8, 56, 72, 120, 200, 600])
+def test_gemm_mfma_k_not_a_multiple_of_the_k_tile(K, tile):
+    # shorter than one k-tile, one chunk short of / past a k-tile, several tiles; every layout; segments; column sums
+    for akS, bkS in ((False, False), (False, True), (True, False), (True, True)):
+        gemm_case(B.DTYPE_BF16, 136, 200, K, akS, bkS, B.EPI_BIAS, expect_mfma=True, tile=tile)
+        gemm_case(B.DTYPE_BF16, 136, 72, 3 * K, akS, bkS, B.EPI_ADD, nseg=3, expect_mfma=True, tile=tile)
+    gemm_case(B.DTYPE_BF16, 136, 200, K + 3, True, True, B.EPI_ACC32 | B.EPI_BSUM, expect_mfma=True, tile=tile)
+
+
 def test_gemm_ragged_n_not_multiple_of_4():
     gemm_case(B.DTYPE_BF16, 130, 124, 64, False, False, B.EPI_BIAS, expect_mfma=True)
     gemm_case(B.DTYPE_BF16, 130, 122, 64, False, False, B.EPI_BIAS, expect_mfma=False)   # ldc % 4 != 0
@@ -218,6 +228,12 @@ def attention_case(dtype, b, s, A, d):
 def test_attention_mfma():
     attention_case(B.DTYPE_BF16, 2, 192, 3, 64)      # ragged: 192 = 128 + 64 rows
     attention_case(B.DTYPE_BF16, 1, 512, 2, 64)
+
+
+@pytest.mark.parametrize("d", [8, 32, 40, 64, 96, 128])
+@pytest.mark.parametrize("s", [1, 31, 64, 65, 200])
+def test_attention_mfma_head_widths_and_ragged_lengths(d, s):
+    attention_case(B.DTYPE_BF16, 2, s, 3, d)
 
 
 @pytest.mark.parametrize("dtype", [B.DTYPE_F32, B.DTYPE_BF16])
