@@ -26,8 +26,8 @@
 // from the epilogue of the product that makes dctx (delta_blocks), a caller
 // without that product gets it from a small kernel of its own first.
 //
-// Plain kernels (any dtype and shape): one thread per output element, used by the
-// fp32 configuration and by shapes the MFMA kernels do not take.
+// Plain kernels (any dtype and shape): one thread per output element, for shapes neither
+// these MFMA kernels nor those of attention_f32.hip take.
 #include "device_common.h"
 #include "kernels.h"
 
@@ -695,6 +695,7 @@ hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
     });
     return hipGetLastError();
   }
+  if (dt == DT_F32 && attn_f32_takes(a)) return launch_attn_fwd_f32(a, st);
   long total = (long)a.b * a.A * a.s * a.d;
   dim3 grid((unsigned)((total + 255) / 256));
   if (dt == DT_BF16) hipLaunchKernelGGL(attn_fwd_plain<bf16>, grid, dim3(256), 0, st, a, scale2);
@@ -724,6 +725,7 @@ hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
     });
     return hipGetLastError();
   }
+  if (dt == DT_F32 && attn_f32_takes(a)) return launch_attn_bwd_f32(a, st);
   if (dt == DT_BF16) hipLaunchKernelGGL(attn_delta_kernel<bf16>, gd, dim3(256), 0, st, a);
   else hipLaunchKernelGGL(attn_delta_kernel<float>, gd, dim3(256), 0, st, a);
   e = hipGetLastError();

@@ -12,39 +12,15 @@
 //    first operand: each lane then owns 4 consecutive output columns of one
 //    output row, which the epilogue stages through LDS into coalesced stores.
 //  * gemm_plain_kernel: one thread per output element, fp32 accumulation in k
-//    order; used for fp32 stages (the tiny configuration) and for shapes the MFMA
-//    kernel does not take.
+//    order; used for shapes neither the MFMA kernel nor the fp32 kernels (gemm_f32.hip) take.
 #include <type_traits>
 #include <utility>
 
 #include "device_common.h"
+#include "gemm_epilogue.h"
 #include "kernels.h"
 
 namespace dapple {
-
-// ------------------------------------------------------------------ epilogue
-template <typename T>
-__device__ __forceinline__ void epilogue_store(const GemmArgs& g, long zc, long zbias, int row, int col, float t) {
-  if (g.epi & EPI_BIAS) t += to_f32(((const T*)g.bias)[zbias + col]);
-  if (g.epi & (EPI_ADD | EPI_MUL)) {
-    long ao = zc + (long)row * g.ldaux + col;
-    float x = (g.epi & EPI_AUX32) ? ((const float*)g.aux)[ao] : to_f32(((const T*)g.aux)[ao]);
-    t = (g.epi & EPI_ADD) ? t + x : t * x;
-  }
-  long o = zc + (long)row * g.ldc + col;
-  if (g.epi & EPI_GELU) {
-    float a, b;
-    gelu_both(t, a, b);
-    ((T*)g.C)[o] = from_f32<T>(a);
-    ((T*)g.C2)[o] = from_f32<T>(b);
-  } else if (g.epi & EPI_ACC32) {
-    ((float*)g.C)[o] += t;
-  } else if (g.epi & EPI_OUT32) {
-    ((float*)g.C)[o] = t;
-  } else {
-    ((T*)g.C)[o] = from_f32<T>(t);
-  }
-}
 
 // ------------------------------------------------------------------ plain kernel
 template <typename T>
@@ -895,6 +871,7 @@ hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st) {
                            : launch_mfma_layout<128, 64, 2, 2, 3, 64>(g, st);
     }
   }
+  if (dt == DT_F32 && gemm_f32_takes(g)) return launch_gemm_f32(g, st);
   dim3 blk(32, 8);
   dim3 grid((g.N + 31) / 32, (g.M + 7) / 8, g.batch);
   if (dt == DT_BF16)

@@ -1,0 +1,57 @@
+// The epilogue of one output element, shared by the GEMM kernels that store element by element.
+#pragma once
+#include "device_common.h"
+#include "kernels.h"
+
+namespace dapple {
+
+template <typename T>
+__device__ __forceinline__ void epilogue_store(const GemmArgs& g, long zc, long zbias, int row, int col, float t) {
+  if (g.epi & EPI_BIAS) t += to_f32(((const T*)g.bias)[zbias + col]);
+  if (g.epi & (EPI_ADD | EPI_MUL)) {
+    long ao = zc + (long)row * g.ldaux + col;
+    float x = (g.epi & EPI_AUX32) ? ((const float*)g.aux)[ao] : to_f32(((const T*)g.aux)[ao]);
+    t = (g.epi & EPI_ADD) ? t + x : t * x;
+  }
+  long o = zc + (long)row * g.ldc + col;
+  if (g.epi & EPI_GELU) {
+    float a, b;
+    gelu_both(t, a, b);
+    ((T*)g.C)[o] = from_f32<T>(a);
+    ((T*)g.C2)[o] = from_f32<T>(b);
+  } else if (g.epi & EPI_ACC32) {
+    ((float*)g.C)[o] += t;
+  } else if (g.epi & EPI_OUT32) {
+    ((float*)g.C)[o] = t;
+  } else {
+    ((T*)g.C)[o] = from_f32<T>(t);
+  }
+}
+
+// four consecutive columns of one row of an fp32 product (every pointer and stride 16-byte aligned)
+__device__ __forceinline__ void epilogue_store4(const GemmArgs& g, long zc, long zbias, int row, int col, f32x4 t) {
+  if (g.epi & EPI_BIAS) t += *(const f32x4*)((const float*)g.bias + zbias + col);
+  if (g.epi & (EPI_ADD | EPI_MUL)) {
+    const f32x4 x = *(const f32x4*)((const float*)g.aux + zc + (long)row * g.ldaux + col);
+    t = (g.epi & EPI_ADD) ? t + x : t * x;
+  }
+  float* const c = (float*)g.C + zc + (long)row * g.ldc + col;
+  if (g.epi & EPI_GELU) {
+    f32x4 a, b;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float x, y;
+      gelu_both(t[e], x, y);
+      a[e] = x;
+      b[e] = y;
+    }
+    *(f32x4*)c = a;
+    *(f32x4*)((float*)g.C2 + zc + (long)row * g.ldc + col) = b;
+  } else if (g.epi & EPI_ACC32) {
+    *(f32x4*)c = *(const f32x4*)c + t;
+  } else {
+    *(f32x4*)c = t;
+  }
+}
+
+}  // namespace dapple

@@ -1,0 +1,318 @@
+// fp32 products on the fp32 matrix instructions: exact fp32 multiply-adds, fp32 accumulation.
+//
+// v_mfma_f32_32x32x2_f32 / 16x16x4_f32 do 256 flops per clock and compute unit (157 TFLOP/s for the chip), a
+// sixteenth of the bf16 rate, so operand delivery is never the wall here: LDS and the vector caches are used far
+// below their rates, and the kernels are bound by the matrix pipe once every SIMD has a wave.  What decides the time
+// is therefore how many SIMDs a product reaches:
+//  * gemm_f32_kernel<128> / <64>: a square tile per workgroup of 2x2 waves, 32-wide k-tiles through a double buffer
+//    in LDS (2 x 37 KB: two workgroups per unit), the next tile's global loads in flight behind the MFMAs;
+//  * gemm_f32_small<TW>: 16 TW square tiles, one per workgroup whose four waves take every fourth 16-wide piece of K
+//    straight from global memory and add their partial tiles in wave order through LDS: for products with so few
+//    tiles that the length of one wave's MFMA chain is the time.
+// Measured before -> after: 2 layers of 1024 x 4096, 2 x 512 tokens, 2 micro-batches: 412 -> 3.9 ms per iteration
+// with the attention kernels of attention_f32.hip (one thread per output element before).
+#include <type_traits>
+#include <utility>
+
+#include "device_common.h"
+#include "gemm_epilogue.h"
+#include "kernels.h"
+
+namespace dapple {
+
+// per-instance pointers picked with constant indices (a variable index would move the argument struct to scratch)
+template <typename A>
+__device__ __forceinline__ auto pick4(A& arr, int z) {
+  return z == 0 ? arr[0] : (z == 1 ? arr[1] : (z == 2 ? arr[2] : arr[3]));
+}
+
+// ------------------------------------------------------------------ LDS-tiled kernel
+constexpr int FBK = 32;
+
+// One operand's [R x 32] k-tile.  k-contiguous: LDS [R][32 + 4]; 16 lanes reading 16 rows 16 bytes each hit all 64
+// banks.  k-strided: LDS [32][R + 8]; the two half waves of a 4-byte read lie 4 rows = 32 banks apart.
+template <int R, bool KS>
+struct F32Tile {
+  static constexpr int LD = KS ? R + 8 : FBK + 4;
+  static constexpr int FLOATS = KS ? FBK * LD : R * LD;
+  static constexpr int N = R * FBK / 4 / 256;   // float4 per thread
+  f32x4 v[N];
+  // rows r0.. of an operand with `rows` valid rows; k0..: k inside a segment with klen valid entries
+  __device__ __forceinline__ void load(const float* X, int ld, int r0, int rows, int k0, int klen, int tid) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int pos = tid + 256 * i;
+      const int r = KS ? r0 + pos % (R / 4) * 4 : r0 + pos / (FBK / 4);
+      const int k = KS ? k0 + pos / (R / 4) : k0 + pos % (FBK / 4) * 4;
+      v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (r < rows && k < klen) v[i] = *(const f32x4*)(X + (KS ? (long)k * ld + r : (long)r * ld + k));
+    }
+  }
+  __device__ __forceinline__ void store(float* S, int tid) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int pos = tid + 256 * i;
+      const int a = KS ? pos / (R / 4) : pos / (FBK / 4), b = (KS ? pos % (R / 4) : pos % (FBK / 4)) * 4;
+      *(f32x4*)(S + a * LD + b) = v[i];
+    }
+  }
+  // row r, k = 8 kk + 4 h + 0..3
+  static __device__ __forceinline__ f32x4 frag(const float* S, int r, int kk, int h) {
+    const int k = 8 * kk + 4 * h;
+    if (!KS) return *(const f32x4*)(S + r * LD + k);
+    return f32x4{S[k * LD + r], S[(k + 1) * LD + r], S[(k + 2) * LD + r], S[(k + 3) * LD + r]};
+  }
+};
+
+template <int BT, bool AKS, bool BKS>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, int tiles_n) {
+  typedef F32Tile<BT, AKS> TA;
+  typedef F32Tile<BT, BKS> TB;
+  constexpr int W = BT / 2, NB = W / 32;   // wave tile, 32-blocks per side
+  extern __shared__ __attribute__((aligned(16))) float fsm[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l31 = lane & 31, h = lane >> 5;
+  const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n, z = blockIdx.z;
+  const int m0 = tm * BT, n0 = tn * BT, wm0 = (wave >> 1) * W, wn0 = (wave & 1) * W;
+  const float* A = g.Az[0] ? (const float*)pick4(g.Az, z) : (const float*)g.A + z * g.sA;
+  const float* B = g.Bz[0] ? (const float*)pick4(g.Bz, z) : (const float*)g.B + z * g.sB;
+  if (g.Cz[0]) {
+    g.C = pick4(g.Cz, z);
+    g.sC = 0;
+  }
+  float* const bs = (g.epi & EPI_BSUM) ? pick4(g.bsum_z, z) : nullptr;
+  const bool do_cs = bs != nullptr && tm == 0 && wm0 == 0;
+  const int klen = g.K > g.kseg_len ? g.kseg_len : min(g.K, g.k_valid);
+  const int per_seg = (g.kseg_len + FBK - 1) / FBK, nt = g.K / g.kseg_len * per_seg;
+  f32x16 acc[NB][NB];
+  float cs[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    cs[i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  }
+  TA ta;
+  TB tb;
+  int seg = 0, kt = 0;   // the tile the next load fetches
+  auto load = [&]() {
+    ta.load(A + seg * g.segA, g.lda, m0, g.m_valid, kt * FBK, klen, tid);
+    tb.load(B + seg * g.segB, g.ldb, n0, g.n_valid, kt * FBK, klen, tid);
+    if (++kt == per_seg) { kt = 0; ++seg; }
+  };
+  constexpr int STAGE = TA::FLOATS + TB::FLOATS;
+  load();
+  ta.store(fsm, tid);
+  tb.store(fsm + TA::FLOATS, tid);
+  __syncthreads();
+  for (int t = 0; t < nt; ++t) {
+    const float *SA = fsm + (t & 1) * STAGE, *SB = SA + TA::FLOATS;
+    const bool more = t + 1 < nt;
+    if (more) load();
+#pragma unroll
+    for (int kk = 0; kk < FBK / 8; ++kk) {
+      f32x4 a[NB], b[NB];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) a[i] = TA::frag(SA, wm0 + 32 * i + l31, kk, h);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) b[j] = TB::frag(SB, wn0 + 32 * j + l31, kk, h);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)   // B first: a lane then owns 4 consecutive columns of one row
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][e], a[i][e], acc[i][j], 0, 0, 0);
+      if (do_cs) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) cs[j] += (b[j][0] + b[j][1]) + (b[j][2] + b[j][3]);
+      }
+    }
+    if (more) {
+      float* nb = fsm + ((t + 1) & 1) * STAGE;
+      ta.store(nb, tid);
+      tb.store(nb + TA::FLOATS, tid);
+    }
+    __syncthreads();
+  }
+  if (do_cs) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const float t = cs[j] + __shfl_xor(cs[j], 32, 64);
+      const int col = n0 + wn0 + 32 * j + l31;
+      if (h == 0 && col < g.N) bs[col] += t;
+    }
+  }
+  const long zc = z * g.sC, zb = z * g.sBias;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const int row = m0 + wm0 + 32 * i + l31;
+    if (row >= g.M) continue;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int col = n0 + wn0 + 32 * j + 8 * q + 4 * h;
+        if (col >= g.N) continue;
+        epilogue_store4(g, zc, zb, row, col,
+                        f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]});
+      }
+  }
+}
+
+// ------------------------------------------------------------------ few tiles: K split over the waves
+template <int TW, bool AKS, bool BKS>
+__global__ __launch_bounds__(256) void gemm_f32_small(GemmArgs g, int tiles_n) {
+  constexpr int BT = 16 * TW, LD = BT + 4;
+  __shared__ __attribute__((aligned(16))) float part[4][BT * LD];
+  __shared__ float cpart[4][BT];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l15 = lane & 15, q4 = lane >> 4;
+  const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n, z = blockIdx.z;
+  const int m0 = tm * BT, n0 = tn * BT;
+  const float* A = g.Az[0] ? (const float*)pick4(g.Az, z) : (const float*)g.A + z * g.sA;
+  const float* B = g.Bz[0] ? (const float*)pick4(g.Bz, z) : (const float*)g.B + z * g.sB;
+  if (g.Cz[0]) {
+    g.C = pick4(g.Cz, z);
+    g.sC = 0;
+  }
+  float* const bs = (g.epi & EPI_BSUM) ? pick4(g.bsum_z, z) : nullptr;
+  const int klen = g.K > g.kseg_len ? g.kseg_len : min(g.K, g.k_valid);
+  const int per_seg = (g.kseg_len + 15) / 16, nc = g.K / g.kseg_len * per_seg;
+  f32x4 acc[TW][TW];
+  float cs[TW];
+#pragma unroll
+  for (int i = 0; i < TW; ++i) {
+    cs[i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < TW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  // rows l15 of the 16-row block at r0, k = k0 + 4 q4 + 0..3
+  auto fetch = [&](const float* X, int ld, bool ks, int r, int rows, int k0) {
+    const int k = k0 + 4 * q4;
+    f32x4 v{0.f, 0.f, 0.f, 0.f};
+    if (r < rows) {
+      if (!ks) {
+        if (k < klen) v = *(const f32x4*)(X + (long)r * ld + k);   // klen is a multiple of 4 here
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (k + e < klen) v[e] = X[(long)(k + e) * ld + r];
+      }
+    }
+    return v;
+  };
+  constexpr int U = TW == 1 ? 8 : 4;   // 16-wide pieces of K whose loads are in flight together
+  for (int c0 = wave; c0 < nc; c0 += 4 * U) {
+    f32x4 a[U][TW], b[U][TW];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = c0 + 4 * u, seg = c / per_seg, k0 = c < nc ? (c - seg * per_seg) * 16 : klen;
+      const float *As = A + (c < nc ? seg : 0) * g.segA, *Bs = B + (c < nc ? seg : 0) * g.segB;
+#pragma unroll
+      for (int i = 0; i < TW; ++i) {
+        a[u][i] = fetch(As, g.lda, AKS, m0 + 16 * i + l15, g.m_valid, k0);
+        b[u][i] = fetch(Bs, g.ldb, BKS, n0 + 16 * i + l15, g.n_valid, k0);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < TW; ++i)
+#pragma unroll
+          for (int j = 0; j < TW; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[u][j][e], a[u][i][e], acc[i][j], 0, 0, 0);
+      if (bs) {
+#pragma unroll
+        for (int j = 0; j < TW; ++j) cs[j] += (b[u][j][0] + b[u][j][1]) + (b[u][j][2] + b[u][j][3]);
+      }
+    }
+  }
+  // acc[i][j]: row 16 i + l15, columns 16 j + 4 q4 + 0..3
+#pragma unroll
+  for (int i = 0; i < TW; ++i)
+#pragma unroll
+    for (int j = 0; j < TW; ++j) *(f32x4*)(part[wave] + (16 * i + l15) * LD + 16 * j + 4 * q4) = acc[i][j];
+  if (bs && tm == 0) {
+#pragma unroll
+    for (int j = 0; j < TW; ++j) {
+      float t = cs[j];
+      t += __shfl_xor(t, 16, 64);
+      t += __shfl_xor(t, 32, 64);
+      if (q4 == 0) cpart[wave][16 * j + l15] = t;
+    }
+  }
+  __syncthreads();
+  if (bs && tm == 0 && tid < BT && n0 + tid < g.N)
+    bs[n0 + tid] += ((cpart[0][tid] + cpart[1][tid]) + cpart[2][tid]) + cpart[3][tid];
+  const long zc = z * g.sC, zb = z * g.sBias;
+  for (int i = tid * 4; i < BT * BT; i += 1024) {
+    const int r = i / BT, c = i % BT, row = m0 + r, col = n0 + c;
+    if (row >= g.M || col >= g.N) continue;
+    const int o = r * LD + c;
+    const f32x4 p0 = *(const f32x4*)(part[0] + o), p1 = *(const f32x4*)(part[1] + o), p2 = *(const f32x4*)(part[2] + o),
+                p3 = *(const f32x4*)(part[3] + o);
+    epilogue_store4(g, zc, zb, row, col, ((p0 + p1) + p2) + p3);
+  }
+}
+
+// ------------------------------------------------------------------ host side
+static bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
+
+bool gemm_f32_takes(const GemmArgs& g) {
+  if (g.K < 1 || g.kseg_len < 1 || g.K % g.kseg_len || g.N % 4 || g.lda % 4 || g.ldb % 4 || g.ldc % 4) return false;
+  if (g.kseg_len % 4 && !(g.a_kstrided && g.b_kstrided)) return false;
+  if (g.sA % 4 || g.sB % 4 || g.sC % 4 || g.sBias % 4 || g.segA % 4 || g.segB % 4) return false;
+  if (!al16(g.A) || !al16(g.B) || !al16(g.C) || (g.epi & EPI_ROWDOT)) return false;
+  // a k-strided operand is read four rows' entries at a time: what lies past the last row must be the padding of its
+  // leading dimension, and must not reach a stored element
+  if (g.a_kstrided && g.m_valid % 4 && (g.m_valid != g.M || (g.m_valid + 3) / 4 * 4 > g.lda)) return false;
+  if (g.b_kstrided && g.n_valid % 4) return false;
+  if (!g.a_kstrided && !g.b_kstrided && g.k_valid < g.K) return false;   // k_valid cuts k-strided operands
+  if ((g.epi & EPI_BIAS) && !al16(g.bias)) return false;
+  if ((g.epi & (EPI_ADD | EPI_MUL)) && (g.ldaux % 4 || !al16(g.aux))) return false;
+  if ((g.epi & EPI_GELU) && !al16(g.C2)) return false;
+  if ((g.epi & EPI_BSUM) && !(g.a_kstrided && g.b_kstrided)) return false;
+  if ((g.Az[0] || g.Bz[0] || g.Cz[0] || (g.epi & EPI_BSUM)) && g.batch > 4) return false;
+  if (g.Az[0] || g.Bz[0] || g.Cz[0])
+    for (int z = 0; z < g.batch; ++z)
+      if (!al16(g.Az[z]) || !al16(g.Bz[z]) || !al16(g.Cz[z])) return false;
+  return true;
+}
+
+template <int BT, bool AKS, bool BKS>
+static hipError_t launch_tile(const GemmArgs& g, hipStream_t st) {
+  auto kern = gemm_f32_kernel<BT, AKS, BKS>;
+  constexpr int lds = 2 * 4 * (F32Tile<BT, AKS>::FLOATS + F32Tile<BT, BKS>::FLOATS);
+  static const hipError_t attr_rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (attr_rc != hipSuccess) return attr_rc;
+  const int tm = (g.M + BT - 1) / BT, tn = (g.N + BT - 1) / BT;
+  hipLaunchKernelGGL(kern, dim3(tm * tn, 1, g.batch), dim3(256), lds, st, g, tn);
+  return hipGetLastError();
+}
+template <int TW, bool AKS, bool BKS>
+static hipError_t launch_small(const GemmArgs& g, hipStream_t st) {
+  const int tm = (g.M + 16 * TW - 1) / (16 * TW), tn = (g.N + 16 * TW - 1) / (16 * TW);
+  hipLaunchKernelGGL((gemm_f32_small<TW, AKS, BKS>), dim3(tm * tn, 1, g.batch), dim3(256), 0, st, g, tn);
+  return hipGetLastError();
+}
+
+template <bool AKS, bool BKS>
+static hipError_t launch_layout(const GemmArgs& g, hipStream_t st) {
+  auto tiles = [&](long t) { return (long)((g.M + t - 1) / t) * ((g.N + t - 1) / t) * g.batch; };
+  // The largest tile that still gives most of the 256 units a workgroup.  Below that the 32- and 16-wide tiles with K
+  // split over the waves: a 16-wide one has a quarter of the MFMA chain but reads every operand element twice as often.
+  if (tiles(128) >= 192) return launch_tile<128, AKS, BKS>(g, st);
+  if (tiles(64) >= 160) return launch_tile<64, AKS, BKS>(g, st);
+  if (tiles(32) >= 160) return launch_small<2, AKS, BKS>(g, st);
+  return launch_small<1, AKS, BKS>(g, st);
+}
+
+hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st) {
+  if (g.a_kstrided) return g.b_kstrided ? launch_layout<true, true>(g, st) : launch_layout<true, false>(g, st);
+  return g.b_kstrided ? launch_layout<false, true>(g, st) : launch_layout<false, false>(g, st);
+}
+
+}  // namespace dapple

@@ -61,6 +61,10 @@ struct GemmArgs {
 };
 
 hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st);
+// fp32 products on the fp32 matrix instructions (gemm_f32.hip): whether they take this problem (else the plain
+// kernel does), and the launch
+bool gemm_f32_takes(const GemmArgs& g);
+hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st);
 // true when the MFMA kernel takes this problem (else the plain ALU kernel does)
 bool gemm_uses_mfma(Dtype dt, const GemmArgs& g);
 
@@ -88,6 +92,10 @@ struct AttnArgs {
 hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st);
 hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& a, hipStream_t st);
 bool attn_uses_mfma(Dtype dt, const AttnArgs& a);
+// fp32 stages (attention_f32.hip; ctx32, delta and delta_blocks are not used there)
+bool attn_f32_takes(const AttnArgs& a);
+hipError_t launch_attn_fwd_f32(const AttnArgs& a, hipStream_t st);
+hipError_t launch_attn_bwd_f32(const AttnArgs& a, hipStream_t st);
 // true when its backward can take delta_blocks (a head is a whole number of 32-column blocks)
 bool attn_takes_delta_blocks(Dtype dt, const AttnArgs& a);
 

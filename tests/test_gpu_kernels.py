@@ -195,6 +195,18 @@ def test_gemm_plain_kernel(dtype):
     gemm_case(dtype, 19, 28, 16, False, True, B.EPI_BIAS | B.EPI_GELU, expect_mfma=False)
 
 
+@pytest.mark.parametrize("M,N,K", [(4, 4, 4), (17, 20, 36), (33, 60, 260), (200, 136, 100), (520, 1028, 68), (1032, 3080, 96)])
+def test_gemm_fp32_tiles(M, N, K):
+    # the 16- and 32-wide tiles with K split over the waves, the 64- and 128-wide ones; ragged against each of them
+    for akS, bkS in ((False, False), (False, True), (True, False), (True, True)):
+        if akS and M % 4:
+            continue
+        gemm_case(B.DTYPE_F32, M, N, K, akS, bkS, B.EPI_BIAS | B.EPI_ADD)
+        gemm_case(B.DTYPE_F32, M, N, 3 * K, akS, bkS, B.EPI_BIAS | B.EPI_GELU, nseg=3)
+    if M % 4 == 0:
+        gemm_case(B.DTYPE_F32, M, N, K + 3, True, True, B.EPI_ACC32 | B.EPI_BSUM)
+
+
 def attention_case(dtype, b, s, A, d):
     bf = dtype == B.DTYPE_BF16
     td = TD[dtype]
@@ -231,9 +243,15 @@ def test_attention_mfma():
 
 
 @pytest.mark.parametrize("d", [8, 32, 40, 64, 96, 128])
-@pytest.mark.parametrize("s", [1, 31, 64, 65, 200])
+@pytest.mark.parametrize("s", [3, 31, 64, 65, 200])
 def test_attention_mfma_head_widths_and_ragged_lengths(d, s):
     attention_case(B.DTYPE_BF16, 2, s, 3, d)
+
+
+@pytest.mark.parametrize("d", [4, 16, 20, 64, 128])
+@pytest.mark.parametrize("s", [3, 32, 65, 130])
+def test_attention_fp32_head_widths_and_ragged_lengths(d, s):
+    attention_case(B.DTYPE_F32, 2, s, 3, d)
 
 
 @pytest.mark.parametrize("dtype", [B.DTYPE_F32, B.DTYPE_BF16])
