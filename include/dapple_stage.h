@@ -112,10 +112,12 @@ typedef struct {
   uint64_t weight_bytes;    /* bytes of the caller's flat parameter vector */
   uint64_t grad_bytes;      /* fp32 accumulators */
   uint64_t slot_bytes;      /* activations one resident micro-batch keeps from F to B */
-  uint64_t workspace_bytes; /* transient buffers shared by all tasks (one copy) */
-  uint64_t arena_bytes;     /* grad_bytes + max_slots * slot_bytes + copies * workspace_bytes (+ alignment, + the
-                               forward tasks' activation buffer under STAGE_FLAG_RECOMPUTE); copies = 2 (one
-                               workspace per backward lane), 1 under STAGE_FLAG_ONE_STREAM */
+  uint64_t workspace_bytes; /* transient buffers of one micro-batch's task */
+  uint64_t arena_bytes;     /* grad_bytes + max_slots * slot_bytes + copies * group * workspace_bytes (+ alignment, +
+                               the forward tasks' activation buffer under STAGE_FLAG_RECOMPUTE); copies = 2 (one
+                               workspace per backward lane), 1 under STAGE_FLAG_ONE_STREAM; group = the micro-batches
+                               one set of launches may cover (up to 8192 token rows, at most 8; 1 under
+                               STAGE_FLAG_RECOMPUTE and with one slot) */
 } stage_sizes;
 
 typedef struct {
@@ -164,6 +166,11 @@ int stage_schedule_ops(int M, int K, int order, int32_t* ops_out, int capacity);
  * alternate between the caller's stream and a second backward stream (each with
  * its own workspace), and every gradient-accumulator update of every backward task
  * goes to the one side stream in list order, which fixes the order of every sum.
+ * In both built-in orders neighbouring tasks of one kind go out together where their slots lie side by side: one set of
+ * launches over the rows of several micro-batches (as many as divide the resident count and make up to 8192 rows);
+ * at most K micro-batches are resident as before, and every accumulator gets each micro-batch's sum on its own, in
+ * list order.  Buffers of consecutive micro-batches that lie one behind the other (xs[m+1] = xs[m] + b*s*H, likewise
+ * ys, dys, dxs, auxs) save a few launches at the ends of the stage.
  * The GPipe order alternates its backward tasks the same way but starts none before
  * the last forward listed before it has finished; an explicit list keeps one backward
  * stream and the same rule.  Results do not depend on the overlap: they are the same

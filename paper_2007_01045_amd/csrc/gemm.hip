@@ -23,6 +23,11 @@
 namespace dapple {
 
 // ------------------------------------------------------------------ plain kernel
+__device__ __forceinline__ void plain_bsum(const GemmArgs& g, int z, int col, float t) {
+  float* bs = z == 0 ? g.bsum_z[0] : (z == 1 ? g.bsum_z[1] : (z == 2 ? g.bsum_z[2] : g.bsum_z[3]));
+  if (bs) bs[col] += t;
+}
+
 template <typename T>
 __global__ void gemm_plain_kernel(GemmArgs g) {
   int col = blockIdx.x * blockDim.x + threadIdx.x;
@@ -37,7 +42,13 @@ __global__ void gemm_plain_kernel(GemmArgs g) {
   }
   float acc = 0.f, bsum = 0.f;
   int nseg = g.K / g.kseg_len;
+  const bool segacc = (g.epi & EPI_SEGACC) != 0;
   for (int s = 0; s < nseg; ++s) {
+    if (segacc && s) {   // the segment before is complete
+      epilogue_store<T>(g, z * g.sC, z * g.sBias, row, col, acc);
+      if ((g.epi & EPI_BSUM) && row == 0) plain_bsum(g, z, col, bsum);
+      acc = bsum = 0.f;
+    }
     const T* As = A + s * g.segA;
     const T* Bs = B + s * g.segB;
     for (int k = 0; k < g.kseg_len; ++k) {
@@ -48,10 +59,7 @@ __global__ void gemm_plain_kernel(GemmArgs g) {
       bsum += b;
     }
   }
-  if ((g.epi & EPI_BSUM) && row == 0) {
-    float* bs = z == 0 ? g.bsum_z[0] : (z == 1 ? g.bsum_z[1] : (z == 2 ? g.bsum_z[2] : g.bsum_z[3]));
-    if (bs) bs[col] += bsum;
-  }
+  if ((g.epi & EPI_BSUM) && row == 0) plain_bsum(g, z, col, bsum);
   epilogue_store<T>(g, z * g.sC, z * g.sBias, row, col, acc);
 }
 
@@ -245,7 +253,7 @@ __device__ __forceinline__ float sum8(float v) {
   return v;
 }
 
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool KT = false>
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool KT = false, int NSEG = 1>
 struct GemmTile {
   static constexpr int NW = WGM * WGN, NT = 64 * NW;
   static constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
@@ -255,15 +263,16 @@ struct GemmTile {
   static constexpr int EPI_LD = WN + 4;  // fp32 staging row
   static constexpr size_t MAIN_BYTES = NS * (size_t)STAGE_ELEMS * sizeof(bf16);
   static constexpr int LOADS_PER_TILE = TA::NI + TB::NI;  // per wave
-  static constexpr size_t EPI_BYTES = (size_t)NW * 32 * EPI_LD * sizeof(float);
+  static constexpr size_t EPI_BYTES = (size_t)NSEG * NW * 32 * EPI_LD * sizeof(float);
   static constexpr size_t LDS_BYTES = MAIN_BYTES > EPI_BYTES ? MAIN_BYTES : EPI_BYTES;
 };
 
 // CS: the variant that can also sum B over k (EPI_BSUM); KT: the variant for K segments that are no multiple of 64
-// when an operand is k-contiguous (see OperandTile)
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-  typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT> CFG;
+// when an operand is k-contiguous (see OperandTile); NSEG = 2: two K segments whose sums are added to C one after the
+// other (EPI_SEGACC), each in accumulators of its own
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false, int NSEG = 1>
+__global__ __launch_bounds__(64 * WGM * WGN, NSEG) void gemm_mfma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, NSEG> CFG;
   typedef typename CFG::TA TA;
   typedef typename CFG::TB TB;
   constexpr int MI = CFG::MI, NI = CFG::NI;
@@ -310,7 +319,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, i
   const bf16* Ab = g.Az[0] ? (const bf16*)pick(g.Az) : (const bf16*)g.A + z * g.sA;
   const bf16* Bb = g.Bz[0] ? (const bf16*)pick(g.Bz) : (const bf16*)g.B + z * g.sB;
   void* const Cb = g.Cz[0] ? pick(g.Cz) : g.C;
-  const int tiles_per_seg = (g.kseg_len + BK - 1) / BK;
+  // (two segments: whole turns of the ring each; the k-tiles beyond a segment's end read nothing)
+  const int seg_tiles = (g.kseg_len + BK - 1) / BK;
+  const int tiles_per_seg = NSEG == 1 ? seg_tiles : (seg_tiles + NS - 1) / NS * NS;
   const int nk = g.K / g.kseg_len * tiles_per_seg;
   const int k_rows = g.K > g.kseg_len ? g.kseg_len : g.k_valid;   // rows of one segment of a k-strided operand
   // bytes of one segment of each operand that may be read (beyond: zero)
@@ -380,13 +391,15 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, i
     advance();
   };
 
-  f32x16 acc[MI][NI];
+  f32x16 accs[NSEG][MI][NI];
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
+  for (int s = 0; s < NSEG; ++s)
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) accs[s][i][j][v] = 0.f;
 
   // Software pipeline.  Global->LDS: a k-tile is requested NS-1 iterations before it is
   // used, as soon as every wave has left the ring slot it goes to.  LDS->registers: the
@@ -426,29 +439,32 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, i
   // in the order the next step's MFMAs need them: a0, b0 .. b_NI-1, a1 ..) and this step's share of the requests
   // for the tile that goes to ring slot SN
   // EPI_BSUM: bsum[n] += sum_k B(n,k) for this tile's columns, by the workgroups of the first tile row (tm == 0)
-  // and there by the waves that hold the tile's first rows: one more MFMA per column block and k-step with an
-  // A fragment of ones -- every row of its result is the column sum, exact products, fp32 adds in k order.
-  // The matrix pipe has the room (the products wait for the global -> LDS path), and the column sums of the
-  // output gradient need no pass of their own over it.
-  f32x16 csum[CS ? NI : 1];
+  // and there by the waves that hold the tile's first rows: each lane adds up the B fragments it holds anyway, two
+  // products with one per instruction (exact, fp32 sums), between the MFMAs.  One register per 32 columns: sums
+  // taken with MFMAs against a fragment of ones needed sixteen, which two sets of accumulators leave no room for.
+  float csum[NSEG][NI];
 #pragma unroll
-  for (int j = 0; j < (CS ? NI : 1); ++j)
+  for (int s = 0; s < NSEG; ++s)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) csum[j][v] = 0.f;
-  bf16x8 ones;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = (bf16)1.0f;
+    for (int j = 0; j < NI; ++j) csum[s][j] = 0.f;
+  const bf16x2 one2 = {(bf16)1.0f, (bf16)1.0f};
   float* const bsum_ptr = CS ? pick(g.bsum_z) : nullptr;
   const bool do_cs = CS && (g.epi & EPI_BSUM) && tm == 0 && wm0 == 0 && bsum_ptr != nullptr;
-  auto step = [&](const Frags& use, Frags& fill, auto S, auto SN, auto J, auto WCS) {
+  auto add_cols = [&](float& t, bf16x8 b) {
+    t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(b, b, 0, 1), one2, t, false);
+    t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(b, b, 2, 3), one2, t, false);
+    t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(b, b, 4, 5), one2, t, false);
+    t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(b, b, 6, 7), one2, t, false);
+  };
+  auto step = [&](const Frags& use, Frags& fill, auto S, auto SN, auto J, auto WCS, auto SEG) {
     constexpr int off = decltype(S)::value * CFG::STAGE_ELEMS * 2, offn = decltype(SN)::value * CFG::STAGE_ELEMS * 2;
     constexpr int j = decltype(J)::value;
     constexpr int e0 = j * EXTRA / KSTEPS, e1 = (j + 1) * EXTRA / KSTEPS, P = NFRAG + (e1 - e0);
     static_for<NM>([&](auto Q) {
       constexpr int q = decltype(Q)::value, mi = q / NI, ni = q % NI;
+      auto& acc = accs[decltype(SEG)::value];
       acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(use.b[ni], use.a[mi], acc[mi][ni], 0, 0, 0);
-      if constexpr (decltype(WCS)::value && mi == 0)
-        csum[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(use.b[ni], ones, csum[ni], 0, 0, 0);
+      if constexpr (decltype(WCS)::value && mi == 0) add_cols(csum[decltype(SEG)::value][ni], use.b[ni]);
       __builtin_amdgcn_sched_barrier(0);
       constexpr int p0 = q * P / NM, p1 = (q + 1) * P / NM;
       static_for<p1 - p0>([&](auto D) {
@@ -469,8 +485,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, i
       if constexpr (p1 > p0) __builtin_amdgcn_sched_barrier(0);
     });
   };
-  const int turns = (nk + NS - 1) / NS;
-  auto main_loop = [&](auto WCS) {
+  const int turns = NSEG == 1 ? (nk + NS - 1) / NS : tiles_per_seg / NS;   // per segment
+  auto seg_loop = [&](auto WCS, auto SEG) {
     for (int t = 0; t < turns; ++t) {
       static_for<NS>([&](auto S) {
         typedef std::integral_constant<int, (decltype(S)::value + NS - 1) % NS> SN;
@@ -480,19 +496,24 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, i
         asm volatile("" ::: "memory");  // ... and no LDS read of this tile may be hoisted above it
         static_for<KSTEPS / 2>([&](auto H) {
           constexpr int kk = 2 * decltype(H)::value;
-          step(f1, f0, S, SN{}, std::integral_constant<int, kk>{}, WCS);      // MFMAs of k-step kk - 1 (the previous tile's last when kk == 0)
-          step(f0, f1, S, SN{}, std::integral_constant<int, kk + 1>{}, WCS);
+          step(f1, f0, S, SN{}, std::integral_constant<int, kk>{}, WCS, SEG);      // MFMAs of k-step kk - 1 (the previous tile's last when kk == 0)
+          step(f0, f1, S, SN{}, std::integral_constant<int, kk + 1>{}, WCS, SEG);
         });
       });
     }
     // the last k-step of the last tile
     static_for<NM>([&](auto Q) {
       constexpr int q = decltype(Q)::value, mi = q / NI, ni = q % NI;
+      auto& acc = accs[decltype(SEG)::value];
       acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1.b[ni], f1.a[mi], acc[mi][ni], 0, 0, 0);
-      if constexpr (decltype(WCS)::value && mi == 0)
-        csum[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1.b[ni], ones, csum[ni], 0, 0, 0);
+      if constexpr (decltype(WCS)::value && mi == 0) add_cols(csum[decltype(SEG)::value][ni], f1.b[ni]);
     });
+    if constexpr (decltype(SEG)::value + 1 < NSEG) {   // the next segment's first rotated step multiplies zeros again
+      static_for<MI>([&](auto I) { f1.a[decltype(I)::value] = bf16x8{}; });
+      static_for<NI>([&](auto J) { f1.b[decltype(J)::value] = bf16x8{}; });
+    }
   };
+  auto main_loop = [&](auto WCS) { static_for<NSEG>([&](auto SEG) { seg_loop(WCS, SEG); }); };
   // (two copies of the loop under one uniform branch, none inside it)
   if constexpr (CS) {
     if (do_cs) main_loop(std::true_type{});
@@ -501,16 +522,21 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, i
     main_loop(std::false_type{});
   }
   if constexpr (CS) {
-    // every row of csum holds the column sums: the lanes of row 0 add them to bsum (one workgroup per column
-    // range does, so the add needs no atomic)
-    if (do_cs && (lane & 31) == 0) {
+    // the two half waves hold the sums over different k (one workgroup per column range adds to bsum: no atomic)
+    if (do_cs) {
 #pragma unroll
-      for (int j = 0; j < NI; ++j)
+      for (int j = 0; j < NI; ++j) {
+        const int col = n0 + wn0 + 32 * j + (lane & 31);
+        float t[NSEG];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int col = n0 + wn0 + 32 * j + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-          if (col < g.N) bsum_ptr[col] += csum[j][v];
+        for (int s = 0; s < NSEG; ++s) t[s] = csum[s][j] + __shfl_xor(csum[s][j], 32, 64);
+        if (lane < 32 && col < g.N) {
+          float o = bsum_ptr[col];
+#pragma unroll
+          for (int s = 0; s < NSEG; ++s) o += t[s];
+          bsum_ptr[col] = o;
         }
+      }
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // the tail requests (they read nothing) must be done before LDS is reused
@@ -522,8 +548,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, i
   const long zc = g.Cz[0] ? 0 : z * g.sC, zbias = z * g.sBias;
   constexpr int C4 = CFG::WN / 4;             // float4 per staged row
   constexpr int NIT = 32 * C4 / 64;           // float4 per lane per 32-row block
-  constexpr int HB = NIT > 8 ? 8 : NIT;       // processed HB at a time
-  constexpr bool PRE = !CS && MI * NIT <= 16;   // (the column-sum variant serves accumulating products only)
+  constexpr int HB = NSEG == 2 ? (NIT > 4 ? 4 : NIT) : (NIT > 8 ? 8 : NIT);   // processed HB at a time
+  constexpr bool PRE = !CS && NSEG == 1 && MI * NIT <= 16;   // (the column-sum variant serves accumulating products only)
   const int epi = g.epi;
   // (native vectors: arrays of the runtime's float4, a struct around a union, stay in scratch memory; a bf16
   // operand's four values sit in the first two lanes)
@@ -566,20 +592,24 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, i
   // acc[i][j][v]: row = wm0 + 32 i + (lane & 31), col = wn0 + 32 j + 8 (v>>2) + 4 (lane>>5) + (v&3)
   // All LDS reads (and aux / C reads) of a half block are issued before the first use,
   // so their latencies overlap instead of adding up.
-  float* stg = (float*)smem + wave * 32 * CFG::EPI_LD;
+  float* stg = (float*)smem + wave * NSEG * 32 * CFG::EPI_LD;
   // one 32-row block; the block index is a compile-time constant so that the
   // accumulators are always addressed statically (they must stay in registers)
   auto store_block = [&](auto I, auto FULLC) {
     constexpr int i = decltype(I)::value;
     // FULL: the whole tile lies inside the matrix, no element needs a bounds test
     constexpr bool FULL = decltype(FULLC)::value;
+    auto stage = [&](auto& acc, float* stg) {
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
+      for (int j = 0; j < NI; ++j)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float4 v4 = make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-        *(float4*)(stg + (lane & 31) * CFG::EPI_LD + j * 32 + 8 * q + 4 * (lane >> 5)) = v4;
-      }
+        for (int q = 0; q < 4; ++q) {
+          float4 v4 = make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+          *(float4*)(stg + (lane & 31) * CFG::EPI_LD + j * 32 + 8 * q + 4 * (lane >> 5)) = v4;
+        }
+    };
+    stage(accs[0], stg);
+    if constexpr (NSEG == 2) stage(accs[1], stg + 32 * CFG::EPI_LD);
     // the staging tile is private to the wave and a wave's LDS instructions execute in
     // order: no workgroup barrier is needed (one would also wait for the stores below)
     __builtin_amdgcn_wave_barrier();
@@ -594,6 +624,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, i
         rows[u] = m0 + wm0 + i * 32 + r;
         cols[u] = n0 + wn0 + c4 * 4;
         t[u] = *(const float4*)(stg + r * CFG::EPI_LD + c4 * 4);
+      }
+      float4 t1[NSEG == 2 ? HB : 1];   // the second segment's sums
+      if constexpr (NSEG == 2) {
+#pragma unroll
+        for (int u = 0; u < HB; ++u) {
+          int idx = (hb + u) * 64 + lane;
+          t1[u] = *(const float4*)(stg + (32 + idx / C4) * CFG::EPI_LD + idx % C4 * 4);
+        }
       }
       {
         if (epi & EPI_BIAS) {
@@ -667,6 +705,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_kernel(GemmArgs g, i
           for (int u = 0; u < HB; ++u)
             if (FULL || (rows[u] < g.M && cols[u] < g.N)) {
               cv[u].x += t[u].x; cv[u].y += t[u].y; cv[u].z += t[u].z; cv[u].w += t[u].w;
+              if constexpr (NSEG == 2) { cv[u].x += t1[u].x; cv[u].y += t1[u].y; cv[u].z += t1[u].z; cv[u].w += t1[u].w; }
               *(float4*)((float*)Cb + zc + (long)rows[u] * g.ldc + cols[u]) = cv[u];
             }
         } else if (epi & EPI_GELU) {
@@ -728,6 +767,11 @@ template __global__ void gemm_mfma_kernel<128, 128, 2, 2, 2, true, true, 64, tru
 template __global__ void gemm_mfma_kernel<128, 64, 2, 2, 3, true, true, 64, true>(GemmArgs, int, int);
 template __global__ void gemm_mfma_kernel<128, 128, 2, 2, 4, true, true, 32, true>(GemmArgs, int, int);
 template __global__ void gemm_mfma_kernel<128, 128, 2, 2, 4, true, true, 32, false>(GemmArgs, int, int);
+// two micro-batches' sums into one accumulator (EPI_SEGACC)
+template __global__ void gemm_mfma_kernel<128, 128, 2, 2, 4, true, true, 32, true, false, 2>(GemmArgs, int, int);
+template __global__ void gemm_mfma_kernel<128, 128, 2, 2, 4, true, true, 32, false, false, 2>(GemmArgs, int, int);
+template __global__ void gemm_mfma_kernel<128, 64, 2, 2, 3, true, true, 64, true, false, 2>(GemmArgs, int, int);
+template __global__ void gemm_mfma_kernel<128, 64, 2, 2, 3, true, true, 64, false, false, 2>(GemmArgs, int, int);
 #define DAPPLE_GEMM_INST_KT(BM, BN, WGM, WGN, NS, BK)                                                                  \
   template __global__ void gemm_mfma_kernel<BM, BN, WGM, WGN, NS, false, false, BK, false, true>(GemmArgs, int, int); \
   template __global__ void gemm_mfma_kernel<BM, BN, WGM, WGN, NS, false, true, BK, false, true>(GemmArgs, int, int);  \
@@ -738,10 +782,10 @@ DAPPLE_GEMM_INST_KT(128, 64, 2, 2, 3, 64)
 #undef DAPPLE_GEMM_INST
 
 // ------------------------------------------------------------------ host side
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS = false, bool KT = false>
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS = false, bool KT = false, int NSEG = 1>
 static hipError_t launch_mfma(const GemmArgs& g, hipStream_t st) {
-  typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT> CFG;
-  auto kern = gemm_mfma_kernel<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT>;
+  typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, NSEG> CFG;
+  auto kern = gemm_mfma_kernel<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT, NSEG>;
   // once per instantiation, whichever host thread comes first (initialisation of a function-local static is
   // thread-safe)
   static const hipError_t attr_rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -807,6 +851,7 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
   if ((g.epi & EPI_BIAS) && !aligned_to(g.bias, 8)) return false;
   if ((g.epi & EPI_GELU) && !aligned_to(g.C2, 8)) return false;
   if ((g.epi & EPI_BSUM) && !(g.a_kstrided && g.b_kstrided && g.batch <= 4)) return false;
+  if ((g.epi & EPI_SEGACC) && !((g.epi & EPI_ACC32) && g.a_kstrided && g.b_kstrided && g.K == 2 * g.kseg_len)) return false;
   return true;
 }
 
@@ -819,6 +864,13 @@ hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st) {
     const long t256 = (long)((g.M + 255) / 256) * ((g.N + 255) / 256) * g.batch;
     const bool tt = g.a_kstrided && g.b_kstrided;   // the weight-gradient layout
     const bool bsum = (g.epi & EPI_BSUM) != 0;      // (offered for that layout only: checked above)
+    if (g.epi & EPI_SEGACC) {   // tiles 5 and 4 (see below) with a second set of accumulators
+      if (t128 >= 192)
+        return bsum ? launch_mfma<128, 128, 2, 2, 4, true, true, 32, true, false, 2>(g, st)
+                    : launch_mfma<128, 128, 2, 2, 4, true, true, 32, false, false, 2>(g, st);
+      return bsum ? launch_mfma<128, 64, 2, 2, 3, true, true, 64, true, false, 2>(g, st)
+                  : launch_mfma<128, 64, 2, 2, 3, true, true, 64, false, false, 2>(g, st);
+    }
     const bool short_k = g.kseg_len % 64 != 0 && !tt;
     // Tile choice.  Every k-tile goes global -> LDS through the compute unit's vector cache at 64 bytes per
     // clock, and from LDS to the waves at 128 bytes per clock, against 4096 MFMA flops per clock.  A 128x128

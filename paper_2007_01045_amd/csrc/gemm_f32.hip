@@ -106,6 +106,32 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, int tiles_n) 
   ta.store(fsm, tid);
   tb.store(fsm + TA::FLOATS, tid);
   __syncthreads();
+  const bool segacc = (g.epi & EPI_SEGACC) != 0;
+  const long zc = z * g.sC, zb = z * g.sBias;
+  auto finish = [&]() {   // add the column sums and store the tile
+    if (do_cs) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const float t = cs[j] + __shfl_xor(cs[j], 32, 64);
+        const int col = n0 + wn0 + 32 * j + l31;
+        if (h == 0 && col < g.N) bs[col] += t;
+        cs[j] = 0.f;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int row = m0 + wm0 + 32 * i + l31;
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int col = n0 + wn0 + 32 * j + 8 * q + 4 * h;
+          if (row < g.M && col < g.N)
+            epilogue_store4(g, zc, zb, row, col,
+                            f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]});
+        }
+    }
+  };
   for (int t = 0; t < nt; ++t) {
     const float *SA = fsm + (t & 1) * STAGE, *SB = SA + TA::FLOATS;
     const bool more = t + 1 < nt;
@@ -135,30 +161,17 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, int tiles_n) 
       tb.store(nb + TA::FLOATS, tid);
     }
     __syncthreads();
-  }
-  if (do_cs) {
+    if (segacc && more && (t + 1) % per_seg == 0) {   // a segment's sum is complete: it goes to C on its own
+      finish();
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const float t = cs[j] + __shfl_xor(cs[j], 32, 64);
-      const int col = n0 + wn0 + 32 * j + l31;
-      if (h == 0 && col < g.N) bs[col] += t;
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
     }
   }
-  const long zc = z * g.sC, zb = z * g.sBias;
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int row = m0 + wm0 + 32 * i + l31;
-    if (row >= g.M) continue;
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int col = n0 + wn0 + 32 * j + 8 * q + 4 * h;
-        if (col >= g.N) continue;
-        epilogue_store4(g, zc, zb, row, col,
-                        f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]});
-      }
-  }
+  finish();
 }
 
 // ------------------------------------------------------------------ few tiles: K split over the waves
@@ -178,83 +191,89 @@ __global__ __launch_bounds__(256) void gemm_f32_small(GemmArgs g, int tiles_n) {
   }
   float* const bs = (g.epi & EPI_BSUM) ? pick4(g.bsum_z, z) : nullptr;
   const int klen = g.K > g.kseg_len ? g.kseg_len : min(g.K, g.k_valid);
-  const int per_seg = (g.kseg_len + 15) / 16, nc = g.K / g.kseg_len * per_seg;
-  f32x4 acc[TW][TW];
-  float cs[TW];
+  const int per_seg = (g.kseg_len + 15) / 16, nseg = g.K / g.kseg_len;
+  // EPI_SEGACC: the segments one after the other, each added to C; else all of them as one sum
+  const bool segacc = (g.epi & EPI_SEGACC) != 0;
+  const int nc = segacc ? per_seg : nseg * per_seg;
+  for (int turn = 0; turn < (segacc ? nseg : 1); ++turn, A += g.segA, B += g.segB) {
+    f32x4 acc[TW][TW];
+    float cs[TW];
 #pragma unroll
-  for (int i = 0; i < TW; ++i) {
-    cs[i] = 0.f;
+    for (int i = 0; i < TW; ++i) {
+      cs[i] = 0.f;
 #pragma unroll
-    for (int j = 0; j < TW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  // rows l15 of the 16-row block at r0, k = k0 + 4 q4 + 0..3
-  auto fetch = [&](const float* X, int ld, bool ks, int r, int rows, int k0) {
-    const int k = k0 + 4 * q4;
-    f32x4 v{0.f, 0.f, 0.f, 0.f};
-    if (r < rows) {
-      if (!ks) {
-        if (k < klen) v = *(const f32x4*)(X + (long)r * ld + k);   // klen is a multiple of 4 here
-      } else {
+      for (int j = 0; j < TW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    // rows l15 of the 16-row block at r0, k = k0 + 4 q4 + 0..3
+    auto fetch = [&](const float* X, int ld, bool ks, int r, int rows, int k0) {
+      const int k = k0 + 4 * q4;
+      f32x4 v{0.f, 0.f, 0.f, 0.f};
+      if (r < rows) {
+        if (!ks) {
+          if (k < klen) v = *(const f32x4*)(X + (long)r * ld + k);   // klen is a multiple of 4 here
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (k + e < klen) v[e] = X[(long)(k + e) * ld + r];
+        }
+      }
+      return v;
+    };
+    constexpr int U = TW == 1 ? 8 : 4;   // 16-wide pieces of K whose loads are in flight together
+    for (int c0 = wave; c0 < nc; c0 += 4 * U) {
+      f32x4 a[U][TW], b[U][TW];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int c = c0 + 4 * u, seg = c / per_seg, k0 = c < nc ? (c - seg * per_seg) * 16 : klen;
+        const float *As = A + (c < nc ? seg : 0) * g.segA, *Bs = B + (c < nc ? seg : 0) * g.segB;
+#pragma unroll
+        for (int i = 0; i < TW; ++i) {
+          a[u][i] = fetch(As, g.lda, AKS, m0 + 16 * i + l15, g.m_valid, k0);
+          b[u][i] = fetch(Bs, g.ldb, BKS, n0 + 16 * i + l15, g.n_valid, k0);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (k + e < klen) v[e] = X[(long)(k + e) * ld + r];
+#pragma unroll
+          for (int i = 0; i < TW; ++i)
+#pragma unroll
+            for (int j = 0; j < TW; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[u][j][e], a[u][i][e], acc[i][j], 0, 0, 0);
+        if (bs) {
+#pragma unroll
+          for (int j = 0; j < TW; ++j) cs[j] += (b[u][j][0] + b[u][j][1]) + (b[u][j][2] + b[u][j][3]);
+        }
       }
     }
-    return v;
-  };
-  constexpr int U = TW == 1 ? 8 : 4;   // 16-wide pieces of K whose loads are in flight together
-  for (int c0 = wave; c0 < nc; c0 += 4 * U) {
-    f32x4 a[U][TW], b[U][TW];
+    if (turn) __syncthreads();   // the partial tiles of the segment before have been read
+    // acc[i][j]: row 16 i + l15, columns 16 j + 4 q4 + 0..3
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int c = c0 + 4 * u, seg = c / per_seg, k0 = c < nc ? (c - seg * per_seg) * 16 : klen;
-      const float *As = A + (c < nc ? seg : 0) * g.segA, *Bs = B + (c < nc ? seg : 0) * g.segB;
+    for (int i = 0; i < TW; ++i)
 #pragma unroll
-      for (int i = 0; i < TW; ++i) {
-        a[u][i] = fetch(As, g.lda, AKS, m0 + 16 * i + l15, g.m_valid, k0);
-        b[u][i] = fetch(Bs, g.ldb, BKS, n0 + 16 * i + l15, g.n_valid, k0);
+      for (int j = 0; j < TW; ++j) *(f32x4*)(part[wave] + (16 * i + l15) * LD + 16 * j + 4 * q4) = acc[i][j];
+    if (bs && tm == 0) {
+#pragma unroll
+      for (int j = 0; j < TW; ++j) {
+        float t = cs[j];
+        t += __shfl_xor(t, 16, 64);
+        t += __shfl_xor(t, 32, 64);
+        if (q4 == 0) cpart[wave][16 * j + l15] = t;
       }
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int i = 0; i < TW; ++i)
-#pragma unroll
-          for (int j = 0; j < TW; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[u][j][e], a[u][i][e], acc[i][j], 0, 0, 0);
-      if (bs) {
-#pragma unroll
-        for (int j = 0; j < TW; ++j) cs[j] += (b[u][j][0] + b[u][j][1]) + (b[u][j][2] + b[u][j][3]);
-      }
+    __syncthreads();
+    if (bs && tm == 0 && tid < BT && n0 + tid < g.N)
+      bs[n0 + tid] += ((cpart[0][tid] + cpart[1][tid]) + cpart[2][tid]) + cpart[3][tid];
+    const long zc = z * g.sC, zb = z * g.sBias;
+    for (int i = tid * 4; i < BT * BT; i += 1024) {
+      const int r = i / BT, c = i % BT, row = m0 + r, col = n0 + c;
+      if (row >= g.M || col >= g.N) continue;
+      const int o = r * LD + c;
+      const f32x4 p0 = *(const f32x4*)(part[0] + o), p1 = *(const f32x4*)(part[1] + o), p2 = *(const f32x4*)(part[2] + o),
+                  p3 = *(const f32x4*)(part[3] + o);
+      epilogue_store4(g, zc, zb, row, col, ((p0 + p1) + p2) + p3);
     }
-  }
-  // acc[i][j]: row 16 i + l15, columns 16 j + 4 q4 + 0..3
-#pragma unroll
-  for (int i = 0; i < TW; ++i)
-#pragma unroll
-    for (int j = 0; j < TW; ++j) *(f32x4*)(part[wave] + (16 * i + l15) * LD + 16 * j + 4 * q4) = acc[i][j];
-  if (bs && tm == 0) {
-#pragma unroll
-    for (int j = 0; j < TW; ++j) {
-      float t = cs[j];
-      t += __shfl_xor(t, 16, 64);
-      t += __shfl_xor(t, 32, 64);
-      if (q4 == 0) cpart[wave][16 * j + l15] = t;
-    }
-  }
-  __syncthreads();
-  if (bs && tm == 0 && tid < BT && n0 + tid < g.N)
-    bs[n0 + tid] += ((cpart[0][tid] + cpart[1][tid]) + cpart[2][tid]) + cpart[3][tid];
-  const long zc = z * g.sC, zb = z * g.sBias;
-  for (int i = tid * 4; i < BT * BT; i += 1024) {
-    const int r = i / BT, c = i % BT, row = m0 + r, col = n0 + c;
-    if (row >= g.M || col >= g.N) continue;
-    const int o = r * LD + c;
-    const f32x4 p0 = *(const f32x4*)(part[0] + o), p1 = *(const f32x4*)(part[1] + o), p2 = *(const f32x4*)(part[2] + o),
-                p3 = *(const f32x4*)(part[3] + o);
-    epilogue_store4(g, zc, zb, row, col, ((p0 + p1) + p2) + p3);
   }
 }
 

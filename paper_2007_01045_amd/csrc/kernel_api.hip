@@ -111,7 +111,7 @@ int dapple_layernorm_bwd(int dtype, const void* dy, const void* z, const float* 
   if (bad_dtype(dtype) || !ln_shape_ok(dtype, rows, H)) return STAGE_E_CONFIG;
   int nblk = 0;
   hipError_t e = launch_ln_bwd(dtype == STAGE_DTYPE_BF16 ? DT_BF16 : DT_F32, dy, z, false, stats, gamma, dz, partial, &nblk,
-                               rows, H, (hipStream_t)stream);
+                               rows, H, 1, (hipStream_t)stream);
   if (e != hipSuccess) return STAGE_E_DEVICE;
   return dev_rc(launch_partial_reduce(partial, nblk, 3, H, dgamma, dbeta, dbias, (hipStream_t)stream));
 }

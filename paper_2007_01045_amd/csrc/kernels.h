@@ -28,7 +28,10 @@ enum GemmEpi {
   // rowdot[j*M + m] = sum over the 32 columns n of block j of C[m,n] (as stored, rounded to bf16) * aux[m,n];
   // aux is neither added nor multiplied in.  MFMA kernel only, bf16 output, batch 1.  (The attention
   // backward's delta = rowsum(dctx o ctx) per head leaves the product that makes dctx this way.)
-  EPI_ROWDOT = 256
+  EPI_ROWDOT = 256,
+  // with EPI_ACC32, both operands k-strided: every K segment's sum is added to C (and with EPI_BSUM to bsum) on its
+  // own, in segment order -- the bits of one accumulating product per segment.  The MFMA kernel takes two segments.
+  EPI_SEGACC = 512
 };
 
 struct GemmArgs {
@@ -107,9 +110,10 @@ hipError_t launch_ln_fwd(Dtype dt, const void* z, bool z_f32, const void* gamma,
                          float* y32, float* stats, int rows, int H, float eps, hipStream_t st);
 // dz = LN backward; partial[(blk*3 + {0,1,2})*H + c] = block partial sums of
 // dy*xhat (dgamma), dy (dbeta), dz (bias of the linear that produced z).
-// Returns the number of partial blocks through *nblk.
+// Returns the number of partial blocks through *nblk.  nmb micro-batches of `rows` rows each lie one behind the
+// other; each has its own *nblk blocks.
 hipError_t launch_ln_bwd(Dtype dt, const void* dy, const void* z, bool z_f32, const float* stats,
-                         const void* gamma, void* dz, float* partial, int* nblk, int rows, int H,
+                         const void* gamma, void* dz, float* partial, int* nblk, int rows, int H, int nmb,
                          hipStream_t st);
 // o_v[c] += sum over blk (ascending) of partial[(blk*nvec + v)*H + c], v < nvec <= 3;
 // a NULL o_v is skipped
@@ -123,7 +127,8 @@ hipError_t launch_colsum(Dtype dt, const void* X, int rows, int cols, int ld, fl
 hipError_t launch_colsum_partials(Dtype dt, const void* X, int rows, int cols, int ld, float* partial, int nb, long zs_x,
                                   int* nblk, int* PS_out, hipStream_t st);
 // out[c] += sum over blk (ascending, in the order of launch_partial_reduce) of partial[blk*stride + c], c < cols,
-// for up to 12 such jobs in one launch
+// for up to 12 such jobs in one launch.  nmb > 1: the same for partial + mb_stride, partial + 2 mb_stride, ..., one
+// micro-batch's sum after the other
 struct ReduceJob {
   const float* partial;
   float* out;
@@ -133,6 +138,8 @@ struct ReduceJob {
 struct ReduceJobs {
   ReduceJob j[12];
   int n;
+  int nmb;          // 0 counts as 1
+  long mb_stride;
 };
 hipError_t launch_reduce_jobs(const ReduceJobs& J, hipStream_t st);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t st);
@@ -142,23 +149,27 @@ hipError_t launch_zero(void* dst, size_t bytes, hipStream_t st);
 // e[r] = E_w[ids[r]] + E_p[r % s]
 hipError_t launch_embed_gather(Dtype dt, const int32_t* ids, const void* Ew, const void* Ep, void* e, int rows, int s,
                                int H, int vocab, hipStream_t st);
+// for each of the nmb micro-batches of b sequences, one after the other:
 // dEw[id] += sum over rows r with ids[r] == id (ascending r) of de[r];
 // dEp[p] += sum over the b sequences of de[bi*s + p]
 hipError_t launch_embed_bwd(Dtype dt, const int32_t* ids, const void* de, float* dEw, float* dEp, int b, int s, int H,
-                            int vocab, hipStream_t st);
+                            int vocab, int nmb, hipStream_t st);
 // rows_idx / tgt [np], np >= cap: the rows with target >= 0 in ascending order, at most cap of them
 // (-1 / 0 in every other entry); info[0] = count, info[1] set to 1 if more than cap rows are predicted
-hipError_t launch_mlm_compact(const int32_t* targets, int T, int cap, int np, int vocab, int32_t* rows_idx,
+// (nmb micro-batches: targets T apart, rows_idx and tgt np apart; the indices count within a micro-batch)
+hipError_t launch_mlm_compact(const int32_t* targets, int T, int nmb, int cap, int np, int vocab, int32_t* rows_idx,
                               int32_t* tgt, int32_t* info, hipStream_t st);
 // dst[i] = src[idx[i]] (zero row if idx[i] is outside [0, nsrc)); dst[idx[i]] = src[i]
-hipError_t launch_gather_rows(Dtype dt, const void* src, const int32_t* idx, void* dst, int n, int H, int nsrc,
+// (for nmb micro-batches of n gathered and nsrc / ndst full rows)
+hipError_t launch_gather_rows(Dtype dt, const void* src, const int32_t* idx, void* dst, int n, int H, int nsrc, int nmb,
                               hipStream_t st);
-hipError_t launch_scatter_rows(Dtype dt, const void* src, const int32_t* idx, void* dst, int n, int H, int ndst,
+hipError_t launch_scatter_rows(Dtype dt, const void* src, const int32_t* idx, void* dst, int n, int H, int ndst, int nmb,
                                hipStream_t st);
-// logits fp32 [n, VP] (+ bias over v < V) -> dz [n, VP], row_loss [n], loss_out[0] = loss_scale * sum(row_loss)
+// logits fp32 [n, VP] (+ bias over v < V) -> dz [n, VP], row_loss [n]
 hipError_t launch_mlm_ce(Dtype dt, const float* logits, const void* bias, const int32_t* rows_idx, const int32_t* tgt,
-                         int n, int V, int VP, float loss_scale, void* dz, float* row_loss, float* loss_out,
-                         hipStream_t st);
+                         int n, int V, int VP, float loss_scale, void* dz, float* row_loss, hipStream_t st);
+// loss_out[i] = scale * (sum of row_loss[i*n .. i*n + n - 1]), i < nmb
+hipError_t launch_loss_sum(const float* row_loss, int n, int nmb, float scale, float* loss_out, hipStream_t st);
 hipError_t launch_mul(Dtype dt, const void* a, const void* b, void* c, long n, hipStream_t st);
 
 // ---------------------------------------------------------------- weight update

@@ -123,6 +123,14 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const T* __restrict__ dy, c
                                                      const float* __restrict__ stats, const T* __restrict__ gamma,
                                                      T* __restrict__ dz, float* __restrict__ partial, int rows, int H) {
   constexpr int V = Vec<T>::N;
+  {  // micro-batch blockIdx.y: its rows, and its own partial sums
+    const long r0 = (long)blockIdx.y * rows;
+    dy += r0 * H;
+    z = (const char*)z + r0 * H * (Z32 ? 4 : sizeof(T));
+    stats += 2 * r0;
+    dz += r0 * H;
+    partial += (long)blockIdx.y * gridDim.x * 3 * H;
+  }
   extern __shared__ __attribute__((aligned(16))) float red[];  // [4 waves][3][H]
   int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float pg[NCH][V], pb[NCH][V], pz[NCH][V], g[NCH][V];
@@ -258,35 +266,43 @@ __global__ __launch_bounds__(256) void partial_reduce_kernel(const float* __rest
 }
 
 // Several partial_reduce jobs in one launch (blockIdx.y = job): the summation of a job is that of
-// partial_reduce_kernel, addition for addition.
-__global__ __launch_bounds__(256) void reduce_jobs_kernel(ReduceJobs J) {
-  __shared__ float red[4][64];
+// partial_reduce_kernel, addition for addition, and with several micro-batches each one's sum is added to the output
+// on its own, in order.  Four waves per micro-batch, up to four micro-batches at a time.
+__global__ __launch_bounds__(1024) void reduce_jobs_kernel(ReduceJobs J) {
+  __shared__ float red[16][64];
   const ReduceJob& job = J.j[blockIdx.y];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3, grp = threadIdx.x >> 8, ngrp = blockDim.x >> 8;
   const int c = blockIdx.x * 64 + lane;
   if (blockIdx.x * 64 >= job.cols) return;   // the whole workgroup: no barrier is skipped by part of it
-  float t = 0.f;
-  if (c < job.cols) {
-    const float* p = job.partial + c;
-    const long stride = job.stride;
-    const int nblk = job.nblk;
-    int b = w;
-    for (; b + 28 < nblk; b += 32) {
-      float x[8];
+  for (int i0 = 0; i0 < J.nmb; i0 += ngrp) {
+    float t = 0.f;
+    if (c < job.cols && i0 + grp < J.nmb) {
+      const float* p = job.partial + (i0 + grp) * J.mb_stride + c;
+      const long stride = job.stride;
+      const int nblk = job.nblk;
+      int b = w;
+      for (; b + 28 < nblk; b += 32) {
+        float x[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) x[u] = p[(long)(b + 4 * u) * stride];
+        for (int u = 0; u < 8; ++u) x[u] = p[(long)(b + 4 * u) * stride];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) t += x[u];
+        for (int u = 0; u < 8; ++u) t += x[u];
+      }
+      for (; b < nblk; b += 4) t += p[(long)b * stride];
     }
-    for (; b < nblk; b += 4) t += p[(long)b * stride];
-  }
-  red[w][lane] = t;
-  __syncthreads();
-  if (w == 0 && c < job.cols) {
-    float r = red[0][lane] + red[1][lane];
-    r += red[2][lane];
-    r += red[3][lane];
-    job.out[c] += r;
+    red[grp * 4 + w][lane] = t;
+    __syncthreads();
+    if (threadIdx.x < 64 && c < job.cols) {
+      float o = job.out[c];
+      for (int q = 0; q < ngrp && i0 + q < J.nmb; ++q) {
+        float r = red[4 * q][lane] + red[4 * q + 1][lane];
+        r += red[4 * q + 2][lane];
+        r += red[4 * q + 3][lane];
+        o += r;
+      }
+      job.out[c] = o;
+    }
+    __syncthreads();
   }
 }
 
@@ -380,7 +396,7 @@ hipError_t launch_ln_fwd(Dtype dt, const void* z, bool z_f32, const void* gamma,
 
 template <typename T, int N, bool Z32>
 static hipError_t ln_bwd_launch(const void* dy, const void* z, const float* stats, const void* g, void* dz,
-                                float* partial, int nb, int rows, int H, hipStream_t st) {
+                                float* partial, int nb, int rows, int H, int nmb, hipStream_t st) {
   // up to 96 KiB of LDS for the widest rows; set once per instantiation by whichever host thread comes first
   // (initialisation of a function-local static is thread-safe)
   static const hipError_t attr_rc = hipFuncSetAttribute((const void*)ln_bwd_kernel<T, N, Z32>,
@@ -388,28 +404,28 @@ static hipError_t ln_bwd_launch(const void* dy, const void* z, const float* stat
                                                         12 * 64 * Vec<T>::N * N * 4);
   if (attr_rc != hipSuccess) return attr_rc;
   size_t sh = (size_t)12 * H * sizeof(float);
-  hipLaunchKernelGGL((ln_bwd_kernel<T, N, Z32>), dim3(nb), dim3(256), sh, st, (const T*)dy, z, stats, (const T*)g,
+  hipLaunchKernelGGL((ln_bwd_kernel<T, N, Z32>), dim3(nb, nmb), dim3(256), sh, st, (const T*)dy, z, stats, (const T*)g,
                      (T*)dz, partial, rows, H);
   return hipGetLastError();
 }
 
 template <typename T, bool Z32>
 static hipError_t ln_bwd_t(const void* dy, const void* z, const float* stats, const void* g, void* dz,
-                           float* partial, int nb, int rows, int H, hipStream_t st) {
+                           float* partial, int nb, int rows, int H, int nmb, hipStream_t st) {
   int n = nch_for<T>(H);
-  if (n <= 1) return ln_bwd_launch<T, 1, Z32>(dy, z, stats, g, dz, partial, nb, rows, H, st);
-  if (n <= 2) return ln_bwd_launch<T, 2, Z32>(dy, z, stats, g, dz, partial, nb, rows, H, st);
-  if (n <= 4) return ln_bwd_launch<T, 4, Z32>(dy, z, stats, g, dz, partial, nb, rows, H, st);
+  if (n <= 1) return ln_bwd_launch<T, 1, Z32>(dy, z, stats, g, dz, partial, nb, rows, H, nmb, st);
+  if (n <= 2) return ln_bwd_launch<T, 2, Z32>(dy, z, stats, g, dz, partial, nb, rows, H, nmb, st);
+  if (n <= 4) return ln_bwd_launch<T, 4, Z32>(dy, z, stats, g, dz, partial, nb, rows, H, nmb, st);
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_ln_bwd(Dtype dt, const void* dy, const void* z, bool z_f32, const float* stats, const void* gamma,
-                         void* dz, float* partial, int* nblk, int rows, int H, hipStream_t st) {
+                         void* dz, float* partial, int* nblk, int rows, int H, int nmb, hipStream_t st) {
   int nb = (rows + LNB_ROWS - 1) / LNB_ROWS;
   *nblk = nb;
-  if (dt != DT_BF16) return ln_bwd_t<float, false>(dy, z, stats, gamma, dz, partial, nb, rows, H, st);
-  return z_f32 ? ln_bwd_t<bf16, true>(dy, z, stats, gamma, dz, partial, nb, rows, H, st)
-               : ln_bwd_t<bf16, false>(dy, z, stats, gamma, dz, partial, nb, rows, H, st);
+  if (dt != DT_BF16) return ln_bwd_t<float, false>(dy, z, stats, gamma, dz, partial, nb, rows, H, nmb, st);
+  return z_f32 ? ln_bwd_t<bf16, true>(dy, z, stats, gamma, dz, partial, nb, rows, H, nmb, st)
+               : ln_bwd_t<bf16, false>(dy, z, stats, gamma, dz, partial, nb, rows, H, nmb, st);
 }
 
 hipError_t launch_partial_reduce(const float* partial, int nblk, int nvec, int H, float* o0, float* o1, float* o2,
@@ -461,7 +477,9 @@ hipError_t launch_reduce_jobs(const ReduceJobs& J, hipStream_t st) {
   int maxc = 0;
   for (int i = 0; i < J.n; ++i) maxc = J.j[i].cols > maxc ? J.j[i].cols : maxc;
   dim3 grid((maxc + 63) / 64, J.n);
-  hipLaunchKernelGGL(reduce_jobs_kernel, grid, dim3(256), 0, st, J);
+  ReduceJobs K = J;
+  if (K.nmb < 1) K.nmb = 1;
+  hipLaunchKernelGGL(reduce_jobs_kernel, grid, dim3(256 * (K.nmb < 4 ? K.nmb : 4)), 0, st, K);
   return hipGetLastError();
 }
 

@@ -6,6 +6,7 @@
 // in gemm.hip, attention.hip, rowops.hip, embed_head.hip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -55,9 +56,20 @@ const char* const kClassNames[KC_COUNT] = {"gemm_fwd", "gemm_dgrad", "gemm_wgrad
 struct LayerParams {
   size_t Wq, bq, Wk, bk, Wv, bv, Wo, bo, ln1g, ln1b, W1, b1, W2, b2, ln2g, ln2b;
 };
-// byte offsets of one layer's stash inside an activation slot
+// one tensor of the activation slots: the slots' copies lie one behind the other (sz bytes each, no gap), so that
+// the rows of micro-batches in consecutive slots are the rows of one taller matrix
+struct Tensor {
+  size_t off = 0, sz = 0;
+};
+// a layer's tensors
 struct LayerStash {
-  size_t qkv, lse, ctx, ctx32, z1, st1, y1, gp, g, z2, st2, y;
+  Tensor q, k, v, lse, ctx, ctx32, z1, st1, y1, gp, g, z2, st2, y;
+};
+// the activations of a run of consecutive slots, seen from the first of them
+struct Act {
+  char* base;
+  int slot;
+  char* operator()(const Tensor& t) const { return base + t.off + (size_t)slot * t.sz; }
 };
 
 struct Layout {
@@ -67,11 +79,11 @@ struct Layout {
   std::vector<LayerParams> lp;
   size_t hWt = 0, hbt = 0, hG = 0, hB = 0, hEout = 0, hbout = 0;
   // slot
-  size_t slot_x0 = 0, slot_ids = 0, slot_embsum = 0, slot_embst = 0;
+  Tensor slot_x0, slot_ids, slot_embsum, slot_embst;
   std::vector<LayerStash> ls;
   // masked-LM head: NP gathered rows (multiple of 64), VP padded vocabulary (multiple of 64)
   int NP = 0, VP = 0;
-  size_t sh_rows = 0, sh_tgt = 0, sh_r = 0, sh_gl = 0, sh_glp = 0, sh_st = 0, sh_t = 0, sh_dz = 0;
+  Tensor sh_rows, sh_tgt, sh_r, sh_gl, sh_glp, sh_st, sh_t, sh_dz;
   size_t wh_logits = 0, wh_rowloss = 0, wh_dt = 0, wh_dgl = 0, wh_dh = 0, wh_dr = 0, wh_dyfull = 0, wh_part = 0,
          wh_part_cz = 0, wh_info = 0;
   size_t wh_logits2 = 0, wh_rowloss2 = 0, wh_info2 = 0;  // second set: the forward re-run inside a backward task
@@ -87,13 +99,16 @@ struct Layout {
   int ws_copies = 1;
   size_t act_bytes = 0, st_x = 0, st_aux = 0, ws_act = 0, ws_ydummy = 0, arena_fwd_act = 0;
   // workspace (bytes)
-  // buffers the side stream reads exist twice (layers alternate between the sets)
   size_t ws_dx[2] = {0, 0}, ws_dy1 = 0, ws_dctx = 0, ws_delta = 0, ws_head = 0;
   // what the side stream reads of a layer's backward (one set per layer: the backward chain of a task never
   // waits for the side stream before its end)
-  struct SideSet { size_t dz2, du, dz1, dqkv, part_ln2, part_ln1; };
+  struct SideSet { size_t dz2, du, dz1, dq, dk, dv, part_ln2, part_ln1; };
   std::vector<SideSet> ws_side;
-  size_t workspace_bytes = 0;
+  size_t workspace_bytes = 0;   // of one micro-batch's task
+  // Micro-batches whose tasks may go out as one set of launches (see stage_run_schedule); the workspace holds that
+  // many: ws_stride bytes per lane
+  int group = 1;
+  size_t ws_stride = 0;
   // arena
   size_t grad_bytes = 0, arena_grads = 0, arena_slots = 0, arena_ws = 0, arena_bytes = 0;
 };
@@ -121,6 +136,19 @@ int check_config(const stage_config& c) {
   return STAGE_OK;
 }
 
+// How many micro-batches may share a set of launches: enough for 8192 token rows, at most 8.  A micro-batch of 1024 or
+// 2048 tokens is too little for 256 compute units: its products have 2-17 GFLOP, which leaves the 9-14 us a launch
+// costs before and after its k-loop standing, and on the smallest stages the host's 5 us per launch are the time.
+// Iteration times at 1 / 2 / 4 micro-batches per set of launches: 6 layers of 1024, 2048 tokens 14.7 / 12.9 / 12.8 ms;
+// 12 layers, 1024 tokens 40.7 / 30.1 / 29.7 ms; 768 wide, 600 tokens 3.7 / - / 2.3 ms (3 at a time); the tiny
+// configuration 0.95 / 0.49 ms.  A micro-batch of 8192 rows fills the chip by itself.
+int group_limit(const stage_config& c) {
+  if ((c.flags & STAGE_FLAG_RECOMPUTE) || c.max_slots < 2) return 1;   // re-computation keeps ONE set of activations per lane
+  const long T = (long)c.micro_batch * c.seq;
+  long g = 8192 / T;
+  return (int)(g < 1 ? 1 : (g > 8 ? 8 : g));
+}
+
 void build_layout(const stage_config& c, Layout& L) {
   const size_t H = c.hidden, F = c.ffn, T = (size_t)c.micro_batch * c.seq, E = c.dtype == STAGE_DTYPE_BF16 ? 2 : 4;
   const size_t V = c.vocab, P = c.max_pos;
@@ -141,8 +169,15 @@ void build_layout(const stage_config& c, Layout& L) {
   L.n_params = off;
 
   // activation slot: what F_m leaves for B_m
-  size_t so = 0;
-  auto stake = [&](size_t bytes) { size_t o = so; so += align_up(bytes); return o; };
+  L.recompute = (c.flags & STAGE_FLAG_RECOMPUTE) != 0;
+  const size_t copies = L.recompute ? 1 : c.max_slots;
+  size_t so = 0, sall = 0;
+  auto stake = [&](size_t bytes) {
+    Tensor t{sall, bytes};
+    so += align_up(bytes);
+    sall += align_up(bytes * copies);   // never more than copies * align_up(bytes)
+    return t;
+  };
   const size_t U = T * H * E;
   if (c.has_embedding) {
     L.slot_ids = stake(T * 4); L.slot_embsum = stake(U); L.slot_embst = stake(2 * T * 4);
@@ -151,13 +186,13 @@ void build_layout(const stage_config& c, Layout& L) {
   L.ls.resize(c.n_layers);
   for (int l = 0; l < c.n_layers; ++l) {
     auto& s = L.ls[l];
-    s.qkv = stake(3 * U);   // q, k, v contiguous (3U is a multiple of 256 whenever U is)
+    s.q = stake(U); s.k = stake(U); s.v = stake(U);
     s.lse = stake((size_t)c.micro_batch * c.n_heads * c.seq * 4);
     // z1, z2 (the pre-LayerNorm sums = the residual stream) are fp32 whatever the stage dtype
-    s.ctx = stake(U); s.ctx32 = c.dtype == STAGE_DTYPE_BF16 ? stake(T * H * 4) : 0; s.z1 = stake(T * H * 4); s.st1 = stake(2 * T * 4); s.y1 = stake(U);
+    s.ctx = stake(U); s.ctx32 = c.dtype == STAGE_DTYPE_BF16 ? stake(T * H * 4) : Tensor{}; s.z1 = stake(T * H * 4); s.st1 = stake(2 * T * 4); s.y1 = stake(U);
     s.gp = stake(T * F * E); s.g = stake(T * F * E); s.z2 = stake(T * H * 4); s.st2 = stake(2 * T * 4);
     bool keep_y = l + 1 < c.n_layers || c.has_mlm_head;
-    s.y = keep_y ? stake(U) : 0;
+    s.y = keep_y ? stake(U) : Tensor{};
   }
   if (c.has_mlm_head) {
     int cap = c.mlm_max_rows > 0 && c.mlm_max_rows < (int)T ? c.mlm_max_rows : (int)T;
@@ -168,7 +203,6 @@ void build_layout(const stage_config& c, Layout& L) {
     L.sh_glp = stake(NP * H * E); L.sh_st = stake(2 * NP * 4); L.sh_t = stake(NP * H * E); L.sh_dz = stake(NP * VP * E);
   }
   L.act_bytes = so;
-  L.recompute = (c.flags & STAGE_FLAG_RECOMPUTE) != 0;
   if (L.recompute) {
     size_t st = 0;
     L.st_x = st; st += align_up(c.has_embedding ? T * 4 : U);
@@ -178,8 +212,10 @@ void build_layout(const stage_config& c, Layout& L) {
     L.slot_bytes = so;
   }
 
-  size_t wo = 0;
-  auto wtake = [&](size_t bytes) { size_t o = wo; wo += align_up(bytes); return o; };
+  L.group = group_limit(c);
+  const size_t G = L.group;
+  size_t wo = 0, w1 = 0;
+  auto wtake = [&](size_t bytes) { size_t o = wo; wo += align_up(bytes * G); w1 += align_up(bytes); return o; };
   L.ws_dx[0] = wtake(U); L.ws_dx[1] = wtake(U); L.ws_dy1 = wtake(U); L.ws_dctx = wtake(U);
   // delta of the attention backward: [b, A, s], or one row sum per block of 32 columns, [ceil(H/32)][T]
   L.ws_delta = wtake(std::max((size_t)c.micro_batch * c.n_heads * c.seq, (size_t)((c.hidden + 31) / 32) * T) * 4);
@@ -191,7 +227,8 @@ void build_layout(const stage_config& c, Layout& L) {
   const size_t ln_part = ((T + 7) / 8) * 3 * H * 4;
   L.ws_side.resize(c.n_layers);
   for (auto& ss : L.ws_side) {
-    ss.dz2 = wtake(U); ss.du = wtake(T * F * E); ss.dz1 = wtake(U); ss.dqkv = wtake(3 * U);
+    ss.dz2 = wtake(U); ss.du = wtake(T * F * E); ss.dz1 = wtake(U);
+    ss.dq = wtake(U); ss.dk = wtake(U); ss.dv = wtake(U);
     ss.part_ln2 = wtake(ln_part); ss.part_ln1 = wtake(ln_part);
   }
   if (c.has_mlm_head) {
@@ -199,7 +236,7 @@ void build_layout(const stage_config& c, Layout& L) {
     L.wh_logits = wtake(NP * VP * 4); L.wh_rowloss = wtake(NP * 4); L.wh_dt = wtake(NP * H * E);
     L.wh_dgl = wtake(NP * H * E); L.wh_dh = wtake(NP * H * E); L.wh_dr = wtake(NP * H * E); L.wh_dyfull = wtake(U);
     size_t lp = ((NP + 7) / 8) * 3 * H * 4, cp = ((NP + 63) / 64) * VP * 4;
-    // three partial-sum buffers: the LayerNorm backward writes its own on the backward stream while the side
+    // partial-sum buffers of their own: the LayerNorm backward writes its own on the backward stream while the side
     // stream is still reducing a column sum
     L.wh_part = wtake(lp); L.wh_part_cz = wtake(cp); L.wh_info = wtake(16);
     if (L.recompute) { L.wh_logits2 = wtake(NP * VP * 4); L.wh_rowloss2 = wtake(NP * 4); L.wh_info2 = wtake(16); }
@@ -210,7 +247,8 @@ void build_layout(const stage_config& c, Layout& L) {
   if (L.recompute) {
     L.ws_act = wtake(L.act_bytes); L.ws_ydummy = wtake(U);
   }
-  L.workspace_bytes = wo;
+  L.workspace_bytes = w1;
+  L.ws_stride = wo;
 
   L.grad_bytes = align_up(L.n_params * 4);
   L.arena_grads = 0;
@@ -220,8 +258,10 @@ void build_layout(const stage_config& c, Layout& L) {
   // two copies of the workspace: consecutive backward tasks run on two lanes and must not share
   // temporaries (a stage without lanes has one backward lane and one copy)
   L.ws_copies = (c.flags & STAGE_FLAG_ONE_STREAM) ? 1 : 2;
-  L.arena_bytes = L.arena_ws + L.ws_copies * L.workspace_bytes;
+  L.arena_bytes = L.arena_ws + L.ws_copies * L.ws_stride;
 }
+
+#define TRY(expr) do { int rc_ = (expr); if (rc_ != STAGE_OK) return rc_; } while (0)
 
 struct ProfEvent { hipEvent_t a, b; int cls; double flops; int lane; int M, N, K, batch; };
 
@@ -262,7 +302,9 @@ struct dapple_stage {
   size_t E() const { return cfg.dtype == STAGE_DTYPE_BF16 ? 2 : 4; }
   const char* w(size_t elem_off) const { return W + elem_off * E(); }
   float* gr(size_t elem_off) const { return grads + elem_off; }
-  char* slot(int s) const { return arena + L.arena_slots + (size_t)s * L.slot_bytes; }
+  // re-computation: what slot s keeps of its micro-batch
+  char* stash(int s) const { return arena + L.arena_slots + (size_t)s * L.slot_bytes; }
+  Act acts(int s) const { return Act{arena + L.arena_slots, s}; }
   size_t ws_shift = 0;  // selects the workspace copy of the task being enqueued
   char* ws(size_t off) const { return arena + L.arena_ws + ws_shift + off; }
 
@@ -324,18 +366,51 @@ struct dapple_stage {
     return run_on(s_, cls, flops, [&](hipStream_t s) { return launch_gemm(dt, g, s); }, &g);
   }
 
-  // sl: where the task's activations live; fs: forward workspace set
-  int forward(char* sl, int fs, const void* x, void* y, const void* aux);
-  int backward(char* sl, const void* dy, void* dx);
+  // a weight-gradient product over n micro-batches of T1 rows each (both operands k-strided, rows one micro-batch
+  // behind the other), on the side stream: C gets the micro-batches' sums in order, two of them per launch
+  int wgrad(int cls, GemmArgs g, int n, int T1) {
+    const char *A0 = (const char*)g.A, *B0 = (const char*)g.B;
+    const void* Az0[4] = {g.Az[0], g.Az[1], g.Az[2], g.Az[3]};
+    const void* Bz0[4] = {g.Bz[0], g.Bz[1], g.Bz[2], g.Bz[3]};
+    for (int i = 0; i < n; i += 2) {
+      const int c = n - i < 2 ? n - i : 2;
+      const size_t ra = (size_t)i * T1 * g.lda * E(), rb = (size_t)i * T1 * g.ldb * E();
+      g.A = A0 + ra; g.B = B0 + rb;
+      for (int z = 0; z < 4 && Az0[0]; ++z) {
+        g.Az[z] = (const char*)Az0[z] + ra;
+        g.Bz[z] = (const char*)Bz0[z] + rb;
+      }
+      g.K = c * T1; g.kseg_len = T1; g.segA = (long)T1 * g.lda; g.segB = (long)T1 * g.ldb; g.k_valid = 0;
+      if (c > 1) g.epi |= EPI_SEGACC;
+      else g.epi &= ~EPI_SEGACC;
+      TRY(gemm(cls, g, true));
+    }
+    return STAGE_OK;
+  }
+  // n micro-batches in consecutive slots as one task: every product sees n T rows, every row-wise kernel n T rows,
+  // the attention n b sequences, and every accumulator gets the micro-batches' sums one after the other, so that the
+  // bits are those of n tasks.  sl: where the activations live; fs: forward workspace set
+  int forward(const Act& sl, int fs, int n, const void* const* xs, void* const* ys, const void* const* auxs);
+  int backward(const Act& sl, int n, const void* const* dys, void* const* dxs);
+  // f(first, count) once if the n buffers of `bytes` lie one behind the other, else for each of them
+  template <typename P, typename Fn>
+  int each_run(P const* ptrs, int n, size_t bytes, Fn&& f) {
+    bool one = true;
+    for (int i = 1; i < n && !dry; ++i) one = one && (const char*)ptrs[i] == (const char*)ptrs[0] + i * bytes;
+    if (one) return f(0, n);
+    for (int i = 0; i < n; ++i) {
+      int rc = f(i, 1);
+      if (rc != STAGE_OK) return rc;
+    }
+    return STAGE_OK;
+  }
 };
 
-#define TRY(expr) do { int rc_ = (expr); if (rc_ != STAGE_OK) return rc_; } while (0)
 
-int dapple_stage::forward(char* sl, int fs, const void* x, void* y, const void* aux) {
-  const int H = cfg.hidden, F = cfg.ffn, T = cfg.micro_batch * cfg.seq;
-  const size_t U = (size_t)T * H * E();
-  (void)aux;
-  const char* xin = sl + L.slot_x0;
+int dapple_stage::forward(const Act& sl, int fs, int n, const void* const* xs, void* const* ys, const void* const* auxs) {
+  const int H = cfg.hidden, F = cfg.ffn, T1 = cfg.micro_batch * cfg.seq, T = n * T1;   // T1: rows of one micro-batch
+  const size_t U1 = (size_t)T1 * H * E();
+  const char* xin = sl(L.slot_x0);
   // bf16 stages keep the residual stream unrounded: the pre-LayerNorm sums z1, z2 and the copy
   // of each LayerNorm output that feeds the next residual add are fp32; only GEMM operands are bf16
   const bool mixed = dt == DT_BF16;
@@ -345,38 +420,41 @@ int dapple_stage::forward(char* sl, int fs, const void* x, void* y, const void* 
     resid = mixed ? (const void*)ws(L.ws_yf[fs][1]) : (const void*)xin;
     resid_f32 = mixed;
     // x = LN(E_w[id] + E_p[pos]); the ids and the pre-LN sum are kept for the backward
-    int32_t* ids = (int32_t*)(sl + L.slot_ids);
-    char* esum = sl + L.slot_embsum;
-    TRY(run(KC_COPY, 0, [&](hipStream_t q) { return launch_copy(ids, x, (size_t)T * 4, q); }));
+    int32_t* ids = (int32_t*)sl(L.slot_ids);
+    char* esum = sl(L.slot_embsum);
+    TRY(each_run(xs, n, (size_t)T1 * 4, [&](int i, int c) {
+      return run(KC_COPY, 0, [&](hipStream_t q) { return launch_copy(ids + (size_t)i * T1, xs[i], (size_t)c * T1 * 4, q); });
+    }));
     TRY(run(KC_EMBED, 0, [&](hipStream_t q) {
       return launch_embed_gather(dt, ids, w(L.embEw), w(L.embEp), esum, T, cfg.seq, H, cfg.vocab, q);
     }));
     TRY(run(KC_LN_FWD, 0, [&](hipStream_t q) {
-      return launch_ln_fwd(dt, esum, false, w(L.embG), w(L.embB), sl + L.slot_x0, mixed ? (float*)ws(L.ws_yf[fs][1]) : nullptr,
-                           (float*)(sl + L.slot_embst), T, H, cfg.ln_eps, q);
+      return launch_ln_fwd(dt, esum, false, w(L.embG), w(L.embB), sl(L.slot_x0), mixed ? (float*)ws(L.ws_yf[fs][1]) : nullptr,
+                           (float*)sl(L.slot_embst), T, H, cfg.ln_eps, q);
     }));
   } else {
-    TRY(run(KC_COPY, 0, [&](hipStream_t q) { return launch_copy(sl + L.slot_x0, x, U, q); }));
+    TRY(each_run(xs, n, U1, [&](int i, int c) {
+      return run(KC_COPY, 0, [&](hipStream_t q) { return launch_copy(sl(L.slot_x0) + i * U1, xs[i], c * U1, q); });
+    }));
   }
   for (int l = 0; l < cfg.n_layers; ++l) {
     const LayerParams& p = L.lp[l];
     const LayerStash& a = L.ls[l];
-    char *qkv = sl + a.qkv, *ctx = sl + a.ctx, *z1 = sl + a.z1, *y1 = sl + a.y1, *gp = sl + a.gp, *g = sl + a.g,
-         *z2 = sl + a.z2;
-    float *lse = (float*)(sl + a.lse), *st1 = (float*)(sl + a.st1), *st2 = (float*)(sl + a.st2);
-    char* yout = (l + 1 < cfg.n_layers || cfg.has_mlm_head) ? sl + a.y : (char*)y;
+    char *q_ = sl(a.q), *ctx = sl(a.ctx), *z1 = sl(a.z1), *y1 = sl(a.y1), *gp = sl(a.gp), *g = sl(a.g), *z2 = sl(a.z2);
+    float *lse = (float*)sl(a.lse), *st1 = (float*)sl(a.st1), *st2 = (float*)sl(a.st2);
+    const bool keep_y = l + 1 < cfg.n_layers || cfg.has_mlm_head;
     {  // q, k, v = x Wq + bq, x Wk + bk, x Wv + bv  (three products in one launch)
       GemmArgs ga{};
       ga.A = xin; ga.lda = H; ga.B = w(p.Wq); ga.ldb = H; ga.b_kstrided = 1; ga.bias = w(p.bq);
-      ga.C = qkv; ga.ldc = H; ga.M = T; ga.N = H; ga.K = H; ga.batch = 3;
-      ga.sA = 0; ga.sB = (long)H * H + H; ga.sBias = (long)H * H + H; ga.sC = (long)T * H; ga.epi = EPI_BIAS;
+      ga.C = q_; ga.ldc = H; ga.M = T; ga.N = H; ga.K = H; ga.batch = 3;
+      ga.sA = 0; ga.sB = (long)H * H + H; ga.sBias = (long)H * H + H; ga.sC = (long)((a.k.off - a.q.off) / E()); ga.epi = EPI_BIAS;
       TRY(gemm(KC_GEMM_FWD, ga));
     }
     {
       AttnArgs aa{};
-      aa.q = qkv; aa.k = qkv + U; aa.v = qkv + 2 * U; aa.ctx = ctx; aa.lse = lse;
-      aa.ctx32 = dt == DT_BF16 ? (float*)(sl + a.ctx32) : nullptr;
-      aa.b = cfg.micro_batch; aa.s = cfg.seq; aa.A = cfg.n_heads; aa.d = H / cfg.n_heads; aa.H = H;
+      aa.q = q_; aa.k = sl(a.k); aa.v = sl(a.v); aa.ctx = ctx; aa.lse = lse;
+      aa.ctx32 = dt == DT_BF16 ? (float*)sl(a.ctx32) : nullptr;
+      aa.b = n * cfg.micro_batch; aa.s = cfg.seq; aa.A = cfg.n_heads; aa.d = H / cfg.n_heads; aa.H = H;
       double fl = 4.0 * T * (double)cfg.seq * H;
       TRY(run(KC_ATTN_FWD, fl, [&](hipStream_t q) { return launch_attn_fwd(dt, aa, q); }));
     }
@@ -404,63 +482,80 @@ int dapple_stage::forward(char* sl, int fs, const void* x, void* y, const void* 
       ga.K = F; ga.epi = EPI_BIAS | EPI_ADD | (mixed ? EPI_OUT32 | EPI_AUX32 : 0);
       TRY(gemm(KC_GEMM_FWD, ga));
     }
-    float* yf = (mixed && l + 1 < cfg.n_layers) ? (float*)ws(L.ws_yf[fs][l & 1]) : nullptr;
-    TRY(run(KC_LN_FWD, 0, [&](hipStream_t q) {
-      return launch_ln_fwd(dt, z2, mixed, w(p.ln2g), w(p.ln2b), yout, yf, st2, T, H, cfg.ln_eps, q);
-    }));
-    xin = yout;
-    resid = yf ? (const void*)yf : (const void*)yout;
-    resid_f32 = yf != nullptr;
+    if (keep_y) {
+      float* yf = (mixed && l + 1 < cfg.n_layers) ? (float*)ws(L.ws_yf[fs][l & 1]) : nullptr;
+      TRY(run(KC_LN_FWD, 0, [&](hipStream_t q) {
+        return launch_ln_fwd(dt, z2, mixed, w(p.ln2g), w(p.ln2b), sl(a.y), yf, st2, T, H, cfg.ln_eps, q);
+      }));
+      xin = sl(a.y);
+      resid = yf ? (const void*)yf : (const void*)xin;
+      resid_f32 = yf != nullptr;
+    } else {   // the last layer's output goes to the caller's buffers
+      TRY(each_run(ys, n, U1, [&](int i, int c) {
+        const size_t r = (size_t)i * T1;
+        return run(KC_LN_FWD, 0, [&](hipStream_t q) {
+          return launch_ln_fwd(dt, z2 + r * H * (mixed ? 4 : E()), mixed, w(p.ln2g), w(p.ln2b), ys[i], nullptr, st2 + 2 * r,
+                               c * T1, H, cfg.ln_eps, q);
+        });
+      }));
+    }
   }
   if (cfg.has_mlm_head) {
     // gather the predicted rows, t = LN(GELU(r Wt + bt)), z = t E_out^T (+ b_out inside the
     // cross-entropy kernel), loss -> y[0]; dz is kept in the slot for the backward
     const int NP = L.NP, VP = L.VP, V = cfg.vocab;
-    int32_t *rows_idx = (int32_t*)(sl + L.sh_rows), *tgt = (int32_t*)(sl + L.sh_tgt), *info = (int32_t*)ws(fs ? L.wh_info2 : L.wh_info);
-    char *r = sl + L.sh_r, *gl = sl + L.sh_gl, *glp = sl + L.sh_glp, *t = sl + L.sh_t, *dz = sl + L.sh_dz;
-    float *hst = (float*)(sl + L.sh_st), *logits = (float*)ws(fs ? L.wh_logits2 : L.wh_logits), *rowloss = (float*)ws(fs ? L.wh_rowloss2 : L.wh_rowloss);
-    const int cap = cfg.mlm_max_rows > 0 && cfg.mlm_max_rows < T ? cfg.mlm_max_rows : T;
-    TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_mlm_compact((const int32_t*)aux, T, cap, NP, V, rows_idx, tgt, info, q); }));
-    TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_gather_rows(dt, xin, rows_idx, r, NP, H, T, q); }));
+    int32_t *rows_idx = (int32_t*)sl(L.sh_rows), *tgt = (int32_t*)sl(L.sh_tgt), *info = (int32_t*)ws(fs ? L.wh_info2 : L.wh_info);
+    char *r = sl(L.sh_r), *gl = sl(L.sh_gl), *glp = sl(L.sh_glp), *t = sl(L.sh_t), *dz = sl(L.sh_dz);
+    float *hst = (float*)sl(L.sh_st), *logits = (float*)ws(fs ? L.wh_logits2 : L.wh_logits), *rowloss = (float*)ws(fs ? L.wh_rowloss2 : L.wh_rowloss);
+    const int cap = cfg.mlm_max_rows > 0 && cfg.mlm_max_rows < T1 ? cfg.mlm_max_rows : T1;
+    TRY(each_run(auxs, n, (size_t)T1 * 4, [&](int i, int c) {
+      return run(KC_HEAD, 0, [&](hipStream_t q) {
+        return launch_mlm_compact((const int32_t*)auxs[i], T1, c, cap, NP, V, rows_idx + (size_t)i * NP, tgt + (size_t)i * NP, info, q);
+      });
+    }));
+    TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_gather_rows(dt, xin, rows_idx, r, NP, H, T1, n, q); }));
     {
       GemmArgs ga{};
       ga.A = r; ga.lda = H; ga.B = w(L.hWt); ga.ldb = H; ga.b_kstrided = 1; ga.bias = w(L.hbt);
-      ga.C = gl; ga.C2 = glp; ga.ldc = H; ga.M = NP; ga.N = H; ga.K = H; ga.epi = EPI_BIAS | EPI_GELU;
+      ga.C = gl; ga.C2 = glp; ga.ldc = H; ga.M = n * NP; ga.N = H; ga.K = H; ga.epi = EPI_BIAS | EPI_GELU;
       TRY(gemm(KC_HEAD, ga));
     }
-    TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_ln_fwd(dt, gl, false, w(L.hG), w(L.hB), t, nullptr, hst, NP, H, cfg.ln_eps, q); }));
+    TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_ln_fwd(dt, gl, false, w(L.hG), w(L.hB), t, nullptr, hst, n * NP, H, cfg.ln_eps, q); }));
     {
       GemmArgs ga{};
       ga.A = t; ga.lda = H; ga.B = w(L.hEout); ga.ldb = H; ga.n_valid = V;
-      ga.C = logits; ga.ldc = VP; ga.M = NP; ga.N = VP; ga.K = H; ga.epi = EPI_OUT32;
+      ga.C = logits; ga.ldc = VP; ga.M = n * NP; ga.N = VP; ga.K = H; ga.epi = EPI_OUT32;
       TRY(gemm(KC_HEAD, ga));
     }
     TRY(run(KC_HEAD, 0, [&](hipStream_t q) {
-      return launch_mlm_ce(dt, logits, w(L.hbout), rows_idx, tgt, NP, V, VP, cfg.loss_scale, dz, rowloss, (float*)y, q);
+      return launch_mlm_ce(dt, logits, w(L.hbout), rows_idx, tgt, n * NP, V, VP, cfg.loss_scale, dz, rowloss, q);
+    }));
+    TRY(each_run(ys, n, sizeof(float), [&](int i, int c) {
+      return run(KC_HEAD, 0, [&](hipStream_t q) { return launch_loss_sum(rowloss + (size_t)i * NP, NP, c, cfg.loss_scale, (float*)ys[i], q); });
     }));
   }
   return STAGE_OK;
 }
 
-int dapple_stage::backward(char* sl, const void* dy, void* dx) {
+int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* const* dxs) {
   // Two streams.  The caller's stream runs the chain that produces dx (LayerNorm backward,
   // data-gradient products, attention backward): it is the critical path.  Everything that only
   // feeds the gradient accumulators (weight-gradient products, bias column sums, LayerNorm
   // parameter sums) goes to the side stream as soon as its inputs exist, so those kernels fill
   // the CUs the small data-gradient products leave idle.  All accumulator updates happen on the
   // side stream in program order: the result does not depend on how the two streams interleave.
-  const int H = cfg.hidden, F = cfg.ffn, T = cfg.micro_batch * cfg.seq;
-  const size_t U = (size_t)T * H * E();
+  const int H = cfg.hidden, F = cfg.ffn, T1 = cfg.micro_batch * cfg.seq, T = n * T1;
+  const size_t U1 = (size_t)T1 * H * E();
   char *dy1 = ws(L.ws_dy1), *dctx = ws(L.ws_dctx);
   float* delta = (float*)ws(L.ws_delta);
-  const char* dyin = (const char*)dy;
+  const char* dyin = nullptr;   // NULL: the caller's dys
   if (cfg.has_mlm_head) {
     // backward of the head: dE_out, db_out, dt -> LN -> GELU gate -> dWt, dbt, dr, scattered back
     // into a full [T,H] gradient of the encoder output (zero on rows that are not predicted)
     const int NP = L.NP, VP = L.VP, V = cfg.vocab;
-    int32_t* rows_idx = (int32_t*)(sl + L.sh_rows);
-    char *r = sl + L.sh_r, *gl = sl + L.sh_gl, *glp = sl + L.sh_glp, *t = sl + L.sh_t, *dz = sl + L.sh_dz;
-    float *hst = (float*)(sl + L.sh_st), *part = (float*)ws(L.wh_part);
+    int32_t* rows_idx = (int32_t*)sl(L.sh_rows);
+    char *r = sl(L.sh_r), *gl = sl(L.sh_gl), *glp = sl(L.sh_glp), *t = sl(L.sh_t), *dz = sl(L.sh_dz);
+    float *hst = (float*)sl(L.sh_st), *part = (float*)ws(L.wh_part);
     char *dtb = ws(L.wh_dt), *dgl = ws(L.wh_dgl), *dh = ws(L.wh_dh), *dr = ws(L.wh_dr), *dyfull = ws(L.wh_dyfull);
     int nblk = 0;
     // The head's accumulator updates go to the side stream like the layers' (fork events of the pseudo-layer
@@ -471,59 +566,81 @@ int dapple_stage::backward(char* sl, const void* dy, void* dx) {
     {  // dE_out += dz^T t
       GemmArgs ga{};
       ga.A = dz; ga.lda = VP; ga.a_kstrided = 1; ga.B = t; ga.ldb = H; ga.b_kstrided = 1;
-      ga.C = gr(L.hEout); ga.ldc = H; ga.M = V; ga.N = H; ga.K = NP; ga.epi = EPI_ACC32;
-      TRY(gemm(KC_HEAD, ga, true));
+      ga.C = gr(L.hEout); ga.ldc = H; ga.M = V; ga.N = H; ga.epi = EPI_ACC32;
+      TRY(wgrad(KC_HEAD, ga, n, NP));
     }
-    TRY(run_on(side, KC_HEAD, 0, [&](hipStream_t q) { return launch_colsum(dt, dz, NP, V, VP, part_cz, gr(L.hbout), 1, 0, 0, q); }));
+    {  // db_out += the column sums of dz
+      int nb = 0, PS = 0;
+      TRY(run_on(side, KC_HEAD, 0, [&](hipStream_t q) { return launch_colsum_partials(dt, dz, NP, V, VP, part_cz, n, (long)NP * VP, &nb, &PS, q); }));
+      ReduceJobs J{};
+      J.nmb = n; J.mb_stride = (long)nb * PS;
+      J.j[J.n++] = ReduceJob{part_cz, gr(L.hbout), nb, V, PS};
+      TRY(run_on(side, KC_HEAD, 0, [&](hipStream_t q) { return launch_reduce_jobs(J, q); }));
+    }
     {  // dt = dz E_out
       GemmArgs ga{};
       ga.A = dz; ga.lda = VP; ga.B = w(L.hEout); ga.ldb = H; ga.b_kstrided = 1; ga.k_valid = V;
-      ga.C = dtb; ga.ldc = H; ga.M = NP; ga.N = H; ga.K = VP;
+      ga.C = dtb; ga.ldc = H; ga.M = n * NP; ga.N = H; ga.K = VP;
       TRY(gemm(KC_HEAD, ga));
     }
-    TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_ln_bwd(dt, dtb, gl, false, hst, w(L.hG), dgl, part, &nblk, NP, H, q); }));
+    TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_ln_bwd(dt, dtb, gl, false, hst, w(L.hG), dgl, part, &nblk, NP, H, n, q); }));
     TRY(fork(HL, 1));
-    TRY(run_on(side, KC_HEAD, 0, [&](hipStream_t q) { return launch_partial_reduce(part, nblk, 3, H, gr(L.hG), gr(L.hB), nullptr, q); }));
-    TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_mul(dt, dgl, glp, dh, (long)NP * H, q); }));
+    {
+      ReduceJobs J{};
+      J.nmb = n; J.mb_stride = (long)nblk * 3 * H;
+      J.j[J.n++] = ReduceJob{part, gr(L.hG), nblk, H, 3L * H};
+      J.j[J.n++] = ReduceJob{part + H, gr(L.hB), nblk, H, 3L * H};
+      TRY(run_on(side, KC_HEAD, 0, [&](hipStream_t q) { return launch_reduce_jobs(J, q); }));
+    }
+    TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_mul(dt, dgl, glp, dh, (long)n * NP * H, q); }));
     TRY(fork(HL, 0));   // event 0 again: the side stream's first wait on it is already enqueued
     {  // dWt += r^T dh, dbt += the column sums of dh
       GemmArgs ga{};
       ga.A = r; ga.lda = H; ga.a_kstrided = 1; ga.B = dh; ga.ldb = H; ga.b_kstrided = 1;
-      ga.C = gr(L.hWt); ga.ldc = H; ga.M = H; ga.N = H; ga.K = NP; ga.epi = EPI_ACC32 | EPI_BSUM;
+      ga.C = gr(L.hWt); ga.ldc = H; ga.M = H; ga.N = H; ga.epi = EPI_ACC32 | EPI_BSUM;
       ga.bsum_z[0] = gr(L.hbt);
-      TRY(gemm(KC_HEAD, ga, true));
+      TRY(wgrad(KC_HEAD, ga, n, NP));
     }
     TRY(side_done(HL));
     {  // dr = dh Wt^T
       GemmArgs ga{};
-      ga.A = dh; ga.lda = H; ga.B = w(L.hWt); ga.ldb = H; ga.C = dr; ga.ldc = H; ga.M = NP; ga.N = H; ga.K = H;
+      ga.A = dh; ga.lda = H; ga.B = w(L.hWt); ga.ldb = H; ga.C = dr; ga.ldc = H; ga.M = n * NP; ga.N = H; ga.K = H;
       TRY(gemm(KC_HEAD, ga));
     }
-    TRY(run(KC_COPY, 0, [&](hipStream_t q) { return launch_zero(dyfull, U, q); }));
-    TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_scatter_rows(dt, dr, rows_idx, dyfull, NP, H, T, q); }));
+    TRY(run(KC_COPY, 0, [&](hipStream_t q) { return launch_zero(dyfull, n * U1, q); }));
+    TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_scatter_rows(dt, dr, rows_idx, dyfull, NP, H, T1, n, q); }));
     dyin = dyfull;
   }
   for (int l = cfg.n_layers - 1; l >= 0; --l) {
     const LayerParams& p = L.lp[l];
     const LayerStash& a = L.ls[l];
     const Layout::SideSet& ss = L.ws_side[l];  // this layer's buffers that the side stream reads
-    char *dz2 = ws(ss.dz2), *du = ws(ss.du), *dz1 = ws(ss.dz1), *dqkv = ws(ss.dqkv);
+    char *dz2 = ws(ss.dz2), *du = ws(ss.du), *dz1 = ws(ss.dz1), *dq = ws(ss.dq), *dk = ws(ss.dk), *dv = ws(ss.dv);
     float *part_ln2 = (float*)ws(ss.part_ln2), *part_ln1 = (float*)ws(ss.part_ln1);
-    const char* xl = l == 0 ? sl + L.slot_x0 : sl + L.ls[l - 1].y;
-    char *qkv = sl + a.qkv, *ctx = sl + a.ctx, *z1 = sl + a.z1, *y1 = sl + a.y1, *gp = sl + a.gp, *g = sl + a.g,
-         *z2 = sl + a.z2;
-    float *lse = (float*)(sl + a.lse), *st1 = (float*)(sl + a.st1), *st2 = (float*)(sl + a.st2);
-    char* dxout = l == 0 ? (cfg.has_embedding ? ws(L.we_dx0) : (char*)dx) : ws(L.ws_dx[l & 1]);
+    const char* xl = l == 0 ? sl(L.slot_x0) : sl(L.ls[l - 1].y);
+    char *ctx = sl(a.ctx), *z1 = sl(a.z1), *y1 = sl(a.y1), *gp = sl(a.gp), *g = sl(a.g), *z2 = sl(a.z2);
+    float *lse = (float*)sl(a.lse), *st1 = (float*)sl(a.st1), *st2 = (float*)sl(a.st2);
     const size_t pstride = (size_t)H * H + H;
     int nblk = 0;
 
     // y = LN(z2): dz2, and block partial sums for the gradients of ln2 gain/shift and of b2
-    TRY(run(KC_LN_BWD, 0, [&](hipStream_t q) { return launch_ln_bwd(dt, dyin, z2, dt == DT_BF16, st2, w(p.ln2g), dz2, part_ln2, &nblk, T, H, q); }));
+    if (dyin) {
+      TRY(run(KC_LN_BWD, 0, [&](hipStream_t q) {
+        return launch_ln_bwd(dt, dyin, z2, dt == DT_BF16, st2, w(p.ln2g), dz2, part_ln2, &nblk, T1, H, n, q);
+      }));
+    } else {
+      TRY(each_run(dys, n, U1, [&](int i, int c) {
+        const size_t r = (size_t)i * T1;
+        return run(KC_LN_BWD, 0, [&](hipStream_t q) {
+          return launch_ln_bwd(dt, dys[i], z2 + r * H * 4, dt == DT_BF16, st2 + 2 * r, w(p.ln2g), dz2 + r * H * E(),
+                               part_ln2 + (size_t)i * ((T1 + 7) / 8) * 3 * H, &nblk, T1, H, c, q);
+        });
+      }));
+    }
     // One side stream: the layer's bias and LayerNorm-parameter reductions wait and go out as ONE
     // launch after the last weight-gradient product (the side stream is the longest chain of a
     // step, and a small kernel costs it a dispatch of ~15 us when the GPU is full).  Each
     // reduction adds in the same order as the stand-alone kernels.
-    const int nblk_ln2 = nblk;
     {  // du = (dz2 W2^T) o GELU'(u)
       GemmArgs ga{};
       ga.A = dz2; ga.lda = H; ga.B = w(p.W2); ga.ldb = H; ga.aux = gp; ga.ldaux = F;
@@ -537,15 +654,15 @@ int dapple_stage::backward(char* sl, const void* dy, void* dx) {
     {  // dW2 += g^T dz2
       GemmArgs ga{};
       ga.A = g; ga.lda = F; ga.a_kstrided = 1; ga.B = dz2; ga.ldb = H; ga.b_kstrided = 1;
-      ga.C = gr(p.W2); ga.ldc = H; ga.M = F; ga.N = H; ga.K = T; ga.epi = EPI_ACC32;
-      TRY(gemm(KC_GEMM_WGRAD, ga, true));
+      ga.C = gr(p.W2); ga.ldc = H; ga.M = F; ga.N = H; ga.epi = EPI_ACC32;
+      TRY(wgrad(KC_GEMM_WGRAD, ga, n, T1));
     }
     {  // dW1 += y1^T du, and db1 += the column sums of du in the same launch
       GemmArgs ga{};
       ga.A = y1; ga.lda = H; ga.a_kstrided = 1; ga.B = du; ga.ldb = F; ga.b_kstrided = 1;
-      ga.C = gr(p.W1); ga.ldc = F; ga.M = H; ga.N = F; ga.K = T; ga.epi = EPI_ACC32 | EPI_BSUM;
+      ga.C = gr(p.W1); ga.ldc = F; ga.M = H; ga.N = F; ga.epi = EPI_ACC32 | EPI_BSUM;
       ga.bsum_z[0] = gr(p.b1);
-      TRY(gemm(KC_GEMM_WGRAD, ga, true));
+      TRY(wgrad(KC_GEMM_WGRAD, ga, n, T1));
     }
     {  // dy1 = du W1^T + dz2 (residual branch)
       GemmArgs ga{};
@@ -553,13 +670,12 @@ int dapple_stage::backward(char* sl, const void* dy, void* dx) {
       ga.C = dy1; ga.ldc = H; ga.M = T; ga.N = H; ga.K = F; ga.epi = EPI_ADD;
       TRY(gemm(KC_GEMM_DGRAD, ga));
     }
-    TRY(run(KC_LN_BWD, 0, [&](hipStream_t q) { return launch_ln_bwd(dt, dy1, z1, dt == DT_BF16, st1, w(p.ln1g), dz1, part_ln1, &nblk, T, H, q); }));
-    const int nblk_ln1 = nblk;
+    TRY(run(KC_LN_BWD, 0, [&](hipStream_t q) { return launch_ln_bwd(dt, dy1, z1, dt == DT_BF16, st1, w(p.ln1g), dz1, part_ln1, &nblk, T1, H, n, q); }));
     AttnArgs aa{};
-    aa.q = qkv; aa.k = qkv + U; aa.v = qkv + 2 * U; aa.ctx = ctx; aa.lse = lse; aa.dctx = dctx;
-    aa.ctx32 = dt == DT_BF16 ? (float*)(sl + a.ctx32) : nullptr;
-    aa.dq = dqkv; aa.dk = dqkv + U; aa.dv = dqkv + 2 * U; aa.delta = delta;
-    aa.b = cfg.micro_batch; aa.s = cfg.seq; aa.A = cfg.n_heads; aa.d = H / cfg.n_heads; aa.H = H;
+    aa.q = sl(a.q); aa.k = sl(a.k); aa.v = sl(a.v); aa.ctx = ctx; aa.lse = lse; aa.dctx = dctx;
+    aa.ctx32 = dt == DT_BF16 ? (float*)sl(a.ctx32) : nullptr;
+    aa.dq = dq; aa.dk = dk; aa.dv = dv; aa.delta = delta;
+    aa.b = n * cfg.micro_batch; aa.s = cfg.seq; aa.A = cfg.n_heads; aa.d = H / cfg.n_heads; aa.H = H;
     {  // dctx = dz1 Wo^T; where the MFMA kernels run, its epilogue also leaves rowsum(dctx o ctx) per block of
        // 32 columns, the delta of the attention backward
       GemmArgs ga{};
@@ -585,52 +701,67 @@ int dapple_stage::backward(char* sl, const void* dy, void* dx) {
        // also add the column sums of dq, dk, dv to the bias gradients
       GemmArgs ga{};
       ga.lda = H; ga.a_kstrided = 1; ga.ldb = H; ga.b_kstrided = 1;
-      ga.ldc = H; ga.M = H; ga.N = H; ga.K = T; ga.batch = 4; ga.epi = EPI_ACC32 | EPI_BSUM;
+      ga.ldc = H; ga.M = H; ga.N = H; ga.batch = 4; ga.epi = EPI_ACC32 | EPI_BSUM;
+      const char* dqkv[3] = {dq, dk, dv};
       for (int z = 0; z < 3; ++z) {
-        ga.Az[z] = xl; ga.Bz[z] = dqkv + z * U; ga.Cz[z] = gr(p.Wq + z * pstride);
+        ga.Az[z] = xl; ga.Bz[z] = dqkv[z]; ga.Cz[z] = gr(p.Wq + z * pstride);
         ga.bsum_z[z] = gr(p.bq + z * pstride);
       }
       ga.Az[3] = ctx; ga.Bz[3] = dz1; ga.Cz[3] = gr(p.Wo);
       ga.A = ga.Az[0]; ga.B = ga.Bz[0]; ga.C = ga.Cz[0];
-      TRY(gemm(KC_GEMM_WGRAD, ga, true));
+      TRY(wgrad(KC_GEMM_WGRAD, ga, n, T1));
     }
     {
       ReduceJobs J{};
-      auto add = [&](const float* partial, long stride, int nb, int cols, float* out) {
-        J.j[J.n++] = ReduceJob{partial, out, nb, cols, stride};
-      };
+      J.nmb = n; J.mb_stride = (long)nblk * 3 * H;
+      auto add = [&](const float* partial, float* out) { J.j[J.n++] = ReduceJob{partial, out, nblk, H, 3L * H}; };
       float* o2[3] = {gr(p.ln2g), gr(p.ln2b), gr(p.b2)};
       float* o1[3] = {gr(p.ln1g), gr(p.ln1b), gr(p.bo)};
-      for (int v = 0; v < 3; ++v) add(part_ln2 + (size_t)v * H, 3L * H, nblk_ln2, H, o2[v]);
-      for (int v = 0; v < 3; ++v) add(part_ln1 + (size_t)v * H, 3L * H, nblk_ln1, H, o1[v]);
+      for (int v = 0; v < 3; ++v) add(part_ln2 + (size_t)v * H, o2[v]);
+      for (int v = 0; v < 3; ++v) add(part_ln1 + (size_t)v * H, o1[v]);
       TRY(run_on(side, KC_REDUCE, 0, [&](hipStream_t q) { return launch_reduce_jobs(J, q); }));
     }
     TRY(side_done(l));
     {  // dx = dq Wq^T + dk Wk^T + dv Wv^T + dz1 (residual branch): one product over K = 3H
-      GemmArgs ga{};
-      ga.A = dqkv; ga.lda = H; ga.B = w(p.Wq); ga.ldb = H; ga.aux = dz1; ga.ldaux = H;
-      ga.C = dxout; ga.ldc = H; ga.M = T; ga.N = H; ga.K = 3 * H; ga.kseg_len = H;
-      ga.segA = (long)T * H; ga.segB = (long)pstride; ga.epi = EPI_ADD;
-      TRY(gemm(KC_GEMM_DGRAD, ga));
+      auto dx_gemm = [&](char* out, int i, int c) {
+        const size_t r = (size_t)i * T1 * H * E();
+        GemmArgs ga{};
+        ga.A = dq + r; ga.lda = H; ga.B = w(p.Wq); ga.ldb = H; ga.aux = dz1 + r; ga.ldaux = H;
+        ga.C = out; ga.ldc = H; ga.M = c * T1; ga.N = H; ga.K = 3 * H; ga.kseg_len = H;
+        ga.segA = (long)((ss.dk - ss.dq) / E()); ga.segB = (long)pstride; ga.epi = EPI_ADD;
+        return gemm(KC_GEMM_DGRAD, ga);
+      };
+      if (l == 0 && !cfg.has_embedding) {   // to the caller's buffers
+        TRY(each_run(dxs, n, U1, [&](int i, int c) { return dx_gemm((char*)dxs[i], i, c); }));
+      } else {
+        char* dxout = l == 0 ? ws(L.we_dx0) : ws(L.ws_dx[l & 1]);
+        TRY(dx_gemm(dxout, 0, n));
+        dyin = dxout;
+      }
     }
-    dyin = dxout;
   }
   if (cfg.has_embedding) {
     // x = LN(e): de, the gradients of the embedding LayerNorm, then the two table gradients
-    char *de = ws(L.we_de), *esum = sl + L.slot_embsum;
+    char *de = ws(L.we_de), *esum = sl(L.slot_embsum);
     float* part = (float*)ws(L.we_part);
     int nblk = 0;
     TRY(run(KC_EMBED, 0, [&](hipStream_t q) {
-      return launch_ln_bwd(dt, dyin, esum, false, (const float*)(sl + L.slot_embst), w(L.embG), de, part, &nblk, T, H, q);
+      return launch_ln_bwd(dt, dyin, esum, false, (const float*)sl(L.slot_embst), w(L.embG), de, part, &nblk, T1, H, n, q);
     }));
     // the three accumulations (LayerNorm gain and shift, the two tables) join the side stream's queue like every
     // other accumulator update, so that backward tasks may run on two lanes: fork event 3 of layer 0 is free
     // again (its side work was enqueued above), and the task's closing join below waits for this too
     TRY(fork(0, 3));
-    TRY(run_on(side, KC_EMBED, 0, [&](hipStream_t q) { return launch_partial_reduce(part, nblk, 3, H, gr(L.embG), gr(L.embB), nullptr, q); }));
+    {
+      ReduceJobs J{};
+      J.nmb = n; J.mb_stride = (long)nblk * 3 * H;
+      J.j[J.n++] = ReduceJob{part, gr(L.embG), nblk, H, 3L * H};
+      J.j[J.n++] = ReduceJob{part + H, gr(L.embB), nblk, H, 3L * H};
+      TRY(run_on(side, KC_EMBED, 0, [&](hipStream_t q) { return launch_reduce_jobs(J, q); }));
+    }
     TRY(run_on(side, KC_EMBED, 0, [&](hipStream_t q) {
-      return launch_embed_bwd(dt, (const int32_t*)(sl + L.slot_ids), de, gr(L.embEw), gr(L.embEp), cfg.micro_batch,
-                              cfg.seq, H, cfg.vocab, q);
+      return launch_embed_bwd(dt, (const int32_t*)sl(L.slot_ids), de, gr(L.embEw), gr(L.embEp), cfg.micro_batch,
+                              cfg.seq, H, cfg.vocab, n, q);
     }));
     TRY(side_done(0));
   }
@@ -776,7 +907,7 @@ int stage_init(stage_handle* out, const stage_config* cfg, const void* weights_d
     rc = h->run(KC_COPY, 0, [&](hipStream_t q) { return launch_zero(h->ws(h->L.wh_info), 16, q); });
     for (int c = 0; rc == STAGE_OK && h->L.recompute && c < h->L.ws_copies; ++c)   // one flag per backward lane
       rc = h->run(KC_COPY, 0, [&](hipStream_t q) {
-        return launch_zero(h->ws((size_t)c * h->L.workspace_bytes + h->L.wh_info2), 16, q);
+        return launch_zero(h->ws((size_t)c * h->L.ws_stride + h->L.wh_info2), 16, q);
       });
   }
   if (rc != STAGE_OK) { delete h; return rc; }
@@ -813,6 +944,51 @@ static int find_slot(stage_handle h, int mb) {
   return -1;
 }
 
+// F of micro-batches m0 .. m0+n-1 into slots s .. s+n-1 (checked and free)
+static int fwd_group(stage_handle h, int m0, int n, int s, const void* const* xs, void* const* ys, const void* const* auxs) {
+  if (h->L.recompute && !h->dry) {   // n == 1
+    // keep only what the forward cannot be re-run without: the input (token ids on a first stage)
+    // and the targets; the activations go to the forward tasks' buffer and are dropped
+    char* stash = h->stash(s);
+    const Layout& L = h->L;
+    const size_t xb = h->cfg.has_embedding ? (size_t)h->cfg.micro_batch * h->cfg.seq * 4
+                                            : (size_t)h->cfg.micro_batch * h->cfg.seq * h->cfg.hidden * h->E();
+    TRY(h->run(KC_COPY, 0, [&](hipStream_t q) { return launch_copy(stash + L.st_x, xs[0], xb, q); }));
+    if (h->cfg.has_mlm_head)
+      TRY(h->run(KC_COPY, 0, [&](hipStream_t q) {
+        return launch_copy(stash + L.st_aux, auxs[0], (size_t)h->cfg.micro_batch * h->cfg.seq * 4, q);
+      }));
+    TRY(h->forward(Act{h->arena + L.arena_fwd_act, 0}, 0, 1, xs, ys, auxs));
+  } else {
+    TRY(h->forward(h->acts(s), 0, n, xs, ys, auxs));
+  }
+  for (int i = 0; i < n; ++i) h->slot_of_mb[s + i] = m0 + i;
+  h->live += n;
+  if (h->live > h->peak_live) h->peak_live = h->live;
+  h->fwd_tasks += n;
+  return STAGE_OK;
+}
+
+// B of the n micro-batches in slots s .. s+n-1
+static int bwd_group(stage_handle h, int n, int s, const void* const* dys, void* const* dxs) {
+  if (h->L.recompute && !h->dry) {
+    // re-run the forward from the kept input into the backward tasks' buffer, then go backward
+    const Layout& L = h->L;
+    char* stash = h->stash(s);
+    const Act act{h->ws(L.ws_act), 0};
+    const void *x = stash + L.st_x, *aux = h->cfg.has_mlm_head ? stash + L.st_aux : nullptr;
+    void* y = h->ws(L.ws_ydummy);
+    TRY(h->forward(act, 1, 1, &x, &y, &aux));
+    TRY(h->backward(act, 1, dys, dxs));
+  } else {
+    TRY(h->backward(h->acts(s), n, dys, dxs));
+  }
+  for (int i = 0; i < n; ++i) h->slot_of_mb[s + i] = -1;   // released: the next injected micro-batches reuse them
+  h->live -= n;
+  h->bwd_tasks += n;
+  return STAGE_OK;
+}
+
 int stage_fwd(stage_handle h, int mb, const void* x_dev, void* y_dev, const void* aux_dev) {
   if (!h) return fail(STAGE_E_NULL, "handle is NULL");
   if (mb < 0) return fail(STAGE_E_BAD_ORDER, "micro-batch index %d is negative", mb);
@@ -821,27 +997,7 @@ int stage_fwd(stage_handle h, int mb, const void* x_dev, void* y_dev, const void
   if (find_slot(h, mb) >= 0) return fail(STAGE_E_DUP_MB, "micro-batch %d is already resident", mb);
   int s = find_slot(h, -1);
   if (s < 0) return fail(STAGE_E_NO_SLOT, "all %d activation slots are in use", h->cfg.max_slots);
-  if (h->L.recompute && !h->dry) {
-    // keep only what the forward cannot be re-run without: the input (token ids on a first stage)
-    // and the targets; the activations go to the forward tasks' buffer and are dropped
-    char* stash = h->slot(s);
-    const Layout& L = h->L;
-    const size_t xb = h->cfg.has_embedding ? (size_t)h->cfg.micro_batch * h->cfg.seq * 4
-                                            : (size_t)h->cfg.micro_batch * h->cfg.seq * h->cfg.hidden * h->E();
-    TRY(h->run(KC_COPY, 0, [&](hipStream_t q) { return launch_copy(stash + L.st_x, x_dev, xb, q); }));
-    if (h->cfg.has_mlm_head)
-      TRY(h->run(KC_COPY, 0, [&](hipStream_t q) {
-        return launch_copy(stash + L.st_aux, aux_dev, (size_t)h->cfg.micro_batch * h->cfg.seq * 4, q);
-      }));
-    TRY(h->forward(h->arena + L.arena_fwd_act, 0, x_dev, y_dev, aux_dev));
-  } else {
-    TRY(h->forward(h->slot(s), 0, x_dev, y_dev, aux_dev));
-  }
-  h->slot_of_mb[s] = mb;
-  ++h->live;
-  if (h->live > h->peak_live) h->peak_live = h->live;
-  ++h->fwd_tasks;
-  return STAGE_OK;
+  return fwd_group(h, mb, 1, s, &x_dev, &y_dev, &aux_dev);
 }
 
 int stage_bwd(stage_handle h, int mb, const void* dy_dev, void* dx_dev) {
@@ -850,19 +1006,7 @@ int stage_bwd(stage_handle h, int mb, const void* dy_dev, void* dx_dev) {
   if (!h->dry && !h->cfg.has_embedding && !dx_dev) return fail(STAGE_E_NULL, "dx_dev must not be NULL");
   int s = mb < 0 ? -1 : find_slot(h, mb);
   if (s < 0) return fail(STAGE_E_NOT_RESIDENT, "micro-batch %d has no live forward", mb);
-  if (h->L.recompute && !h->dry) {
-    // re-run the forward from the kept input into the backward tasks' buffer, then go backward
-    const Layout& L = h->L;
-    char *stash = h->slot(s), *act = h->ws(L.ws_act);
-    TRY(h->forward(act, 1, stash + L.st_x, h->ws(L.ws_ydummy), h->cfg.has_mlm_head ? stash + L.st_aux : nullptr));
-    TRY(h->backward(act, dy_dev, dx_dev));
-  } else {
-    TRY(h->backward(h->slot(s), dy_dev, dx_dev));
-  }
-  h->slot_of_mb[s] = -1;   // released after its backward: the next injected micro-batch reuses it
-  --h->live;
-  ++h->bwd_tasks;
-  return STAGE_OK;
+  return bwd_group(h, 1, s, &dy_dev, &dx_dev);
 }
 
 int stage_schedule_ops(int M, int K, int order, int32_t* ops_out, int capacity) {
@@ -872,6 +1016,15 @@ int stage_schedule_ops(int M, int K, int order, int32_t* ops_out, int capacity) 
   if ((int)ops.size() > capacity) return fail(STAGE_E_BAD_ORDER, "capacity %d too small for %zu tasks", capacity, ops.size());
   memcpy(ops_out, ops.data(), ops.size() * sizeof(int32_t));
   return (int)ops.size();
+}
+
+// Micro-batches per set of launches: the largest divisor of the resident count (GPipe order: any number) within what
+// the workspace holds
+static int group_size(stage_handle h, int order, int M, int limit) {
+  int g = std::min(h->L.group, limit);
+  if (order == STAGE_ORDER_GPIPE) return g;
+  while (limit % g) --g;
+  return g;
 }
 
 static int ensure_lanes(stage_handle h) {
@@ -909,26 +1062,44 @@ int stage_run_schedule(stage_handle h, int M, int K, int order, const void* cons
       if (!xs[m] || !ys[m] || (need_dy && !dys[m]) || (need_dx && !dxs[m]) || (need_aux && !auxs[m]))
         return fail(STAGE_E_NULL, "a device pointer of micro-batch %d is NULL", m);
   }
+  // Groups.  The micro-batches of a call are all given at its start, so neighbouring tasks of one kind whose slots lie
+  // side by side go out as ONE set of launches over all their rows: micro-batches g G .. g G + G - 1 in slots
+  // j G .. j G + G - 1.  With K' resident micro-batches that is the same order over groups with K' / G of them
+  // resident, so G divides K' (the GPipe order holds all M anyway).  The dependences are the lists': F_m before B_m,
+  // B_m before the forward that reuses its slot, forwards in order, backwards in order; an accumulator gets every
+  // micro-batch's sum on its own, in list order, so no bit depends on G.
+  const int G = order == STAGE_ORDER_EXPLICIT ? 1 : group_size(h, order, M, limit);
+  struct Group { int kind, m0, n; };
+  std::vector<Group> groups;
+  if (G > 1) {
+    const int NG = (M + G - 1) / G;
+    TRY(make_schedule(NG, order == STAGE_ORDER_GPIPE ? NG : limit / G, order, ops));
+    for (int32_t op : ops) {
+      const int g = (op > 0 ? op : -op) - 1;
+      groups.push_back(Group{op > 0 ? 0 : 1, g * G, std::min(G, M - g * G)});
+    }
+  } else {
+    for (int32_t op : ops) groups.push_back(Group{op > 0 ? 0 : 1, (op > 0 ? op : -op) - 1, 1});
+  }
   // Two lanes: forward tasks go to the library's forward stream, backward tasks stay on the
-  // caller's stream, so that F_{j+K} runs beside B_{j+1} instead of between B_j and B_{j+1}.
+  // caller's stream, so that a forward runs beside the backwards that do not hold its slots.
   // Dependences kept: F_m -> B_m; B_m -> the forward that reuses its slot; forwards among
   // themselves and backwards among themselves in list order (which fixes the order of every
   // gradient accumulation).  The early-backward order needs no more than that; the other orders
   // are run strictly as listed (a backward waits for every forward listed before it).
   const bool lanes = !h->dry && !h->profiling && !h->serial;
   const bool strict = order != STAGE_ORDER_EARLY_BACKWARD;
-  std::vector<char> b_pending(h->cfg.max_slots, 0);
+  std::vector<char> b_pending(h->cfg.max_slots, 0);   // per first slot of a group
   int last_f_slot = -1;
   auto hip_ok = [](hipError_t e) { return e == hipSuccess ? STAGE_OK : fail(STAGE_E_DEVICE, "%s", hipGetErrorString(e)); };
-  // Early-backward order, plain stages: consecutive backward tasks alternate between the caller's
+  // Early-backward and GPipe order, plain stages: consecutive backward groups alternate between the caller's
   // stream and a second backward stream (each with its own copy of the workspace), so the head of
-  // B_{j+1} overlaps the tail of B_j.  Their accumulator updates still happen in list order: all of
+  // the next overlaps the tail of the one before.  Their accumulator updates still happen in list order: all of
   // them are issued, in host order, on the one side stream (the embedding block's and the head's too).
   // A capture keeps to one backward lane: the HIP runtime that ships with PyTorch 2.10 (ROCm 7.0) recurses
   // without end in hipStreamEndCapture once two streams other than the capture's origin have waited for each
   // other's events (side lane <-> second backward lane); the origin may wait for and be waited for by anyone.
-  // (The GPipe order alternates its backward tasks the same way once every forward is done; an explicit list
-  // keeps one backward lane.)
+  // (An explicit list keeps one backward lane.)
   const bool two = lanes && order != STAGE_ORDER_EXPLICIT && h->L.ws_copies == 2 &&
                    !h->no_side && !h->capturing;
   int n_bwd = 0;
@@ -939,39 +1110,45 @@ int stage_run_schedule(stage_handle h, int M, int K, int order, const void* cons
     TRY(hip_ok(hipStreamWaitEvent(h->fwd, h->ev_start, 0)));
   }
   int rc = STAGE_OK;
-  for (int32_t op : ops) {
-    int m = (op > 0 ? op : -op) - 1;
-    if (op > 0) {
+  const std::vector<void*> none(h->dry ? M : 0, nullptr);   // a dry run has no pointers
+  auto at = [&](auto p, int m) { return h->dry ? (decltype(p))none.data() : (p ? p + m : p); };
+  for (const Group& t : groups) {
+    const int m = t.m0;
+    if (t.kind == 0) {
+      int s = -1;   // the lowest free run of slots
+      for (int j = 0; s < 0 && j + t.n <= h->cfg.max_slots; j += G)
+        if (h->slot_of_mb[j] == -1) s = j;
+      if (s < 0) { rc = fail(STAGE_E_NO_SLOT, "all %d activation slots are in use", h->cfg.max_slots); break; }
       if (lanes) {
-        int s = find_slot(h, -1);  // the slot stage_fwd is about to take
-        if (s >= 0 && b_pending[s]) {
+        if (b_pending[s]) {
           if ((rc = hip_ok(hipStreamWaitEvent(h->fwd, h->ev_b[s], 0))) != STAGE_OK) break;
           b_pending[s] = 0;
         }
         h->cur = h->fwd;
-        rc = stage_fwd(h, m, xs[m], ys[m], auxs ? auxs[m] : nullptr);
-        h->cur = h->st;
-        if (rc != STAGE_OK) break;
+      }
+      rc = fwd_group(h, m, t.n, s, at(xs, m), at(ys, m), at(auxs, m));
+      h->cur = h->st;
+      if (rc != STAGE_OK) break;
+      if (lanes) {
         if ((rc = hip_ok(hipEventRecord(h->ev_f[s], h->fwd))) != STAGE_OK) break;
         last_f_slot = s;
-      } else if ((rc = stage_fwd(h, m, xs ? xs[m] : nullptr, ys ? ys[m] : nullptr, auxs ? auxs[m] : nullptr)) != STAGE_OK) break;
+      }
     } else {
-      int s = -1;
       const bool second = two && (n_bwd & 1);
       hipStream_t bs = second ? h->bwd2 : h->st;
       ++n_bwd;
+      const int s = find_slot(h, m);
       if (lanes) {
         if (second && !used_b2) {
           if ((rc = hip_ok(hipStreamWaitEvent(bs, h->ev_start, 0))) != STAGE_OK) break;
           used_b2 = true;
         }
-        s = find_slot(h, m);
         int w = strict ? last_f_slot : s;
         if (w >= 0 && (rc = hip_ok(hipStreamWaitEvent(bs, h->ev_f[w], 0))) != STAGE_OK) break;
       }
       h->cur = bs;
-      h->ws_shift = second ? h->L.workspace_bytes : 0;
-      rc = stage_bwd(h, m, dys ? dys[m] : nullptr, dxs ? dxs[m] : nullptr);
+      h->ws_shift = second ? h->L.ws_stride : 0;
+      rc = bwd_group(h, t.n, s, at(dys, m), at(dxs, m));
       h->cur = h->st;
       h->ws_shift = 0;
       if (rc != STAGE_OK) break;
@@ -1162,7 +1339,7 @@ int stage_sync(stage_handle h) {
     if (hipMemcpy(info, h->ws(h->L.wh_info), 8, hipMemcpyDeviceToHost) != hipSuccess)
       return fail(STAGE_E_DEVICE, "hipMemcpy failed");
     for (int c = 0; h->L.recompute && !info[1] && c < h->L.ws_copies; ++c)
-      if (hipMemcpy(info, h->ws((size_t)c * h->L.workspace_bytes + h->L.wh_info2), 8, hipMemcpyDeviceToHost) != hipSuccess)
+      if (hipMemcpy(info, h->ws((size_t)c * h->L.ws_stride + h->L.wh_info2), 8, hipMemcpyDeviceToHost) != hipSuccess)
         return fail(STAGE_E_DEVICE, "hipMemcpy failed");
     if (info[1]) return fail(STAGE_E_CONFIG, "a micro-batch predicted more rows than mlm_max_rows; the surplus was dropped");
   }

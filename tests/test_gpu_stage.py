@@ -443,3 +443,42 @@ def test_graph_replays_of_the_other_stage_kinds(kind):
                 assert np.array_equal(r.grads.cpu().numpy(), eager["grads"])
         finally:
             r.close()
+
+
+@pytest.mark.parametrize("kind", ["middle", "first", "last", "f32", "odd"])
+@pytest.mark.parametrize("M,K,order", [(7, 4, "early"), (5, 3, "early"), (8, 6, "early"), (5, 5, "gpipe")])
+def test_groups_of_micro_batches_change_no_bit(kind, M, K, order):
+    """Several micro-batches per set of launches (buffers one behind the other: what the built-in orders make of
+    them) against the same list task by task, separate buffers: group sizes that divide K, a short last group, token
+    counts that are no multiple of 8 or of a k-tile, every stage kind."""
+    import torch
+    s, b = (37, 3) if kind == "odd" else (60, 2)
+    cfg = I.StageConfig(2, 128, 2, 256, s, b, M, K, "f32" if kind == "f32" else "bf16", has_embedding=kind == "first",
+                        has_mlm_head=kind == "last", vocab=200, max_pos=64)
+    theta, mbs = make_inputs(cfg, SEED, M)
+    ordr = B.ORDER_GPIPE if order == "gpipe" else B.ORDER_EARLY_BACKWARD
+    ops = B.stage_schedule_ops(M, K, ordr)
+    ref = run_gpu(cfg, theta, mbs, M, K, B.ORDER_EXPLICIT, max_slots=K, explicit_ops=ops)
+    T, H = cfg.tokens, cfg.hidden
+    r = B.StageRunner(c_config(cfg, K), theta)
+    try:
+        td = torch.float32 if kind == "f32" else torch.bfloat16
+        stack = lambda key, shape, dt: torch.stack([torch.as_tensor(mb[key]).reshape(shape) for mb in mbs]).to(dt).cuda().contiguous()
+        emb, head = cfg.has_embedding, cfg.has_mlm_head
+        xs = stack("ids", (T,), torch.int32) if emb else stack("x", (T, H), td)
+        dys = None if head else stack("dy", (T, H), td)
+        auxs = stack("targets", (T,), torch.int32) if head else None
+        ys = torch.zeros(M, 1, device="cuda") if head else torch.zeros(M, T, H, dtype=td, device="cuda")
+        dxs = None if emb else torch.zeros(M, T, H, dtype=td, device="cuda")
+        ptr = lambda t: None if t is None else [t[m].data_ptr() for m in range(M)]
+        B.stage_run_schedule(r.h, M, K, ordr, ptr(xs), ptr(dys), ptr(ys), ptr(dxs), ptr(auxs))
+        B.stage_sync(r.h)
+        st = B.stage_stats(r.h)
+        assert st.peak_live_slots == K and st.fwd_tasks == M and st.bwd_tasks == M
+        assert st.kernel_launches < ref["stats"]["launches"]
+        assert np.array_equal(r.grads.cpu().numpy(), ref["grads"])
+        for m in range(M):
+            assert np.array_equal(to_np(ys[m]), ref["ys"][m])
+            assert emb or np.array_equal(to_np(dxs[m]), ref["dxs"][m])
+    finally:
+        r.close()
