@@ -64,6 +64,12 @@ struct GemmArgs {
 };
 
 hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st);
+// the MFMA kernel's launches per operand layout (a = A k-strided, b = B k-strided: nn, nt, tn, tt); tile: see
+// launch_gemm; short_k: K segments that are no multiple of 64
+hipError_t launch_mfma_nn(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
+hipError_t launch_mfma_nt(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
+hipError_t launch_mfma_tn(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
+hipError_t launch_mfma_tt(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
 // fp32 products on the fp32 matrix instructions (gemm_f32.hip): whether they take this problem (else the plain
 // kernel does), and the launch
 bool gemm_f32_takes(const GemmArgs& g);
