@@ -116,28 +116,32 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 //                                      256-byte rows, and three tiles are in flight in the LDS of two of 64
 //   6: 128x128, five stages of 64      one workgroup per unit: T=4096 N=1024 K=4096 67 -> 45
 //   7: 64x64, four stages of 64        T=512 N=1024 K=4096 24 (128x64) -> 17, K=1024 10.5 -> 7.6; T=1024 25 -> 19
+// A stream restricted to part of the units (GemmArgs::units) moves the lines with it: four stages of 2048 rows on 64
+// units each, 36.7 -> 32.2 ms per iteration.  Where another stream's products run beside this one (GemmArgs::shared: the
+// data gradients beside the weight gradients) the tile with the whole LDS keeps them off its unit: 12 layers of 1024
+// with 4096 rows take 28.4 ms with the five-stage ring and 27.3 with two stages, though alone it is the faster one.
 // No bit of a result depends on the choice: an output element is one wave's sum in ascending k whatever the tile.
 static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   auto tiles = [&](long m, long n) { return ((g.M + m - 1) / m) * ((g.N + n - 1) / n) * g.batch; };
-  const long t128 = tiles(128, 128);
+  const long t128 = tiles(128, 128), U = g.units > 0 ? g.units : 256, most = 3 * U / 4;
   const bool bsum = (g.epi & EPI_BSUM) != 0;   // (offered for the weight-gradient layout only)
   int tile = g.tile;   // GemmArgs::tile names a configuration instead (tests, timing)
   if (tile == 5 && !tt) tile = 3;
   if (bsum && (tile == 1 || tile == 2 || tile == 6)) tile = 0;
-  if (short_k) return tile == 3 || (tile != 4 && t128 >= 192) ? 3 : 4;
+  if (short_k) return tile == 3 || (tile != 4 && t128 >= most) ? 3 : 4;
   if (g.epi & EPI_SEGACC) tile = 0;
   if (tile) return tile;
   if (tt) {
-    if (t128 >= 192) return 5;
-    return tiles(128, 64) >= 192 ? 4 : 7;
+    if (t128 >= most) return 5;
+    return tiles(128, 64) >= most ? 4 : 7;
   }
   const bool second = (g.epi & (EPI_ADD | EPI_MUL | EPI_GELU)) != 0;   // an epilogue that moves a second matrix
   const long t256 = tiles(256, 128);
-  if (tiles(256, 256) >= 192 && !(g.epi & (EPI_ADD | EPI_MUL))) return 1;
-  if (t256 >= 192 && t256 <= 256 && (g.K >= 2048 || !second || g.N <= 1024)) return 2;
-  if (t128 > 256) return 3;
-  if (t128 >= 192) return g.K >= 2048 ? 6 : 4;
-  return g.K >= 2048 && tiles(64, 64) > 256 ? 4 : 7;
+  if (tiles(256, 256) >= most && !(g.epi & (EPI_ADD | EPI_MUL))) return 1;
+  if (t256 >= most && t256 <= U && (g.K >= 2048 || !second || g.N <= 1024)) return 2;
+  if (t128 > U) return 3;
+  if (t128 >= most) return g.K >= 2048 ? (g.shared ? 3 : 6) : 4;
+  return g.K >= 2048 && tiles(64, 64) > U ? 4 : 7;
 }
 
 hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st) {

@@ -291,6 +291,7 @@ struct dapple_stage {
   std::vector<hipEvent_t> ev_f, ev_b;  // per slot: forward done (fwd lane), backward done (caller's stream)
   hipEvent_t ev_start = nullptr;
   bool serial = false, no_side = false;
+  int units = 0;               // compute units of the caller's stream when it is a partition (0 = all)
   std::vector<hipEvent_t> ev;  // per layer: 4 "inputs ready" events (main -> side) + 1 "layer done" (side -> main)
   std::vector<int> slot_of_mb;   // slot -> micro-batch id, -1 = free
   int live = 0, peak_live = 0;
@@ -361,6 +362,8 @@ struct dapple_stage {
     if (g.m_valid == 0) g.m_valid = g.M;
     if (g.n_valid == 0) g.n_valid = g.N;
     if (g.batch == 0) g.batch = 1;
+    g.units = units;
+    g.shared = cls == KC_GEMM_DGRAD && side != cur;
     double flops = 2.0 * g.M * g.N * (double)g.K * g.batch;
     hipStream_t s_ = on_side ? side : cur;
     return run_on(s_, cls, flops, [&](hipStream_t s) { return launch_gemm(dt, g, s); }, &g);
@@ -872,6 +875,11 @@ int stage_init(stage_handle* out, const stage_config* cfg, const void* weights_d
   h->grads = (float*)arena_dev;
   h->st = (hipStream_t)hip_stream;
   h->slot_of_mb.assign(cfg->max_slots, -1);
+  {
+    int n = 0;
+    if (const uint32_t* mask = partition_mask_of(h->st, &n))
+      for (int i = 0; i < n; ++i) h->units += __builtin_popcount(mask[i]);
+  }
   if (!dry) {
     // default priority on purpose; the side stream never outlives the handle
     h->serial = h->no_side = (cfg->flags & STAGE_FLAG_ONE_STREAM) != 0;
