@@ -147,33 +147,102 @@ __device__ __forceinline__ int aswz(int r) {
   return (r >> 2) & 3;
 }
 
-// a 64 x D block in flight from global memory: D/32 chunks of 16 bytes per thread (256 threads)
+// The streamed side: blocks of 64 rows of two matrices X and Y (keys and values; queries and output gradients) go
+// through a ring of NS blocks in LDS, requested NS - 1 blocks ahead with loads that write LDS directly.  (Through
+// registers, one block ahead, every block waited for memory: a block's arithmetic is about 0.6 us, a request takes
+// longer.)  1 KiB per wave instruction in lane order, so the swizzle is applied to WHICH chunk a lane fetches; rows
+// past the end lie beyond the buffer's record count and read as zero, columns past d get an offset out of range.
+// A wave owns PER consecutive instructions of one of the two matrices.
 typedef int i32x4 __attribute__((ext_vector_type(4)));
-template <int D, bool RAG>
-struct BlockD {
-  static constexpr int N = D / 32, CPR = D / 8;
-  // native vectors: with the runtime's uint4 (a struct around a union) the compiler kept the block in scratch
-  // memory and waited for the loads at once
-  i32x4 c[N];
-  // rows: how many of the 64 rows exist; d: columns that exist
-  __device__ __forceinline__ void load(const bf16* g, int ldg, int tid, int rows, int d) {
+template <int D, int NW, int NS_, bool STATS>
+struct Ring {
+  static constexpr int NS = NS_, IPM = D / 8, PER = 2 * IPM / NW;          // instructions per matrix and block; per wave
+  static constexpr int Y_OFF = 64 * D * 2, S_OFF = 2 * Y_OFF;              // X, Y, then four rows of 64 fp32 (STATS)
+  static constexpr int STAGE = S_OFF + (STATS ? 1024 : 0), BYTES = NS * STAGE;
+  static constexpr int SPW = STATS ? 4 / NW : 0;   // rows of the statistics per wave
+  static constexpr int BIAS = 3072, LOADS = PER + SPW;
+  static_assert(PER <= IPM && (PER == 2 || PER % 4 == 0), "a wave's share lies in one matrix");
+  static_assert((NS - 2) * LOADS < 64, "vmcnt is a 6-bit counter");
+  int voff[PER];
+  i32x4 rs, st[SPW ? SPW : 1];   // buffer resources: the wave's matrix; its rows of the statistics
+  int step, left, sleft[SPW ? SPW : 1], m0w, m0s;
+  // g: the wave's matrix (head's first column of row 0); ld in elements; stat(r): row r of the statistics, fp32 per row
+  // of X and Y, or NULL (reads zero)
+  template <typename F>
+  __device__ __forceinline__ void init(const bf16* g, int ld, int s, int d, int wave, int lane, F&& stat) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int r = (tid + 256 * i) / CPR, kc = tid % CPR;
-      if (RAG) {
-        c[i] = i32x4{0, 0, 0, 0};
-        if (r < rows && kc * 8 < d) c[i] = *(const i32x4*)(g + (long)r * ldg + kc * 8);
-      } else {
-        c[i] = *(const i32x4*)(g + (long)r * ldg + kc * 8);
-      }
+    for (int j = 0; j < PER; ++j) {
+      const int pos = ((wave * PER + j) % IPM) * 64 + lane, r = pos / (D / 8), c = (pos % (D / 8)) ^ aswz<D>(r);
+      voff[j] = c * 8 < d ? (r * ld + c * 8) * 2 + BIAS - (j % 4) * 1024 : (int)0x80000000;
     }
+    set(rs, (uint64_t)g - BIAS);
+    step = 64 * ld * 2;
+    left = ((s - 1) * ld + d) * 2;
+    m0w = __builtin_amdgcn_readfirstlane(wave * PER * 1024);
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) {
+      const float* p = stat(wave + NW * i);
+      set(st[i], (uint64_t)p);
+      sleft[i] = p ? s * 4 : 0;
+    }
+    m0s = __builtin_amdgcn_readfirstlane(S_OFF + wave * 256);
   }
-  __device__ __forceinline__ void store(bf16* S, int tid) const {
+  static __device__ __forceinline__ void set(i32x4& r, uint64_t p) {
+    r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+    r[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32));
+    r[3] = 0x00020000;   // raw buffer, 32-bit data format
+  }
+  // request the next block into stage `stage`.  Inline assembly, and the waits counted by hand, for the reasons given
+  // at OperandTile::load_group in gemm_mfma.h (which also has the wait states).
+  __device__ __forceinline__ void request(int stage, int lane) {
+    const int base = __builtin_amdgcn_readfirstlane(stage * STAGE);
+    rs[2] = __builtin_amdgcn_readfirstlane(left > 0 ? left + BIAS : 0);
+    const int mw = __builtin_amdgcn_readfirstlane(base + m0w);
+    if constexpr (PER == 2) {
+      asm volatile(
+          "s_nop 4\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\t"
+          "buffer_load_dwordx4 %1, %3, 0 offen lds\n\t"
+          "buffer_load_dwordx4 %2, %3, 0 offen offset:1024 lds"
+          :
+          : "s"(mw), "v"(voff[0]), "v"(voff[1]), "s"(rs)
+          : "memory", "m0");
+    } else {
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int r = (tid + 256 * i) / CPR, kc = tid % CPR;
-      *(i32x4*)(S + r * D + ((kc ^ aswz<D>(r)) << 3)) = c[i];
+      for (int j = 0; j < PER; j += 4)
+        asm volatile(
+            "s_nop 4\n\ts_add_u32 m0, %0, %1\n\ts_nop 0\n\t"
+            "buffer_load_dwordx4 %2, %6, 0 offen lds\n\t"
+            "buffer_load_dwordx4 %3, %6, 0 offen offset:1024 lds\n\t"
+            "buffer_load_dwordx4 %4, %6, 0 offen offset:2048 lds\n\t"
+            "buffer_load_dwordx4 %5, %6, 0 offen offset:3072 lds"
+            :
+            : "s"(mw), "s"(j * 1024), "v"(voff[j]), "v"(voff[j + 1]), "v"(voff[j + 2]), "v"(voff[j + 3]), "s"(rs)
+            : "memory", "m0", "scc");
     }
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) {
+      st[i][2] = __builtin_amdgcn_readfirstlane(sleft[i] > 0 ? sleft[i] : 0);
+      const int ms = __builtin_amdgcn_readfirstlane(base + m0s + i * NW * 256);
+      const int off = lane * 4;
+      asm volatile(
+          "s_nop 4\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\t"
+          "buffer_load_dword %1, %2, 0 offen lds"
+          :
+          : "s"(ms), "v"(off), "s"(st[i])
+          : "memory", "m0");
+      set(st[i], (((uint64_t)(uint32_t)st[i][1] << 32) | (uint32_t)st[i][0]) + 256);
+      sleft[i] -= 256;
+    }
+    set(rs, (((uint64_t)(uint32_t)rs[1] << 32) | (uint32_t)rs[0]) + (uint64_t)step);
+    left -= step;
+  }
+  // every wave's part of the oldest block is in LDS, and every wave is done with the block before it
+  static __device__ __forceinline__ void wait() {
+    constexpr int N = (NS - 2) * LOADS;
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);   // vmcnt(N), lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
   }
 };
 // operand fragment, contraction index contiguous in LDS: rows r0 + (lane&31), k = 16 kk + 8 (lane>>5) + e
@@ -241,6 +310,17 @@ __device__ __forceinline__ float delta_at(const AttnArgs& a, int bi, int hh, int
 // rescale denormal results, and a probability below 2^-126 may as well be zero
 __device__ __forceinline__ float exp2_neg(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// max / sum of the two half waves' values (a row's 64 keys sit in lanes l and l + 32), in both; v_permlane32_swap is an
+// ordinary vector instruction where a shuffle is a trip through the LDS crossbar
+__device__ __forceinline__ float halves_max(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+}
+__device__ __forceinline__ float halves_sum(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
 __device__ __forceinline__ f32x16 zero16() {
   f32x16 z;
 #pragma unroll
@@ -248,46 +328,41 @@ __device__ __forceinline__ f32x16 zero16() {
   return z;
 }
 
-// (Forward with the key blocks split over two waves per SIMD, merged at the end: 12.9 instead of 14.7 us alone, but
-// the iteration gets 0.7% slower: the workgroup then fills both wave slots of its SIMDs and keeps the other streams'
-// kernels off the compute unit.  One wave per SIMD it stays.)
-template <int D, bool RAG, bool HL>
-__global__ __launch_bounds__(256) void attn_fwd_mfma(AttnArgs a, float scale2) {
+// NW: waves per workgroup (4, or 2 where the grid is small), each with 32 query rows
+template <int D, bool RAG, bool HL, int NW>
+__global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnArgs a, float scale2) {
   constexpr int NKK = D / 16, NDB = D / 32;
-  __shared__ __attribute__((aligned(16))) bf16 Ks[64 * D];
-  __shared__ __attribute__((aligned(16))) bf16 Vs[64 * D];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
+  typedef Ring<D, NW, D == 128 ? 2 : 3, false> R;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char asm_[];
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int bi = blockIdx.y / a.A, hh = blockIdx.y % a.A;
   const int d = RAG ? a.d : D;
   const long hb = (long)bi * a.s * a.H + hh * d;
   const bf16 *Q = (const bf16*)a.q + hb, *K = (const bf16*)a.k + hb, *V = (const bf16*)a.v + hb;
-  const int qrow = blockIdx.x * 128 + wave * 32 + (lane & 31);
+  const int qrow = blockIdx.x * (32 * NW) + wave * 32 + (lane & 31);
   const bool qok = qrow < a.s;
   const int nkb = RAG ? (a.s + 63) / 64 : a.s / 64;
-  BlockD<D, RAG> kblk, vblk;  // the next key/value block, in flight while the current one is used
-  kblk.load(K, a.H, tid, a.s, d);
-  vblk.load(V, a.H, tid, a.s, d);
-
   bf16x8 qf[NKK];
 #pragma unroll
   for (int kk = 0; kk < NKK; ++kk) qf[kk] = frag_global<RAG>(Q, qrow, qok, a.H, kk, lane, d);
+  R ring;
+  ring.init(wave < NW / 2 ? K : V, a.H, a.s, d, wave, lane, [](int) { return (const float*)nullptr; });
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // the query fragments are here: the counts below are the ring's alone
+#pragma unroll
+  for (int t = 0; t < R::NS - 1; ++t) ring.request(t, lane);
 
   float m = -INFINITY, l = 0.f;
   f32x16 o[NDB];  // rows d = 32 dblk + 8 blk + 4 h + e, column = the lane's query
 #pragma unroll
   for (int db = 0; db < NDB; ++db) o[db] = zero16();
 
+  int stage = 0;
   for (int kb = 0; kb < nkb; ++kb) {
-    __syncthreads();
-    kblk.store(Ks, tid);
-    vblk.store(Vs, tid);
-    __syncthreads();
-    {  // unconditional: the last iteration fetches its own block again (harmless, and it keeps
-       // the in-flight block in registers instead of scratch)
-      const int nb = kb + 1 < nkb ? kb + 1 : kb;
-      kblk.load(K + (long)nb * 64 * a.H, a.H, tid, a.s - nb * 64, d);
-      vblk.load(V + (long)nb * 64 * a.H, a.H, tid, a.s - nb * 64, d);
-    }
+    R::wait();
+    ring.request(stage == 0 ? R::NS - 1 : stage - 1, lane);   // (past the last block: reads nothing)
+    const bf16 *Ks = (const bf16*)(asm_ + stage * R::STAGE), *Vs = (const bf16*)((const unsigned char*)Ks + R::Y_OFF);
+    stage = stage + 1 == R::NS ? 0 : stage + 1;
     float p[2][16];
     float mx = -INFINITY;
     // All LDS reads of a phase are issued before its first MFMA (left to itself the compiler
@@ -314,7 +389,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(AttnArgs a, float scale2) {
       for (int kk = 0; kk < NKK; ++kk) sa = MFMA(kf[kb2][kk], qf[kk], sa);
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        p[kb2][v] = sa[v] * scale2;
+        p[kb2][v] = sa[v];
         if (RAG && kb * 64 + kb2 * 32 + 8 * (v >> 2) + 4 * h + (v & 3) >= a.s) p[kb2][v] = -INFINITY;
         mx = fmaxf(mx, p[kb2][v]);
       }
@@ -326,19 +401,18 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(AttnArgs a, float scale2) {
         for (int db = 0; db < NDB; ++db) vf[ks][db] = frag_cols<D>(Vs, db * 32, ks * 16, lane);
       __builtin_amdgcn_sched_barrier(0);
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    float mn = fmaxf(m, mx);
-    float alpha = exp2_neg(m - mn);
+    // the maximum is taken over the raw products (the scale is positive): one multiply-add per logit, not two steps
+    const float mn = fmaxf(m, halves_max(mx) * scale2);
+    const float alpha = exp2_neg(m - mn);
     float rs = 0.f;
 #pragma unroll
     for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        p[kb2][v] = exp2_neg(p[kb2][v] - mn);
+        p[kb2][v] = exp2_neg(fmaf(p[kb2][v], scale2, -mn));
         rs += p[kb2][v];
       }
-    rs += __shfl_xor(rs, 32, 64);
-    l = l * alpha + rs;
+    l = l * alpha + halves_sum(rs);
     m = mn;
     // the running maximum of most rows settles after the first key blocks: skip the rescale of
     // the accumulator registers when no lane of the wave needs it (alpha == 1 exactly)
@@ -364,6 +438,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(AttnArgs a, float scale2) {
       }
     }
   }
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // the ring's last requests (they read nothing) before the wave may end
   if (qok) {
     float inv = 1.0f / l;
     bf16* C = (bf16*)a.ctx + hb + (long)qrow * a.H;
@@ -385,19 +460,20 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(AttnArgs a, float scale2) {
   }
 }
 
-// dk, dv: the wave owns 32 key rows; query blocks of 64 stream through LDS (Qs, Gs; Ls, Ds: their lse and delta)
-template <int D, bool RAG, bool HL>
-__device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, float scale, bf16* Qs, bf16* Gs, float* Ls,
-                                               float* Ds) {
+// dk, dv: the wave owns 32 key rows; query blocks of 64 stream through LDS with their lse and delta (the two blocks
+// of 32 columns a head of 64 has are added where they are read)
+template <int D, bool RAG, bool HL, int NW, typename R>
+__device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, float scale, const unsigned char* sm) {
   constexpr int NKK = D / 16, NDB = D / 32;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int bi = blockIdx.y / a.A, hh = blockIdx.y % a.A;
   const int d = RAG ? a.d : D;
   const long hb = (long)bi * a.s * a.H + hh * d;
   const bf16 *Q = (const bf16*)a.q + hb, *K = (const bf16*)a.k + hb, *V = (const bf16*)a.v + hb,
              *G = (const bf16*)a.dctx + hb;
   const float* lse = a.lse + ((long)bi * a.A + hh) * a.s;
-  const int krow = blockIdx.x * 128 + wave * 32 + (lane & 31);
+  const int krow = blockIdx.x * (32 * NW) + wave * 32 + (lane & 31);
   const bool kok = krow < a.s;
 
   bf16x8 kf[NKK], vf[NKK];
@@ -410,30 +486,27 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
 #pragma unroll
   for (int db = 0; db < NDB; ++db) dv[db] = dk[db] = zero16();
   const int nqb = RAG ? (a.s + 63) / 64 : a.s / 64;
-  BlockD<D, RAG> qblk, gblk;  // the next query / dctx block, in flight while the current one is used
-  // a query beyond the last has zero rows, lse 0 and delta 0: probability 1 times a zero row, dS = 0
-  auto load_stat = [&](int qb) {
-    const int q = qb * 64 + (tid & 63);
-    if (tid >= 128 || (RAG && q >= a.s)) return 0.f;
-    return tid < 64 ? lse[q] : delta_at<D>(a, bi, hh, q);
-  };
-  qblk.load(Q, a.H, tid, a.s, d);
-  gblk.load(G, a.H, tid, a.s, d);
-  float stat = load_stat(0);
+  // row 0 of the statistics: lse; 1 and 2: delta, or its blocks of 32 columns; 3: unused.
+  // A query beyond the last has zero rows, lse 0 and delta 0: probability 1 times a zero row, dS = 0.
+  const long T = (long)a.b * a.s;
+  const float *d0 = a.delta + ((long)bi * a.A + hh) * a.s, *d1 = nullptr;
+  if (a.delta_blocks) {
+    d0 = a.delta_blocks + (long)(D / 32 * hh) * T + (long)bi * a.s;
+    if (D >= 64) d1 = d0 + T;
+  }
+  R ring;
+  ring.init(wave < NW / 2 ? Q : G, a.H, a.s, d, wave, lane, [&](int r) { return r == 0 ? lse : (r == 1 ? d0 : (r == 2 ? d1 : nullptr)); });
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // the key and value fragments are here: the counts below are the ring's alone
+#pragma unroll
+  for (int t = 0; t < R::NS - 1; ++t) ring.request(t, lane);
 
+  int stage = 0;
   for (int qb = 0; qb < nqb; ++qb) {
-    __syncthreads();
-    qblk.store(Qs, tid);
-    gblk.store(Gs, tid);
-    if (tid < 64) Ls[tid] = stat;
-    else if (tid < 128) Ds[tid - 64] = stat;
-    __syncthreads();
-    {  // unconditional (the last iteration fetches its own block again): keeps the block in registers
-      const int nb = qb + 1 < nqb ? qb + 1 : qb;
-      qblk.load(Q + (long)nb * 64 * a.H, a.H, tid, a.s - nb * 64, d);
-      gblk.load(G + (long)nb * 64 * a.H, a.H, tid, a.s - nb * 64, d);
-      stat = load_stat(nb);
-    }
+    R::wait();
+    ring.request(stage == 0 ? R::NS - 1 : stage - 1, lane);
+    const bf16 *Qs = (const bf16*)(sm + stage * R::STAGE), *Gs = (const bf16*)((const unsigned char*)Qs + R::Y_OFF);
+    const float *Ls = (const float*)((const unsigned char*)Qs + R::S_OFF), *Ds = Ls + 64;
+    stage = stage + 1 == R::NS ? 0 : stage + 1;
 #pragma unroll
     for (int qb2 = 0; qb2 < 2; ++qb2) {
       // every LDS read of a phase before its first MFMA (see attn_fwd_mfma)
@@ -448,6 +521,10 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
       for (int blk = 0; blk < 4; ++blk) {
         L4s[blk] = *(const float4*)(Ls + qb2 * 32 + 8 * blk + 4 * h);
         D4s[blk] = *(const float4*)(Ds + qb2 * 32 + 8 * blk + 4 * h);
+        if (D >= 64) {   // the second block of delta (zero where delta comes whole)
+          const float4 x = *(const float4*)(Ds + 64 + qb2 * 32 + 8 * blk + 4 * h);
+          D4s[blk].x += x.x; D4s[blk].y += x.y; D4s[blk].z += x.z; D4s[blk].w += x.w;
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
       f32x16 sa = zero16(), dp = zero16();  // rows: query 32 qb2 + 8 blk + 4 h + e, column: key
@@ -471,7 +548,7 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
         float Lv[4] = {L4.x, L4.y, L4.z, L4.w}, Dv[4] = {D4.x, D4.y, D4.z, D4.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          float pv = exp2_neg(sa[4 * blk + e] * scale2 - Lv[e]);
+          float pv = exp2_neg(fmaf(sa[4 * blk + e], scale2, -Lv[e]));
           p[4 * blk + e] = pv;
           ds[4 * blk + e] = pv * (dp[4 * blk + e] - Dv[e]);
         }
@@ -495,6 +572,7 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
       }
     }
   }
+  __builtin_amdgcn_s_waitcnt(0x0F70);
   if (kok) {
     bf16* DK = (bf16*)a.dk + hb + (long)krow * a.H;
     bf16* DV = (bf16*)a.dv + hb + (long)krow * a.H;
@@ -517,16 +595,17 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
 }
 
 // dq: the wave owns 32 query rows; key blocks of 64 stream through LDS
-template <int D, bool RAG, bool HL>
-__device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, float scale, bf16* Ks, bf16* Vs) {
+template <int D, bool RAG, bool HL, int NW, typename R>
+__device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, float scale, const unsigned char* sm) {
   constexpr int NKK = D / 16, NDB = D / 32;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int bi = blockIdx.y / a.A, hh = blockIdx.y % a.A;
   const int d = RAG ? a.d : D;
   const long hb = (long)bi * a.s * a.H + hh * d;
   const bf16 *Q = (const bf16*)a.q + hb, *K = (const bf16*)a.k + hb, *V = (const bf16*)a.v + hb,
              *G = (const bf16*)a.dctx + hb;
-  const int qrow = blockIdx.x * 128 + wave * 32 + (lane & 31);
+  const int qrow = blockIdx.x * (32 * NW) + wave * 32 + (lane & 31);
   const bool qok = qrow < a.s;
   const float Lq = qok ? a.lse[((long)bi * a.A + hh) * a.s + qrow] : 0.f;
 
@@ -541,21 +620,18 @@ __device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, fl
 #pragma unroll
   for (int db = 0; db < NDB; ++db) dq[db] = zero16();
   const int nkb = RAG ? (a.s + 63) / 64 : a.s / 64;
-  BlockD<D, RAG> kblk, vblk;
-  kblk.load(K, a.H, tid, a.s, d);
-  vblk.load(V, a.H, tid, a.s, d);
+  R ring;
+  ring.init(wave < NW / 2 ? K : V, a.H, a.s, d, wave, lane, [](int) { return (const float*)nullptr; });   // (the statistics' loads read nothing)
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+#pragma unroll
+  for (int t = 0; t < R::NS - 1; ++t) ring.request(t, lane);
 
+  int stage = 0;
   for (int kb = 0; kb < nkb; ++kb) {
-    __syncthreads();
-    kblk.store(Ks, tid);
-    vblk.store(Vs, tid);
-    __syncthreads();
-    {  // unconditional: the last iteration fetches its own block again (harmless, and it keeps
-       // the in-flight block in registers instead of scratch)
-      const int nb = kb + 1 < nkb ? kb + 1 : kb;
-      kblk.load(K + (long)nb * 64 * a.H, a.H, tid, a.s - nb * 64, d);
-      vblk.load(V + (long)nb * 64 * a.H, a.H, tid, a.s - nb * 64, d);
-    }
+    R::wait();
+    ring.request(stage == 0 ? R::NS - 1 : stage - 1, lane);
+    const bf16 *Ks = (const bf16*)(sm + stage * R::STAGE), *Vs = (const bf16*)((const unsigned char*)Ks + R::Y_OFF);
+    stage = stage + 1 == R::NS ? 0 : stage + 1;
 #pragma unroll
     for (int kb2 = 0; kb2 < 2; ++kb2) {
       // every LDS read of a phase before its first MFMA (see attn_fwd_mfma)
@@ -580,7 +656,7 @@ __device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, fl
       float ds[16];
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        ds[v] = exp2_neg(sa[v] * scale2 - Lq) * (dp[v] - Dq);
+        ds[v] = exp2_neg(fmaf(sa[v], scale2, -Lq)) * (dp[v] - Dq);
         // a key beyond the last: its logit 0 may lie far above the row's logsumexp, so it is masked, not multiplied away
         if (RAG && kb * 64 + kb2 * 32 + 8 * (v >> 2) + 4 * h + (v & 3) >= a.s) ds[v] = 0.f;
       }
@@ -597,6 +673,7 @@ __device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, fl
       }
     }
   }
+  __builtin_amdgcn_s_waitcnt(0x0F70);
   if (qok) {
     bf16* DQ = (bf16*)a.dq + hb + (long)qrow * a.H;
 #pragma unroll
@@ -645,14 +722,16 @@ __global__ __launch_bounds__(256) void attn_delta_rows(AttnArgs a) {
 
 // both roles in one launch: grid.z = 0 the dq workgroups, 1 the dk/dv workgroups.  At most 256 registers per lane up
 // to D = 64, so that a workgroup of each role shares a compute unit; D = 128 keeps twice the accumulators.
-template <int D, bool RAG, bool HL>
-__global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_mfma(AttnArgs a, float scale2, float scale) {
-  __shared__ __attribute__((aligned(16))) bf16 X[64 * D];
-  __shared__ __attribute__((aligned(16))) bf16 Y[64 * D];
-  __shared__ __attribute__((aligned(16))) float Ls[64];
-  __shared__ __attribute__((aligned(16))) float Ds[64];
-  if (blockIdx.z == 0) attn_dq_body<D, RAG, HL>(a, scale2, scale, X, Y);
-  else attn_dkdv_body<D, RAG, HL>(a, scale2, scale, X, Y, Ls, Ds);
+template <int D, int NW>
+struct BwdRing {
+  typedef Ring<D, NW, D == 128 ? 2 : 3, true> R;
+};
+template <int D, bool RAG, bool HL, int NW>
+__global__ __launch_bounds__(64 * NW, D <= 64 ? 2 : 1) void attn_bwd_mfma(AttnArgs a, float scale2, float scale) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char asm_[];
+  typedef typename BwdRing<D, NW>::R R;
+  if (blockIdx.z == 0) attn_dq_body<D, RAG, HL, NW, R>(a, scale2, scale, asm_);
+  else attn_dkdv_body<D, RAG, HL, NW, R>(a, scale2, scale, asm_);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -660,40 +739,50 @@ static bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 // Every bf16 head of up to 128 columns in whole 16-byte chunks, at any sequence length
 bool attn_uses_mfma(Dtype dt, const AttnArgs& a) {
-  return dt == DT_BF16 && a.d % 8 == 0 && a.d <= 128 && a.H % 8 == 0 && al16(a.q) && al16(a.k) && al16(a.v) &&
+  return dt == DT_BF16 && a.d % 8 == 0 && a.d <= 128 && a.H % 8 == 0 && (long)a.s * a.H < (1L << 30) - 4096 && al16(a.q) && al16(a.k) && al16(a.v) &&
          al16(a.ctx) && (a.dctx == nullptr || (al16(a.dctx) && al16(a.dq) && al16(a.dk) && al16(a.dv)));
 }
 bool attn_takes_delta_blocks(Dtype dt, const AttnArgs& a) {
-  return attn_uses_mfma(dt, a) && (a.d == 32 || a.d == 64 || a.d == 128);
+  return attn_uses_mfma(dt, a) && (a.d == 32 || a.d == 64);
 }
 
-// f(D, RAG, HL) as constants for the shape: the narrowest block that holds a head
+// f(D, RAG, HL, NW) as constants for the shape: the narrowest block that holds a head; workgroups of four waves (128
+// rows), or of two where four would leave a quarter of the 256 units without one (one sample of 512 tokens, 16 heads:
+// 64 workgroups of four); roles: workgroups per block of rows (the backward has two)
 template <typename F>
-static void pick_variant(const AttnArgs& a, F&& f) {
+static void pick_variant(const AttnArgs& a, int roles, F&& f) {
   typedef std::true_type T;
   typedef std::false_type N;
   const bool rag = a.s % 64 != 0;
+  auto waves = [&](auto D, auto RAG, auto HL) {
+    if ((long)((a.s + 127) / 128) * a.b * a.A * roles < 192) f(D, RAG, HL, std::integral_constant<int, 2>{});
+    else f(D, RAG, HL, std::integral_constant<int, 4>{});
+  };
   if (a.d <= 32) {
-    if (rag || a.d != 32) f(std::integral_constant<int, 32>{}, T{}, T{});
-    else f(std::integral_constant<int, 32>{}, N{}, T{});
+    if (rag || a.d != 32) waves(std::integral_constant<int, 32>{}, T{}, T{});
+    else waves(std::integral_constant<int, 32>{}, N{}, T{});
   } else if (a.d <= 64) {
-    if (rag || a.d != 64) f(std::integral_constant<int, 64>{}, T{}, T{});
-    else f(std::integral_constant<int, 64>{}, N{}, N{});
+    if (rag || a.d != 64) waves(std::integral_constant<int, 64>{}, T{}, T{});
+    else waves(std::integral_constant<int, 64>{}, N{}, N{});
   } else {
-    if (rag || a.d != 128) f(std::integral_constant<int, 128>{}, T{}, T{});
-    else f(std::integral_constant<int, 128>{}, N{}, T{});
+    if (rag || a.d != 128) waves(std::integral_constant<int, 128>{}, T{}, T{});
+    else waves(std::integral_constant<int, 128>{}, N{}, T{});
   }
 }
 
 hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
   float scale2 = LOG2E / sqrtf((float)a.d);
   if (attn_uses_mfma(dt, a)) {
-    dim3 grid((a.s + 127) / 128, a.b * a.A);
-    pick_variant(a, [&](auto D, auto RAG, auto HL) {
-      auto kern = attn_fwd_mfma<decltype(D)::value, decltype(RAG)::value, decltype(HL)::value>;
-      hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a, scale2);
+    hipError_t e = hipSuccess;
+    pick_variant(a, 1, [&](auto D, auto RAG, auto HL, auto NW) {
+      constexpr int d = decltype(D)::value, nw = decltype(NW)::value, lds = Ring<d, nw, d == 128 ? 2 : 3, false>::BYTES;
+      auto kern = attn_fwd_mfma<d, decltype(RAG)::value, decltype(HL)::value, nw>;
+      static const hipError_t rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      if ((e = rc) != hipSuccess) return;
+      hipLaunchKernelGGL(kern, dim3((a.s + 32 * nw - 1) / (32 * nw), a.b * a.A), dim3(64 * nw), lds, st, a, scale2);
+      e = hipGetLastError();
     });
-    return hipGetLastError();
+    return e;
   }
   if (dt == DT_F32 && attn_f32_takes(a)) return launch_attn_fwd_f32(a, st);
   long total = (long)a.b * a.A * a.s * a.d;
@@ -718,12 +807,15 @@ hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
-    dim3 grid((a.s + 127) / 128, a.b * a.A, 2);
-    pick_variant(a, [&](auto D, auto RAG, auto HL) {
-      auto kern = attn_bwd_mfma<decltype(D)::value, decltype(RAG)::value, decltype(HL)::value>;
-      hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a, scale2, scale);
+    pick_variant(a, 2, [&](auto D, auto RAG, auto HL, auto NW) {
+      constexpr int d = decltype(D)::value, nw = decltype(NW)::value, lds = BwdRing<d, nw>::R::BYTES;
+      auto kern = attn_bwd_mfma<d, decltype(RAG)::value, decltype(HL)::value, nw>;
+      static const hipError_t rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      if ((e = rc) != hipSuccess) return;
+      hipLaunchKernelGGL(kern, dim3((a.s + 32 * nw - 1) / (32 * nw), a.b * a.A, 2), dim3(64 * nw), lds, st, a, scale2, scale);
+      e = hipGetLastError();
     });
-    return hipGetLastError();
+    return e;
   }
   if (dt == DT_F32 && attn_f32_takes(a)) return launch_attn_bwd_f32(a, st);
   if (dt == DT_BF16) hipLaunchKernelGGL(attn_delta_kernel<bf16>, gd, dim3(256), 0, st, a);

@@ -144,6 +144,30 @@ static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   return g.K >= 2048 && tiles(64, 64) > U ? 4 : 7;
 }
 
+GemmArgs wgrad_args(const WgradGroup& w, int i) {
+  const WgradProblem& p = w.p[i];
+  GemmArgs g{};
+  g.A = p.A; g.B = p.B; g.C = p.C; g.M = g.m_valid = p.M; g.N = g.n_valid = p.N; g.K = g.k_valid = w.K;
+  g.lda = p.lda; g.ldb = p.ldb; g.ldc = p.ldc; g.a_kstrided = g.b_kstrided = 1; g.batch = 1;
+  g.kseg_len = w.kseg; g.segA = (long)w.kseg * p.lda; g.segB = (long)w.kseg * p.ldb;
+  g.epi = EPI_ACC32 | (p.bsum ? EPI_BSUM : 0) | (w.K > w.kseg ? EPI_SEGACC : 0);
+  g.bsum_z[0] = p.bsum; g.units = w.units;
+  return g;
+}
+
+bool wgrad_group_takes(Dtype dt, const WgradGroup& w) {
+  if (w.n < 1 || w.n > WgradGroup::MAX || w.kseg < 1 || (w.K != w.kseg && w.K != 2 * w.kseg)) return false;
+  for (int i = 0; i < w.n; ++i) {
+    const GemmArgs g = wgrad_args(w, i);
+    if (!(dt == DT_BF16 ? gemm_uses_mfma(dt, g) : gemm_f32_takes(g))) return false;
+  }
+  return true;
+}
+
+hipError_t launch_wgrad_group(Dtype dt, const WgradGroup& w, hipStream_t st) {
+  return dt == DT_BF16 ? launch_wgrad_group_mfma(w, st) : launch_wgrad_group_f32(w, st);
+}
+
 hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
   const bool mfma = gemm_uses_mfma(dt, g);

@@ -65,13 +65,13 @@ struct F32Tile {
 };
 
 template <int BT, bool AKS, bool BKS>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, int tiles_n) {
+__device__ __forceinline__ void f32_tile(GemmArgs g, int tiles_n, const int bid, const int z) {
   typedef F32Tile<BT, AKS> TA;
   typedef F32Tile<BT, BKS> TB;
   constexpr int W = BT / 2, NB = W / 32;   // wave tile, 32-blocks per side
   extern __shared__ __attribute__((aligned(16))) float fsm[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l31 = lane & 31, h = lane >> 5;
-  const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n, z = blockIdx.z;
+  const int tm = bid / tiles_n, tn = bid % tiles_n;
   const int m0 = tm * BT, n0 = tn * BT, wm0 = (wave >> 1) * W, wn0 = (wave & 1) * W;
   const float* A = g.Az[0] ? (const float*)pick4(g.Az, z) : (const float*)g.A + z * g.sA;
   const float* B = g.Bz[0] ? (const float*)pick4(g.Bz, z) : (const float*)g.B + z * g.sB;
@@ -176,12 +176,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, int tiles_n) 
 
 // ------------------------------------------------------------------ few tiles: K split over the waves
 template <int TW, bool AKS, bool BKS>
-__global__ __launch_bounds__(256) void gemm_f32_small(GemmArgs g, int tiles_n) {
+__device__ __forceinline__ void f32_small_tile(GemmArgs g, int tiles_n, const int bid, const int z) {
   constexpr int BT = 16 * TW, LD = BT + 4;
   __shared__ __attribute__((aligned(16))) float part[4][BT * LD];
   __shared__ float cpart[4][BT];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l15 = lane & 15, q4 = lane >> 4;
-  const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n, z = blockIdx.z;
+  const int tm = bid / tiles_n, tn = bid % tiles_n;
   const int m0 = tm * BT, n0 = tn * BT;
   const float* A = g.Az[0] ? (const float*)pick4(g.Az, z) : (const float*)g.A + z * g.sA;
   const float* B = g.Bz[0] ? (const float*)pick4(g.Bz, z) : (const float*)g.B + z * g.sB;
@@ -277,6 +277,44 @@ __global__ __launch_bounds__(256) void gemm_f32_small(GemmArgs g, int tiles_n) {
   }
 }
 
+// ------------------------------------------------------------------ kernels
+template <int BT, bool AKS, bool BKS>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, int tiles_n) {
+  f32_tile<BT, AKS, BKS>(g, tiles_n, blockIdx.x, blockIdx.z);
+}
+template <int TW, bool AKS, bool BKS>
+__global__ __launch_bounds__(256) void gemm_f32_small(GemmArgs g, int tiles_n) {
+  f32_small_tile<TW, AKS, BKS>(g, tiles_n, blockIdx.x, blockIdx.z);
+}
+
+// a list of weight-gradient products in one launch (first[k]: first workgroup of problem k); BT = 128, 64: the tile
+// kernel, 32, 16: the small one
+struct F32Tiles {
+  int first[WgradGroup::MAX + 1];
+};
+template <int BT>
+__global__ __launch_bounds__(256) void wgrad_group_f32(WgradGroup w, F32Tiles t) {
+  int i = 0;
+#pragma unroll
+  for (int k = 1; k < WgradGroup::MAX; ++k) i += k < w.n && (int)blockIdx.x >= t.first[k];
+  GemmArgs g{};
+  int first = 0;
+#pragma unroll
+  for (int k = 0; k < WgradGroup::MAX; ++k)
+    if (i == k) {
+      const WgradProblem& p = w.p[k];
+      g.A = p.A; g.B = p.B; g.C = p.C; g.bsum_z[0] = p.bsum;
+      g.M = p.M; g.N = p.N; g.lda = p.lda; g.ldb = p.ldb; g.ldc = p.ldc;
+      first = t.first[k];
+    }
+  g.m_valid = g.M; g.n_valid = g.N; g.K = g.k_valid = w.K; g.kseg_len = w.kseg;
+  g.segA = (long)w.kseg * g.lda; g.segB = (long)w.kseg * g.ldb;
+  g.epi = EPI_ACC32 | (g.bsum_z[0] ? EPI_BSUM : 0) | (w.K > w.kseg ? EPI_SEGACC : 0);
+  const int tn = (g.N + BT - 1) / BT, bid = blockIdx.x - first;
+  if constexpr (BT >= 64) f32_tile<BT, true, true>(g, tn, bid, 0);
+  else f32_small_tile<BT / 16, true, true>(g, tn, bid, 0);
+}
+
 // ------------------------------------------------------------------ host side
 static bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
@@ -327,6 +365,34 @@ static hipError_t launch_layout(const GemmArgs& g, hipStream_t st) {
   if (tiles(64) >= 160) return launch_tile<64, AKS, BKS>(g, st);
   if (tiles(32) >= 160) return launch_small<2, AKS, BKS>(g, st);
   return launch_small<1, AKS, BKS>(g, st);
+}
+
+template <int BT>
+static hipError_t launch_group(const WgradGroup& w, hipStream_t st) {
+  auto kern = wgrad_group_f32<BT>;
+  int lds = 0;
+  if constexpr (BT >= 64) {
+    constexpr int bytes = 2 * 4 * 2 * F32Tile<BT, true>::FLOATS;
+    static const hipError_t attr_rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (attr_rc != hipSuccess) return attr_rc;
+    lds = bytes;
+  }
+  F32Tiles t{};
+  for (int i = 0; i < w.n; ++i) t.first[i + 1] = t.first[i] + ((w.p[i].M + BT - 1) / BT) * ((w.p[i].N + BT - 1) / BT);
+  hipLaunchKernelGGL(kern, dim3(t.first[w.n]), dim3(256), lds, st, w, t);
+  return hipGetLastError();
+}
+
+hipError_t launch_wgrad_group_f32(const WgradGroup& w, hipStream_t st) {
+  auto tiles = [&](long b) {
+    long n = 0;
+    for (int i = 0; i < w.n; ++i) n += ((w.p[i].M + b - 1) / b) * ((w.p[i].N + b - 1) / b);
+    return n;
+  };
+  if (tiles(128) >= 192) return launch_group<128>(w, st);   // the lines of launch_layout
+  if (tiles(64) >= 160) return launch_group<64>(w, st);
+  if (tiles(32) >= 160) return launch_group<32>(w, st);
+  return launch_group<16>(w, st);
 }
 
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st) {

@@ -223,7 +223,7 @@ struct GemmTile {
 // when an operand is k-contiguous (see OperandTile); NSEG = 2: two K segments whose sums are added to C one after the
 // other (EPI_SEGACC), each in accumulators of its own
 template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false, int NSEG = 1>
-__global__ __launch_bounds__(64 * WGM * WGN, NSEG) void gemm_mfma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+__device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, int tiles_n, const int bid, const int z) {
   typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, NSEG> CFG;
   typedef typename CFG::TA TA;
   typedef typename CFG::TB TB;
@@ -240,7 +240,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, NSEG) void gemm_mfma_kernel(GemmArg
   // all its tiles out of its L2; inside a rectangle walk column-blocks of 4 tiles.
   int tm, tn;
   {
-    const int bid = blockIdx.x;
     const int ntiles = tiles_m * tiles_n;
     int pm = 0, best = 1 << 30;
 #pragma unroll
@@ -263,7 +262,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, NSEG) void gemm_mfma_kernel(GemmArg
     }
   }
   const int m0 = tm * BM, n0 = tn * BN;
-  const int z = blockIdx.z;
 
   // (the per-instance pointers are picked with constant indices: a variable index would move the whole
   // argument struct to scratch memory, and with it every value the k-loop derives from it out of scalar registers)
@@ -706,6 +704,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, NSEG) void gemm_mfma_kernel(GemmArg
   if (interior) store_tile(std::true_type{});
   else store_tile(std::false_type{});
   static_assert(MI <= 4, "at most four 32-row blocks per wave");
+}
+
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false, int NSEG = 1>
+__global__ __launch_bounds__(64 * WGM * WGN, NSEG) void gemm_mfma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  gemm_mfma_tile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT, NSEG>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.z);
 }
 
 template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS = false, bool KT = false, int NSEG = 1>

@@ -74,6 +74,28 @@ hipError_t launch_mfma_nn(int tile, bool short_k, const GemmArgs& g, hipStream_t
 hipError_t launch_mfma_nt(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
 hipError_t launch_mfma_tn(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
 hipError_t launch_mfma_tt(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
+// Several weight-gradient products over the same rows in one launch: for each problem C += sum over the micro-batches'
+// rows of A^T B, both operands [rows][...] with the rows of the micro-batches one behind the other; K = rows in all (one
+// or two micro-batches of kseg rows), each micro-batch's sum added to C -- and its column sums of B to bsum, if given --
+// on its own, in order (EPI_SEGACC).
+struct WgradProblem {
+  const void *A, *B;
+  float *C, *bsum;
+  int M, N, lda, ldb, ldc;
+};
+struct WgradGroup {
+  static constexpr int MAX = 6;
+  WgradProblem p[MAX];
+  int n, K, kseg;
+  int units;   // as in GemmArgs
+};
+// the same as one accumulating product
+GemmArgs wgrad_args(const WgradGroup& w, int i);
+bool wgrad_group_takes(Dtype dt, const WgradGroup& w);
+hipError_t launch_wgrad_group(Dtype dt, const WgradGroup& w, hipStream_t st);
+hipError_t launch_wgrad_group_mfma(const WgradGroup& w, hipStream_t st);
+hipError_t launch_wgrad_group_f32(const WgradGroup& w, hipStream_t st);
+
 // fp32 products on the fp32 matrix instructions (gemm_f32.hip): whether they take this problem (else the plain
 // kernel does), and the launch
 bool gemm_f32_takes(const GemmArgs& g);

@@ -369,24 +369,28 @@ struct dapple_stage {
     return run_on(s_, cls, flops, [&](hipStream_t s) { return launch_gemm(dt, g, s); }, &g);
   }
 
-  // a weight-gradient product over n micro-batches of T1 rows each (both operands k-strided, rows one micro-batch
-  // behind the other), on the side stream: C gets the micro-batches' sums in order, two of them per launch
-  int wgrad(int cls, GemmArgs g, int n, int T1) {
-    const char *A0 = (const char*)g.A, *B0 = (const char*)g.B;
-    const void* Az0[4] = {g.Az[0], g.Az[1], g.Az[2], g.Az[3]};
-    const void* Bz0[4] = {g.Bz[0], g.Bz[1], g.Bz[2], g.Bz[3]};
+  // weight-gradient products over n micro-batches of T1 rows each (rows one micro-batch behind the other), on the side
+  // stream: every C gets the micro-batches' sums in order, two of them per launch
+  int wgrad(int cls, WgradGroup w, int n, int T1) {
+    const WgradGroup w0 = w;
+    w.units = units;
     for (int i = 0; i < n; i += 2) {
       const int c = n - i < 2 ? n - i : 2;
-      const size_t ra = (size_t)i * T1 * g.lda * E(), rb = (size_t)i * T1 * g.ldb * E();
-      g.A = A0 + ra; g.B = B0 + rb;
-      for (int z = 0; z < 4 && Az0[0]; ++z) {
-        g.Az[z] = (const char*)Az0[z] + ra;
-        g.Bz[z] = (const char*)Bz0[z] + rb;
+      w.K = c * T1; w.kseg = T1;
+      double flops = 0;
+      for (int k = 0; k < w.n; ++k) {
+        w.p[k].A = (const char*)w0.p[k].A + (size_t)i * T1 * w.p[k].lda * E();
+        w.p[k].B = (const char*)w0.p[k].B + (size_t)i * T1 * w.p[k].ldb * E();
+        flops += 2.0 * w.p[k].M * w.p[k].N * (double)w.K;
       }
-      g.K = c * T1; g.kseg_len = T1; g.segA = (long)T1 * g.lda; g.segB = (long)T1 * g.ldb; g.k_valid = 0;
-      if (c > 1) g.epi |= EPI_SEGACC;
-      else g.epi &= ~EPI_SEGACC;
-      TRY(gemm(cls, g, true));
+      if (dry || wgrad_group_takes(dt, w)) {
+        TRY(run_on(side, cls, flops, [&](hipStream_t s) { return launch_wgrad_group(dt, w, s); }));
+      } else {
+        for (int k = 0; k < w.n; ++k) {
+          const GemmArgs g = wgrad_args(w, k);
+          TRY(run_on(side, cls, 2.0 * g.M * g.N * (double)g.K, [&](hipStream_t s) { return launch_gemm(dt, g, s); }, &g));
+        }
+      }
     }
     return STAGE_OK;
   }
@@ -567,10 +571,9 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
     float* part_cz = (float*)ws(L.wh_part_cz);
     TRY(fork(HL, 0));
     {  // dE_out += dz^T t
-      GemmArgs ga{};
-      ga.A = dz; ga.lda = VP; ga.a_kstrided = 1; ga.B = t; ga.ldb = H; ga.b_kstrided = 1;
-      ga.C = gr(L.hEout); ga.ldc = H; ga.M = V; ga.N = H; ga.epi = EPI_ACC32;
-      TRY(wgrad(KC_HEAD, ga, n, NP));
+      WgradGroup w{};
+      w.p[w.n++] = WgradProblem{dz, t, gr(L.hEout), nullptr, V, H, VP, H, H};
+      TRY(wgrad(KC_HEAD, w, n, NP));
     }
     {  // db_out += the column sums of dz
       int nb = 0, PS = 0;
@@ -598,11 +601,9 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
     TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_mul(dt, dgl, glp, dh, (long)n * NP * H, q); }));
     TRY(fork(HL, 0));   // event 0 again: the side stream's first wait on it is already enqueued
     {  // dWt += r^T dh, dbt += the column sums of dh
-      GemmArgs ga{};
-      ga.A = r; ga.lda = H; ga.a_kstrided = 1; ga.B = dh; ga.ldb = H; ga.b_kstrided = 1;
-      ga.C = gr(L.hWt); ga.ldc = H; ga.M = H; ga.N = H; ga.epi = EPI_ACC32 | EPI_BSUM;
-      ga.bsum_z[0] = gr(L.hbt);
-      TRY(wgrad(KC_HEAD, ga, n, NP));
+      WgradGroup w{};
+      w.p[w.n++] = WgradProblem{r, dh, gr(L.hWt), gr(L.hbt), H, H, H, H, H};
+      TRY(wgrad(KC_HEAD, w, n, NP));
     }
     TRY(side_done(HL));
     {  // dr = dh Wt^T
@@ -650,22 +651,18 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
       ga.C = du; ga.ldc = F; ga.M = T; ga.N = F; ga.K = H; ga.epi = EPI_MUL;
       TRY(gemm(KC_GEMM_DGRAD, ga));
     }
-    // two forks per layer (here and after the attention backward), not one per side launch: every event
-    // recorded on this stream sits between two kernels of the task's chain (14.17 -> 14.14 ms; a single fork per
-    // layer holds the side stream back too long: 14.35)
-    TRY(fork(l, 1));
-    {  // dW2 += g^T dz2
-      GemmArgs ga{};
-      ga.A = g; ga.lda = F; ga.a_kstrided = 1; ga.B = dz2; ga.ldb = H; ga.b_kstrided = 1;
-      ga.C = gr(p.W2); ga.ldc = H; ga.M = F; ga.N = H; ga.epi = EPI_ACC32;
-      TRY(wgrad(KC_GEMM_WGRAD, ga, n, T1));
-    }
-    {  // dW1 += y1^T du, and db1 += the column sums of du in the same launch
-      GemmArgs ga{};
-      ga.A = y1; ga.lda = H; ga.a_kstrided = 1; ga.B = du; ga.ldb = F; ga.b_kstrided = 1;
-      ga.C = gr(p.W1); ga.ldc = F; ga.M = H; ga.N = F; ga.epi = EPI_ACC32 | EPI_BSUM;
-      ga.bsum_z[0] = gr(p.b1);
-      TRY(wgrad(KC_GEMM_WGRAD, ga, n, T1));
+    // The layer's weight gradients go out in one launch (gemm_wgrad.hip), the bias gradients of W1, Wq, Wk, Wv as column
+    // sums along the way -- in two where there is a side stream and the feed-forward pair fills the chip by itself
+    // (three 128x128 tiles for every two units): the first then starts while the attention's gradients are computed.
+    // 6 layers of 1024, 2048 tokens, M = 8: 12.1 ms with one launch, 11.9 with two; launches of one product each 12.05.
+    const bool early = side != cur && (long)((H + 127) / 128) * ((F + 127) / 128) * 4 >= 3 * (units ? units : 256);
+    WgradGroup wg{};
+    wg.p[wg.n++] = WgradProblem{g, dz2, gr(p.W2), nullptr, F, H, F, H, H};    // dW2 += g^T dz2
+    wg.p[wg.n++] = WgradProblem{y1, du, gr(p.W1), gr(p.b1), H, F, H, F, F};   // dW1 += y1^T du
+    if (early) {
+      TRY(fork(l, 1));
+      TRY(wgrad(KC_GEMM_WGRAD, wg, n, T1));
+      wg.n = 0;
     }
     {  // dy1 = du W1^T + dz2 (residual branch)
       GemmArgs ga{};
@@ -699,21 +696,11 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
       TRY(run(KC_ATTN_BWD, fl, [&](hipStream_t q) { return launch_attn_bwd(dt, aa, q); }));
     }
     TRY(fork(l, 3));
-    {  // dWq, dWk, dWv += x^T dq, x^T dk, x^T dv and dWo += ctx^T dz1: four products of one
-       // shape in one launch (alone, each would leave most of the CUs idle); the first three
-       // also add the column sums of dq, dk, dv to the bias gradients
-      GemmArgs ga{};
-      ga.lda = H; ga.a_kstrided = 1; ga.ldb = H; ga.b_kstrided = 1;
-      ga.ldc = H; ga.M = H; ga.N = H; ga.batch = 4; ga.epi = EPI_ACC32 | EPI_BSUM;
-      const char* dqkv[3] = {dq, dk, dv};
-      for (int z = 0; z < 3; ++z) {
-        ga.Az[z] = xl; ga.Bz[z] = dqkv[z]; ga.Cz[z] = gr(p.Wq + z * pstride);
-        ga.bsum_z[z] = gr(p.bq + z * pstride);
-      }
-      ga.Az[3] = ctx; ga.Bz[3] = dz1; ga.Cz[3] = gr(p.Wo);
-      ga.A = ga.Az[0]; ga.B = ga.Bz[0]; ga.C = ga.Cz[0];
-      TRY(wgrad(KC_GEMM_WGRAD, ga, n, T1));
-    }
+    wg.p[wg.n++] = WgradProblem{xl, dq, gr(p.Wq), gr(p.bq), H, H, H, H, H};   // dWq, dWk, dWv += x^T dq, x^T dk, x^T dv
+    wg.p[wg.n++] = WgradProblem{xl, dk, gr(p.Wk), gr(p.bk), H, H, H, H, H};
+    wg.p[wg.n++] = WgradProblem{xl, dv, gr(p.Wv), gr(p.bv), H, H, H, H, H};
+    wg.p[wg.n++] = WgradProblem{ctx, dz1, gr(p.Wo), nullptr, H, H, H, H, H};  // dWo += ctx^T dz1
+    TRY(wgrad(KC_GEMM_WGRAD, wg, n, T1));
     {
       ReduceJobs J{};
       J.nmb = n; J.mb_stride = (long)nblk * 3 * H;
