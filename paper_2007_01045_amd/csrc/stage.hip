@@ -313,9 +313,17 @@ struct dapple_stage {
   template <typename Fn>
   int run(int cls, double flops, Fn&& fn) { return run_on(cur, cls, flops, fn); }
 
+  // Whether tasks over n micro-batches are too small for lanes: an event per hand-over costs the host 2-5 us and the
+  // streams' kernels a wait, and on a chip that a launch does not fill anyway the launches in a row are faster.  In
+  // matrix flops of a layer's forward: 256-wide stage, 0.8 GFLOP, 470 us with lanes, 330 without; 512-wide, 3 GFLOP,
+  // 722 / 700; 1024-wide, 3 GFLOP, 1133 / 1111, 13 GFLOP 1251 / 1288.  (fp32 products take eight times as long.)
+  bool small_tasks(int n) const {
+    const double T = (double)n * cfg.micro_batch * cfg.seq, H = cfg.hidden, F = cfg.ffn;
+    return 8.0 * T * H * H + 4.0 * T * H * F < (dt == DT_BF16 ? 6e9 : 7.5e8);
+  }
   // main -> side: the side stream may start once the main stream has passed this point
   int fork(int layer, int which) {
-    if (dry) return STAGE_OK;
+    if (dry || side == cur) return STAGE_OK;
     hipEvent_t e = ev[layer * 5 + which];
     if (hipEventRecord(e, cur) != hipSuccess || hipStreamWaitEvent(side, e, 0) != hipSuccess)
       return fail(STAGE_E_DEVICE, "event record / wait failed");
@@ -323,12 +331,12 @@ struct dapple_stage {
   }
   // side -> main, in two halves: mark the side work of a layer done; later make main wait for it
   int side_done(int layer) {
-    if (dry) return STAGE_OK;
+    if (dry || side == cur) return STAGE_OK;
     if (hipEventRecord(ev[layer * 5 + 4], side) != hipSuccess) return fail(STAGE_E_DEVICE, "event record failed");
     return STAGE_OK;
   }
   int join(int layer) {
-    if (dry) return STAGE_OK;
+    if (dry || side == cur) return STAGE_OK;
     if (hipStreamWaitEvent(cur, ev[layer * 5 + 4], 0) != hipSuccess) return fail(STAGE_E_DEVICE, "event wait failed");
     return STAGE_OK;
   }
@@ -1001,7 +1009,11 @@ int stage_bwd(stage_handle h, int mb, const void* dy_dev, void* dx_dev) {
   if (!h->dry && !h->cfg.has_embedding && !dx_dev) return fail(STAGE_E_NULL, "dx_dev must not be NULL");
   int s = mb < 0 ? -1 : find_slot(h, mb);
   if (s < 0) return fail(STAGE_E_NOT_RESIDENT, "micro-batch %d has no live forward", mb);
-  return bwd_group(h, 1, s, &dy_dev, &dx_dev);
+  hipStream_t side = h->side;
+  if (h->small_tasks(1)) h->side = h->cur;
+  const int rc = bwd_group(h, 1, s, &dy_dev, &dx_dev);
+  h->side = side;
+  return rc;
 }
 
 int stage_schedule_ops(int M, int K, int order, int32_t* ops_out, int capacity) {
@@ -1082,7 +1094,8 @@ int stage_run_schedule(stage_handle h, int M, int K, int order, const void* cons
   // themselves and backwards among themselves in list order (which fixes the order of every
   // gradient accumulation).  The early-backward order needs no more than that; the other orders
   // are run strictly as listed (a backward waits for every forward listed before it).
-  const bool lanes = !h->dry && !h->profiling && !h->serial;
+  const bool small = h->small_tasks(G);   // everything on the caller's stream
+  const bool lanes = !h->dry && !h->profiling && !h->serial && !small;
   const bool strict = order != STAGE_ORDER_EARLY_BACKWARD;
   std::vector<char> b_pending(h->cfg.max_slots, 0);   // per first slot of a group
   int last_f_slot = -1;
@@ -1100,7 +1113,9 @@ int stage_run_schedule(stage_handle h, int M, int K, int order, const void* cons
   int n_bwd = 0;
   bool used_b2 = false;
   if (lanes) TRY(ensure_lanes(h));
-  if (lanes) {
+  hipStream_t side = h->side;
+  if (small) h->side = h->st;
+  if (lanes) {   // (nothing is small here: no early return leaves the side stream replaced)
     TRY(hip_ok(hipEventRecord(h->ev_start, h->st)));
     TRY(hip_ok(hipStreamWaitEvent(h->fwd, h->ev_start, 0)));
   }
@@ -1153,6 +1168,7 @@ int stage_run_schedule(stage_handle h, int M, int K, int order, const void* cons
       }
     }
   }
+  h->side = side;
   // the caller's stream ends behind everything the forward lane was given, also on an error
   if (lanes && last_f_slot >= 0) {
     int rc2 = hip_ok(hipStreamWaitEvent(h->st, h->ev_f[last_f_slot], 0));
