@@ -24,8 +24,7 @@ namespace dapple {
 
 // ------------------------------------------------------------------ plain kernel
 __device__ __forceinline__ void plain_bsum(const GemmArgs& g, int z, int col, float t) {
-  float* bs = z == 0 ? g.bsum_z[0] : (z == 1 ? g.bsum_z[1] : (z == 2 ? g.bsum_z[2] : g.bsum_z[3]));
-  if (bs) bs[col] += t;
+  if (z == 0 && g.bsum) g.bsum[col] += t;
 }
 
 template <typename T>
@@ -34,12 +33,7 @@ __global__ void gemm_plain_kernel(GemmArgs g) {
   int row = blockIdx.y * blockDim.y + threadIdx.y;
   int z = blockIdx.z;
   if (row >= g.M || col >= g.N) return;
-  const T* A = g.Az[0] ? (const T*)g.Az[z] : (const T*)g.A + z * g.sA;
-  const T* B = g.Bz[0] ? (const T*)g.Bz[z] : (const T*)g.B + z * g.sB;
-  if (g.Cz[0]) {
-    g.C = g.Cz[z];
-    g.sC = 0;
-  }
+  const T *A = (const T*)g.A + z * g.sA, *B = (const T*)g.B + z * g.sB;
   float acc = 0.f, bsum = 0.f;
   int nseg = g.K / g.kseg_len;
   const bool segacc = (g.epi & EPI_SEGACC) != 0;
@@ -76,13 +70,6 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
   if (g.lda % 8 || g.ldb % 8 || g.ldc % 4 || g.N % 4) return false;
   if (g.sA % 8 || g.sB % 8 || g.sC % 4 || g.sBias % 4 || g.segA % 8 || g.segB % 8) return false;
   if (!aligned_to(g.A, 16) || !aligned_to(g.B, 16) || !aligned_to(g.C, 16)) return false;
-  if (g.Az[0] || g.Bz[0] || g.Cz[0]) {
-    if (g.batch > 4) return false;
-    for (int z = 0; z < g.batch; ++z)
-      if (!g.Az[z] || !g.Bz[z] || !g.Cz[z] || !aligned_to(g.Az[z], 16) || !aligned_to(g.Bz[z], 16) ||
-          !aligned_to(g.Cz[z], 16))
-        return false;
-  }
   {  // the kernel counts the readable bytes of an operand segment in a 32-bit buffer field
     const int kv = g.k_valid > 0 ? g.k_valid : g.K, mv = g.m_valid > 0 ? g.m_valid : g.M, nv = g.n_valid > 0 ? g.n_valid : g.N;
     const long a_ext = g.a_kstrided ? ((long)(kv - 1) * g.lda + mv) * 2 : ((long)(mv - 1) * g.lda + g.kseg_len) * 2;
@@ -96,7 +83,7 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
     return false;
   if ((g.epi & EPI_BIAS) && !aligned_to(g.bias, 8)) return false;
   if ((g.epi & EPI_GELU) && !aligned_to(g.C2, 8)) return false;
-  if ((g.epi & EPI_BSUM) && !(g.a_kstrided && g.b_kstrided && g.batch <= 4)) return false;
+  if ((g.epi & EPI_BSUM) && !(g.a_kstrided && g.b_kstrided)) return false;
   if ((g.epi & EPI_SEGACC) && !((g.epi & EPI_ACC32) && g.a_kstrided && g.b_kstrided && g.K == 2 * g.kseg_len)) return false;
   return true;
 }
@@ -151,7 +138,7 @@ GemmArgs wgrad_args(const WgradGroup& w, int i) {
   g.lda = p.lda; g.ldb = p.ldb; g.ldc = p.ldc; g.a_kstrided = g.b_kstrided = 1; g.batch = 1;
   g.kseg_len = w.kseg; g.segA = (long)w.kseg * p.lda; g.segB = (long)w.kseg * p.ldb;
   g.epi = EPI_ACC32 | (p.bsum ? EPI_BSUM : 0) | (w.K > w.kseg ? EPI_SEGACC : 0);
-  g.bsum_z[0] = p.bsum; g.units = w.units;
+  g.bsum = p.bsum; g.units = w.units;
   return g;
 }
 

@@ -28,13 +28,21 @@ __device__ __forceinline__ void epilogue_store(const GemmArgs& g, long zc, long 
   }
 }
 
-// four consecutive columns of one row of an fp32 product (every pointer and stride 16-byte aligned)
-__device__ __forceinline__ void epilogue_store4(const GemmArgs& g, long zc, long zbias, int row, int col, f32x4 t) {
-  if (g.epi & EPI_BIAS) t += *(const f32x4*)((const float*)g.bias + zbias + col);
-  if (g.epi & (EPI_ADD | EPI_MUL)) {
-    const f32x4 x = *(const f32x4*)((const float*)g.aux + zc + (long)row * g.ldaux + col);
-    t = (g.epi & EPI_ADD) ? t + x : t * x;
-  }
+// four consecutive columns of one row of an fp32 product (every pointer and stride 16-byte aligned): what the epilogue
+// reads, and the store
+struct Epilogue4 {
+  f32x4 bias, x, c;
+};
+__device__ __forceinline__ Epilogue4 epilogue_load4(const GemmArgs& g, long zc, long zbias, int row, int col) {
+  Epilogue4 in{};
+  if (g.epi & EPI_BIAS) in.bias = *(const f32x4*)((const float*)g.bias + zbias + col);
+  if (g.epi & (EPI_ADD | EPI_MUL)) in.x = *(const f32x4*)((const float*)g.aux + zc + (long)row * g.ldaux + col);
+  if (g.epi & EPI_ACC32) in.c = *(const f32x4*)((const float*)g.C + zc + (long)row * g.ldc + col);
+  return in;
+}
+__device__ __forceinline__ void epilogue_store4(const GemmArgs& g, long zc, int row, int col, f32x4 t, const Epilogue4& in) {
+  if (g.epi & EPI_BIAS) t += in.bias;
+  if (g.epi & (EPI_ADD | EPI_MUL)) t = (g.epi & EPI_ADD) ? t + in.x : t * in.x;
   float* const c = (float*)g.C + zc + (long)row * g.ldc + col;
   if (g.epi & EPI_GELU) {
     f32x4 a, b;
@@ -48,7 +56,7 @@ __device__ __forceinline__ void epilogue_store4(const GemmArgs& g, long zc, long
     *(f32x4*)c = a;
     *(f32x4*)((float*)g.C2 + zc + (long)row * g.ldc + col) = b;
   } else if (g.epi & EPI_ACC32) {
-    *(f32x4*)c = *(const f32x4*)c + t;
+    *(f32x4*)c = in.c + t;
   } else {
     *(f32x4*)c = t;
   }

@@ -20,12 +20,6 @@
 
 namespace dapple {
 
-// per-instance pointers picked with constant indices (a variable index would move the argument struct to scratch)
-template <typename A>
-__device__ __forceinline__ auto pick4(A& arr, int z) {
-  return z == 0 ? arr[0] : (z == 1 ? arr[1] : (z == 2 ? arr[2] : arr[3]));
-}
-
 // ------------------------------------------------------------------ LDS-tiled kernel
 constexpr int FBK = 32;
 
@@ -73,13 +67,8 @@ __device__ __forceinline__ void f32_tile(GemmArgs g, int tiles_n, const int bid,
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l31 = lane & 31, h = lane >> 5;
   const int tm = bid / tiles_n, tn = bid % tiles_n;
   const int m0 = tm * BT, n0 = tn * BT, wm0 = (wave >> 1) * W, wn0 = (wave & 1) * W;
-  const float* A = g.Az[0] ? (const float*)pick4(g.Az, z) : (const float*)g.A + z * g.sA;
-  const float* B = g.Bz[0] ? (const float*)pick4(g.Bz, z) : (const float*)g.B + z * g.sB;
-  if (g.Cz[0]) {
-    g.C = pick4(g.Cz, z);
-    g.sC = 0;
-  }
-  float* const bs = (g.epi & EPI_BSUM) ? pick4(g.bsum_z, z) : nullptr;
+  const float *A = (const float*)g.A + z * g.sA, *B = (const float*)g.B + z * g.sB;
+  float* const bs = (g.epi & EPI_BSUM) && z == 0 ? g.bsum : nullptr;
   const bool do_cs = bs != nullptr && tm == 0 && wm0 == 0;
   const int klen = g.K > g.kseg_len ? g.kseg_len : min(g.K, g.k_valid);
   const int per_seg = (g.kseg_len + FBK - 1) / FBK, nt = g.K / g.kseg_len * per_seg;
@@ -127,8 +116,9 @@ __device__ __forceinline__ void f32_tile(GemmArgs g, int tiles_n, const int bid,
         for (int q = 0; q < 4; ++q) {
           const int col = n0 + wn0 + 32 * j + 8 * q + 4 * h;
           if (row < g.M && col < g.N)
-            epilogue_store4(g, zc, zb, row, col,
-                            f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]});
+            epilogue_store4(g, zc, row, col,
+                            f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]},
+                            epilogue_load4(g, zc, zb, row, col));
         }
     }
   };
@@ -175,35 +165,42 @@ __device__ __forceinline__ void f32_tile(GemmArgs g, int tiles_n, const int bid,
 }
 
 // ------------------------------------------------------------------ few tiles: K split over the waves
-template <int TW, bool AKS, bool BKS>
+// (NSG = 2: accumulating products over an even number of segments, two of them in flight together)
+template <int TW, bool AKS, bool BKS, int NSG = 1>
 __device__ __forceinline__ void f32_small_tile(GemmArgs g, int tiles_n, const int bid, const int z) {
   constexpr int BT = 16 * TW, LD = BT + 4;
-  __shared__ __attribute__((aligned(16))) float part[4][BT * LD];
-  __shared__ float cpart[4][BT];
+  __shared__ __attribute__((aligned(16))) float part[NSG][4][BT * LD];
+  __shared__ float cpart[NSG][4][BT];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l15 = lane & 15, q4 = lane >> 4;
   const int tm = bid / tiles_n, tn = bid % tiles_n;
   const int m0 = tm * BT, n0 = tn * BT;
-  const float* A = g.Az[0] ? (const float*)pick4(g.Az, z) : (const float*)g.A + z * g.sA;
-  const float* B = g.Bz[0] ? (const float*)pick4(g.Bz, z) : (const float*)g.B + z * g.sB;
-  if (g.Cz[0]) {
-    g.C = pick4(g.Cz, z);
-    g.sC = 0;
-  }
-  float* const bs = (g.epi & EPI_BSUM) ? pick4(g.bsum_z, z) : nullptr;
+  const float *A = (const float*)g.A + z * g.sA, *B = (const float*)g.B + z * g.sB;
+  float* const bs = (g.epi & EPI_BSUM) && z == 0 ? g.bsum : nullptr;
   const int klen = g.K > g.kseg_len ? g.kseg_len : min(g.K, g.k_valid);
   const int per_seg = (g.kseg_len + 15) / 16, nseg = g.K / g.kseg_len;
-  // EPI_SEGACC: the segments one after the other, each added to C; else all of them as one sum
+  // EPI_SEGACC: the segments one after the other, NSG of them at a time, each one's sum added to C; else all of them
+  // as one sum
   const bool segacc = (g.epi & EPI_SEGACC) != 0;
   const int nc = segacc ? per_seg : nseg * per_seg;
-  for (int turn = 0; turn < (segacc ? nseg : 1); ++turn, A += g.segA, B += g.segB) {
-    f32x4 acc[TW][TW];
-    float cs[TW];
+  const long zc = z * g.sC, zb = z * g.sBias;
+  // the part of the tile a thread stores (at most one piece of four columns), and what its epilogue reads: requested
+  // first of all, a launch this small is little else than memory latencies in a row
+  const int er = tid * 4 / BT, ec = tid * 4 % BT, row = m0 + er, col = n0 + ec;
+  const bool stores = tid * 4 < BT * BT && row < g.M && col < g.N;
+  const bool sums = bs && tm == 0 && tid < BT && n0 + tid < g.N;
+  for (int turn = 0; turn < (segacc ? nseg : 1); turn += NSG, A += NSG * g.segA, B += NSG * g.segB) {
+    const Epilogue4 in = stores ? epilogue_load4(g, zc, zb, row, col) : Epilogue4{};
+    float bsum0 = sums ? bs[n0 + tid] : 0.f;
+    f32x4 acc[NSG][TW][TW];
+    float cs[NSG][TW];
 #pragma unroll
-    for (int i = 0; i < TW; ++i) {
-      cs[i] = 0.f;
+    for (int s = 0; s < NSG; ++s)
 #pragma unroll
-      for (int j = 0; j < TW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+      for (int i = 0; i < TW; ++i) {
+        cs[s][i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < TW; ++j) acc[s][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
     // rows l15 of the 16-row block at r0, k = k0 + 4 q4 + 0..3
     auto fetch = [&](const float* X, int ld, bool ks, int r, int rows, int k0) {
       const int k = k0 + 4 * q4;
@@ -219,60 +216,73 @@ __device__ __forceinline__ void f32_small_tile(GemmArgs g, int tiles_n, const in
       }
       return v;
     };
-    constexpr int U = TW == 1 ? 8 : 4;   // 16-wide pieces of K whose loads are in flight together
+    constexpr int U = (TW == 1 ? 8 : 4) / NSG;   // 16-wide pieces of K (of each segment) whose loads are in flight together
     for (int c0 = wave; c0 < nc; c0 += 4 * U) {
-      f32x4 a[U][TW], b[U][TW];
+      f32x4 a[NSG][U][TW], b[NSG][U][TW];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int c = c0 + 4 * u, seg = c / per_seg, k0 = c < nc ? (c - seg * per_seg) * 16 : klen;
-        const float *As = A + (c < nc ? seg : 0) * g.segA, *Bs = B + (c < nc ? seg : 0) * g.segB;
+      for (int s = 0; s < NSG; ++s)
 #pragma unroll
-        for (int i = 0; i < TW; ++i) {
-          a[u][i] = fetch(As, g.lda, AKS, m0 + 16 * i + l15, g.m_valid, k0);
-          b[u][i] = fetch(Bs, g.ldb, BKS, n0 + 16 * i + l15, g.n_valid, k0);
+        for (int u = 0; u < U; ++u) {
+          const int c = c0 + 4 * u, seg = NSG > 1 ? s : c / per_seg, k0 = c < nc ? (c - (NSG > 1 ? 0 : seg * per_seg)) * 16 : klen;
+          const float *As = A + (c < nc ? seg : 0) * g.segA, *Bs = B + (c < nc ? seg : 0) * g.segB;
+#pragma unroll
+          for (int i = 0; i < TW; ++i) {
+            a[s][u][i] = fetch(As, g.lda, AKS, m0 + 16 * i + l15, g.m_valid, k0);
+            b[s][u][i] = fetch(Bs, g.ldb, BKS, n0 + 16 * i + l15, g.n_valid, k0);
+          }
         }
-      }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
+      for (int s = 0; s < NSG; ++s)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
+        for (int u = 0; u < U; ++u) {
 #pragma unroll
-          for (int i = 0; i < TW; ++i)
+          for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int j = 0; j < TW; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[u][j][e], a[u][i][e], acc[i][j], 0, 0, 0);
-        if (bs) {
+            for (int i = 0; i < TW; ++i)
 #pragma unroll
-          for (int j = 0; j < TW; ++j) cs[j] += (b[u][j][0] + b[u][j][1]) + (b[u][j][2] + b[u][j][3]);
+              for (int j = 0; j < TW; ++j)
+                acc[s][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[s][u][j][e], a[s][u][i][e], acc[s][i][j], 0, 0, 0);
+          if (bs) {
+#pragma unroll
+            for (int j = 0; j < TW; ++j) cs[s][j] += (b[s][u][j][0] + b[s][u][j][1]) + (b[s][u][j][2] + b[s][u][j][3]);
+          }
         }
-      }
     }
-    if (turn) __syncthreads();   // the partial tiles of the segment before have been read
-    // acc[i][j]: row 16 i + l15, columns 16 j + 4 q4 + 0..3
+    if (turn) __syncthreads();   // the partial tiles of the segments before have been read
+    // acc[s][i][j]: row 16 i + l15, columns 16 j + 4 q4 + 0..3
 #pragma unroll
-    for (int i = 0; i < TW; ++i)
+    for (int s = 0; s < NSG; ++s) {
 #pragma unroll
-      for (int j = 0; j < TW; ++j) *(f32x4*)(part[wave] + (16 * i + l15) * LD + 16 * j + 4 * q4) = acc[i][j];
-    if (bs && tm == 0) {
+      for (int i = 0; i < TW; ++i)
 #pragma unroll
-      for (int j = 0; j < TW; ++j) {
-        float t = cs[j];
-        t += __shfl_xor(t, 16, 64);
-        t += __shfl_xor(t, 32, 64);
-        if (q4 == 0) cpart[wave][16 * j + l15] = t;
+        for (int j = 0; j < TW; ++j) *(f32x4*)(part[s][wave] + (16 * i + l15) * LD + 16 * j + 4 * q4) = acc[s][i][j];
+      if (bs && tm == 0) {
+#pragma unroll
+        for (int j = 0; j < TW; ++j) {
+          float t = cs[s][j];
+          t += __shfl_xor(t, 16, 64);
+          t += __shfl_xor(t, 32, 64);
+          if (q4 == 0) cpart[s][wave][16 * j + l15] = t;
+        }
       }
     }
     __syncthreads();
-    if (bs && tm == 0 && tid < BT && n0 + tid < g.N)
-      bs[n0 + tid] += ((cpart[0][tid] + cpart[1][tid]) + cpart[2][tid]) + cpart[3][tid];
-    const long zc = z * g.sC, zb = z * g.sBias;
-    for (int i = tid * 4; i < BT * BT; i += 1024) {
-      const int r = i / BT, c = i % BT, row = m0 + r, col = n0 + c;
-      if (row >= g.M || col >= g.N) continue;
-      const int o = r * LD + c;
-      const f32x4 p0 = *(const f32x4*)(part[0] + o), p1 = *(const f32x4*)(part[1] + o), p2 = *(const f32x4*)(part[2] + o),
-                  p3 = *(const f32x4*)(part[3] + o);
-      epilogue_store4(g, zc, zb, row, col, ((p0 + p1) + p2) + p3);
+    if (sums) {
+#pragma unroll
+      for (int s = 0; s < NSG; ++s) bsum0 += ((cpart[s][0][tid] + cpart[s][1][tid]) + cpart[s][2][tid]) + cpart[s][3][tid];
+      bs[n0 + tid] = bsum0;
+    }
+    if (!stores) continue;
+    auto sum_of = [&](int s) {
+      const int o = er * LD + ec;
+      const f32x4 p0 = *(const f32x4*)(part[s][0] + o), p1 = *(const f32x4*)(part[s][1] + o), p2 = *(const f32x4*)(part[s][2] + o),
+                  p3 = *(const f32x4*)(part[s][3] + o);
+      return ((p0 + p1) + p2) + p3;
+    };
+    if constexpr (NSG == 2) {   // an accumulating product
+      *(f32x4*)((float*)g.C + zc + (long)row * g.ldc + col) = (in.c + sum_of(0)) + sum_of(1);
+    } else {
+      epilogue_store4(g, zc, row, col, sum_of(0), in);
     }
   }
 }
@@ -292,7 +302,7 @@ __global__ __launch_bounds__(256) void gemm_f32_small(GemmArgs g, int tiles_n) {
 struct F32Tiles {
   int first[WgradGroup::MAX + 1];
 };
-template <int BT>
+template <int BT, int NSG>
 __global__ __launch_bounds__(256) void wgrad_group_f32(WgradGroup w, F32Tiles t) {
   int i = 0;
 #pragma unroll
@@ -303,16 +313,16 @@ __global__ __launch_bounds__(256) void wgrad_group_f32(WgradGroup w, F32Tiles t)
   for (int k = 0; k < WgradGroup::MAX; ++k)
     if (i == k) {
       const WgradProblem& p = w.p[k];
-      g.A = p.A; g.B = p.B; g.C = p.C; g.bsum_z[0] = p.bsum;
+      g.A = p.A; g.B = p.B; g.C = p.C; g.bsum = p.bsum;
       g.M = p.M; g.N = p.N; g.lda = p.lda; g.ldb = p.ldb; g.ldc = p.ldc;
       first = t.first[k];
     }
   g.m_valid = g.M; g.n_valid = g.N; g.K = g.k_valid = w.K; g.kseg_len = w.kseg;
   g.segA = (long)w.kseg * g.lda; g.segB = (long)w.kseg * g.ldb;
-  g.epi = EPI_ACC32 | (g.bsum_z[0] ? EPI_BSUM : 0) | (w.K > w.kseg ? EPI_SEGACC : 0);
+  g.epi = EPI_ACC32 | (g.bsum ? EPI_BSUM : 0) | (w.K > w.kseg ? EPI_SEGACC : 0);
   const int tn = (g.N + BT - 1) / BT, bid = blockIdx.x - first;
   if constexpr (BT >= 64) f32_tile<BT, true, true>(g, tn, bid, 0);
-  else f32_small_tile<BT / 16, true, true>(g, tn, bid, 0);
+  else f32_small_tile<BT / 16, true, true, NSG>(g, tn, bid, 0);
 }
 
 // ------------------------------------------------------------------ host side
@@ -332,10 +342,6 @@ bool gemm_f32_takes(const GemmArgs& g) {
   if ((g.epi & (EPI_ADD | EPI_MUL)) && (g.ldaux % 4 || !al16(g.aux))) return false;
   if ((g.epi & EPI_GELU) && !al16(g.C2)) return false;
   if ((g.epi & EPI_BSUM) && !(g.a_kstrided && g.b_kstrided)) return false;
-  if ((g.Az[0] || g.Bz[0] || g.Cz[0] || (g.epi & EPI_BSUM)) && g.batch > 4) return false;
-  if (g.Az[0] || g.Bz[0] || g.Cz[0])
-    for (int z = 0; z < g.batch; ++z)
-      if (!al16(g.Az[z]) || !al16(g.Bz[z]) || !al16(g.Cz[z])) return false;
   return true;
 }
 
@@ -367,9 +373,9 @@ static hipError_t launch_layout(const GemmArgs& g, hipStream_t st) {
   return launch_small<1, AKS, BKS>(g, st);
 }
 
-template <int BT>
-static hipError_t launch_group(const WgradGroup& w, hipStream_t st) {
-  auto kern = wgrad_group_f32<BT>;
+template <int BT, int NSG>
+static hipError_t launch_group_of(const WgradGroup& w, hipStream_t st) {
+  auto kern = wgrad_group_f32<BT, NSG>;
   int lds = 0;
   if constexpr (BT >= 64) {
     constexpr int bytes = 2 * 4 * 2 * F32Tile<BT, true>::FLOATS;
@@ -381,6 +387,13 @@ static hipError_t launch_group(const WgradGroup& w, hipStream_t st) {
   for (int i = 0; i < w.n; ++i) t.first[i + 1] = t.first[i] + ((w.p[i].M + BT - 1) / BT) * ((w.p[i].N + BT - 1) / BT);
   hipLaunchKernelGGL(kern, dim3(t.first[w.n]), dim3(256), lds, st, w, t);
   return hipGetLastError();
+}
+
+template <int BT>
+static hipError_t launch_group(const WgradGroup& w, hipStream_t st) {
+  if constexpr (BT < 64)   // (the tile kernel takes the segments one after the other)
+    if (w.K > w.kseg) return launch_group_of<BT, 2>(w, st);
+  return launch_group_of<BT, 1>(w, st);
 }
 
 hipError_t launch_wgrad_group_f32(const WgradGroup& w, hipStream_t st) {

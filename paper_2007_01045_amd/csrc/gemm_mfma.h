@@ -263,12 +263,8 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   }
   const int m0 = tm * BM, n0 = tn * BN;
 
-  // (the per-instance pointers are picked with constant indices: a variable index would move the whole
-  // argument struct to scratch memory, and with it every value the k-loop derives from it out of scalar registers)
-  auto pick = [&](auto& arr) { return z == 0 ? arr[0] : (z == 1 ? arr[1] : (z == 2 ? arr[2] : arr[3])); };
-  const bf16* Ab = g.Az[0] ? (const bf16*)pick(g.Az) : (const bf16*)g.A + z * g.sA;
-  const bf16* Bb = g.Bz[0] ? (const bf16*)pick(g.Bz) : (const bf16*)g.B + z * g.sB;
-  void* const Cb = g.Cz[0] ? pick(g.Cz) : g.C;
+  const bf16 *Ab = (const bf16*)g.A + z * g.sA, *Bb = (const bf16*)g.B + z * g.sB;
+  void* const Cb = g.C;
   // (two segments: whole turns of the ring each; the k-tiles beyond a segment's end read nothing)
   const int seg_tiles = (g.kseg_len + BK - 1) / BK;
   const int tiles_per_seg = NSEG == 1 ? seg_tiles : (seg_tiles + NS - 1) / NS * NS;
@@ -341,6 +337,79 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
     advance();
   };
 
+  // The epilogue's reads.  A wave's vector-memory requests complete in the order they were issued, stores among them:
+  // waiting for a value requested AFTER a store waits for the store's acknowledgement as well.  So nothing is requested
+  // between two blocks' stores that is not needed until the block after: the bias (the same four columns for every row
+  // a lane stores) is read once, and the second operand (residual, gate) or the fp32 C of an accumulating product is
+  // requested one unit (16 or 32 rows) ahead -- the first one's before the workgroup's last barrier and the staging of
+  // the accumulators through LDS -- or all of it there where the registers allow (PRE: the tiles with at most 64 rows
+  // per wave); or, in the small tiles, before the first k-tile (EARLY): a launch of those is mostly memory latencies in
+  // a row, and this takes one of them off.
+  const long zc = z * g.sC, zbias = z * g.sBias;
+  constexpr int C4 = CFG::WN / 4;             // float4 per staged row
+  constexpr int NIT = 32 * C4 / 64;           // float4 per lane per 32-row block
+  static_assert(64 % C4 == 0, "a lane stores the same columns of every row");
+  constexpr int HB = NSEG == 2 || MI > 2 ? (NIT > 4 ? 4 : NIT) : (NIT > 8 ? 8 : NIT);   // processed HB at a time
+  constexpr bool PRE = !CS && NSEG == 1 && MI * NIT <= 16;   // (the column-sum variant serves accumulating products only)
+  constexpr bool EARLY = NSEG * MI * NIT <= 8;
+  const int epi = g.epi;
+  const int lane_col = n0 + wn0 + lane % C4 * 4;   // the lane's four columns
+  const bool interior = m0 + BM <= g.M && n0 + BN <= g.N;
+  // (native vectors: arrays of the runtime's float4, a struct around a union, stay in scratch memory; a bf16
+  // operand's four values sit in the first two lanes)
+  typedef float f32x2 __attribute__((__vector_size__(2 * sizeof(float))));
+  // PRE: the whole operand; else two units of HB pieces, the one in use and the one after
+  constexpr int UNITS = MI * (NIT / HB);
+  f32x4 pre[PRE ? UNITS : 2][HB];
+  // Addresses: a lane's piece n of block i is row m0 + wm0 + 32 i + n RS + lane / C4.  All but the last term is the same
+  // for the whole wave and stays in scalar registers; a lane keeps one 32-bit offset per matrix (64-bit addresses per
+  // piece had the 256x256 tile's accumulators spill).
+  constexpr int RS = 64 / C4;
+  const unsigned c_off4 = (unsigned)((lane / C4) * g.ldc + lane % C4 * 4) * 4u, a_off4 = (unsigned)((lane / C4) * g.ldaux + lane % C4 * 4) * 4u;
+  auto row_of = [&](int i, int n) { return m0 + wm0 + i * 32 + n * RS + lane / C4; };
+  auto at = [&](const void* base, int ld, unsigned lane_off, int i, int n, int es) {
+    const long u = (zc + (long)(m0 + wm0 + i * 32 + n * RS) * ld + n0 + wn0) * es;
+    return (char*)base + u + lane_off;
+  };
+  // HB pieces of that operand (unit k), as each lane will use them in store_block
+  auto load_unit = [&](int k, f32x4 (&dst)[HB], auto ACC) {
+    const int i = k / (NIT / HB), hb = k % (NIT / HB) * HB;
+#pragma unroll
+    for (int u = 0; u < HB; ++u) {
+      const int n = hb + u;
+      dst[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (!(interior || (row_of(i, n) < g.M && lane_col < g.N))) continue;
+      if (decltype(ACC)::value) {
+        dst[u] = *(const f32x4*)at(Cb, g.ldc, c_off4, i, n, 4);
+      } else if (epi & EPI_AUX32) {
+        dst[u] = *(const f32x4*)at(g.aux, g.ldaux, a_off4, i, n, 4);
+      } else {
+        const f32x2 h2 = *(const f32x2*)at(g.aux, g.ldaux, a_off4 >> 1, i, n, 2);
+        dst[u] = f32x4{h2[0], h2[1], 0.f, 0.f};
+      }
+    }
+  };
+  const bool has_aux = (epi & (EPI_ADD | EPI_MUL | EPI_ROWDOT)) != 0, has_acc = (epi & EPI_ACC32) != 0;
+  // what the rolling buffers carry: C of an accumulating product without a second operand (no product of the stage
+  // has both; one that does reads C in place), else the second operand
+  const bool roll_acc = has_acc && !has_aux;
+  auto request = [&](int k, f32x4 (&dst)[HB]) {
+    if (has_aux) load_unit(k, dst, std::false_type{});
+    else if (has_acc) load_unit(k, dst, std::true_type{});
+  };
+  float bias4[4] = {0.f, 0.f, 0.f, 0.f};
+  auto request_first = [&]() {
+    request(0, pre[0]);
+    if constexpr (PRE) {
+#pragma unroll
+      for (int k = 1; k < UNITS; ++k) request(k, pre[k]);
+    }
+    if ((epi & EPI_BIAS) && lane_col < g.N) {
+      const bf16x4 bv = *(const bf16x4*)((const bf16*)g.bias + zbias + lane_col);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bias4[e] = (float)bv[e];
+    }
+  };
   f32x16 accs[NSEG][MI][NI];
 #pragma unroll
   for (int s = 0; s < NSEG; ++s)
@@ -372,6 +441,20 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   // been issued, before the barrier lets other waves refill that slot (a request that reads
   // nothing delivers its zeros within a few clocks)
   constexpr int WAIT_TILE = (INFLIGHT & 15) | ((INFLIGHT >> 4) << 14) | 0x0070;  // expcnt: no wait
+  float* const bsum_ptr = CS && z == 0 ? g.bsum : nullptr;
+  const bool do_cs = CS && (g.epi & EPI_BSUM) && tm == 0 && wm0 == 0 && bsum_ptr != nullptr;
+  float bsum0[NI];   // (EARLY: what the column sums are added to)
+  auto load_bsum = [&]() {
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int col = n0 + wn0 + 32 * j + (lane & 31);
+      bsum0[j] = do_cs && lane < 32 && col < g.N ? bsum_ptr[col] : 0.f;
+    }
+  };
+  if constexpr (EARLY) {
+    request_first();
+    if constexpr (CS) load_bsum();
+  }
   static_for<NS - 1>([&](auto T) { issue_loads(T); });
   // The k-steps are rotated by one against the tiles: the MFMAs of a tile's LAST k-step are issued after the
   // barrier that opens the next tile (their fragments were read before it).  Everything else a tile needs --
@@ -398,8 +481,6 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
 #pragma unroll
     for (int j = 0; j < NI; ++j) csum[s][j] = 0.f;
   const bf16x2 one2 = {(bf16)1.0f, (bf16)1.0f};
-  float* const bsum_ptr = CS ? pick(g.bsum_z) : nullptr;
-  const bool do_cs = CS && (g.epi & EPI_BSUM) && tm == 0 && wm0 == 0 && bsum_ptr != nullptr;
   auto add_cols = [&](float& t, bf16x8 b) {
     t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(b, b, 0, 1), one2, t, false);
     t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(b, b, 2, 3), one2, t, false);
@@ -474,6 +555,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   if constexpr (CS) {
     // the two half waves hold the sums over different k (one workgroup per column range adds to bsum: no atomic)
     if (do_cs) {
+      if constexpr (!EARLY) load_bsum();
 #pragma unroll
       for (int j = 0; j < NI; ++j) {
         const int col = n0 + wn0 + 32 * j + (lane & 31);
@@ -481,7 +563,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
 #pragma unroll
         for (int s = 0; s < NSEG; ++s) t[s] = csum[s][j] + __shfl_xor(csum[s][j], 32, 64);
         if (lane < 32 && col < g.N) {
-          float o = bsum_ptr[col];
+          float o = bsum0[j];
 #pragma unroll
           for (int s = 0; s < NSEG; ++s) o += t[s];
           bsum_ptr[col] = o;
@@ -490,75 +572,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // the tail requests (they read nothing) must be done before LDS is reused
-  // The epilogue's reads.  A wave's vector-memory requests complete in the order they were issued, stores among them:
-  // waiting for a value requested AFTER a store waits for the store's acknowledgement as well.  So nothing is requested
-  // between two blocks' stores that is not needed until the block after: the bias (the same four columns for every row
-  // a lane stores) is read once, and the second operand (residual, gate) or the fp32 C of an accumulating product is
-  // requested one unit (16 or 32 rows) ahead -- the first one's HERE, before the workgroup's last barrier and the staging of
-  // the accumulators through LDS -- or all of it here where the registers allow (PRE: the tiles with at most 64 rows
-  // per wave).
-  const long zc = g.Cz[0] ? 0 : z * g.sC, zbias = z * g.sBias;
-  constexpr int C4 = CFG::WN / 4;             // float4 per staged row
-  constexpr int NIT = 32 * C4 / 64;           // float4 per lane per 32-row block
-  static_assert(64 % C4 == 0, "a lane stores the same columns of every row");
-  constexpr int HB = NSEG == 2 || MI > 2 ? (NIT > 4 ? 4 : NIT) : (NIT > 8 ? 8 : NIT);   // processed HB at a time
-  constexpr bool PRE = !CS && NSEG == 1 && MI * NIT <= 16;   // (the column-sum variant serves accumulating products only)
-  const int epi = g.epi;
-  const int lane_col = n0 + wn0 + lane % C4 * 4;   // the lane's four columns
-  const bool interior = m0 + BM <= g.M && n0 + BN <= g.N;
-  // (native vectors: arrays of the runtime's float4, a struct around a union, stay in scratch memory; a bf16
-  // operand's four values sit in the first two lanes)
-  typedef float f32x2 __attribute__((__vector_size__(2 * sizeof(float))));
-  // PRE: the whole operand; else two units of HB pieces, the one in use and the one after
-  constexpr int UNITS = MI * (NIT / HB);
-  f32x4 pre[PRE ? UNITS : 2][HB];
-  // Addresses: a lane's piece n of block i is row m0 + wm0 + 32 i + n RS + lane / C4.  All but the last term is the same
-  // for the whole wave and stays in scalar registers; a lane keeps one 32-bit offset per matrix (64-bit addresses per
-  // piece had the 256x256 tile's accumulators spill).
-  constexpr int RS = 64 / C4;
-  const unsigned c_off4 = (unsigned)((lane / C4) * g.ldc + lane % C4 * 4) * 4u, a_off4 = (unsigned)((lane / C4) * g.ldaux + lane % C4 * 4) * 4u;
-  auto row_of = [&](int i, int n) { return m0 + wm0 + i * 32 + n * RS + lane / C4; };
-  auto at = [&](const void* base, int ld, unsigned lane_off, int i, int n, int es) {
-    const long u = (zc + (long)(m0 + wm0 + i * 32 + n * RS) * ld + n0 + wn0) * es;
-    return (char*)base + u + lane_off;
-  };
-  // HB pieces of that operand (unit k), as each lane will use them in store_block
-  auto load_unit = [&](int k, f32x4 (&dst)[HB], auto ACC) {
-    const int i = k / (NIT / HB), hb = k % (NIT / HB) * HB;
-#pragma unroll
-    for (int u = 0; u < HB; ++u) {
-      const int n = hb + u;
-      dst[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (!(interior || (row_of(i, n) < g.M && lane_col < g.N))) continue;
-      if (decltype(ACC)::value) {
-        dst[u] = *(const f32x4*)at(Cb, g.ldc, c_off4, i, n, 4);
-      } else if (epi & EPI_AUX32) {
-        dst[u] = *(const f32x4*)at(g.aux, g.ldaux, a_off4, i, n, 4);
-      } else {
-        const f32x2 h2 = *(const f32x2*)at(g.aux, g.ldaux, a_off4 >> 1, i, n, 2);
-        dst[u] = f32x4{h2[0], h2[1], 0.f, 0.f};
-      }
-    }
-  };
-  const bool has_aux = (epi & (EPI_ADD | EPI_MUL | EPI_ROWDOT)) != 0, has_acc = (epi & EPI_ACC32) != 0;
-  // what the rolling buffers carry: C of an accumulating product without a second operand (no product of the stage
-  // has both; one that does reads C in place), else the second operand
-  const bool roll_acc = has_acc && !has_aux;
-  auto request = [&](int k, f32x4 (&dst)[HB]) {
-    if (has_aux) load_unit(k, dst, std::false_type{});
-    else if (has_acc) load_unit(k, dst, std::true_type{});
-  };
-  request(0, pre[0]);
-  if constexpr (PRE) {
-#pragma unroll
-    for (int k = 1; k < UNITS; ++k) request(k, pre[k]);
-  }
-  float bias4[4] = {0.f, 0.f, 0.f, 0.f};
-  if ((epi & EPI_BIAS) && lane_col < g.N) {
-    const bf16x4 bv = *(const bf16x4*)((const bf16*)g.bias + zbias + lane_col);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) bias4[e] = (float)bv[e];
-  }
+  if constexpr (!EARLY) request_first();
   // every wave has read its last fragments (lgkmcnt(0)): LDS can be reused after the barrier.  The raw barrier on
   // purpose: __syncthreads() would also wait for the requests just issued.
   __builtin_amdgcn_s_waitcnt(0xC07F);

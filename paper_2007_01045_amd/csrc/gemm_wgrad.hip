@@ -18,20 +18,20 @@ __global__ __launch_bounds__(64 * WGM * WGN, NSEG) void wgrad_group_kernel(Wgrad
   int i = 0;
 #pragma unroll
   for (int k = 1; k < WgradGroup::MAX; ++k) i += k < w.n && (int)blockIdx.x >= t.first[k];
-  // the problem's fields picked with constant indices (see pick in gemm_mfma_tile)
+  // the problem's fields picked with constant indices (a variable index would move the list to scratch memory)
   GemmArgs g{};
   int first = 0;
 #pragma unroll
   for (int k = 0; k < WgradGroup::MAX; ++k)
     if (i == k) {
       const WgradProblem& p = w.p[k];
-      g.A = p.A; g.B = p.B; g.C = p.C; g.bsum_z[0] = p.bsum;
+      g.A = p.A; g.B = p.B; g.C = p.C; g.bsum = p.bsum;
       g.M = p.M; g.N = p.N; g.lda = p.lda; g.ldb = p.ldb; g.ldc = p.ldc;
       first = t.first[k];
     }
   g.m_valid = g.M; g.n_valid = g.N; g.K = g.k_valid = w.K; g.kseg_len = w.kseg;
   g.segA = (long)w.kseg * g.lda; g.segB = (long)w.kseg * g.ldb;
-  g.epi = EPI_ACC32 | (g.bsum_z[0] ? EPI_BSUM : 0);
+  g.epi = EPI_ACC32 | (g.bsum ? EPI_BSUM : 0);
   gemm_mfma_tile<BM, BN, WGM, WGN, NS, true, true, BK, true, false, NSEG>(g, (g.M + BM - 1) / BM, (g.N + BN - 1) / BN,
                                                                           blockIdx.x - first, 0);
 }

@@ -48,14 +48,7 @@ struct GemmArgs {
   long segA, segB;
   int batch;
   long sA, sB, sC, sBias;
-  // optional per-instance operand pointers (batch <= 4); when Az[0] / Bz[0] / Cz[0] is set
-  // they replace A + z*sA / B + z*sB / C + z*sC, so unrelated products of one shape can
-  // share a launch
-  const void* Az[4];
-  const void* Bz[4];
-  void* Cz[4];
-  // EPI_BSUM: fp32 [N] per instance (a NULL entry skips that instance); both operands k-strided
-  float* bsum_z[4];
+  float* bsum;    // EPI_BSUM: fp32 [N], of instance 0; both operands k-strided
   float* rowdot;  // EPI_ROWDOT: fp32 [ceil(N/32)][M]
   int k_valid;  // k-strided operands: rows k >= k_valid read as zero (K itself is padded)
   int m_valid, n_valid;  // rows of A / B that exist in memory (0 = M / N); rows beyond read as zero

@@ -64,13 +64,15 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const void* __restrict__ z,
   constexpr int V = Vec<T>::N;
   int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
-  float x[NCH][V];
+  float x[NCH][V], g[NCH][V], b[NCH][V];
   float s = 0.f;
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
     int col = (c * 64 + lane) * V;
     if (col < H) {
       load_z<T, Z32>(z, (long)row * H + col, x[c]);
+      load_vec<T>(gamma + col, g[c]);   // with the row, not behind its two sums
+      load_vec<T>(beta + col, b[c]);
 #pragma unroll
       for (int e = 0; e < V; ++e) s += x[c][e];
     }
@@ -97,11 +99,9 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const void* __restrict__ z,
   for (int c = 0; c < NCH; ++c) {
     int col = (c * 64 + lane) * V;
     if (col < H) {
-      float g[V], b[V], o[V];
-      load_vec<T>(gamma + col, g);
-      load_vec<T>(beta + col, b);
+      float o[V];
 #pragma unroll
-      for (int e = 0; e < V; ++e) o[e] = (x[c][e] - mean) * rstd * g[e] + b[e];
+      for (int e = 0; e < V; ++e) o[e] = (x[c][e] - mean) * rstd * g[c][e] + b[c][e];
       store_vec<T>(y + (long)row * H + col, o);
       if (y32) {  // unrounded copy for the residual branch
 #pragma unroll
