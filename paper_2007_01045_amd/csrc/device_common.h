@@ -26,13 +26,14 @@ template <> __device__ __forceinline__ bf16 from_f32<bf16>(float v) { return (bf
 // error below 1.5e-7 -- far inside the fp32 and bf16 parity tolerances, and a fifth of
 // the instructions of the library erff.  The same exponential gives phi(u).
 __device__ __forceinline__ void gelu_both(float u, float& g, float& gp) {
-  float x = fabsf(u) * 0.70710678118654752f;
-  float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, x, 1.0f));
+  // (constants folded: x = |u| / sqrt 2 goes into p and into the exponent's log2(e), the factor 1/2 into the a_i)
+  float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, fabsf(u), 1.0f));
   // = exp(-u^2 / 2), as the bare v_exp_f32 (the argument is never positive; a result below 2^-126 may be zero)
-  float e = __builtin_amdgcn_exp2f(-x * x * 1.4426950408889634f);
-  float poly = t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 1.061405429f, -1.453152027f), 1.421413741f), -0.284496736f),
-                        0.254829592f);
-  float half_erfc = 0.5f * poly * e;                 // Phi(-|u|)
+  float e = __builtin_amdgcn_exp2f(u * u * (-0.5f * 1.4426950408889634f));
+  float poly = t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 0.5f * 1.061405429f, 0.5f * -1.453152027f), 0.5f * 1.421413741f),
+                                0.5f * -0.284496736f),
+                        0.5f * 0.254829592f);
+  float half_erfc = poly * e;                        // Phi(-|u|)
   float Phi = u >= 0.f ? 1.0f - half_erfc : half_erfc;
   g = u * Phi;
   gp = fmaf(u * 0.39894228040143268f, e, Phi);

@@ -95,9 +95,9 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 // from HBM: the fewer workgroups share a unit, the deeper the ring has to be), and a launch's fixed cost -- first
 // tile's latency, epilogue -- is only hidden by another workgroup on the same unit.  Eight waves (two per SIMD) beat
 // four on every tile of 128x128 and up.  Alone, in us (T rows; "->" four waves -> eight where both were measured):
-//   1: 256x256, four stages of 32      T=8192 N=4096 K=1024 GELU 112 -> 97; T=4096 52 -> 44 (128x128: 51)
-//   2: 256x128, three stages of 64     T=8192 N=1024 K=4096 residual 77 -> 72 (128x128: 83), gradient 81 -> 69
-//   3: 128x128, two stages of 64       two workgroups per unit: T=8192 N=4096 K=1024 gate 119 -> 107 (256x256: 110)
+//   1: 256x256, four stages of 32      T=8192 N=4096 K=1024 GELU 112 -> 92, gate 90 (128x128: 101); T=4096 44 and 42
+//   2: 256x128, three stages of 64     T=8192 N=1024 K=4096 residual 77 -> 72 (128x128: 84), gradient 81 -> 65
+//   3: 128x128, two stages of 64       two workgroups per unit: T=2048 N=4096 K=1024 GELU 26, gate 23 (256x256: 36, 31)
 //   4: 128x64, three stages of 64      T=2048 N=1024 K=4096 27 (128x128: 46); T=4096 N=1024 K=1024 17 (20)
 //   5: 128x128, four stages of 32      weight gradients: both operands k-strided, so a 32-deep tile still reads whole
 //                                      256-byte rows, and three tiles are in flight in the LDS of two of 64
@@ -124,7 +124,7 @@ static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   }
   const bool second = (g.epi & (EPI_ADD | EPI_MUL | EPI_GELU)) != 0;   // an epilogue that moves a second matrix
   const long t256 = tiles(256, 128);
-  if (tiles(256, 256) >= most && !(g.epi & (EPI_ADD | EPI_MUL))) return 1;
+  if (tiles(256, 256) >= most && !(g.epi & (EPI_ADD | EPI_AUX32))) return 1;
   if (t256 >= most && t256 <= U && (g.K >= 2048 || !second || g.N <= 1024)) return 2;
   if (t128 > U) return 3;
   if (t128 >= most) return g.K >= 2048 ? (g.shared ? 3 : 6) : 4;

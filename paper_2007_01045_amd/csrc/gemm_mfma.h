@@ -217,6 +217,8 @@ struct GemmTile {
   static constexpr int LOADS_PER_TILE = TA::NI + TB::NI;  // per wave
   static constexpr size_t EPI_BYTES = (size_t)NSEG * NW * 32 * EPI_LD * sizeof(float);
   static constexpr size_t LDS_BYTES = MAIN_BYTES > EPI_BYTES ? MAIN_BYTES : EPI_BYTES;
+  // waves per SIMD the registers must allow: two workgroups of eight waves where LDS has room for them
+  static constexpr int MIN_WAVES = NSEG == 1 && NW == 8 && LDS_BYTES <= 80 * 1024 ? 4 : NSEG;
 };
 
 // CS: the variant that can also sum B over k (EPI_BSUM); KT: the variant for K segments that are no multiple of 64
@@ -351,16 +353,33 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   static_assert(64 % C4 == 0, "a lane stores the same columns of every row");
   constexpr int HB = NSEG == 2 || MI > 2 ? (NIT > 4 ? 4 : NIT) : (NIT > 8 ? 8 : NIT);   // processed HB at a time
   constexpr bool PRE = !CS && NSEG == 1 && MI * NIT <= 16;   // (the column-sum variant serves accumulating products only)
-  constexpr bool EARLY = NSEG * MI * NIT <= 8;
+  constexpr bool EARLY = CFG::NW == 4 && NSEG * MI * NIT <= 8;
   const int epi = g.epi;
   const int lane_col = n0 + wn0 + lane % C4 * 4;   // the lane's four columns
   const bool interior = m0 + BM <= g.M && n0 + BN <= g.N;
-  // (native vectors: arrays of the runtime's float4, a struct around a union, stay in scratch memory; a bf16
-  // operand's four values sit in the first two lanes)
+  // What a product's epilogue reads, as a constant: flags tested per request have the loads wait for each other where
+  // the branches meet (gate of 8192 x 4096 x 1024: 108 us, 89 with the whole operand requested in one go).
+  //   AUXH: a bf16 second operand, all of it ahead; AUXF: an fp32 one; ACCF: the fp32 C of an accumulating product;
+  //   ANY: nothing ahead (no operand, or a combination that no product of the stage has, read in place)
+  enum { AUXH, AUXF, ACCF, ANY };
+  const bool has_aux = (epi & (EPI_ADD | EPI_MUL | EPI_ROWDOT)) != 0, has_acc = (epi & EPI_ACC32) != 0;
+  auto with_mode = [&](auto&& f) __attribute__((always_inline)) {
+    constexpr bool TT = AKS && BKS;   // the weight-gradient layout: the only one that accumulates
+    if constexpr (TT) {
+      if (has_acc && !has_aux) return f(std::integral_constant<int, ACCF>{});
+    } else {
+      if (has_aux && !has_acc) {
+        if (epi & EPI_AUX32) return f(std::integral_constant<int, AUXF>{});
+        if (!(epi & EPI_ROWDOT)) return f(std::integral_constant<int, AUXH>{});
+      }
+    }
+    return f(std::integral_constant<int, ANY>{});
+  };
+  // (native vectors: arrays of the runtime's float4, a struct around a union, stay in scratch memory)
   typedef float f32x2 __attribute__((__vector_size__(2 * sizeof(float))));
-  // PRE: the whole operand; else two units of HB pieces, the one in use and the one after
   constexpr int UNITS = MI * (NIT / HB);
-  f32x4 pre[PRE ? UNITS : 2][HB];
+  f32x4 pre[PRE ? UNITS : 2][HB];    // fp32 operands: whole (PRE), or the unit in use and the one after
+  f32x2 preh[UNITS][HB];             // a bf16 operand
   // Addresses: a lane's piece n of block i is row m0 + wm0 + 32 i + n RS + lane / C4.  All but the last term is the same
   // for the whole wave and stays in scalar registers; a lane keeps one 32-bit offset per matrix (64-bit addresses per
   // piece had the 256x256 tile's accumulators spill).
@@ -372,38 +391,19 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
     return (char*)base + u + lane_off;
   };
   // HB pieces of that operand (unit k), as each lane will use them in store_block
-  auto load_unit = [&](int k, f32x4 (&dst)[HB], auto ACC) {
-    const int i = k / (NIT / HB), hb = k % (NIT / HB) * HB;
-#pragma unroll
-    for (int u = 0; u < HB; ++u) {
-      const int n = hb + u;
-      dst[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (!(interior || (row_of(i, n) < g.M && lane_col < g.N))) continue;
-      if (decltype(ACC)::value) {
-        dst[u] = *(const f32x4*)at(Cb, g.ldc, c_off4, i, n, 4);
-      } else if (epi & EPI_AUX32) {
-        dst[u] = *(const f32x4*)at(g.aux, g.ldaux, a_off4, i, n, 4);
-      } else {
-        const f32x2 h2 = *(const f32x2*)at(g.aux, g.ldaux, a_off4 >> 1, i, n, 2);
-        dst[u] = f32x4{h2[0], h2[1], 0.f, 0.f};
-      }
-    }
-  };
-  const bool has_aux = (epi & (EPI_ADD | EPI_MUL | EPI_ROWDOT)) != 0, has_acc = (epi & EPI_ACC32) != 0;
-  // what the rolling buffers carry: C of an accumulating product without a second operand (no product of the stage
-  // has both; one that does reads C in place), else the second operand
-  const bool roll_acc = has_acc && !has_aux;
-  auto request = [&](int k, f32x4 (&dst)[HB]) {
-    if (has_aux) load_unit(k, dst, std::false_type{});
-    else if (has_acc) load_unit(k, dst, std::true_type{});
+  auto request = [&](auto K, auto MODE, auto FULLC) __attribute__((always_inline)) {
+    constexpr int k = decltype(K)::value, i = k / (NIT / HB), hb = k % (NIT / HB) * HB, mode = decltype(MODE)::value;
+    static_for<HB>([&](auto U) __attribute__((always_inline)) {
+      constexpr int u = decltype(U)::value, n = hb + u, slot = PRE ? k : (k & 1);
+      const bool in = decltype(FULLC)::value || (row_of(i, n) < g.M && lane_col < g.N);
+      if constexpr (mode == AUXH) preh[k][u] = in ? *(const f32x2*)at(g.aux, g.ldaux, a_off4 >> 1, i, n, 2) : f32x2{0.f, 0.f};
+      if constexpr (mode == AUXF) pre[slot][u] = in ? *(const f32x4*)at(g.aux, g.ldaux, a_off4, i, n, 4) : f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (mode == ACCF) pre[slot][u] = in ? *(const f32x4*)at(Cb, g.ldc, c_off4, i, n, 4) : f32x4{0.f, 0.f, 0.f, 0.f};
+    });
   };
   float bias4[4] = {0.f, 0.f, 0.f, 0.f};
-  auto request_first = [&]() {
-    request(0, pre[0]);
-    if constexpr (PRE) {
-#pragma unroll
-      for (int k = 1; k < UNITS; ++k) request(k, pre[k]);
-    }
+  auto request_first = [&](auto MODE, auto FULLC) __attribute__((always_inline)) {
+    static_for<PRE || decltype(MODE)::value == AUXH ? UNITS : 1>([&](auto K) __attribute__((always_inline)) { request(K, MODE, FULLC); });
     if ((epi & EPI_BIAS) && lane_col < g.N) {
       const bf16x4 bv = *(const bf16x4*)((const bf16*)g.bias + zbias + lane_col);
 #pragma unroll
@@ -452,7 +452,10 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
     }
   };
   if constexpr (EARLY) {
-    request_first();
+    with_mode([&](auto MODE) __attribute__((always_inline)) {
+      if (interior) request_first(MODE, std::true_type{});
+      else request_first(MODE, std::false_type{});
+    });
     if constexpr (CS) load_bsum();
   }
   static_for<NS - 1>([&](auto T) { issue_loads(T); });
@@ -572,13 +575,6 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // the tail requests (they read nothing) must be done before LDS is reused
-  if constexpr (!EARLY) request_first();
-  // every wave has read its last fragments (lgkmcnt(0)): LDS can be reused after the barrier.  The raw barrier on
-  // purpose: __syncthreads() would also wait for the requests just issued.
-  __builtin_amdgcn_s_waitcnt(0xC07F);
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-
   // epilogue: per wave, 32 output rows at a time through an fp32 LDS staging tile that
   // turns "a lane owns 4 columns of one row" into row-contiguous stores.
   // acc[i][j][v]: row = wm0 + 32 i + (lane & 31), col = wn0 + 32 j + 8 (v>>2) + 4 (lane>>5) + (v&3)
@@ -587,11 +583,11 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   float* stg = (float*)smem + wave * NSEG * 32 * CFG::EPI_LD;
   // one 32-row block; the block index is a compile-time constant so that the
   // accumulators are always addressed statically (they must stay in registers)
-  auto store_block = [&](auto I, auto FULLC) {
-    constexpr int i = decltype(I)::value;
+  auto store_block = [&](auto I, auto FULLC, auto MODE) __attribute__((always_inline)) {
+    constexpr int i = decltype(I)::value, mode = decltype(MODE)::value;
     // FULL: the whole tile lies inside the matrix, no element needs a bounds test
     constexpr bool FULL = decltype(FULLC)::value;
-    auto stage = [&](auto& acc, float* stg) {
+    auto stage = [&](auto& acc, float* stg) __attribute__((always_inline)) {
 #pragma unroll
       for (int j = 0; j < NI; ++j)
 #pragma unroll
@@ -605,9 +601,9 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
     // the staging tile is private to the wave and a wave's LDS instructions execute in
     // order: no workgroup barrier is needed (one would also wait for the stores below)
     __builtin_amdgcn_wave_barrier();
-    static_for<NIT / HB>([&](auto Hc) {
+    static_for<NIT / HB>([&](auto Hc) __attribute__((always_inline)) {
       constexpr int hb = decltype(Hc)::value * HB, k = i * (NIT / HB) + decltype(Hc)::value;
-      if constexpr (!PRE && k + 1 < UNITS) request(k + 1, pre[(k + 1) & 1]);   // ahead of this unit's stores
+      if constexpr (!PRE && mode != AUXH && k + 1 < UNITS) request(std::integral_constant<int, k + 1>{}, MODE, FULLC);   // ahead of this unit's stores
       f32x4 (&in)[HB] = pre[PRE ? k : (k & 1)];
       float4 t[HB];
       bool ok[HB];
@@ -628,19 +624,28 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
           t[u].x += bias4[0]; t[u].y += bias4[1]; t[u].z += bias4[2]; t[u].w += bias4[3];
         }
       }
-      if (has_aux) {
+      if (mode == AUXH || mode == AUXF || (mode == ANY && has_aux)) {
         float4 xv[HB];
 #pragma unroll
         for (int u = 0; u < HB; ++u) {
-          const f32x4 pv = in[u];
-          if (epi & EPI_AUX32) {
-            xv[u] = make_float4(pv[0], pv[1], pv[2], pv[3]);
-          } else {
-            const bf16x4 b4 = __builtin_bit_cast(bf16x4, f32x2{pv[0], pv[1]});
+          f32x4 x{0.f, 0.f, 0.f, 0.f};
+          f32x2 h{0.f, 0.f};
+          bool half = mode == AUXH;
+          if constexpr (mode == AUXH) h = preh[k][u];
+          if constexpr (mode == AUXF) x = in[u];
+          if constexpr (mode == ANY) {
+            half = !(epi & EPI_AUX32);
+            if (half) h = ok[u] ? *(const f32x2*)at(g.aux, g.ldaux, a_off4 >> 1, i, hb + u, 2) : h;
+            else x = ok[u] ? *(const f32x4*)at(g.aux, g.ldaux, a_off4, i, hb + u, 4) : x;
+          }
+          if (half) {
+            const bf16x4 b4 = __builtin_bit_cast(bf16x4, h);
             xv[u] = make_float4((float)b4[0], (float)b4[1], (float)b4[2], (float)b4[3]);
+          } else {
+            xv[u] = make_float4(x[0], x[1], x[2], x[3]);
           }
         }
-        if (epi & EPI_ROWDOT) {
+        if (mode != AUXH && (epi & EPI_ROWDOT)) {
           // a row's 32 columns of a block sit in 8 consecutive lanes (4 columns each): products of the
           // outputs as they are stored, summed over the lane's four, then over the eight lanes in a fixed tree
 #pragma unroll
@@ -666,11 +671,11 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
 #pragma unroll
         for (int u = 0; u < HB; ++u)
           if (ok[u]) *(float4*)at(Cb, g.ldc, c_off4, i, hb + u, 4) = t[u];
-      } else if (has_acc) {
+      } else if (mode == ACCF || (mode == ANY && has_acc)) {
         float4 cv[HB];
 #pragma unroll
         for (int u = 0; u < HB; ++u) {
-          if (roll_acc) cv[u] = make_float4(in[u][0], in[u][1], in[u][2], in[u][3]);
+          if constexpr (mode == ACCF) cv[u] = make_float4(in[u][0], in[u][1], in[u][2], in[u][3]);
           else cv[u] = ok[u] ? *(const float4*)at(Cb, g.ldc, c_off4, i, hb + u, 4) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
 #pragma unroll
@@ -708,20 +713,25 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
     });
     __builtin_amdgcn_wave_barrier();
   };
-  auto store_tile = [&](auto FULLC) {
-    store_block(std::integral_constant<int, 0>{}, FULLC);
-    if constexpr (MI > 1) store_block(std::integral_constant<int, 1>{}, FULLC);
-    if constexpr (MI > 2) store_block(std::integral_constant<int, 2>{}, FULLC);
-    if constexpr (MI > 3) store_block(std::integral_constant<int, 3>{}, FULLC);
+  auto finish = [&](auto MODE, auto FULLC) __attribute__((always_inline)) {
+    if constexpr (!EARLY) request_first(MODE, FULLC);
+    // every wave has read its last fragments (lgkmcnt(0)): LDS can be reused after the barrier.  The raw barrier on
+    // purpose: __syncthreads() would also wait for the requests just issued.
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    static_for<MI>([&](auto I) __attribute__((always_inline)) { store_block(I, FULLC, MODE); });
   };
   // interior tiles (nearly all of them) take the path without per-element bounds tests
-  if (interior) store_tile(std::true_type{});
-  else store_tile(std::false_type{});
+  with_mode([&](auto MODE) __attribute__((always_inline)) {
+    if (interior) finish(MODE, std::true_type{});
+    else finish(MODE, std::false_type{});
+  });
   static_assert(MI <= 4, "at most four 32-row blocks per wave");
 }
 
 template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false, int NSEG = 1>
-__global__ __launch_bounds__(64 * WGM * WGN, NSEG) void gemm_mfma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(64 * WGM * WGN, (GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, NSEG>::MIN_WAVES)) void gemm_mfma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
   gemm_mfma_tile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT, NSEG>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.z);
 }
 
