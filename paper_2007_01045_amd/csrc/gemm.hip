@@ -84,7 +84,7 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
   if ((g.epi & EPI_BIAS) && !aligned_to(g.bias, 8)) return false;
   if ((g.epi & EPI_GELU) && !aligned_to(g.C2, 8)) return false;
   if ((g.epi & EPI_BSUM) && !(g.a_kstrided && g.b_kstrided)) return false;
-  if ((g.epi & EPI_SEGACC) && !((g.epi & EPI_ACC32) && g.a_kstrided && g.b_kstrided && g.K == 2 * g.kseg_len)) return false;
+  if ((g.epi & EPI_SEGACC) && !((g.epi & EPI_ACC32) && g.a_kstrided && g.b_kstrided && !(g.epi & (EPI_BIAS | EPI_ADD | EPI_MUL)))) return false;
   return true;
 }
 
@@ -143,7 +143,7 @@ GemmArgs wgrad_args(const WgradGroup& w, int i) {
 }
 
 bool wgrad_group_takes(Dtype dt, const WgradGroup& w) {
-  if (w.n < 1 || w.n > WgradGroup::MAX || w.kseg < 1 || (w.K != w.kseg && w.K != 2 * w.kseg)) return false;
+  if (w.n < 1 || w.n > WgradGroup::MAX || w.kseg < 1 || w.K < w.kseg || w.K % w.kseg) return false;
   for (int i = 0; i < w.n; ++i) {
     const GemmArgs g = wgrad_args(w, i);
     if (!(dt == DT_BF16 ? gemm_uses_mfma(dt, g) : gemm_f32_takes(g))) return false;

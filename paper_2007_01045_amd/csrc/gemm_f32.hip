@@ -392,7 +392,7 @@ static hipError_t launch_group_of(const WgradGroup& w, hipStream_t st) {
 template <int BT>
 static hipError_t launch_group(const WgradGroup& w, hipStream_t st) {
   if constexpr (BT < 64)   // (the tile kernel takes the segments one after the other)
-    if (w.K > w.kseg) return launch_group_of<BT, 2>(w, st);
+    if (w.K / w.kseg % 2 == 0) return launch_group_of<BT, 2>(w, st);
   return launch_group_of<BT, 1>(w, st);
 }
 

@@ -205,7 +205,7 @@ __device__ __forceinline__ float sum8(float v) {
   return v;
 }
 
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool KT = false, int NSEG = 1>
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool KT = false, bool SEG = false>
 struct GemmTile {
   static constexpr int NW = WGM * WGN, NT = 64 * NW;
   static constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
@@ -215,18 +215,19 @@ struct GemmTile {
   static constexpr int EPI_LD = WN + 4;  // fp32 staging row
   static constexpr size_t MAIN_BYTES = NS * (size_t)STAGE_ELEMS * sizeof(bf16);
   static constexpr int LOADS_PER_TILE = TA::NI + TB::NI;  // per wave
-  static constexpr size_t EPI_BYTES = (size_t)NSEG * NW * 32 * EPI_LD * sizeof(float);
+  static constexpr size_t EPI_BYTES = (size_t)NW * 32 * EPI_LD * sizeof(float);
   static constexpr size_t LDS_BYTES = MAIN_BYTES > EPI_BYTES ? MAIN_BYTES : EPI_BYTES;
   // waves per SIMD the registers must allow: two workgroups of eight waves where LDS has room for them
-  static constexpr int MIN_WAVES = NSEG == 1 && NW == 8 && LDS_BYTES <= 80 * 1024 ? 4 : NSEG;
+  static constexpr int MIN_WAVES = !SEG && NW == 8 && LDS_BYTES <= 80 * 1024 ? 4 : (SEG ? 2 : 1);
 };
 
 // CS: the variant that can also sum B over k (EPI_BSUM); KT: the variant for K segments that are no multiple of 64
-// when an operand is k-contiguous (see OperandTile); NSEG = 2: two K segments whose sums are added to C one after the
-// other (EPI_SEGACC), each in accumulators of its own
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false, int NSEG = 1>
+// when an operand is k-contiguous (see OperandTile); SEG: an accumulating product over several K segments, each one's
+// sum added to C on its own, in order (EPI_SEGACC): a second set of accumulators holds C and takes the sums of the
+// segments as they are complete, so C is read and written once whatever their number
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false, bool SEG = false>
 __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, int tiles_n, const int bid, const int z) {
-  typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, NSEG> CFG;
+  typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, SEG> CFG;
   typedef typename CFG::TA TA;
   typedef typename CFG::TB TB;
   constexpr int MI = CFG::MI, NI = CFG::NI;
@@ -267,9 +268,9 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
 
   const bf16 *Ab = (const bf16*)g.A + z * g.sA, *Bb = (const bf16*)g.B + z * g.sB;
   void* const Cb = g.C;
-  // (two segments: whole turns of the ring each; the k-tiles beyond a segment's end read nothing)
+  // (SEG: whole turns of the ring each; the k-tiles beyond a segment's end read nothing)
   const int seg_tiles = (g.kseg_len + BK - 1) / BK;
-  const int tiles_per_seg = NSEG == 1 ? seg_tiles : (seg_tiles + NS - 1) / NS * NS;
+  const int tiles_per_seg = !SEG ? seg_tiles : (seg_tiles + NS - 1) / NS * NS;
   const int nk = g.K / g.kseg_len * tiles_per_seg;
   const int k_rows = g.K > g.kseg_len ? g.kseg_len : g.k_valid;   // rows of one segment of a k-strided operand
   // bytes of one segment of each operand that may be read (beyond: zero)
@@ -351,9 +352,9 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   constexpr int C4 = CFG::WN / 4;             // float4 per staged row
   constexpr int NIT = 32 * C4 / 64;           // float4 per lane per 32-row block
   static_assert(64 % C4 == 0, "a lane stores the same columns of every row");
-  constexpr int HB = NSEG == 2 || MI > 2 ? (NIT > 4 ? 4 : NIT) : (NIT > 8 ? 8 : NIT);   // processed HB at a time
-  constexpr bool PRE = !CS && NSEG == 1 && MI * NIT <= 16;   // (the column-sum variant serves accumulating products only)
-  constexpr bool EARLY = CFG::NW == 4 && NSEG * MI * NIT <= 8;
+  constexpr int HB = MI > 2 ? (NIT > 4 ? 4 : NIT) : (NIT > 8 ? 8 : NIT);   // processed HB at a time
+  constexpr bool PRE = !CS && !SEG && MI * NIT <= 16;   // (the column-sum variant serves accumulating products only)
+  constexpr bool EARLY = CFG::NW == 4 && MI * NIT <= 8;
   const int epi = g.epi;
   const int lane_col = n0 + wn0 + lane % C4 * 4;   // the lane's four columns
   const bool interior = m0 + BM <= g.M && n0 + BN <= g.N;
@@ -365,7 +366,9 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   const bool has_aux = (epi & (EPI_ADD | EPI_MUL | EPI_ROWDOT)) != 0, has_acc = (epi & EPI_ACC32) != 0;
   auto with_mode = [&](auto&& f) __attribute__((always_inline)) {
     constexpr bool TT = AKS && BKS;   // the weight-gradient layout: the only one that accumulates
-    if constexpr (TT) {
+    if constexpr (SEG) {
+      // (C is in the second set of accumulators)
+    } else if constexpr (TT) {
       if (has_acc && !has_aux) return f(std::integral_constant<int, ACCF>{});
     } else {
       if (has_aux && !has_acc) {
@@ -410,15 +413,16 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
       for (int e = 0; e < 4; ++e) bias4[e] = (float)bv[e];
     }
   };
-  f32x16 accs[NSEG][MI][NI];
-#pragma unroll
-  for (int s = 0; s < NSEG; ++s)
+  f32x16 acc[MI][NI], tot[SEG ? MI : 1][SEG ? NI : 1];
+  auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NI; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) accs[s][i][j][v] = 0.f;
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  };
+  clear();
 
   // Software pipeline.  Global->LDS: a k-tile is requested NS-1 iterations before it is
   // used, as soon as every wave has left the ring slot it goes to.  LDS->registers: the
@@ -436,27 +440,25 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   // vmcnt(N): at most N of this wave's requests still in flight; requests complete in order,
   // so N = (NS - 2) * LOADS_PER_TILE means "tile kt has landed"
   constexpr int INFLIGHT = (NS - 2) * CFG::LOADS_PER_TILE;
-  static_assert(INFLIGHT < 64, "vmcnt is a 6-bit counter");
+  constexpr int C_LOADS = SEG ? MI * NI * 4 : 0;   // SEG: requests for C, in flight behind those for the tiles once
+  static_assert(INFLIGHT + C_LOADS < 64, "vmcnt is a 6-bit counter");
   // ... and lgkmcnt(0): this wave's LDS reads of the previous tile must have EXECUTED, not just
   // been issued, before the barrier lets other waves refill that slot (a request that reads
   // nothing delivers its zeros within a few clocks)
-  constexpr int WAIT_TILE = (INFLIGHT & 15) | ((INFLIGHT >> 4) << 14) | 0x0070;  // expcnt: no wait
+  constexpr auto wait_tile = [](int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; };  // expcnt: no wait
   float* const bsum_ptr = CS && z == 0 ? g.bsum : nullptr;
   const bool do_cs = CS && (g.epi & EPI_BSUM) && tm == 0 && wm0 == 0 && bsum_ptr != nullptr;
-  float bsum0[NI];   // (EARLY: what the column sums are added to)
-  auto load_bsum = [&]() {
+  float bsum0[NI];   // what the column sums are added to
 #pragma unroll
-    for (int j = 0; j < NI; ++j) {
-      const int col = n0 + wn0 + 32 * j + (lane & 31);
-      bsum0[j] = do_cs && lane < 32 && col < g.N ? bsum_ptr[col] : 0.f;
-    }
-  };
+  for (int j = 0; j < NI; ++j) {
+    const int col = n0 + wn0 + 32 * j + (lane & 31);
+    bsum0[j] = do_cs && lane < 32 && col < g.N ? bsum_ptr[col] : 0.f;
+  }
   if constexpr (EARLY) {
     with_mode([&](auto MODE) __attribute__((always_inline)) {
       if (interior) request_first(MODE, std::true_type{});
       else request_first(MODE, std::false_type{});
     });
-    if constexpr (CS) load_bsum();
   }
   static_for<NS - 1>([&](auto T) { issue_loads(T); });
   // The k-steps are rotated by one against the tiles: the MFMAs of a tile's LAST k-step are issued after the
@@ -478,11 +480,9 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   // and there by the waves that hold the tile's first rows: each lane adds up the B fragments it holds anyway, two
   // products with one per instruction (exact, fp32 sums), between the MFMAs.  One register per 32 columns: sums
   // taken with MFMAs against a fragment of ones needed sixteen, which two sets of accumulators leave no room for.
-  float csum[NSEG][NI];
+  float csum[NI];
 #pragma unroll
-  for (int s = 0; s < NSEG; ++s)
-#pragma unroll
-    for (int j = 0; j < NI; ++j) csum[s][j] = 0.f;
+  for (int j = 0; j < NI; ++j) csum[j] = 0.f;
   const bf16x2 one2 = {(bf16)1.0f, (bf16)1.0f};
   auto add_cols = [&](float& t, bf16x8 b) {
     t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(b, b, 0, 1), one2, t, false);
@@ -490,15 +490,14 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
     t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(b, b, 4, 5), one2, t, false);
     t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(b, b, 6, 7), one2, t, false);
   };
-  auto step = [&](const Frags& use, Frags& fill, auto S, auto SN, auto J, auto WCS, auto SEG) {
+  auto step = [&](const Frags& use, Frags& fill, auto S, auto SN, auto J, auto WCS) {
     constexpr int off = decltype(S)::value * CFG::STAGE_ELEMS * 2, offn = decltype(SN)::value * CFG::STAGE_ELEMS * 2;
     constexpr int j = decltype(J)::value;
     constexpr int e0 = j * EXTRA / KSTEPS, e1 = (j + 1) * EXTRA / KSTEPS, P = NFRAG + (e1 - e0);
     static_for<NM>([&](auto Q) {
       constexpr int q = decltype(Q)::value, mi = q / NI, ni = q % NI;
-      auto& acc = accs[decltype(SEG)::value];
       acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(use.b[ni], use.a[mi], acc[mi][ni], 0, 0, 0);
-      if constexpr (decltype(WCS)::value && mi == 0) add_cols(csum[decltype(SEG)::value][ni], use.b[ni]);
+      if constexpr (decltype(WCS)::value && mi == 0) add_cols(csum[ni], use.b[ni]);
       __builtin_amdgcn_sched_barrier(0);
       constexpr int p0 = q * P / NM, p1 = (q + 1) * P / NM;
       static_for<p1 - p0>([&](auto D) {
@@ -519,35 +518,90 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
       if constexpr (p1 > p0) __builtin_amdgcn_sched_barrier(0);
     });
   };
-  const int turns = NSEG == 1 ? (nk + NS - 1) / NS : tiles_per_seg / NS;   // per segment
-  auto seg_loop = [&](auto WCS, auto SEG) {
-    for (int t = 0; t < turns; ++t) {
-      static_for<NS>([&](auto S) {
-        typedef std::integral_constant<int, (decltype(S)::value + NS - 1) % NS> SN;
-        __builtin_amdgcn_sched_barrier(0);  // no LDS read of the previous tile may sink below the barrier
-        __builtin_amdgcn_s_waitcnt(WAIT_TILE);
-        __builtin_amdgcn_s_barrier();  // every wave's part of this tile is in LDS; the previous tile's slot is free
-        asm volatile("" ::: "memory");  // ... and no LDS read of this tile may be hoisted above it
-        static_for<KSTEPS / 2>([&](auto H) {
-          constexpr int kk = 2 * decltype(H)::value;
-          step(f1, f0, S, SN{}, std::integral_constant<int, kk>{}, WCS, SEG);      // MFMAs of k-step kk - 1 (the previous tile's last when kk == 0)
-          step(f0, f1, S, SN{}, std::integral_constant<int, kk + 1>{}, WCS, SEG);
-        });
+  const int turns = !SEG ? (nk + NS - 1) / NS : tiles_per_seg / NS;   // per segment
+  // one turn of the ring; EXTRA_IN: requests in flight besides those for tiles, issued right before it
+  auto turn = [&](auto WCS, auto EXTRA_IN) __attribute__((always_inline)) {
+    static_for<NS>([&](auto S) {
+      typedef std::integral_constant<int, (decltype(S)::value + NS - 1) % NS> SN;
+      constexpr int inflight = INFLIGHT + (decltype(S)::value < NS - 1 ? decltype(EXTRA_IN)::value : 0);
+      __builtin_amdgcn_sched_barrier(0);  // no LDS read of the previous tile may sink below the barrier
+      __builtin_amdgcn_s_waitcnt(wait_tile(inflight));
+      __builtin_amdgcn_s_barrier();  // every wave's part of this tile is in LDS; the previous tile's slot is free
+      asm volatile("" ::: "memory");  // ... and no LDS read of this tile may be hoisted above it
+      static_for<KSTEPS / 2>([&](auto H) {
+        constexpr int kk = 2 * decltype(H)::value;
+        step(f1, f0, S, SN{}, std::integral_constant<int, kk>{}, WCS);      // MFMAs of k-step kk - 1 (the previous tile's last when kk == 0)
+        step(f0, f1, S, SN{}, std::integral_constant<int, kk + 1>{}, WCS);
       });
-    }
-    // the last k-step of the last tile
+    });
+  };
+  // the last k-step of the last tile
+  auto last_step = [&](auto WCS) __attribute__((always_inline)) {
     static_for<NM>([&](auto Q) {
       constexpr int q = decltype(Q)::value, mi = q / NI, ni = q % NI;
-      auto& acc = accs[decltype(SEG)::value];
       acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1.b[ni], f1.a[mi], acc[mi][ni], 0, 0, 0);
-      if constexpr (decltype(WCS)::value && mi == 0) add_cols(csum[decltype(SEG)::value][ni], f1.b[ni]);
+      if constexpr (decltype(WCS)::value && mi == 0) add_cols(csum[ni], f1.b[ni]);
     });
-    if constexpr (decltype(SEG)::value + 1 < NSEG) {   // the next segment's first rotated step multiplies zeros again
+  };
+  constexpr std::integral_constant<int, 0> none{};
+  // SEG: C, straight into the accumulators' layout, requested before the last turn of the first segment.  A wave's
+  // requests complete in order, so the first tile requested after them waits for them too: NS - 1 tiles later.  Every
+  // lane issues every request (the waits count them): what lies outside the matrix reads some element inside it.
+  auto request_c = [&]() __attribute__((always_inline)) {
+    if constexpr (SEG) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const float* row = (const float*)Cb + zc + (long)min(m0 + wm0 + 32 * i + (lane & 31), g.M - 1) * g.ldc;
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 c = *(const f32x4*)(row + min(n0 + wn0 + 32 * j + 8 * q + 4 * (lane >> 5), g.N - 4));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tot[i][j][4 * q + e] = c[e];
+          }
+      }
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // a segment's sums are complete: add them up, start the next one (its first rotated step multiplies zeros again)
+  auto end_segment = [&](auto WCS) __attribute__((always_inline)) {
+    last_step(WCS);
+    if constexpr (SEG) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) tot[i][j] += acc[i][j];
+      clear();
       static_for<MI>([&](auto I) { f1.a[decltype(I)::value] = bf16x8{}; });
       static_for<NI>([&](auto J) { f1.b[decltype(J)::value] = bf16x8{}; });
     }
+    if constexpr (decltype(WCS)::value) {
+      // the two half waves hold the sums over different k
+#pragma unroll
+      for (int j = 0; j < NI; ++j) {
+        bsum0[j] += csum[j] + __shfl_xor(csum[j], 32, 64);
+        csum[j] = 0.f;
+      }
+    }
   };
-  auto main_loop = [&](auto WCS) { static_for<NSEG>([&](auto SEG) { seg_loop(WCS, SEG); }); };
+  auto main_loop = [&](auto WCS) __attribute__((always_inline)) {
+    if constexpr (SEG) {
+      for (int t = 1; t < turns; ++t) turn(WCS, none);
+      request_c();
+      turn(WCS, std::integral_constant<int, C_LOADS>{});
+      end_segment(WCS);
+      for (int s = g.K / g.kseg_len; s > 1; --s) {
+        for (int t = 0; t < turns; ++t) turn(WCS, none);
+        end_segment(WCS);
+      }
+    } else {
+      for (int t = 0; t < turns; ++t) turn(WCS, none);
+      end_segment(WCS);
+    }
+  };
   // (two copies of the loop under one uniform branch, none inside it)
   if constexpr (CS) {
     if (do_cs) main_loop(std::true_type{});
@@ -556,21 +610,11 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
     main_loop(std::false_type{});
   }
   if constexpr (CS) {
-    // the two half waves hold the sums over different k (one workgroup per column range adds to bsum: no atomic)
-    if (do_cs) {
-      if constexpr (!EARLY) load_bsum();
+    if (do_cs) {   // (one workgroup per column range adds to bsum: no atomic)
 #pragma unroll
       for (int j = 0; j < NI; ++j) {
         const int col = n0 + wn0 + 32 * j + (lane & 31);
-        float t[NSEG];
-#pragma unroll
-        for (int s = 0; s < NSEG; ++s) t[s] = csum[s][j] + __shfl_xor(csum[s][j], 32, 64);
-        if (lane < 32 && col < g.N) {
-          float o = bsum0[j];
-#pragma unroll
-          for (int s = 0; s < NSEG; ++s) o += t[s];
-          bsum_ptr[col] = o;
-        }
+        if (lane < 32 && col < g.N) bsum_ptr[col] = bsum0[j];
       }
     }
   }
@@ -580,7 +624,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   // acc[i][j][v]: row = wm0 + 32 i + (lane & 31), col = wn0 + 32 j + 8 (v>>2) + 4 (lane>>5) + (v&3)
   // All LDS reads of a half block are issued before the first use,
   // so their latencies overlap instead of adding up.
-  float* stg = (float*)smem + wave * NSEG * 32 * CFG::EPI_LD;
+  float* stg = (float*)smem + wave * 32 * CFG::EPI_LD;
   // one 32-row block; the block index is a compile-time constant so that the
   // accumulators are always addressed statically (they must stay in registers)
   auto store_block = [&](auto I, auto FULLC, auto MODE) __attribute__((always_inline)) {
@@ -596,8 +640,8 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
           *(float4*)(stg + (lane & 31) * CFG::EPI_LD + j * 32 + 8 * q + 4 * (lane >> 5)) = v4;
         }
     };
-    stage(accs[0], stg);
-    if constexpr (NSEG == 2) stage(accs[1], stg + 32 * CFG::EPI_LD);
+    if constexpr (SEG) stage(tot, stg);
+    else stage(acc, stg);
     // the staging tile is private to the wave and a wave's LDS instructions execute in
     // order: no workgroup barrier is needed (one would also wait for the stores below)
     __builtin_amdgcn_wave_barrier();
@@ -612,11 +656,6 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
         const int r = ((hb + u) * 64 + lane) / C4;
         ok[u] = FULL || (row_of(i, hb + u) < g.M && lane_col < g.N);
         t[u] = *(const float4*)(stg + r * CFG::EPI_LD + lane % C4 * 4);
-      }
-      float4 t1[NSEG == 2 ? HB : 1];   // the second segment's sums
-      if constexpr (NSEG == 2) {
-#pragma unroll
-        for (int u = 0; u < HB; ++u) t1[u] = *(const float4*)(stg + (32 + ((hb + u) * 64 + lane) / C4) * CFG::EPI_LD + lane % C4 * 4);
       }
       if (epi & EPI_BIAS) {
 #pragma unroll
@@ -667,7 +706,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
           }
         }
       }
-      if (epi & EPI_OUT32) {
+      if (SEG || (epi & EPI_OUT32)) {   // (SEG: C is in the sum already)
 #pragma unroll
         for (int u = 0; u < HB; ++u)
           if (ok[u]) *(float4*)at(Cb, g.ldc, c_off4, i, hb + u, 4) = t[u];
@@ -681,7 +720,6 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
 #pragma unroll
         for (int u = 0; u < HB; ++u) {
           cv[u].x += t[u].x; cv[u].y += t[u].y; cv[u].z += t[u].z; cv[u].w += t[u].w;
-          if constexpr (NSEG == 2) { cv[u].x += t1[u].x; cv[u].y += t1[u].y; cv[u].z += t1[u].z; cv[u].w += t1[u].w; }
           if (ok[u]) *(float4*)at(Cb, g.ldc, c_off4, i, hb + u, 4) = cv[u];
         }
       } else if (epi & EPI_GELU) {
@@ -730,15 +768,15 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   static_assert(MI <= 4, "at most four 32-row blocks per wave");
 }
 
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false, int NSEG = 1>
-__global__ __launch_bounds__(64 * WGM * WGN, (GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, NSEG>::MIN_WAVES)) void gemm_mfma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-  gemm_mfma_tile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT, NSEG>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.z);
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false, bool SEG = false>
+__global__ __launch_bounds__(64 * WGM * WGN, (GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, SEG>::MIN_WAVES)) void gemm_mfma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  gemm_mfma_tile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT, SEG>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.z);
 }
 
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS = false, bool KT = false, int NSEG = 1>
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS = false, bool KT = false, bool SEG = false>
 static hipError_t launch_mfma(const GemmArgs& g, hipStream_t st) {
-  typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, NSEG> CFG;
-  auto kern = gemm_mfma_kernel<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT, NSEG>;
+  typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, SEG> CFG;
+  auto kern = gemm_mfma_kernel<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT, SEG>;
   // once per instantiation, whichever host thread comes first (initialisation of a function-local static is
   // thread-safe)
   static const hipError_t attr_rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,

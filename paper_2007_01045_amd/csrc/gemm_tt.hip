@@ -9,14 +9,14 @@ hipError_t launch_mfma_tt(int tile, bool short_k, const GemmArgs& g, hipStream_t
   if (g.epi & EPI_SEGACC) {
     switch (tile) {
       case 5:
-        return bsum ? launch_mfma<128, 128, 2, 4, 4, true, true, 32, true, false, 2>(g, st)
-                    : launch_mfma<128, 128, 2, 4, 4, true, true, 32, false, false, 2>(g, st);
+        return bsum ? launch_mfma<128, 128, 2, 4, 4, true, true, 32, true, false, true>(g, st)
+                    : launch_mfma<128, 128, 2, 4, 4, true, true, 32, false, false, true>(g, st);
       case 4:
-        return bsum ? launch_mfma<128, 64, 2, 2, 3, true, true, 64, true, false, 2>(g, st)
-                    : launch_mfma<128, 64, 2, 2, 3, true, true, 64, false, false, 2>(g, st);
+        return bsum ? launch_mfma<128, 64, 2, 2, 3, true, true, 64, true, false, true>(g, st)
+                    : launch_mfma<128, 64, 2, 2, 3, true, true, 64, false, false, true>(g, st);
       default:
-        return bsum ? launch_mfma<64, 64, 2, 2, 4, true, true, 64, true, false, 2>(g, st)
-                    : launch_mfma<64, 64, 2, 2, 4, true, true, 64, false, false, 2>(g, st);
+        return bsum ? launch_mfma<64, 64, 2, 2, 4, true, true, 64, true, false, true>(g, st)
+                    : launch_mfma<64, 64, 2, 2, 4, true, true, 64, false, false, true>(g, st);
     }
   }
   switch (tile) {

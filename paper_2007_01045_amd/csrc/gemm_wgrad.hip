@@ -13,8 +13,8 @@ struct TileTable {
   int first[WgradGroup::MAX + 1];   // first workgroup of each problem
 };
 
-template <int BM, int BN, int WGM, int WGN, int NS, int BK, int NSEG>
-__global__ __launch_bounds__(64 * WGM * WGN, NSEG) void wgrad_group_kernel(WgradGroup w, TileTable t) {
+template <int BM, int BN, int WGM, int WGN, int NS, int BK, bool SEG>
+__global__ __launch_bounds__(64 * WGM * WGN, SEG ? 2 : 1) void wgrad_group_kernel(WgradGroup w, TileTable t) {
   int i = 0;
 #pragma unroll
   for (int k = 1; k < WgradGroup::MAX; ++k) i += k < w.n && (int)blockIdx.x >= t.first[k];
@@ -32,14 +32,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, NSEG) void wgrad_group_kernel(Wgrad
   g.m_valid = g.M; g.n_valid = g.N; g.K = g.k_valid = w.K; g.kseg_len = w.kseg;
   g.segA = (long)w.kseg * g.lda; g.segB = (long)w.kseg * g.ldb;
   g.epi = EPI_ACC32 | (g.bsum ? EPI_BSUM : 0);
-  gemm_mfma_tile<BM, BN, WGM, WGN, NS, true, true, BK, true, false, NSEG>(g, (g.M + BM - 1) / BM, (g.N + BN - 1) / BN,
+  gemm_mfma_tile<BM, BN, WGM, WGN, NS, true, true, BK, true, false, SEG>(g, (g.M + BM - 1) / BM, (g.N + BN - 1) / BN,
                                                                           blockIdx.x - first, 0);
 }
 
-template <int BM, int BN, int WGM, int WGN, int NS, int BK, int NSEG>
+template <int BM, int BN, int WGM, int WGN, int NS, int BK, bool SEG>
 static hipError_t launch(const WgradGroup& w, hipStream_t st) {
-  typedef GemmTile<BM, BN, WGM, WGN, NS, true, true, BK, false, NSEG> CFG;
-  auto kern = wgrad_group_kernel<BM, BN, WGM, WGN, NS, BK, NSEG>;
+  typedef GemmTile<BM, BN, WGM, WGN, NS, true, true, BK, false, SEG> CFG;
+  auto kern = wgrad_group_kernel<BM, BN, WGM, WGN, NS, BK, SEG>;
   static const hipError_t attr_rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                         (int)CFG::LDS_BYTES);
   if (attr_rc != hipSuccess) return attr_rc;
@@ -56,14 +56,14 @@ hipError_t launch_wgrad_group_mfma(const WgradGroup& w, hipStream_t st) {
     t128 += (long)((w.p[i].M + 127) / 128) * ((w.p[i].N + 127) / 128);
     t12864 += (long)((w.p[i].M + 127) / 128) * ((w.p[i].N + 63) / 64);
   }
-  const bool two = w.K > w.kseg;
+  const bool seg = w.K > w.kseg;
   const int U = w.units > 0 ? w.units : 256;
   // enough 128x128 tiles for one and a half per unit: four waves, two workgroups per unit; for three quarters of the
   // units: eight waves; else smaller tiles
-  if (2 * t128 >= 3 * U) return two ? launch<128, 128, 2, 2, 4, 32, 2>(w, st) : launch<128, 128, 2, 2, 4, 32, 1>(w, st);
-  if (4 * t128 >= 3 * U) return two ? launch<128, 128, 2, 4, 4, 32, 2>(w, st) : launch<128, 128, 2, 4, 4, 32, 1>(w, st);
-  if (4 * t12864 >= 3 * U) return two ? launch<128, 64, 2, 2, 3, 64, 2>(w, st) : launch<128, 64, 2, 2, 3, 64, 1>(w, st);
-  return two ? launch<64, 64, 2, 2, 4, 64, 2>(w, st) : launch<64, 64, 2, 2, 4, 64, 1>(w, st);
+  if (2 * t128 >= 3 * U) return seg ? launch<128, 128, 2, 2, 4, 32, true>(w, st) : launch<128, 128, 2, 2, 4, 32, false>(w, st);
+  if (4 * t128 >= 3 * U) return seg ? launch<128, 128, 2, 4, 4, 32, true>(w, st) : launch<128, 128, 2, 4, 4, 32, false>(w, st);
+  if (4 * t12864 >= 3 * U) return seg ? launch<128, 64, 2, 2, 3, 64, true>(w, st) : launch<128, 64, 2, 2, 3, 64, false>(w, st);
+  return seg ? launch<64, 64, 2, 2, 4, 64, true>(w, st) : launch<64, 64, 2, 2, 4, 64, false>(w, st);
 }
 
 }  // namespace dapple

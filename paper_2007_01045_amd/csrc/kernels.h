@@ -30,7 +30,7 @@ enum GemmEpi {
   // backward's delta = rowsum(dctx o ctx) per head leaves the product that makes dctx this way.)
   EPI_ROWDOT = 256,
   // with EPI_ACC32, both operands k-strided: every K segment's sum is added to C (and with EPI_BSUM to bsum) on its
-  // own, in segment order -- the bits of one accumulating product per segment.  The MFMA kernel takes two segments.
+  // own, in segment order -- the bits of one accumulating product per segment.
   EPI_SEGACC = 512
 };
 
@@ -68,9 +68,9 @@ hipError_t launch_mfma_nt(int tile, bool short_k, const GemmArgs& g, hipStream_t
 hipError_t launch_mfma_tn(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
 hipError_t launch_mfma_tt(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
 // Several weight-gradient products over the same rows in one launch: for each problem C += sum over the micro-batches'
-// rows of A^T B, both operands [rows][...] with the rows of the micro-batches one behind the other; K = rows in all (one
-// or two micro-batches of kseg rows), each micro-batch's sum added to C -- and its column sums of B to bsum, if given --
-// on its own, in order (EPI_SEGACC).
+// rows of A^T B, both operands [rows][...] with the rows of the micro-batches one behind the other; K = rows in all,
+// kseg = rows of a micro-batch; each one's sum is added to C -- and its column sums of B to bsum, if given -- on its
+// own, in order (EPI_SEGACC).
 struct WgradProblem {
   const void *A, *B;
   float *C, *bsum;

@@ -378,27 +378,15 @@ struct dapple_stage {
   }
 
   // weight-gradient products over n micro-batches of T1 rows each (rows one micro-batch behind the other), on the side
-  // stream: every C gets the micro-batches' sums in order, two of them per launch
+  // stream: every C gets the micro-batches' sums in order
   int wgrad(int cls, WgradGroup w, int n, int T1) {
-    const WgradGroup w0 = w;
-    w.units = units;
-    for (int i = 0; i < n; i += 2) {
-      const int c = n - i < 2 ? n - i : 2;
-      w.K = c * T1; w.kseg = T1;
-      double flops = 0;
-      for (int k = 0; k < w.n; ++k) {
-        w.p[k].A = (const char*)w0.p[k].A + (size_t)i * T1 * w.p[k].lda * E();
-        w.p[k].B = (const char*)w0.p[k].B + (size_t)i * T1 * w.p[k].ldb * E();
-        flops += 2.0 * w.p[k].M * w.p[k].N * (double)w.K;
-      }
-      if (dry || wgrad_group_takes(dt, w)) {
-        TRY(run_on(side, cls, flops, [&](hipStream_t s) { return launch_wgrad_group(dt, w, s); }));
-      } else {
-        for (int k = 0; k < w.n; ++k) {
-          const GemmArgs g = wgrad_args(w, k);
-          TRY(run_on(side, cls, 2.0 * g.M * g.N * (double)g.K, [&](hipStream_t s) { return launch_gemm(dt, g, s); }, &g));
-        }
-      }
+    w.units = units; w.K = n * T1; w.kseg = T1;
+    double flops = 0;
+    for (int k = 0; k < w.n; ++k) flops += 2.0 * w.p[k].M * w.p[k].N * (double)w.K;
+    if (dry || wgrad_group_takes(dt, w)) return run_on(side, cls, flops, [&](hipStream_t s) { return launch_wgrad_group(dt, w, s); });
+    for (int k = 0; k < w.n; ++k) {
+      const GemmArgs g = wgrad_args(w, k);
+      TRY(run_on(side, cls, 2.0 * g.M * g.N * (double)g.K, [&](hipStream_t s) { return launch_gemm(dt, g, s); }, &g));
     }
     return STAGE_OK;
   }

@@ -451,12 +451,23 @@ def test_groups_of_micro_batches_change_no_bit(kind, M, K, order):
     """Several micro-batches per set of launches (buffers one behind the other: what the built-in orders make of
     them) against the same list task by task, separate buffers: group sizes that divide K, a short last group, token
     counts that are no multiple of 8 or of a k-tile, every stage kind."""
-    import torch
     s, b = (37, 3) if kind == "odd" else (60, 2)
     cfg = I.StageConfig(2, 128, 2, 256, s, b, M, K, "f32" if kind == "f32" else "bf16", has_embedding=kind == "first",
                         has_mlm_head=kind == "last", vocab=200, max_pos=64)
+    groups_against_tasks(cfg, M, K, B.ORDER_GPIPE if order == "gpipe" else B.ORDER_EARLY_BACKWARD)
+
+
+@pytest.mark.parametrize("H,dtype", [(384, "bf16"), (512, "bf16"), (1024, "bf16"), (1024, "f32")])
+def test_weight_gradients_over_three_micro_batches(H, dtype):
+    """The weight gradients of a group in one launch, at the widths that take each of its tile shapes: every
+    micro-batch's sum goes to the accumulator on its own, 39 rows each (no multiple of a k-tile)."""
+    groups_against_tasks(I.StageConfig(1, H, H // 64, 4 * H, 39, 1, 3, 3, dtype), 3, 3, B.ORDER_GPIPE)
+
+
+def groups_against_tasks(cfg, M, K, ordr):
+    import torch
+    kind = cfg.dtype
     theta, mbs = make_inputs(cfg, SEED, M)
-    ordr = B.ORDER_GPIPE if order == "gpipe" else B.ORDER_EARLY_BACKWARD
     ops = B.stage_schedule_ops(M, K, ordr)
     ref = run_gpu(cfg, theta, mbs, M, K, B.ORDER_EXPLICIT, max_slots=K, explicit_ops=ops)
     T, H = cfg.tokens, cfg.hidden
