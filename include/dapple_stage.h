@@ -114,8 +114,9 @@ typedef struct {
   uint64_t slot_bytes;      /* activations one resident micro-batch keeps from F to B */
   uint64_t workspace_bytes; /* transient buffers of one micro-batch's task */
   uint64_t arena_bytes;     /* grad_bytes + max_slots * slot_bytes + copies * group * workspace_bytes (+ alignment, +
-                               the forward tasks' activation buffer under STAGE_FLAG_RECOMPUTE); copies = 2 (one
-                               workspace per backward lane), 1 under STAGE_FLAG_ONE_STREAM; group = the micro-batches
+                               the forward tasks' activation buffer under STAGE_FLAG_RECOMPUTE); copies = 2 under
+                               STAGE_FLAG_RECOMPUTE (one workspace per backward lane), else, and under
+                               STAGE_FLAG_ONE_STREAM, 1; group = the micro-batches
                                one set of launches may cover (up to 8192 token rows, at most 8; 1 under
                                STAGE_FLAG_RECOMPUTE and with one slot) */
 } stage_sizes;
@@ -190,7 +191,7 @@ int stage_run_schedule(stage_handle h, int M, int K, int order,
  * node (accumulators and buffers are cleared by kernels).  A new capture replaces the old one;
  * stage_destroy frees it.  Task and launch counters advance per replay as if run eagerly.
  * The captured iteration uses one backward lane (results are the same bits either way), and a
- * replay has measured no faster than the eager lanes: this pair is for callers that need the
+ * replay has measured no faster than the eager iteration: this pair is for callers that need the
  * iteration as one launchable object. */
 int stage_graph_capture(stage_handle h, int M, int K, int order,
                         const void* const* xs, const void* const* dys,

@@ -255,9 +255,9 @@ void build_layout(const stage_config& c, Layout& L) {
   L.arena_slots = L.grad_bytes;
   L.arena_fwd_act = L.arena_slots + (size_t)c.max_slots * L.slot_bytes;
   L.arena_ws = L.arena_fwd_act + (L.recompute ? align_up(L.act_bytes) : 0);
-  // two copies of the workspace: consecutive backward tasks run on two lanes and must not share
+  // under re-computation two copies of the workspace: consecutive backward tasks run on two lanes and must not share
   // temporaries (a stage without lanes has one backward lane and one copy)
-  L.ws_copies = (c.flags & STAGE_FLAG_ONE_STREAM) ? 1 : 2;
+  L.ws_copies = L.recompute && !(c.flags & STAGE_FLAG_ONE_STREAM) ? 2 : 1;
   L.arena_bytes = L.arena_ws + L.ws_copies * L.ws_stride;
 }
 
@@ -290,7 +290,7 @@ struct dapple_stage {
   hipStream_t cur = nullptr;   // where the task being enqueued puts its main-line kernels (st or fwd)
   std::vector<hipEvent_t> ev_f, ev_b;  // per slot: forward done (fwd lane), backward done (caller's stream)
   hipEvent_t ev_start = nullptr;
-  bool serial = false, no_side = false;
+  bool serial = false;
   int units = 0;               // compute units of the caller's stream when it is a partition (0 = all)
   std::vector<hipEvent_t> ev;  // per layer: 4 "inputs ready" events (main -> side) + 1 "layer done" (side -> main)
   std::vector<int> slot_of_mb;   // slot -> micro-batch id, -1 = free
@@ -313,13 +313,17 @@ struct dapple_stage {
   template <typename Fn>
   int run(int cls, double flops, Fn&& fn) { return run_on(cur, cls, flops, fn); }
 
-  // Whether tasks over n micro-batches are too small for lanes: an event per hand-over costs the host 2-5 us and the
-  // streams' kernels a wait, and on a chip that a launch does not fill anyway the launches in a row are faster.  In
-  // matrix flops of a layer's forward: 256-wide stage, 0.8 GFLOP, 470 us with lanes, 330 without; 512-wide, 3 GFLOP,
-  // 722 / 700; 1024-wide, 3 GFLOP, 1133 / 1111, 13 GFLOP 1251 / 1288.  (fp32 products take eight times as long.)
-  bool small_tasks(int n) const {
+  // Whether the weight gradients of tasks over n micro-batches go to the side stream, by the matrix flops of a layer's
+  // forward.  Below 6 GFLOP an event per hand-over costs the host 2-5 us and the streams' kernels a wait, more than
+  // the overlap gives on launches of a few us: 256-wide stage, 0.8 GFLOP, 470 us with streams, 330 without; 1024-wide,
+  // 3 GFLOP, 1133 / 1111, 13 GFLOP 1219 / 1235.  (fp32 products take eight times as long.)  From 150 GFLOP on every
+  // bf16 product fills the chip, and two at a time only take the caches from each other: 1024-wide, 103 GFLOP, 25.2
+  // ms with the side stream, 25.7 without; 206 GFLOP 11.07 / 10.87; 2048-wide, 824 GFLOP, 20.7 / 18.9.
+  bool small_tasks(int n) const { return layer_flops(n) < (dt == DT_BF16 ? 6e9 : 7.5e8); }
+  bool full_tasks(int n) const { return dt == DT_BF16 && layer_flops(n) >= 1.5e11 * (units ? units : 256) / 256; }
+  double layer_flops(int n) const {
     const double T = (double)n * cfg.micro_batch * cfg.seq, H = cfg.hidden, F = cfg.ffn;
-    return 8.0 * T * H * H + 4.0 * T * H * F < (dt == DT_BF16 ? 6e9 : 7.5e8);
+    return 8.0 * T * H * H + 4.0 * T * H * F;
   }
   // main -> side: the side stream may start once the main stream has passed this point
   int fork(int layer, int which) {
@@ -865,8 +869,8 @@ int stage_init(stage_handle* out, const stage_config* cfg, const void* weights_d
   }
   if (!dry) {
     // default priority on purpose; the side stream never outlives the handle
-    h->serial = h->no_side = (cfg->flags & STAGE_FLAG_ONE_STREAM) != 0;
-    if (h->no_side) {
+    h->serial = (cfg->flags & STAGE_FLAG_ONE_STREAM) != 0;
+    if (h->serial) {
       h->side = h->st;
     } else {
       hipError_t e = make_lane(h->st, &h->side);
@@ -998,7 +1002,7 @@ int stage_bwd(stage_handle h, int mb, const void* dy_dev, void* dx_dev) {
   int s = mb < 0 ? -1 : find_slot(h, mb);
   if (s < 0) return fail(STAGE_E_NOT_RESIDENT, "micro-batch %d has no live forward", mb);
   hipStream_t side = h->side;
-  if (h->small_tasks(1)) h->side = h->cur;
+  if (h->small_tasks(1) || h->full_tasks(1)) h->side = h->cur;
   const int rc = bwd_group(h, 1, s, &dy_dev, &dx_dev);
   h->side = side;
   return rc;
@@ -1076,19 +1080,21 @@ int stage_run_schedule(stage_handle h, int M, int K, int order, const void* cons
   } else {
     for (int32_t op : ops) groups.push_back(Group{op > 0 ? 0 : 1, (op > 0 ? op : -op) - 1, 1});
   }
-  // Two lanes: forward tasks go to the library's forward stream, backward tasks stay on the
-  // caller's stream, so that a forward runs beside the backwards that do not hold its slots.
+  // One lane for the tasks (the caller's stream), and the side stream where small_tasks and full_tasks leave it.  Under
+  // STAGE_FLAG_RECOMPUTE, whose tasks are one micro-batch each and seldom fill the chip, more: forward tasks go to the
+  // library's forward stream, so that a forward runs beside the backwards that do not hold its slot (2048 rows of 1024:
+  // 11.1 ms on one stream, 9.5 so; without re-computation groups fill the chip better than lanes, 11.07 ms / 11.15).
   // Dependences kept: F_m -> B_m; B_m -> the forward that reuses its slot; forwards among
   // themselves and backwards among themselves in list order (which fixes the order of every
   // gradient accumulation).  The early-backward order needs no more than that; the other orders
   // are run strictly as listed (a backward waits for every forward listed before it).
-  const bool small = h->small_tasks(G);   // everything on the caller's stream
-  const bool lanes = !h->dry && !h->profiling && !h->serial && !small;
+  const bool alone = h->small_tasks(G) || h->full_tasks(G);   // no side stream
+  const bool lanes = h->L.recompute && !h->dry && !h->profiling && !h->serial && !h->small_tasks(G);
   const bool strict = order != STAGE_ORDER_EARLY_BACKWARD;
   std::vector<char> b_pending(h->cfg.max_slots, 0);   // per first slot of a group
   int last_f_slot = -1;
   auto hip_ok = [](hipError_t e) { return e == hipSuccess ? STAGE_OK : fail(STAGE_E_DEVICE, "%s", hipGetErrorString(e)); };
-  // Early-backward and GPipe order, plain stages: consecutive backward groups alternate between the caller's
+  // There, in the early-backward and GPipe orders, consecutive backward tasks also alternate between the caller's
   // stream and a second backward stream (each with its own copy of the workspace), so the head of
   // the next overlaps the tail of the one before.  Their accumulator updates still happen in list order: all of
   // them are issued, in host order, on the one side stream (the embedding block's and the head's too).
@@ -1096,17 +1102,16 @@ int stage_run_schedule(stage_handle h, int M, int K, int order, const void* cons
   // without end in hipStreamEndCapture once two streams other than the capture's origin have waited for each
   // other's events (side lane <-> second backward lane); the origin may wait for and be waited for by anyone.
   // (An explicit list keeps one backward lane.)
-  const bool two = lanes && order != STAGE_ORDER_EXPLICIT && h->L.ws_copies == 2 &&
-                   !h->no_side && !h->capturing;
+  const bool two = lanes && !alone && order != STAGE_ORDER_EXPLICIT && h->L.ws_copies == 2 && !h->capturing;
   int n_bwd = 0;
   bool used_b2 = false;
   if (lanes) TRY(ensure_lanes(h));
-  hipStream_t side = h->side;
-  if (small) h->side = h->st;
-  if (lanes) {   // (nothing is small here: no early return leaves the side stream replaced)
+  if (lanes) {
     TRY(hip_ok(hipEventRecord(h->ev_start, h->st)));
     TRY(hip_ok(hipStreamWaitEvent(h->fwd, h->ev_start, 0)));
   }
+  hipStream_t side = h->side;
+  if (alone) h->side = h->st;
   int rc = STAGE_OK;
   const std::vector<void*> none(h->dry ? M : 0, nullptr);   // a dry run has no pointers
   auto at = [&](auto p, int m) { return h->dry ? (decltype(p))none.data() : (p ? p + m : p); };
@@ -1183,7 +1188,7 @@ int stage_graph_capture(stage_handle h, int M, int K, int order, const void* con
   if (h->live != 0) return fail(STAGE_E_BAD_ORDER, "%d micro-batches are still resident", h->live);
   if (h->graph_exec) { (void)hipGraphExecDestroy(h->graph_exec); h->graph_exec = nullptr; }
   if (h->graph) { (void)hipGraphDestroy(h->graph); h->graph = nullptr; }
-  if (!h->serial) TRY(ensure_lanes(h));   // no stream is created inside a capture
+  if (h->L.recompute && !h->serial) TRY(ensure_lanes(h));   // no stream is created inside a capture
   const uint64_t f0 = h->fwd_tasks, b0 = h->bwd_tasks, l0 = h->launches;
   if (hipStreamBeginCapture(h->st, hipStreamCaptureModeThreadLocal) != hipSuccess)
     return fail(STAGE_E_DEVICE, "hipStreamBeginCapture failed");
