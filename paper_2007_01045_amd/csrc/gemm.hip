@@ -81,6 +81,9 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
   if ((g.epi & EPI_ROWDOT) && (g.kseg_len % BK || (g.epi & (EPI_ADD | EPI_MUL | EPI_GELU | EPI_ACC32 | EPI_OUT32)) || g.batch != 1 ||
                                !g.rowdot || !g.aux || !aligned_to(g.rowdot, 4)))
     return false;
+  if ((g.epi & EPI_AUXLN) && ((g.epi & (EPI_ADD | EPI_AUX32 | EPI_MUL | EPI_ACC32)) != (EPI_ADD | EPI_AUX32) || g.batch != 1 ||
+                              !aligned_to(g.ln_gamma, 8) || !aligned_to(g.ln_beta, 8)))
+    return false;
   if ((g.epi & EPI_BIAS) && !aligned_to(g.bias, 8)) return false;
   if ((g.epi & EPI_GELU) && !aligned_to(g.C2, 8)) return false;
   if ((g.epi & EPI_BSUM) && !(g.a_kstrided && g.b_kstrided)) return false;

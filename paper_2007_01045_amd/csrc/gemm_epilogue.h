@@ -11,6 +11,8 @@ __device__ __forceinline__ void epilogue_store(const GemmArgs& g, long zc, long 
   if (g.epi & (EPI_ADD | EPI_MUL)) {
     long ao = zc + (long)row * g.ldaux + col;
     float x = (g.epi & EPI_AUX32) ? ((const float*)g.aux)[ao] : to_f32(((const T*)g.aux)[ao]);
+    if (g.epi & EPI_AUXLN)
+      x = (x - g.ln_stats[2 * row]) * g.ln_stats[2 * row + 1] * to_f32(((const T*)g.ln_gamma)[col]) + to_f32(((const T*)g.ln_beta)[col]);
     t = (g.epi & EPI_ADD) ? t + x : t * x;
   }
   long o = zc + (long)row * g.ldc + col;

@@ -332,7 +332,7 @@ bool gemm_f32_takes(const GemmArgs& g) {
   if (g.K < 1 || g.kseg_len < 1 || g.K % g.kseg_len || g.N % 4 || g.lda % 4 || g.ldb % 4 || g.ldc % 4) return false;
   if (g.kseg_len % 4 && !(g.a_kstrided && g.b_kstrided)) return false;
   if (g.sA % 4 || g.sB % 4 || g.sC % 4 || g.sBias % 4 || g.segA % 4 || g.segB % 4) return false;
-  if (!al16(g.A) || !al16(g.B) || !al16(g.C) || (g.epi & EPI_ROWDOT)) return false;
+  if (!al16(g.A) || !al16(g.B) || !al16(g.C) || (g.epi & (EPI_ROWDOT | EPI_AUXLN))) return false;
   // a k-strided operand is read four rows' entries at a time: what lies past the last row must be the padding of its
   // leading dimension, and must not reach a stored element
   if (g.a_kstrided && g.m_valid % 4 && (g.m_valid != g.M || (g.m_valid + 3) / 4 * 4 > g.lda)) return false;

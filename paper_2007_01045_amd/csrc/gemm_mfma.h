@@ -265,6 +265,13 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
     }
   }
   const int m0 = tm * BM, n0 = tn * BN;
+  // (the small tiles: every argument the prologue and the first requests need in one go of scalar loads, not a round trip
+  // per branch that uses some)
+  constexpr bool EARLY = CFG::NW == 4 && MI * (CFG::WN / 8) <= 8;
+  if constexpr (EARLY)
+    asm volatile("" ::"s"(g.A), "s"(g.B), "s"(g.C), "s"(g.bias), "s"(g.aux), "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.lda), "s"(g.ldb),
+                 "s"(g.ldc), "s"(g.ldaux), "s"(g.kseg_len), "s"(g.segA), "s"(g.segB), "s"(g.ln_stats), "s"(g.ln_gamma),
+                 "s"(g.ln_beta), "s"(g.k_valid), "s"(g.m_valid), "s"(g.n_valid), "s"(g.epi));
 
   const bf16 *Ab = (const bf16*)g.A + z * g.sA, *Bb = (const bf16*)g.B + z * g.sB;
   void* const Cb = g.C;
@@ -354,15 +361,15 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   static_assert(64 % C4 == 0, "a lane stores the same columns of every row");
   constexpr int HB = MI > 2 ? (NIT > 4 ? 4 : NIT) : (NIT > 8 ? 8 : NIT);   // processed HB at a time
   constexpr bool PRE = !CS && !SEG && MI * NIT <= 16;   // (the column-sum variant serves accumulating products only)
-  constexpr bool EARLY = CFG::NW == 4 && MI * NIT <= 8;
   const int epi = g.epi;
   const int lane_col = n0 + wn0 + lane % C4 * 4;   // the lane's four columns
   const bool interior = m0 + BM <= g.M && n0 + BN <= g.N;
   // What a product's epilogue reads, as a constant: flags tested per request have the loads wait for each other where
   // the branches meet (gate of 8192 x 4096 x 1024: 108 us, 89 with the whole operand requested in one go).
-  //   AUXH: a bf16 second operand, all of it ahead; AUXF: an fp32 one; ACCF: the fp32 C of an accumulating product;
+  //   AUXH: a bf16 second operand, all of it ahead; AUXF: an fp32 one; AUXL: one whose LayerNorm is added (EPI_AUXLN);
+  //   ACCF: the fp32 C of an accumulating product;
   //   ANY: nothing ahead (no operand, or a combination that no product of the stage has, read in place)
-  enum { AUXH, AUXF, ACCF, ANY };
+  enum { AUXH, AUXF, AUXL, ACCF, ANY };
   const bool has_aux = (epi & (EPI_ADD | EPI_MUL | EPI_ROWDOT)) != 0, has_acc = (epi & EPI_ACC32) != 0;
   auto with_mode = [&](auto&& f) __attribute__((always_inline)) {
     constexpr bool TT = AKS && BKS;   // the weight-gradient layout: the only one that accumulates
@@ -372,6 +379,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
       if (has_acc && !has_aux) return f(std::integral_constant<int, ACCF>{});
     } else {
       if (has_aux && !has_acc) {
+        if (epi & EPI_AUXLN) return f(std::integral_constant<int, AUXL>{});
         if (epi & EPI_AUX32) return f(std::integral_constant<int, AUXF>{});
         if (!(epi & EPI_ROWDOT)) return f(std::integral_constant<int, AUXH>{});
       }
@@ -383,6 +391,10 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   constexpr int UNITS = MI * (NIT / HB);
   f32x4 pre[PRE ? UNITS : 2][HB];    // fp32 operands: whole (PRE), or the unit in use and the one after
   f32x2 preh[UNITS][HB];             // a bf16 operand
+  // AUXL: mean and rstd of the wave's row 64 i + lane; in the small tiles, of each piece's row (no exchange at the end)
+  f32x2 rstat[EARLY ? UNITS * HB : (MI + 1) / 2];
+  f32x2 lng{}, lnb{};                // ... gamma and beta of the lane's columns, four bf16 each (converted where they
+                                     // are used: a conversion here would wait for the load)
   // Addresses: a lane's piece n of block i is row m0 + wm0 + 32 i + n RS + lane / C4.  All but the last term is the same
   // for the whole wave and stays in scalar registers; a lane keeps one 32-bit offset per matrix (64-bit addresses per
   // piece had the 256x256 tile's accumulators spill).
@@ -400,18 +412,28 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
       constexpr int u = decltype(U)::value, n = hb + u, slot = PRE ? k : (k & 1);
       const bool in = decltype(FULLC)::value || (row_of(i, n) < g.M && lane_col < g.N);
       if constexpr (mode == AUXH) preh[k][u] = in ? *(const f32x2*)at(g.aux, g.ldaux, a_off4 >> 1, i, n, 2) : f32x2{0.f, 0.f};
-      if constexpr (mode == AUXF) pre[slot][u] = in ? *(const f32x4*)at(g.aux, g.ldaux, a_off4, i, n, 4) : f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (mode == AUXF || mode == AUXL) pre[slot][u] = in ? *(const f32x4*)at(g.aux, g.ldaux, a_off4, i, n, 4) : f32x4{0.f, 0.f, 0.f, 0.f};
       if constexpr (mode == ACCF) pre[slot][u] = in ? *(const f32x4*)at(Cb, g.ldc, c_off4, i, n, 4) : f32x4{0.f, 0.f, 0.f, 0.f};
     });
   };
-  float bias4[4] = {0.f, 0.f, 0.f, 0.f};
+  f32x2 bias4{};
   auto request_first = [&](auto MODE, auto FULLC) __attribute__((always_inline)) {
     static_for<PRE || decltype(MODE)::value == AUXH ? UNITS : 1>([&](auto K) __attribute__((always_inline)) { request(K, MODE, FULLC); });
-    if ((epi & EPI_BIAS) && lane_col < g.N) {
-      const bf16x4 bv = *(const bf16x4*)((const bf16*)g.bias + zbias + lane_col);
+    if constexpr (decltype(MODE)::value == AUXL) {
+      if constexpr (EARLY) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) bias4[e] = (float)bv[e];
+        for (int p = 0; p < UNITS * HB; ++p) rstat[p] = *(const f32x2*)(g.ln_stats + 2 * min(row_of(p / NIT, p % NIT), g.M - 1));
+      } else {
+#pragma unroll
+        for (int i = 0; i < (MI + 1) / 2; ++i)
+          rstat[i] = *(const f32x2*)(g.ln_stats + 2 * min(m0 + wm0 + 64 * i + (MI > 1 ? lane : lane & 31), g.M - 1));
+      }
+      if (lane_col < g.N) {
+        lng = *(const f32x2*)((const bf16*)g.ln_gamma + lane_col);
+        lnb = *(const f32x2*)((const bf16*)g.ln_beta + lane_col);
+      }
     }
+    if ((epi & EPI_BIAS) && lane_col < g.N) bias4 = *(const f32x2*)((const bf16*)g.bias + zbias + lane_col);
   };
   f32x16 acc[MI][NI], tot[SEG ? MI : 1][SEG ? NI : 1];
   auto clear = [&]() __attribute__((always_inline)) {
@@ -658,12 +680,13 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
         t[u] = *(const float4*)(stg + r * CFG::EPI_LD + lane % C4 * 4);
       }
       if (epi & EPI_BIAS) {
+        const bf16x4 bv = __builtin_bit_cast(bf16x4, bias4);
 #pragma unroll
         for (int u = 0; u < HB; ++u) {
-          t[u].x += bias4[0]; t[u].y += bias4[1]; t[u].z += bias4[2]; t[u].w += bias4[3];
+          t[u].x += (float)bv[0]; t[u].y += (float)bv[1]; t[u].z += (float)bv[2]; t[u].w += (float)bv[3];
         }
       }
-      if (mode == AUXH || mode == AUXF || (mode == ANY && has_aux)) {
+      if (mode == AUXH || mode == AUXF || mode == AUXL || (mode == ANY && has_aux)) {
         float4 xv[HB];
 #pragma unroll
         for (int u = 0; u < HB; ++u) {
@@ -672,6 +695,14 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
           bool half = mode == AUXH;
           if constexpr (mode == AUXH) h = preh[k][u];
           if constexpr (mode == AUXF) x = in[u];
+          if constexpr (mode == AUXL) {
+            const bf16x4 gv = __builtin_bit_cast(bf16x4, lng), bv = __builtin_bit_cast(bf16x4, lnb);
+            const int r = (i & 1) * 32 + (hb + u) * RS + lane / C4;
+            const f32x2 st = rstat[EARLY ? i * NIT + hb + u : i / 2];
+            const float mean = EARLY ? st[0] : __shfl(st[0], r, 64), rstd = EARLY ? st[1] : __shfl(st[1], r, 64);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = (in[u][e] - mean) * rstd * (float)gv[e] + (float)bv[e];
+          }
           if constexpr (mode == ANY) {
             half = !(epi & EPI_AUX32);
             if (half) h = ok[u] ? *(const f32x2*)at(g.aux, g.ldaux, a_off4 >> 1, i, hb + u, 2) : h;
@@ -684,7 +715,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
             xv[u] = make_float4(x[0], x[1], x[2], x[3]);
           }
         }
-        if (mode != AUXH && (epi & EPI_ROWDOT)) {
+        if (mode != AUXH && mode != AUXL && (epi & EPI_ROWDOT)) {
           // a row's 32 columns of a block sit in 8 consecutive lanes (4 columns each): products of the
           // outputs as they are stored, summed over the lane's four, then over the eight lanes in a fixed tree
 #pragma unroll

@@ -31,7 +31,10 @@ enum GemmEpi {
   EPI_ROWDOT = 256,
   // with EPI_ACC32, both operands k-strided: every K segment's sum is added to C (and with EPI_BSUM to bsum) on its
   // own, in segment order -- the bits of one accumulating product per segment.
-  EPI_SEGACC = 512
+  EPI_SEGACC = 512,
+  // with EPI_ADD | EPI_AUX32: what is added is the LayerNorm of aux, (aux[m,n] - mean[m]) rstd[m] gamma[n] + beta[n] --
+  // the residual input of a bf16 stage, unrounded, from the sums it was normalised from.  Batch 1.
+  EPI_AUXLN = 1024
 };
 
 struct GemmArgs {
@@ -49,6 +52,8 @@ struct GemmArgs {
   int batch;
   long sA, sB, sC, sBias;
   float* bsum;    // EPI_BSUM: fp32 [N], of instance 0; both operands k-strided
+  const float* ln_stats;               // EPI_AUXLN: mean and rstd of every row, gamma and beta in the product's type
+  const void *ln_gamma, *ln_beta;
   float* rowdot;  // EPI_ROWDOT: fp32 [ceil(N/32)][M]
   int k_valid;  // k-strided operands: rows k >= k_valid read as zero (K itself is padded)
   int m_valid, n_valid;  // rows of A / B that exist in memory (0 = M / N); rows beyond read as zero
@@ -130,7 +135,7 @@ bool attn_takes_delta_blocks(Dtype dt, const AttnArgs& a);
 // ---------------------------------------------------------------- row kernels
 // y = LN(z) over the last dim (H), stats[2*r] = mean, stats[2*r+1] = rstd.  z_f32: z is fp32
 // although the stage is bf16 (the residual stream is kept unrounded); y32 (may be NULL): an
-// fp32 copy of y for the next residual add.
+// fp32 copy of y for the next residual add (after the embedding; elsewhere EPI_AUXLN takes it from z).
 hipError_t launch_ln_fwd(Dtype dt, const void* z, bool z_f32, const void* gamma, const void* beta, void* y,
                          float* y32, float* stats, int rows, int H, float eps, hipStream_t st);
 // dz = LN backward; partial[(blk*3 + {0,1,2})*H + c] = block partial sums of

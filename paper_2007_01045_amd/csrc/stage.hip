@@ -90,7 +90,7 @@ struct Layout {
   size_t we_dx0 = 0, we_de = 0, we_part = 0;
   // fp32 copies of LayerNorm outputs for the residual adds (bf16 stages); set 1: the forward re-run
   // inside a backward task (re-computation), which may overlap a forward task
-  size_t ws_y1f[2] = {0, 0}, ws_yf[2][2] = {{0, 0}, {0, 0}};
+  size_t ws_x0f[2] = {0, 0};
   size_t slot_bytes = 0;
   // re-computation: a resident micro-batch keeps only its input (and targets); the activations of
   // the task being run live in a buffer of act_bytes: one for forward tasks (arena_fwd_act) and one
@@ -219,11 +219,8 @@ void build_layout(const stage_config& c, Layout& L) {
   L.ws_dx[0] = wtake(U); L.ws_dx[1] = wtake(U); L.ws_dy1 = wtake(U); L.ws_dctx = wtake(U);
   // delta of the attention backward: [b, A, s], or one row sum per block of 32 columns, [ceil(H/32)][T]
   L.ws_delta = wtake(std::max((size_t)c.micro_batch * c.n_heads * c.seq, (size_t)((c.hidden + 31) / 32) * T) * 4);
-  if (c.dtype == STAGE_DTYPE_BF16) {
-    for (int fs = 0; fs < (L.recompute ? 2 : 1); ++fs) {
-      L.ws_y1f[fs] = wtake(T * H * 4); L.ws_yf[fs][0] = wtake(T * H * 4); L.ws_yf[fs][1] = wtake(T * H * 4);
-    }
-  }
+  if (c.dtype == STAGE_DTYPE_BF16 && c.has_embedding)
+    for (int fs = 0; fs < (L.recompute ? 2 : 1); ++fs) L.ws_x0f[fs] = wtake(T * H * 4);
   const size_t ln_part = ((T + 7) / 8) * 3 * H * 4;
   L.ws_side.resize(c.n_layers);
   for (auto& ss : L.ws_side) {
@@ -418,14 +415,25 @@ int dapple_stage::forward(const Act& sl, int fs, int n, const void* const* xs, v
   const int H = cfg.hidden, F = cfg.ffn, T1 = cfg.micro_batch * cfg.seq, T = n * T1;   // T1: rows of one micro-batch
   const size_t U1 = (size_t)T1 * H * E();
   const char* xin = sl(L.slot_x0);
-  // bf16 stages keep the residual stream unrounded: the pre-LayerNorm sums z1, z2 and the copy
-  // of each LayerNorm output that feeds the next residual add are fp32; only GEMM operands are bf16
+  // bf16 stages keep the residual stream unrounded: the pre-LayerNorm sums z1, z2 are fp32, and a residual add takes
+  // the LayerNorm output it needs from them (an fp32 copy of every LayerNorm output was 4 of the 10 bytes per element
+  // that a LayerNorm moved: 8192 x 1024 in 15.6 -> 11 us); only
+  // GEMM operands are bf16
   const bool mixed = dt == DT_BF16;
-  const void* resid = xin;            // residual input of the next attention block
-  bool resid_f32 = false;
+  // residual input of the next attention block: a tensor, or (stats set) the LayerNorm of one
+  struct Resid {
+    const void* x;
+    bool f32;
+    const float* stats;
+    const void *g, *b;
+  } resid{xin, false, nullptr, nullptr, nullptr};
+  auto add_resid = [](GemmArgs& ga, const Resid& r) {
+    ga.aux = r.x; ga.ln_stats = r.stats; ga.ln_gamma = r.g; ga.ln_beta = r.b;
+    ga.epi |= EPI_ADD | (r.f32 ? EPI_AUX32 : 0) | (r.stats ? EPI_AUXLN : 0);
+  };
   if (cfg.has_embedding) {
-    resid = mixed ? (const void*)ws(L.ws_yf[fs][1]) : (const void*)xin;
-    resid_f32 = mixed;
+    float* x0f = mixed ? (float*)ws(L.ws_x0f[fs]) : nullptr;
+    if (mixed) resid = Resid{x0f, true, nullptr, nullptr, nullptr};
     // x = LN(E_w[id] + E_p[pos]); the ids and the pre-LN sum are kept for the backward
     int32_t* ids = (int32_t*)sl(L.slot_ids);
     char* esum = sl(L.slot_embsum);
@@ -436,7 +444,7 @@ int dapple_stage::forward(const Act& sl, int fs, int n, const void* const* xs, v
       return launch_embed_gather(dt, ids, w(L.embEw), w(L.embEp), esum, T, cfg.seq, H, cfg.vocab, q);
     }));
     TRY(run(KC_LN_FWD, 0, [&](hipStream_t q) {
-      return launch_ln_fwd(dt, esum, false, w(L.embG), w(L.embB), sl(L.slot_x0), mixed ? (float*)ws(L.ws_yf[fs][1]) : nullptr,
+      return launch_ln_fwd(dt, esum, false, w(L.embG), w(L.embB), sl(L.slot_x0), x0f,
                            (float*)sl(L.slot_embst), T, H, cfg.ln_eps, q);
     }));
   } else {
@@ -468,13 +476,13 @@ int dapple_stage::forward(const Act& sl, int fs, int n, const void* const* xs, v
     {  // z1 = x + ctx Wo + bo
       GemmArgs ga{};
       ga.A = ctx; ga.lda = H; ga.B = w(p.Wo); ga.ldb = H; ga.b_kstrided = 1; ga.bias = w(p.bo);
-      ga.aux = resid; ga.ldaux = H; ga.C = z1; ga.ldc = H; ga.M = T; ga.N = H; ga.K = H;
-      ga.epi = EPI_BIAS | EPI_ADD | (mixed ? EPI_OUT32 : 0) | (resid_f32 ? EPI_AUX32 : 0);
+      ga.ldaux = H; ga.C = z1; ga.ldc = H; ga.M = T; ga.N = H; ga.K = H;
+      ga.epi = EPI_BIAS | (mixed ? EPI_OUT32 : 0);
+      add_resid(ga, resid);
       TRY(gemm(KC_GEMM_FWD, ga));
     }
-    float* y1f = mixed ? (float*)ws(L.ws_y1f[fs]) : nullptr;
     TRY(run(KC_LN_FWD, 0, [&](hipStream_t q) {
-      return launch_ln_fwd(dt, z1, mixed, w(p.ln1g), w(p.ln1b), y1, y1f, st1, T, H, cfg.ln_eps, q);
+      return launch_ln_fwd(dt, z1, mixed, w(p.ln1g), w(p.ln1b), y1, nullptr, st1, T, H, cfg.ln_eps, q);
     }));
     {  // g = GELU(y1 W1 + b1), gp = GELU'(y1 W1 + b1)
       GemmArgs ga{};
@@ -485,18 +493,16 @@ int dapple_stage::forward(const Act& sl, int fs, int n, const void* const* xs, v
     {  // z2 = y1 + g W2 + b2
       GemmArgs ga{};
       ga.A = g; ga.lda = F; ga.B = w(p.W2); ga.ldb = H; ga.b_kstrided = 1; ga.bias = w(p.b2);
-      ga.aux = mixed ? (const void*)y1f : (const void*)y1; ga.ldaux = H; ga.C = z2; ga.ldc = H; ga.M = T; ga.N = H;
-      ga.K = F; ga.epi = EPI_BIAS | EPI_ADD | (mixed ? EPI_OUT32 | EPI_AUX32 : 0);
+      ga.ldaux = H; ga.C = z2; ga.ldc = H; ga.M = T; ga.N = H; ga.K = F; ga.epi = EPI_BIAS | (mixed ? EPI_OUT32 : 0);
+      add_resid(ga, mixed ? Resid{z1, true, st1, w(p.ln1g), w(p.ln1b)} : Resid{y1, false, nullptr, nullptr, nullptr});
       TRY(gemm(KC_GEMM_FWD, ga));
     }
     if (keep_y) {
-      float* yf = (mixed && l + 1 < cfg.n_layers) ? (float*)ws(L.ws_yf[fs][l & 1]) : nullptr;
       TRY(run(KC_LN_FWD, 0, [&](hipStream_t q) {
-        return launch_ln_fwd(dt, z2, mixed, w(p.ln2g), w(p.ln2b), sl(a.y), yf, st2, T, H, cfg.ln_eps, q);
+        return launch_ln_fwd(dt, z2, mixed, w(p.ln2g), w(p.ln2b), sl(a.y), nullptr, st2, T, H, cfg.ln_eps, q);
       }));
       xin = sl(a.y);
-      resid = yf ? (const void*)yf : (const void*)xin;
-      resid_f32 = yf != nullptr;
+      resid = mixed ? Resid{z2, true, st2, w(p.ln2g), w(p.ln2b)} : Resid{xin, false, nullptr, nullptr, nullptr};
     } else {   // the last layer's output goes to the caller's buffers
       TRY(each_run(ys, n, U1, [&](int i, int c) {
         const size_t r = (size_t)i * T1;
