@@ -142,6 +142,7 @@ hipError_t launch_ln_fwd(Dtype dt, const void* z, bool z_f32, const void* gamma,
 // dy*xhat (dgamma), dy (dbeta), dz (bias of the linear that produced z).
 // Returns the number of partial blocks through *nblk.  nmb micro-batches of `rows` rows each lie one behind the
 // other; each has its own *nblk blocks.
+int ln_bwd_blocks(int rows);   // *nblk for that many rows
 hipError_t launch_ln_bwd(Dtype dt, const void* dy, const void* z, bool z_f32, const float* stats,
                          const void* gamma, void* dz, float* partial, int* nblk, int rows, int H, int nmb,
                          hipStream_t st);

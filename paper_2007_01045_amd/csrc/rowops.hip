@@ -113,12 +113,21 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const void* __restrict__ z,
 }
 
 // ------------------------------------------------------------------ LayerNorm backward
-// A block takes LNB_ROWS consecutive rows (each wave every 4th of them), keeps the
+// A block takes 4 RPW consecutive rows (each wave every 4th of them), keeps the
 // per-column partial sums of dy*xhat, dy and dz in registers, combines the four
 // waves in LDS in wave order and writes partial[(blk*3 + v)*H + col].
-constexpr int LNB_ROWS = 8;
+//
+// Bound by memory: 8 bytes per element of a bf16 stage, and the partial sums, 12 bytes per column and block, which are
+// written here and read again by the reduction: 3 more bytes per element with 8 rows to a block.  16 rows halve that
+// where a micro-batch still makes 64 blocks of them.  (The split depends on a micro-batch's rows alone, never on how
+// many of them share a launch.)
+static int ln_bwd_rpw(int rows) { return rows >= 1024 ? 4 : 2; }
+int ln_bwd_blocks(int rows) {
+  const int per = 4 * ln_bwd_rpw(rows);
+  return (rows + per - 1) / per;
+}
 
-template <typename T, int NCH, bool Z32>
+template <typename T, int NCH, bool Z32, int RPW>
 __global__ __launch_bounds__(256) void ln_bwd_kernel(const T* __restrict__ dy, const void* __restrict__ z,
                                                      const float* __restrict__ stats, const T* __restrict__ gamma,
                                                      T* __restrict__ dz, float* __restrict__ partial, int rows, int H) {
@@ -142,61 +151,65 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const T* __restrict__ dy, c
     if (col < H) load_vec<T>(gamma + col, g[c]);
   }
   // each wave takes rows wave, wave + 4, ...; the loads of all its rows are issued first
-  constexpr int RPW = LNB_ROWS / 4;
-  float d[RPW][NCH][V], zz[RPW][NCH][V], mean[RPW], rstd[RPW];
-  bool live[RPW];
+  // (of two of them where four would not fit the registers)
+  constexpr int RB = NCH > 2 ? 2 : RPW;
 #pragma unroll
-  for (int q = 0; q < RPW; ++q) {
-    int row = blockIdx.x * LNB_ROWS + wave + 4 * q;
-    live[q] = row < rows;
-    mean[q] = live[q] ? stats[2 * row] : 0.f;
-    rstd[q] = live[q] ? stats[2 * row + 1] : 0.f;
+  for (int q0 = 0; q0 < RPW; q0 += RB) {
+    float d[RB][NCH][V], zz[RB][NCH][V], mean[RB], rstd[RB];
+    bool live[RB];
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      int col = (c * 64 + lane) * V;
-      if (live[q] && col < H) {
-        load_vec<T>(dy + (long)row * H + col, d[q][c]);
-        load_z<T, Z32>(z, (long)row * H + col, zz[q][c]);
-      } else {
+    for (int q = 0; q < RB; ++q) {
+      int row = blockIdx.x * (4 * RPW) + wave + 4 * (q0 + q);
+      live[q] = row < rows;
+      mean[q] = live[q] ? stats[2 * row] : 0.f;
+      rstd[q] = live[q] ? stats[2 * row + 1] : 0.f;
 #pragma unroll
-        for (int e = 0; e < V; ++e) d[q][c][e] = zz[q][c][e] = 0.f;
-      }
-    }
-  }
+      for (int c = 0; c < NCH; ++c) {
+        int col = (c * 64 + lane) * V;
+        if (live[q] && col < H) {
+          load_vec<T>(dy + (long)row * H + col, d[q][c]);
+          load_z<T, Z32>(z, (long)row * H + col, zz[q][c]);
+        } else {
 #pragma unroll
-  for (int q = 0; q < RPW; ++q) {
-    if (!live[q]) continue;
-    int row = blockIdx.x * LNB_ROWS + wave + 4 * q;
-    float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      int col = (c * 64 + lane) * V;
-      if (col < H) {
-#pragma unroll
-        for (int e = 0; e < V; ++e) {
-          zz[q][c][e] = (zz[q][c][e] - mean[q]) * rstd[q];  // x-hat
-          float dxh = d[q][c][e] * g[c][e];
-          s1 += dxh;
-          s2 += dxh * zz[q][c][e];
+          for (int e = 0; e < V; ++e) d[q][c][e] = zz[q][c][e] = 0.f;
         }
       }
     }
-    float m1 = wave_sum(s1) / (float)H, m2 = wave_sum(s2) / (float)H;
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      int col = (c * 64 + lane) * V;
-      if (col < H) {
-        float o[V];
+    for (int q = 0; q < RB; ++q) {
+      if (!live[q]) continue;
+      int row = blockIdx.x * (4 * RPW) + wave + 4 * (q0 + q);
+      float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-        for (int e = 0; e < V; ++e) {
-          o[e] = rstd[q] * (d[q][c][e] * g[c][e] - m1 - zz[q][c][e] * m2);
-          pg[c][e] += d[q][c][e] * zz[q][c][e];
-          pb[c][e] += d[q][c][e];
+      for (int c = 0; c < NCH; ++c) {
+        int col = (c * 64 + lane) * V;
+        if (col < H) {
+#pragma unroll
+          for (int e = 0; e < V; ++e) {
+            zz[q][c][e] = (zz[q][c][e] - mean[q]) * rstd[q];  // x-hat
+            float dxh = d[q][c][e] * g[c][e];
+            s1 += dxh;
+            s2 += dxh * zz[q][c][e];
+          }
         }
-        store_vec<T>(dz + (long)row * H + col, o);
-        // the bias gradient of the producing linear sums dz as it is stored
+      }
+      float m1 = wave_sum(s1) / (float)H, m2 = wave_sum(s2) / (float)H;
 #pragma unroll
-        for (int e = 0; e < V; ++e) pz[c][e] += to_f32(from_f32<T>(o[e]));
+      for (int c = 0; c < NCH; ++c) {
+        int col = (c * 64 + lane) * V;
+        if (col < H) {
+          float o[V];
+#pragma unroll
+          for (int e = 0; e < V; ++e) {
+            o[e] = rstd[q] * (d[q][c][e] * g[c][e] - m1 - zz[q][c][e] * m2);
+            pg[c][e] += d[q][c][e] * zz[q][c][e];
+            pb[c][e] += d[q][c][e];
+          }
+          store_vec<T>(dz + (long)row * H + col, o);
+          // the bias gradient of the producing linear sums dz as it is stored
+#pragma unroll
+          for (int e = 0; e < V; ++e) pz[c][e] += to_f32(from_f32<T>(o[e]));
+        }
       }
     }
   }
@@ -394,19 +407,26 @@ hipError_t launch_ln_fwd(Dtype dt, const void* z, bool z_f32, const void* gamma,
                : ln_fwd_t<bf16, false>(z, gamma, beta, y, y32, stats, rows, H, eps, st);
 }
 
-template <typename T, int N, bool Z32>
-static hipError_t ln_bwd_launch(const void* dy, const void* z, const float* stats, const void* g, void* dz,
+template <typename T, int N, bool Z32, int RPW>
+static hipError_t ln_bwd_launch_of(const void* dy, const void* z, const float* stats, const void* g, void* dz,
                                 float* partial, int nb, int rows, int H, int nmb, hipStream_t st) {
   // up to 96 KiB of LDS for the widest rows; set once per instantiation by whichever host thread comes first
   // (initialisation of a function-local static is thread-safe)
-  static const hipError_t attr_rc = hipFuncSetAttribute((const void*)ln_bwd_kernel<T, N, Z32>,
+  static const hipError_t attr_rc = hipFuncSetAttribute((const void*)ln_bwd_kernel<T, N, Z32, RPW>,
                                                         hipFuncAttributeMaxDynamicSharedMemorySize,
                                                         12 * 64 * Vec<T>::N * N * 4);
   if (attr_rc != hipSuccess) return attr_rc;
   size_t sh = (size_t)12 * H * sizeof(float);
-  hipLaunchKernelGGL((ln_bwd_kernel<T, N, Z32>), dim3(nb, nmb), dim3(256), sh, st, (const T*)dy, z, stats, (const T*)g,
+  hipLaunchKernelGGL((ln_bwd_kernel<T, N, Z32, RPW>), dim3(nb, nmb), dim3(256), sh, st, (const T*)dy, z, stats, (const T*)g,
                      (T*)dz, partial, rows, H);
   return hipGetLastError();
+}
+
+template <typename T, int N, bool Z32>
+static hipError_t ln_bwd_launch(const void* dy, const void* z, const float* stats, const void* g, void* dz,
+                                float* partial, int nb, int rows, int H, int nmb, hipStream_t st) {
+  return ln_bwd_rpw(rows) == 4 ? ln_bwd_launch_of<T, N, Z32, 4>(dy, z, stats, g, dz, partial, nb, rows, H, nmb, st)
+                               : ln_bwd_launch_of<T, N, Z32, 2>(dy, z, stats, g, dz, partial, nb, rows, H, nmb, st);
 }
 
 template <typename T, bool Z32>
@@ -421,7 +441,7 @@ static hipError_t ln_bwd_t(const void* dy, const void* z, const float* stats, co
 
 hipError_t launch_ln_bwd(Dtype dt, const void* dy, const void* z, bool z_f32, const float* stats, const void* gamma,
                          void* dz, float* partial, int* nblk, int rows, int H, int nmb, hipStream_t st) {
-  int nb = (rows + LNB_ROWS - 1) / LNB_ROWS;
+  int nb = ln_bwd_blocks(rows);
   *nblk = nb;
   if (dt != DT_BF16) return ln_bwd_t<float, false>(dy, z, stats, gamma, dz, partial, nb, rows, H, nmb, st);
   return z_f32 ? ln_bwd_t<bf16, true>(dy, z, stats, gamma, dz, partial, nb, rows, H, nmb, st)

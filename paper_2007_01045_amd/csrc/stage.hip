@@ -643,7 +643,7 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
         const size_t r = (size_t)i * T1;
         return run(KC_LN_BWD, 0, [&](hipStream_t q) {
           return launch_ln_bwd(dt, dys[i], z2 + r * H * 4, dt == DT_BF16, st2 + 2 * r, w(p.ln2g), dz2 + r * H * E(),
-                               part_ln2 + (size_t)i * ((T1 + 7) / 8) * 3 * H, &nblk, T1, H, c, q);
+                               part_ln2 + (size_t)i * ln_bwd_blocks(T1) * 3 * H, &nblk, T1, H, c, q);
         });
       }));
     }
