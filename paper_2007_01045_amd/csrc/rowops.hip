@@ -294,6 +294,14 @@ __global__ __launch_bounds__(1024) void reduce_jobs_kernel(ReduceJobs J) {
       const long stride = job.stride;
       const int nblk = job.nblk;
       int b = w;
+      // 32 loads in flight per wave: the launch is a hundred workgroups waiting for memory
+      for (; b + 124 < nblk; b += 128) {
+        float x[32];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) x[u] = p[(long)(b + 4 * u) * stride];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) t += x[u];
+      }
       for (; b + 28 < nblk; b += 32) {
         float x[8];
 #pragma unroll
