@@ -1,9 +1,36 @@
-// The epilogue of one output element, shared by the GEMM kernels that store element by element.
+// What the GEMM kernels share: which tile a workgroup computes, and the epilogue of one output element (or four).
 #pragma once
 #include "device_common.h"
 #include "kernels.h"
 
 namespace dapple {
+
+// Tile index.  Consecutive workgroups land on different XCDs (round-robin over 8), and
+// each XCD has its own L2.  Cut the tile grid into pm x pn = 8 rectangles, one per XCD,
+// so that the A and B panels an XCD touches are as few as possible and are reused by
+// all its tiles out of its L2; inside a rectangle walk down its columns of tiles.
+__device__ __forceinline__ void tile_of(int bid, int tiles_m, int tiles_n, int BM, int BN, int& tm, int& tn) {
+  const int ntiles = tiles_m * tiles_n;
+  int pm = 0, best = 1 << 30;
+#pragma unroll
+  for (int c = 1; c <= 8; c <<= 1) {
+    int pn = 8 / c;
+    if (tiles_m % c == 0 && tiles_n % pn == 0) {
+      int cost = (tiles_m / c) * BM + (tiles_n / pn) * BN;
+      if (cost < best) { best = cost; pm = c; }
+    }
+  }
+  if (pm == 0 || (ntiles & 7)) {
+    tm = bid / tiles_n;
+    tn = bid % tiles_n;
+  } else {
+    const int pn = 8 / pm, rm = tiles_m / pm, rn = tiles_n / pn;
+    const int xcd = bid & 7, local = bid >> 3;
+    const int lm = local % rm, ln = local / rm;
+    tm = (xcd / pn) * rm + lm;
+    tn = (xcd % pn) * rn + ln;
+  }
+}
 
 template <typename T>
 __device__ __forceinline__ void epilogue_store(const GemmArgs& g, long zc, long zbias, int row, int col, float t) {

@@ -25,29 +25,51 @@ constexpr int FBK = 32;
 
 // One operand's [R x 32] k-tile.  k-contiguous: LDS [R][32 + 4]; 16 lanes reading 16 rows 16 bytes each hit all 64
 // banks.  k-strided: LDS [32][R + 8]; the two half waves of a 4-byte read lie 4 rows = 32 banks apart.
+// Loads carry no condition: rows past the end and, in a segment's last tile, k entries past its end re-read the last
+// ones, and are zeroed on their way to LDS.
 template <int R, bool KS>
 struct F32Tile {
   static constexpr int LD = KS ? R + 8 : FBK + 4;
   static constexpr int FLOATS = KS ? FBK * LD : R * LD;
   static constexpr int N = R * FBK / 4 / 256;   // float4 per thread
   f32x4 v[N];
-  // rows r0.. of an operand with `rows` valid rows; k0..: k inside a segment with klen valid entries
-  __device__ __forceinline__ void load(const float* X, int ld, int r0, int rows, int k0, int klen, int tid) {
+  unsigned off[N], off_tail[N];   // bytes from the tile's first element; of a segment's last tile
+  const char* next;               // first element of the next tile
+  bool tail;                      // v holds a segment's last tile
+  int tail_k;                     // ... which has this many k entries
+  unsigned live;                  // bit i: piece i lies inside the operand's rows
+  static __device__ __forceinline__ int row_of(int pos) { return KS ? pos % (R / 4) * 4 : pos / (FBK / 4); }
+  static __device__ __forceinline__ int k_of(int pos) { return KS ? pos / (R / 4) : pos % (FBK / 4) * 4; }
+  // X: the operand's row r0, with `rows` valid rows from there on
+  __device__ __forceinline__ void init(const float* X, int ld, int rows, int tk, int tid) {
+    next = (const char*)X;
+    tail_k = tk;
+    live = 0;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const int pos = tid + 256 * i;
-      const int r = KS ? r0 + pos % (R / 4) * 4 : r0 + pos / (FBK / 4);
-      const int k = KS ? k0 + pos / (R / 4) : k0 + pos % (FBK / 4) * 4;
-      v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (r < rows && k < klen) v[i] = *(const f32x4*)(X + (KS ? (long)k * ld + r : (long)r * ld + k));
+      const int pos = tid + 256 * i, r = KS ? min(row_of(pos), (rows - 1) & ~3) : min(row_of(pos), rows - 1);
+      const int k = k_of(pos), kt = min(k, KS ? tk - 1 : (tk - 1) & ~3);
+      live |= row_of(pos) < rows ? 1u << i : 0u;
+      off[i] = 4u * (unsigned)(KS ? k * ld + r : r * ld + k);
+      off_tail[i] = 4u * (unsigned)(KS ? kt * ld + r : r * ld + kt);
     }
   }
+  __device__ __forceinline__ void load(bool is_tail) {
+    tail = is_tail;
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = *(const f32x4*)(next + (is_tail ? off_tail[i] : off[i]));
+  }
   __device__ __forceinline__ void store(float* S, int tid) const {
+    const int valid = tail ? tail_k : FBK;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int pos = tid + 256 * i;
-      const int a = KS ? pos / (R / 4) : pos / (FBK / 4), b = (KS ? pos % (R / 4) : pos % (FBK / 4)) * 4;
-      *(f32x4*)(S + a * LD + b) = v[i];
+      const int a = KS ? k_of(pos) : row_of(pos), b = KS ? row_of(pos) : k_of(pos);
+      const bool in = k_of(pos) < valid && (live >> i & 1);
+      f32x4 x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = in ? v[i][e] : 0.f;
+      *(f32x4*)(S + a * LD + b) = x;
     }
   }
   // row r, k = 8 kk + 4 h + 0..3
@@ -58,110 +80,134 @@ struct F32Tile {
   }
 };
 
-template <int BT, bool AKS, bool BKS>
-__device__ __forceinline__ void f32_tile(GemmArgs g, int tiles_n, const int bid, const int z) {
+// CS: the variant that can also sum B over k (EPI_BSUM).  The k-loop holds no branch: one had the accumulators copied
+// between the register files in every k-tile (2048 x 1024 x 4096: 190 us with it).
+template <int BT, bool AKS, bool BKS, bool CS>
+__device__ __forceinline__ void f32_tile(const GemmArgs& g, int tiles_m, int tiles_n, const int bid, const int z) {
   typedef F32Tile<BT, AKS> TA;
   typedef F32Tile<BT, BKS> TB;
   constexpr int W = BT / 2, NB = W / 32;   // wave tile, 32-blocks per side
   extern __shared__ __attribute__((aligned(16))) float fsm[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l31 = lane & 31, h = lane >> 5;
-  const int tm = bid / tiles_n, tn = bid % tiles_n;
+  int tm, tn;
+  tile_of(bid, tiles_m, tiles_n, BT, BT, tm, tn);
   const int m0 = tm * BT, n0 = tn * BT, wm0 = (wave >> 1) * W, wn0 = (wave & 1) * W;
-  const float *A = (const float*)g.A + z * g.sA, *B = (const float*)g.B + z * g.sB;
-  float* const bs = (g.epi & EPI_BSUM) && z == 0 ? g.bsum : nullptr;
+  float* const bs = CS && (g.epi & EPI_BSUM) && z == 0 ? g.bsum : nullptr;
   const bool do_cs = bs != nullptr && tm == 0 && wm0 == 0;
   const int klen = g.K > g.kseg_len ? g.kseg_len : min(g.K, g.k_valid);
-  const int per_seg = (g.kseg_len + FBK - 1) / FBK, nt = g.K / g.kseg_len * per_seg;
+  const int per_seg = (klen + FBK - 1) / FBK, nseg = g.K / g.kseg_len;
+  const int tail_k = klen - (per_seg - 1) * FBK;
   f32x16 acc[NB][NB];
   float cs[NB];
+  auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    cs[i] = 0.f;
+    for (int i = 0; i < NB; ++i) {
+      cs[i] = 0.f;
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  }
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    }
+  };
+  clear();
   TA ta;
   TB tb;
-  int seg = 0, kt = 0;   // the tile the next load fetches
-  auto load = [&]() {
-    ta.load(A + seg * g.segA, g.lda, m0, g.m_valid, kt * FBK, klen, tid);
-    tb.load(B + seg * g.segB, g.ldb, n0, g.n_valid, kt * FBK, klen, tid);
-    if (++kt == per_seg) { kt = 0; ++seg; }
+  ta.init((const float*)g.A + z * g.sA + (AKS ? (long)m0 : (long)m0 * g.lda), g.lda, g.m_valid - m0, tail_k, tid);
+  tb.init((const float*)g.B + z * g.sB + (BKS ? (long)n0 : (long)n0 * g.ldb), g.ldb, g.n_valid - n0, tail_k, tid);
+  const long a_step = 4L * FBK * (AKS ? g.lda : 1), b_step = 4L * FBK * (BKS ? g.ldb : 1);
+  const long a_jump = 4L * g.segA - (per_seg - 1) * a_step, b_jump = 4L * g.segB - (per_seg - 1) * b_step;
+  int kt = 0, left = nseg * per_seg;   // tile inside its segment, and tiles not yet loaded
+  auto load = [&]() __attribute__((always_inline)) {   // the next tile; past the last one that one again
+    ta.load(kt == per_seg - 1);
+    tb.load(kt == per_seg - 1);
+    --left;
+    const bool last = kt == per_seg - 1, more = left > 0;
+    ta.next += more ? (last ? a_jump : a_step) : 0;
+    tb.next += more ? (last ? b_jump : b_step) : 0;
+    kt = more ? (last ? 0 : kt + 1) : kt;
   };
   constexpr int STAGE = TA::FLOATS + TB::FLOATS;
   load();
   ta.store(fsm, tid);
   tb.store(fsm + TA::FLOATS, tid);
   __syncthreads();
-  const bool segacc = (g.epi & EPI_SEGACC) != 0;
   const long zc = z * g.sC, zb = z * g.sBias;
-  auto finish = [&]() {   // add the column sums and store the tile
-    if (do_cs) {
+  auto finish = [&]() __attribute__((always_inline)) {   // add the column sums and store the tile
+    if (CS && do_cs) {
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
         const float t = cs[j] + __shfl_xor(cs[j], 32, 64);
         const int col = n0 + wn0 + 32 * j + l31;
         if (h == 0 && col < g.N) bs[col] += t;
-        cs[j] = 0.f;
       }
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int row = m0 + wm0 + 32 * i + l31;
 #pragma unroll
-      for (int j = 0; j < NB; ++j)
+      for (int j = 0; j < NB; ++j) {
+        // what a 32x32 block's epilogue reads, all of it before its first store: behind a store to the same matrix the
+        // compiler leaves a load where it stands, one trip to memory after the other
+        Epilogue4 in[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int col = n0 + wn0 + 32 * j + 8 * q + 4 * h;
+          in[q] = row < g.M && col < g.N ? epilogue_load4(g, zc, zb, row, col) : Epilogue4{};
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int col = n0 + wn0 + 32 * j + 8 * q + 4 * h;
           if (row < g.M && col < g.N)
             epilogue_store4(g, zc, row, col,
-                            f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]},
-                            epilogue_load4(g, zc, zb, row, col));
+                            f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]}, in[q]);
         }
-    }
-  };
-  for (int t = 0; t < nt; ++t) {
-    const float *SA = fsm + (t & 1) * STAGE, *SB = SA + TA::FLOATS;
-    const bool more = t + 1 < nt;
-    if (more) load();
-#pragma unroll
-    for (int kk = 0; kk < FBK / 8; ++kk) {
-      f32x4 a[NB], b[NB];
-#pragma unroll
-      for (int i = 0; i < NB; ++i) a[i] = TA::frag(SA, wm0 + 32 * i + l31, kk, h);
-#pragma unroll
-      for (int j = 0; j < NB; ++j) b[j] = TB::frag(SB, wn0 + 32 * j + l31, kk, h);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-          for (int j = 0; j < NB; ++j)   // B first: a lane then owns 4 consecutive columns of one row
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][e], a[i][e], acc[i][j], 0, 0, 0);
-      if (do_cs) {
-#pragma unroll
-        for (int j = 0; j < NB; ++j) cs[j] += (b[j][0] + b[j][1]) + (b[j][2] + b[j][3]);
       }
     }
-    if (more) {
-      float* nb = fsm + ((t + 1) & 1) * STAGE;
-      ta.store(nb, tid);
-      tb.store(nb + TA::FLOATS, tid);
+  };
+  int buf = 0;
+  auto k_loop = [&](int tiles, auto WCS) __attribute__((always_inline)) {
+    for (int t = 0; t < tiles; ++t) {
+      const float *SA = fsm + buf * STAGE, *SB = SA + TA::FLOATS;
+      load();
+      __builtin_amdgcn_sched_barrier(0);   // (the loads would sink to their use, behind the products that cover them)
+#pragma unroll
+      for (int kk = 0; kk < FBK / 8; ++kk) {
+        f32x4 a[NB], b[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) a[i] = TA::frag(SA, wm0 + 32 * i + l31, kk, h);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) b[j] = TB::frag(SB, wn0 + 32 * j + l31, kk, h);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)   // B first: a lane then owns 4 consecutive columns of one row
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][e], a[i][e], acc[i][j], 0, 0, 0);
+        if constexpr (decltype(WCS)::value) {
+#pragma unroll
+          for (int j = 0; j < NB; ++j) cs[j] += (b[j][0] + b[j][1]) + (b[j][2] + b[j][3]);
+        }
+      }
+      buf ^= 1;
+      ta.store(fsm + buf * STAGE, tid);
+      tb.store(fsm + buf * STAGE + TA::FLOATS, tid);
+      __syncthreads();
     }
-    __syncthreads();
-    if (segacc && more && (t + 1) % per_seg == 0) {   // a segment's sum is complete: it goes to C on its own
-      finish();
-#pragma unroll
-      for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  };
+  // EPI_SEGACC: a segment's sum goes to C on its own
+  const bool segacc = (g.epi & EPI_SEGACC) != 0;
+  const int turns = segacc ? nseg : 1, tiles = segacc ? per_seg : nseg * per_seg;
+  for (int s = 0; s < turns; ++s) {
+    if (s) clear();
+    if constexpr (CS) {
+      if (do_cs) k_loop(tiles, std::true_type{});
+      else k_loop(tiles, std::false_type{});
+    } else {
+      k_loop(tiles, std::false_type{});
     }
+    finish();
   }
-  finish();
 }
 
 // ------------------------------------------------------------------ few tiles: K split over the waves
@@ -289,8 +335,8 @@ __device__ __forceinline__ void f32_small_tile(GemmArgs g, int tiles_n, const in
 
 // ------------------------------------------------------------------ kernels
 template <int BT, bool AKS, bool BKS>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, int tiles_n) {
-  f32_tile<BT, AKS, BKS>(g, tiles_n, blockIdx.x, blockIdx.z);
+__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  f32_tile<BT, AKS, BKS, AKS && BKS>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.z);
 }
 template <int TW, bool AKS, bool BKS>
 __global__ __launch_bounds__(256) void gemm_f32_small(GemmArgs g, int tiles_n) {
@@ -303,7 +349,7 @@ struct F32Tiles {
   int first[WgradGroup::MAX + 1];
 };
 template <int BT, int NSG>
-__global__ __launch_bounds__(256) void wgrad_group_f32(WgradGroup w, F32Tiles t) {
+__global__ __launch_bounds__(256, 2) void wgrad_group_f32(WgradGroup w, F32Tiles t) {
   int i = 0;
 #pragma unroll
   for (int k = 1; k < WgradGroup::MAX; ++k) i += k < w.n && (int)blockIdx.x >= t.first[k];
@@ -321,7 +367,7 @@ __global__ __launch_bounds__(256) void wgrad_group_f32(WgradGroup w, F32Tiles t)
   g.segA = (long)w.kseg * g.lda; g.segB = (long)w.kseg * g.ldb;
   g.epi = EPI_ACC32 | (g.bsum ? EPI_BSUM : 0) | (w.K > w.kseg ? EPI_SEGACC : 0);
   const int tn = (g.N + BT - 1) / BT, bid = blockIdx.x - first;
-  if constexpr (BT >= 64) f32_tile<BT, true, true>(g, tn, bid, 0);
+  if constexpr (BT >= 64) f32_tile<BT, true, true, true>(g, (g.M + BT - 1) / BT, tn, bid, 0);
   else f32_small_tile<BT / 16, true, true, NSG>(g, tn, bid, 0);
 }
 
@@ -338,6 +384,8 @@ bool gemm_f32_takes(const GemmArgs& g) {
   if (g.a_kstrided && g.m_valid % 4 && (g.m_valid != g.M || (g.m_valid + 3) / 4 * 4 > g.lda)) return false;
   if (g.b_kstrided && g.n_valid % 4) return false;
   if (!g.a_kstrided && !g.b_kstrided && g.k_valid < g.K) return false;   // k_valid cuts k-strided operands
+  // no tile begins past the last row
+  if (g.M > (g.m_valid + 63) / 64 * 64 || g.N > (g.n_valid + 63) / 64 * 64) return false;
   if ((g.epi & EPI_BIAS) && !al16(g.bias)) return false;
   if ((g.epi & (EPI_ADD | EPI_MUL)) && (g.ldaux % 4 || !al16(g.aux))) return false;
   if ((g.epi & EPI_GELU) && !al16(g.C2)) return false;
@@ -352,7 +400,7 @@ static hipError_t launch_tile(const GemmArgs& g, hipStream_t st) {
   static const hipError_t attr_rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (attr_rc != hipSuccess) return attr_rc;
   const int tm = (g.M + BT - 1) / BT, tn = (g.N + BT - 1) / BT;
-  hipLaunchKernelGGL(kern, dim3(tm * tn, 1, g.batch), dim3(256), lds, st, g, tn);
+  hipLaunchKernelGGL(kern, dim3(tm * tn, 1, g.batch), dim3(256), lds, st, g, tm, tn);
   return hipGetLastError();
 }
 template <int TW, bool AKS, bool BKS>

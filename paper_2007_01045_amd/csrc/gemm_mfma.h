@@ -5,6 +5,7 @@
 #include <utility>
 
 #include "device_common.h"
+#include "gemm_epilogue.h"
 #include "kernels.h"
 
 namespace dapple {
@@ -237,33 +238,8 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm0 = (wave / WGN) * CFG::WM, wn0 = (wave % WGN) * CFG::WN;
 
-  // Tile index.  Consecutive workgroups land on different XCDs (round-robin over 8), and
-  // each XCD has its own L2.  Cut the tile grid into pm x pn = 8 rectangles, one per XCD,
-  // so that the A and B panels an XCD touches are as few as possible and are reused by
-  // all its tiles out of its L2; inside a rectangle walk column-blocks of 4 tiles.
   int tm, tn;
-  {
-    const int ntiles = tiles_m * tiles_n;
-    int pm = 0, best = 1 << 30;
-#pragma unroll
-    for (int c = 1; c <= 8; c <<= 1) {
-      int pn = 8 / c;
-      if (tiles_m % c == 0 && tiles_n % pn == 0) {
-        int cost = (tiles_m / c) * BM + (tiles_n / pn) * BN;
-        if (cost < best) { best = cost; pm = c; }
-      }
-    }
-    if (pm == 0 || (ntiles & 7)) {
-      tm = bid / tiles_n;
-      tn = bid % tiles_n;
-    } else {
-      const int pn = 8 / pm, rm = tiles_m / pm, rn = tiles_n / pn;
-      const int xcd = bid & 7, local = bid >> 3;
-      const int lm = local % rm, ln = local / rm;   // walk down a column of the rectangle first
-      tm = (xcd / pn) * rm + lm;
-      tn = (xcd % pn) * rn + ln;
-    }
-  }
+  tile_of(bid, tiles_m, tiles_n, BM, BN, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
   // (the small tiles: every argument the prologue and the first requests need in one go of scalar loads, not a round trip
   // per branch that uses some)
