@@ -8,7 +8,9 @@
 //    in LDS (2 x 37 KB: two workgroups per unit), the next tile's global loads in flight behind the MFMAs;
 //  * gemm_f32_small<TW>: 16 TW square tiles, one per workgroup whose four waves take every fourth 16-wide piece of K
 //    straight from global memory and add their partial tiles in wave order through LDS: for products with so few
-//    tiles that the length of one wave's MFMA chain is the time.
+//    tiles that the length of one wave's MFMA chain is the time;
+//  * gemm_f32_quad: the sums of gemm_f32_small in the 64-wide tiles of gemm_f32_kernel, every wave with four sets of
+//    accumulators: for a group of micro-batches of which one alone takes the small kernel.
 // Measured before -> after: 2 layers of 1024 x 4096, 2 x 512 tokens, 2 micro-batches: 412 -> 3.9 ms per iteration
 // with the attention kernels of attention_f32.hip (one thread per output element before).
 #include <type_traits>
@@ -27,19 +29,21 @@ constexpr int FBK = 32;
 // banks.  k-strided: LDS [32][R + 8]; the two half waves of a 4-byte read lie 4 rows = 32 banks apart.
 // Loads carry no condition: rows past the end and, in a segment's last tile, k entries past its end re-read the last
 // ones, and are zeroed on their way to LDS.
-template <int R, bool KS>
+// (BK = 64, for 16-row fragments: LDS [64][R + 4] there, the four lane groups of a 4-byte read lie 4 rows = 16 banks
+// apart.)
+template <int R, bool KS, int BK = FBK>
 struct F32Tile {
-  static constexpr int LD = KS ? R + 8 : FBK + 4;
-  static constexpr int FLOATS = KS ? FBK * LD : R * LD;
-  static constexpr int N = R * FBK / 4 / 256;   // float4 per thread
+  static constexpr int LD = KS ? R + (BK == 64 ? 4 : 8) : BK + 4;
+  static constexpr int FLOATS = KS ? BK * LD : R * LD;
+  static constexpr int N = R * BK / 4 / 256;   // float4 per thread
   f32x4 v[N];
   unsigned off[N], off_tail[N];   // bytes from the tile's first element; of a segment's last tile
   const char* next;               // first element of the next tile
   bool tail;                      // v holds a segment's last tile
   int tail_k;                     // ... which has this many k entries
   unsigned live;                  // bit i: piece i lies inside the operand's rows
-  static __device__ __forceinline__ int row_of(int pos) { return KS ? pos % (R / 4) * 4 : pos / (FBK / 4); }
-  static __device__ __forceinline__ int k_of(int pos) { return KS ? pos / (R / 4) : pos % (FBK / 4) * 4; }
+  static __device__ __forceinline__ int row_of(int pos) { return KS ? pos % (R / 4) * 4 : pos / (BK / 4); }
+  static __device__ __forceinline__ int k_of(int pos) { return KS ? pos / (R / 4) : pos % (BK / 4) * 4; }
   // X: the operand's row r0, with `rows` valid rows from there on
   __device__ __forceinline__ void init(const float* X, int ld, int rows, int tk, int tid) {
     next = (const char*)X;
@@ -60,7 +64,7 @@ struct F32Tile {
     for (int i = 0; i < N; ++i) v[i] = *(const f32x4*)(next + (is_tail ? off_tail[i] : off[i]));
   }
   __device__ __forceinline__ void store(float* S, int tid) const {
-    const int valid = tail ? tail_k : FBK;
+    const int valid = tail ? tail_k : BK;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int pos = tid + 256 * i;
@@ -78,6 +82,8 @@ struct F32Tile {
     if (!KS) return *(const f32x4*)(S + r * LD + k);
     return f32x4{S[k * LD + r], S[(k + 1) * LD + r], S[(k + 2) * LD + r], S[(k + 3) * LD + r]};
   }
+  // row r, k = 16 piece + 4 q4 + 0..3
+  static __device__ __forceinline__ f32x4 frag16(const float* S, int r, int piece, int q4) { return frag(S, r, 2 * piece, q4); }
 };
 
 // CS: the variant that can also sum B over k (EPI_BSUM).  The k-loop holds no branch: one had the accumulators copied
@@ -333,7 +339,101 @@ __device__ __forceinline__ void f32_small_tile(GemmArgs g, int tiles_n, const in
   }
 }
 
+// ------------------------------------------------------------------ the small kernel's sums in large tiles
+// A group of micro-batches has rows enough for 64-wide tiles where one of them has not, but must add as one does (see
+// launch_layout): every wave of a 64x64 tile keeps the four chains of f32_small_tile, piece c of K in set c % 4, for
+// its 32x32 part (64 accumulator registers) and adds the sets in the same order.  k-tiles of 64 so that a piece's set
+// is a constant; a segment's last one may be short only where there is one segment (the pieces are counted through).
+// 8 micro-batches of 256 rows, 512 wide, GPipe order: 1.51 ms with the small kernel's 32-wide tiles, 1.13 so.
+template <bool BKS>
+__device__ __forceinline__ void f32_quad_tile(const GemmArgs& g, int tiles_m, int tiles_n, const int bid, const int z) {
+  constexpr int BK = 64;
+  typedef F32Tile<64, false, BK> TA;
+  typedef F32Tile<64, BKS, BK> TB;
+  extern __shared__ __attribute__((aligned(16))) float fsm[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l15 = lane & 15, q4 = lane >> 4;
+  int tm, tn;
+  tile_of(bid, tiles_m, tiles_n, 64, 64, tm, tn);
+  const int m0 = tm * 64, n0 = tn * 64, wm0 = (wave >> 1) * 32, wn0 = (wave & 1) * 32;
+  const int klen = g.K > g.kseg_len ? g.kseg_len : min(g.K, g.k_valid);
+  const int per_seg = (klen + BK - 1) / BK, left0 = g.K / g.kseg_len * per_seg;
+  f32x4 acc[4][2][2];
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[c][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  TA ta;
+  TB tb;
+  ta.init((const float*)g.A + z * g.sA + (long)m0 * g.lda, g.lda, g.m_valid - m0, klen - (per_seg - 1) * BK, tid);
+  tb.init((const float*)g.B + z * g.sB + (BKS ? (long)n0 : (long)n0 * g.ldb), g.ldb, g.n_valid - n0, klen - (per_seg - 1) * BK, tid);
+  const long a_step = 4L * BK, b_step = 4L * BK * (BKS ? g.ldb : 1);
+  const long a_jump = 4L * g.segA - (per_seg - 1) * a_step, b_jump = 4L * g.segB - (per_seg - 1) * b_step;
+  int kt = 0, left = left0;
+  auto load = [&]() __attribute__((always_inline)) {   // the next tile; past the last one that one again
+    ta.load(kt == per_seg - 1);
+    tb.load(kt == per_seg - 1);
+    --left;
+    const bool last = kt == per_seg - 1, more = left > 0;
+    ta.next += more ? (last ? a_jump : a_step) : 0;
+    tb.next += more ? (last ? b_jump : b_step) : 0;
+    kt = more ? (last ? 0 : kt + 1) : kt;
+  };
+  constexpr int STAGE = TA::FLOATS + TB::FLOATS;
+  load();
+  ta.store(fsm, tid);
+  tb.store(fsm + TA::FLOATS, tid);
+  __syncthreads();
+  int buf = 0;
+  for (int t = 0; t < left0; ++t) {
+    const float *SA = fsm + buf * STAGE, *SB = SA + TA::FLOATS;
+    load();
+    __builtin_amdgcn_sched_barrier(0);   // (see f32_tile)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      f32x4 a[2], b[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) a[i] = TA::frag16(SA, wm0 + 16 * i + l15, c, q4);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) b[j] = TB::frag16(SB, wn0 + 16 * j + l15, c, q4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[c][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][e], a[i][e], acc[c][i][j], 0, 0, 0);
+    }
+    buf ^= 1;
+    ta.store(fsm + buf * STAGE, tid);
+    tb.store(fsm + buf * STAGE + TA::FLOATS, tid);
+    __syncthreads();
+  }
+  const long zc = z * g.sC, zb = z * g.sBias;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = m0 + wm0 + 16 * i + l15;
+    Epilogue4 in[2];   // all reads before the first store (see f32_tile)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = n0 + wn0 + 16 * j + 4 * q4;
+      in[j] = row < g.M && col < g.N ? epilogue_load4(g, zc, zb, row, col) : Epilogue4{};
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = n0 + wn0 + 16 * j + 4 * q4;
+      if (row < g.M && col < g.N)
+        epilogue_store4(g, zc, row, col, ((acc[0][i][j] + acc[1][i][j]) + acc[2][i][j]) + acc[3][i][j], in[j]);
+    }
+  }
+}
+
 // ------------------------------------------------------------------ kernels
+template <bool BKS>
+__global__ __launch_bounds__(256, 2) void gemm_f32_quad(GemmArgs g, int tiles_m, int tiles_n) {
+  f32_quad_tile<BKS>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.z);
+}
 template <int BT, bool AKS, bool BKS>
 __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmArgs g, int tiles_m, int tiles_n) {
   f32_tile<BT, AKS, BKS, AKS && BKS>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.z);
@@ -403,6 +503,16 @@ static hipError_t launch_tile(const GemmArgs& g, hipStream_t st) {
   hipLaunchKernelGGL(kern, dim3(tm * tn, 1, g.batch), dim3(256), lds, st, g, tm, tn);
   return hipGetLastError();
 }
+template <bool BKS>
+static hipError_t launch_quad(const GemmArgs& g, hipStream_t st) {
+  auto kern = gemm_f32_quad<BKS>;
+  constexpr int lds = 2 * 4 * (F32Tile<64, false, 64>::FLOATS + F32Tile<64, BKS, 64>::FLOATS);
+  static const hipError_t attr_rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (attr_rc != hipSuccess) return attr_rc;
+  const int tm = (g.M + 63) / 64, tn = (g.N + 63) / 64;
+  hipLaunchKernelGGL(kern, dim3(tm * tn, 1, g.batch), dim3(256), lds, st, g, tm, tn);
+  return hipGetLastError();
+}
 template <int TW, bool AKS, bool BKS>
 static hipError_t launch_small(const GemmArgs& g, hipStream_t st) {
   const int tm = (g.M + 16 * TW - 1) / (16 * TW), tn = (g.N + 16 * TW - 1) / (16 * TW);
@@ -412,11 +522,17 @@ static hipError_t launch_small(const GemmArgs& g, hipStream_t st) {
 
 template <bool AKS, bool BKS>
 static hipError_t launch_layout(const GemmArgs& g, hipStream_t st) {
-  auto tiles = [&](long t) { return (long)((g.M + t - 1) / t) * ((g.N + t - 1) / t) * g.batch; };
-  // The largest tile that still gives most of the 256 units a workgroup.  Below that the 32- and 16-wide tiles with K
-  // split over the waves: a 16-wide one has a quarter of the MFMA chain but reads every operand element twice as often.
-  if (tiles(128) >= 192) return launch_tile<128, AKS, BKS>(g, st);
-  if (tiles(64) >= 160) return launch_tile<64, AKS, BKS>(g, st);
+  auto tiles_of = [&](long rows, long t) { return ((rows + t - 1) / t) * ((g.N + t - 1) / t) * g.batch; };
+  auto tiles = [&](long t) { return tiles_of(g.M, t); };
+  // Two orders of summation: one ascending chain (the tile kernel), and four waves' chains added up (the small one).
+  // Which of them follows from the rows of ONE micro-batch; the tile inside an order, which no bit depends on, from all
+  // the rows.  The largest tile that still gives most of the 256 units a workgroup.  Below that the 32- and 16-wide tiles
+  // with K split over the waves: a 16-wide one has a quarter of the MFMA chain but reads every operand element twice as
+  // often.
+  const bool chain = tiles_of(g.rows1 > 0 ? g.rows1 : g.M, 64) >= 160;
+  if (chain) return tiles(128) >= 192 ? launch_tile<128, AKS, BKS>(g, st) : launch_tile<64, AKS, BKS>(g, st);
+  if constexpr (!AKS)
+    if (tiles(64) >= 160 && !(g.epi & EPI_SEGACC) && (g.K == g.kseg_len || g.kseg_len % 64 == 0)) return launch_quad<BKS>(g, st);
   if (tiles(32) >= 160) return launch_small<2, AKS, BKS>(g, st);
   return launch_small<1, AKS, BKS>(g, st);
 }
@@ -450,8 +566,8 @@ hipError_t launch_wgrad_group_f32(const WgradGroup& w, hipStream_t st) {
     for (int i = 0; i < w.n; ++i) n += ((w.p[i].M + b - 1) / b) * ((w.p[i].N + b - 1) / b);
     return n;
   };
-  if (tiles(128) >= 192) return launch_group<128>(w, st);   // the lines of launch_layout
-  if (tiles(64) >= 160) return launch_group<64>(w, st);
+  if ((w.list_tiles64 > 0 ? w.list_tiles64 : tiles(64)) >= 160)   // the lines of launch_layout
+    return tiles(128) >= 192 ? launch_group<128>(w, st) : launch_group<64>(w, st);
   if (tiles(32) >= 160) return launch_group<32>(w, st);
   return launch_group<16>(w, st);
 }

@@ -63,6 +63,9 @@ struct GemmArgs {
   // beside this one, so a workgroup should leave room on its unit
   int units;
   bool shared;
+  // fp32: rows of one micro-batch, where M holds those of several (0 = M).  The fp32 kernels add in one of two orders,
+  // and which one follows from a micro-batch's rows alone, so that no bit depends on how many share a launch.
+  int rows1;
 };
 
 hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st);
@@ -86,6 +89,9 @@ struct WgradGroup {
   WgradProblem p[MAX];
   int n, K, kseg;
   int units;   // as in GemmArgs
+  // fp32: 64x64 tiles of the whole list that this one is part of (0 = of this one): the order of the sums follows from
+  // them, and must not change where a caller cuts its list in two
+  long list_tiles64;
 };
 // the same as one accumulating product
 GemmArgs wgrad_args(const WgradGroup& w, int i);

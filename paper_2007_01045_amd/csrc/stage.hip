@@ -373,6 +373,7 @@ struct dapple_stage {
     if (g.batch == 0) g.batch = 1;
     g.units = units;
     g.shared = cls == KC_GEMM_DGRAD && side != cur;
+    if (g.rows1 == 0) g.rows1 = cfg.micro_batch * cfg.seq;   // (the head's products: the gathered rows instead)
     double flops = 2.0 * g.M * g.N * (double)g.K * g.batch;
     hipStream_t s_ = on_side ? side : cur;
     return run_on(s_, cls, flops, [&](hipStream_t s) { return launch_gemm(dt, g, s); }, &g);
@@ -530,14 +531,14 @@ int dapple_stage::forward(const Act& sl, int fs, int n, const void* const* xs, v
     {
       GemmArgs ga{};
       ga.A = r; ga.lda = H; ga.B = w(L.hWt); ga.ldb = H; ga.b_kstrided = 1; ga.bias = w(L.hbt);
-      ga.C = gl; ga.C2 = glp; ga.ldc = H; ga.M = n * NP; ga.N = H; ga.K = H; ga.epi = EPI_BIAS | EPI_GELU;
+      ga.C = gl; ga.C2 = glp; ga.ldc = H; ga.M = n * NP; ga.rows1 = NP; ga.N = H; ga.K = H; ga.epi = EPI_BIAS | EPI_GELU;
       TRY(gemm(KC_HEAD, ga));
     }
     TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_ln_fwd(dt, gl, false, w(L.hG), w(L.hB), t, nullptr, hst, n * NP, H, cfg.ln_eps, q); }));
     {
       GemmArgs ga{};
       ga.A = t; ga.lda = H; ga.B = w(L.hEout); ga.ldb = H; ga.n_valid = V;
-      ga.C = logits; ga.ldc = VP; ga.M = n * NP; ga.N = VP; ga.K = H; ga.epi = EPI_OUT32;
+      ga.C = logits; ga.ldc = VP; ga.M = n * NP; ga.rows1 = NP; ga.N = VP; ga.K = H; ga.epi = EPI_OUT32;
       TRY(gemm(KC_HEAD, ga));
     }
     TRY(run(KC_HEAD, 0, [&](hipStream_t q) {
@@ -592,7 +593,7 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
     {  // dt = dz E_out
       GemmArgs ga{};
       ga.A = dz; ga.lda = VP; ga.B = w(L.hEout); ga.ldb = H; ga.b_kstrided = 1; ga.k_valid = V;
-      ga.C = dtb; ga.ldc = H; ga.M = n * NP; ga.N = H; ga.K = VP;
+      ga.C = dtb; ga.ldc = H; ga.M = n * NP; ga.rows1 = NP; ga.N = H; ga.K = VP;
       TRY(gemm(KC_HEAD, ga));
     }
     TRY(run(KC_HEAD, 0, [&](hipStream_t q) { return launch_ln_bwd(dt, dtb, gl, false, hst, w(L.hG), dgl, part, &nblk, NP, H, n, q); }));
@@ -614,7 +615,7 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
     TRY(side_done(HL));
     {  // dr = dh Wt^T
       GemmArgs ga{};
-      ga.A = dh; ga.lda = H; ga.B = w(L.hWt); ga.ldb = H; ga.C = dr; ga.ldc = H; ga.M = n * NP; ga.N = H; ga.K = H;
+      ga.A = dh; ga.lda = H; ga.B = w(L.hWt); ga.ldb = H; ga.C = dr; ga.ldc = H; ga.M = n * NP; ga.rows1 = NP; ga.N = H; ga.K = H;
       TRY(gemm(KC_HEAD, ga));
     }
     TRY(run(KC_COPY, 0, [&](hipStream_t q) { return launch_zero(dyfull, n * U1, q); }));
@@ -663,6 +664,8 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
     // 6 layers of 1024, 2048 tokens, M = 8: 12.1 ms with one launch, 11.9 with two; launches of one product each 12.05.
     const bool early = side != cur && (long)((H + 127) / 128) * ((F + 127) / 128) * 4 >= 3 * (units ? units : 256);
     WgradGroup wg{};
+    const long h64 = (H + 63) / 64, f64 = (F + 63) / 64;
+    wg.list_tiles64 = 2 * h64 * f64 + 4 * h64 * h64;
     wg.p[wg.n++] = WgradProblem{g, dz2, gr(p.W2), nullptr, F, H, F, H, H};    // dW2 += g^T dz2
     wg.p[wg.n++] = WgradProblem{y1, du, gr(p.W1), gr(p.b1), H, F, H, F, F};   // dW1 += y1^T du
     if (early) {

@@ -493,3 +493,39 @@ def groups_against_tasks(cfg, M, K, ordr):
             assert emb or np.array_equal(to_np(dxs[m]), ref["dxs"][m])
     finally:
         r.close()
+
+
+def _bits(run):
+    return (run["grads"], *run["ys"], *(run["dxs"] or []))
+
+
+@pytest.mark.parametrize("H,F,s,b", [
+    (512, 2048, 128, 2),    # one micro-batch: 32 tiles of 64x64 in a product of width 512, eight of them 256
+    (256, 1024, 64, 2),
+    (768, 3072, 100, 2),
+    (520, 2080, 101, 2),    # ragged rows, columns and K in the large tiles that keep the small ones' sums
+    (384, 8192, 64, 1),     # the weight gradients' list cut in two where a side stream takes them
+])
+def test_fp32_sums_do_not_depend_on_how_a_stage_is_driven(H, F, s, b):
+    """fp32 products add in one of two orders; which one must follow from one micro-batch, not from how many of them
+    share a launch: early-backward groups two of them, GPipe eight, an explicit list and re-computation one."""
+    M, K = 8, 2
+    cfg = I.StageConfig(1, H, H // 64 if H % 64 == 0 else 10, F, s, b, M, K, "f32", ln_eps=1e-5)
+    theta, mbs = make_inputs(cfg, SEED, M)
+    ref = _bits(run_gpu(cfg, theta, mbs, M, K, B.ORDER_EARLY_BACKWARD))
+    single = [op for m in range(M) for op in (("F", m), ("B", m))]
+    others = [dict(order=B.ORDER_GPIPE), dict(order=B.ORDER_EXPLICIT, explicit_ops=single),
+              dict(order=B.ORDER_EARLY_BACKWARD, flags=B.FLAG_RECOMPUTE),
+              dict(order=B.ORDER_EARLY_BACKWARD, flags=B.FLAG_ONE_STREAM)]
+    for kw in others:
+        got = _bits(run_gpu(cfg, theta, mbs, M, K, **kw))
+        assert all(np.array_equal(x, y) for x, y in zip(ref, got)), kw
+
+
+def test_fp32_head_sums_do_not_depend_on_the_group():
+    M = 8
+    cfg = I.StageConfig(1, 256, 4, 1024, 64, 2, M, 2, "f32", has_mlm_head=True, vocab=1022, ln_eps=1e-5)
+    theta, mbs = make_inputs(cfg, SEED, M)
+    a = _bits(run_gpu(cfg, theta, mbs, M, 2, B.ORDER_EARLY_BACKWARD))
+    b = _bits(run_gpu(cfg, theta, mbs, M, 2, B.ORDER_GPIPE))
+    assert all(np.array_equal(x, y) for x, y in zip(a, b))
