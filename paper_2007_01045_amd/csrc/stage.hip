@@ -136,6 +136,13 @@ int check_config(const stage_config& c) {
   return STAGE_OK;
 }
 
+int pad64(int v) { return (v + 63) / 64 * 64; }
+// rows the masked-LM head gathers of a micro-batch, padded
+int head_rows(const stage_config& c) {
+  const int T = c.micro_batch * c.seq;
+  return pad64(c.mlm_max_rows > 0 && c.mlm_max_rows < T ? c.mlm_max_rows : T);
+}
+
 // How many micro-batches may share a set of launches: enough for 8192 token rows, at most 8.  A micro-batch of 1024 or
 // 2048 tokens is too little for 256 compute units: its products have 2-17 GFLOP, which leaves the 9-14 us a launch
 // costs before and after its k-loop standing, and on the smallest stages the host's 5 us per launch are the time.
@@ -146,7 +153,13 @@ int group_limit(const stage_config& c) {
   if ((c.flags & STAGE_FLAG_RECOMPUTE) || c.max_slots < 2) return 1;   // re-computation keeps ONE set of activations per lane
   const long T = (long)c.micro_batch * c.seq;
   long g = 8192 / T;
-  return (int)(g < 1 ? 1 : (g > 8 ? 8 : g));
+  g = g < 1 ? 1 : (g > 8 ? 8 : g);
+  // The MFMA products address an operand with 32-bit offsets (gemm_uses_mfma): what one micro-batch's products may read
+  // there -- the widest are the FFN's activations and the head's gradient of the logits -- a group's must too.
+  long widest = T * std::max(c.ffn, c.hidden);
+  if (c.has_mlm_head) widest = std::max(widest, (long)head_rows(c) * pad64(c.vocab));
+  while (g > 1 && c.dtype == STAGE_DTYPE_BF16 && g * widest * 2 > 0x7fffffffL - 4096) --g;
+  return (int)g;
 }
 
 void build_layout(const stage_config& c, Layout& L) {
@@ -195,9 +208,8 @@ void build_layout(const stage_config& c, Layout& L) {
     s.y = keep_y ? stake(U) : Tensor{};
   }
   if (c.has_mlm_head) {
-    int cap = c.mlm_max_rows > 0 && c.mlm_max_rows < (int)T ? c.mlm_max_rows : (int)T;
-    L.NP = (cap + 63) / 64 * 64;
-    L.VP = (c.vocab + 63) / 64 * 64;
+    L.NP = head_rows(c);
+    L.VP = pad64(c.vocab);
     const size_t NP = L.NP, VP = L.VP;
     L.sh_rows = stake(NP * 4); L.sh_tgt = stake(NP * 4); L.sh_r = stake(NP * H * E); L.sh_gl = stake(NP * H * E);
     L.sh_glp = stake(NP * H * E); L.sh_st = stake(2 * NP * 4); L.sh_t = stake(NP * H * E); L.sh_dz = stake(NP * VP * E);

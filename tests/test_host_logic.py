@@ -93,6 +93,29 @@ def test_sizes_scale_with_slots_only():
     assert a.n_params == 2 * (4 * (H * H + H) + 2 * H * F + F + H + 4 * H)
 
 
+def _workspaces(cfg):
+    """Micro-batches the arena holds a workspace for (rounded: the parts are aligned one by one)."""
+    q = B.stage_query_sizes(cfg)
+    return round((q.arena_bytes - q.grad_bytes - cfg.max_slots * q.slot_bytes) / q.workspace_bytes)
+
+
+@pytest.mark.parametrize("vocab,group", [(30522, 4), (131008, 4), (131072, 3), (200000, 2), (400000, 1)])
+def test_a_group_of_micro_batches_stays_addressable(vocab, group):
+    """The gradient of the logits of a group, 2048 rows a micro-batch: from 2 GiB on the matrix-core products no longer
+    address it, so the group must end below that."""
+    cfg = dry(4, n_layers=1, hidden=1024, n_heads=16, ffn=4096, seq=512, micro_batch=4, dtype=B.DTYPE_BF16,
+              has_mlm_head=1, vocab=vocab)
+    assert _workspaces(cfg) == group
+    assert group == 1 or group * 2048 * vocab * 2 < 2 ** 31
+    h = B.stage_init(cfg, None, None, 0)
+    try:
+        B.stage_run_schedule(h, 4, 4, B.ORDER_EARLY_BACKWARD)
+        st = B.stage_stats(h)
+        assert st.peak_live_slots == 4 and st.fwd_tasks == 4
+    finally:
+        B.stage_destroy(h)
+
+
 def test_slot_allocator_error_paths():
     h = B.stage_init(dry(2), None, None, 0)
     try:
