@@ -117,7 +117,8 @@ typedef struct {
                                the forward tasks' activation buffer under STAGE_FLAG_RECOMPUTE); copies = 2 under
                                STAGE_FLAG_RECOMPUTE (one workspace per backward lane), else, and under
                                STAGE_FLAG_ONE_STREAM, 1; group = the micro-batches
-                               one set of launches may cover (up to 8192 token rows, at most 8; 1 under
+                               one set of launches may cover (up to 8192 token rows, at most 8, no more than
+                               max_slots where that saves 2 MiB, every bf16 operand below 2 GiB; 1 under
                                STAGE_FLAG_RECOMPUTE and with one slot) */
 } stage_sizes;
 

@@ -224,40 +224,47 @@ void build_layout(const stage_config& c, Layout& L) {
     L.slot_bytes = so;
   }
 
+  // the workspace of G micro-batches: ws_stride bytes per lane, workspace_bytes with G = 1
+  auto lay_workspace = [&](size_t G) {
+    size_t wo = 0;
+    auto wtake = [&](size_t bytes) { size_t o = wo; wo += align_up(bytes * G); return o; };
+    L.ws_dx[0] = wtake(U); L.ws_dx[1] = wtake(U); L.ws_dy1 = wtake(U); L.ws_dctx = wtake(U);
+    // delta of the attention backward: [b, A, s], or one row sum per block of 32 columns, [ceil(H/32)][T]
+    L.ws_delta = wtake(std::max((size_t)c.micro_batch * c.n_heads * c.seq, (size_t)((c.hidden + 31) / 32) * T) * 4);
+    if (c.dtype == STAGE_DTYPE_BF16 && c.has_embedding)
+      for (int fs = 0; fs < (L.recompute ? 2 : 1); ++fs) L.ws_x0f[fs] = wtake(T * H * 4);
+    const size_t ln_part = ((T + 7) / 8) * 3 * H * 4;
+    L.ws_side.resize(c.n_layers);
+    for (auto& ss : L.ws_side) {
+      ss.dz2 = wtake(U); ss.du = wtake(T * F * E); ss.dz1 = wtake(U);
+      ss.dq = wtake(U); ss.dk = wtake(U); ss.dv = wtake(U);
+      ss.part_ln2 = wtake(ln_part); ss.part_ln1 = wtake(ln_part);
+    }
+    if (c.has_mlm_head) {
+      const size_t NP = L.NP, VP = L.VP;
+      L.wh_logits = wtake(NP * VP * 4); L.wh_rowloss = wtake(NP * 4); L.wh_dt = wtake(NP * H * E);
+      L.wh_dgl = wtake(NP * H * E); L.wh_dh = wtake(NP * H * E); L.wh_dr = wtake(NP * H * E); L.wh_dyfull = wtake(U);
+      size_t lp = ((NP + 7) / 8) * 3 * H * 4, cp = ((NP + 63) / 64) * VP * 4;
+      // partial-sum buffers of their own: the LayerNorm backward writes its own on the backward stream while the side
+      // stream is still reducing a column sum
+      L.wh_part = wtake(lp); L.wh_part_cz = wtake(cp); L.wh_info = wtake(16);
+      if (L.recompute) { L.wh_logits2 = wtake(NP * VP * 4); L.wh_rowloss2 = wtake(NP * 4); L.wh_info2 = wtake(16); }
+    }
+    if (c.has_embedding) {
+      L.we_dx0 = wtake(U); L.we_de = wtake(U); L.we_part = wtake(ln_part);
+    }
+    if (L.recompute) {
+      L.ws_act = wtake(L.act_bytes); L.ws_ydummy = wtake(U);
+    }
+    return wo;
+  };
+  L.workspace_bytes = lay_workspace(1);
+  // A group holds no more micro-batches than there are slots.  (What that saves must be worth more than 2 MiB, the unit
+  // device memory comes in: below it the arena grows by slot_bytes per slot and nothing else.)
   L.group = group_limit(c);
-  const size_t G = L.group;
-  size_t wo = 0, w1 = 0;
-  auto wtake = [&](size_t bytes) { size_t o = wo; wo += align_up(bytes * G); w1 += align_up(bytes); return o; };
-  L.ws_dx[0] = wtake(U); L.ws_dx[1] = wtake(U); L.ws_dy1 = wtake(U); L.ws_dctx = wtake(U);
-  // delta of the attention backward: [b, A, s], or one row sum per block of 32 columns, [ceil(H/32)][T]
-  L.ws_delta = wtake(std::max((size_t)c.micro_batch * c.n_heads * c.seq, (size_t)((c.hidden + 31) / 32) * T) * 4);
-  if (c.dtype == STAGE_DTYPE_BF16 && c.has_embedding)
-    for (int fs = 0; fs < (L.recompute ? 2 : 1); ++fs) L.ws_x0f[fs] = wtake(T * H * 4);
-  const size_t ln_part = ((T + 7) / 8) * 3 * H * 4;
-  L.ws_side.resize(c.n_layers);
-  for (auto& ss : L.ws_side) {
-    ss.dz2 = wtake(U); ss.du = wtake(T * F * E); ss.dz1 = wtake(U);
-    ss.dq = wtake(U); ss.dk = wtake(U); ss.dv = wtake(U);
-    ss.part_ln2 = wtake(ln_part); ss.part_ln1 = wtake(ln_part);
-  }
-  if (c.has_mlm_head) {
-    const size_t NP = L.NP, VP = L.VP;
-    L.wh_logits = wtake(NP * VP * 4); L.wh_rowloss = wtake(NP * 4); L.wh_dt = wtake(NP * H * E);
-    L.wh_dgl = wtake(NP * H * E); L.wh_dh = wtake(NP * H * E); L.wh_dr = wtake(NP * H * E); L.wh_dyfull = wtake(U);
-    size_t lp = ((NP + 7) / 8) * 3 * H * 4, cp = ((NP + 63) / 64) * VP * 4;
-    // partial-sum buffers of their own: the LayerNorm backward writes its own on the backward stream while the side
-    // stream is still reducing a column sum
-    L.wh_part = wtake(lp); L.wh_part_cz = wtake(cp); L.wh_info = wtake(16);
-    if (L.recompute) { L.wh_logits2 = wtake(NP * VP * 4); L.wh_rowloss2 = wtake(NP * 4); L.wh_info2 = wtake(16); }
-  }
-  if (c.has_embedding) {
-    L.we_dx0 = wtake(U); L.we_de = wtake(U); L.we_part = wtake(ln_part);
-  }
-  if (L.recompute) {
-    L.ws_act = wtake(L.act_bytes); L.ws_ydummy = wtake(U);
-  }
-  L.workspace_bytes = w1;
-  L.ws_stride = wo;
+  const int slots = std::min(L.group, c.max_slots);
+  if ((L.group - slots) * L.workspace_bytes >= (2u << 20)) L.group = slots;
+  L.ws_stride = lay_workspace(L.group);
 
   L.grad_bytes = align_up(L.n_params * 4);
   L.arena_grads = 0;

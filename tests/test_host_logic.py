@@ -116,6 +116,12 @@ def test_a_group_of_micro_batches_stays_addressable(vocab, group):
         B.stage_destroy(h)
 
 
+@pytest.mark.parametrize("slots,group", [(1, 1), (2, 2), (4, 4), (7, 7), (8, 8), (12, 8)])
+def test_no_workspace_beyond_the_slots(slots, group):
+    # 1024 tokens a micro-batch: eight of them make the 8192 rows a group may have
+    assert _workspaces(dry(slots, n_layers=12, hidden=1024, n_heads=16, ffn=4096, seq=512, dtype=B.DTYPE_BF16)) == group
+
+
 def test_slot_allocator_error_paths():
     h = B.stage_init(dry(2), None, None, 0)
     try:
