@@ -100,10 +100,12 @@ struct Layout {
   size_t act_bytes = 0, st_x = 0, st_aux = 0, ws_act = 0, ws_ydummy = 0, arena_fwd_act = 0;
   // workspace (bytes)
   size_t ws_dx[2] = {0, 0}, ws_dy1 = 0, ws_dctx = 0, ws_delta = 0, ws_head = 0;
-  // what the side stream reads of a layer's backward (one set per layer: the backward chain of a task never
-  // waits for the side stream before its end)
+  // What the weight gradients of a layer's backward read: a set per layer where a side stream runs them (the backward
+  // chain of a task never waits for the side stream before its end), one for all layers where they stay on the task's
+  // stream.  Offsets inside a set of one micro-batch; a task over n of them takes n times each.
   struct SideSet { size_t dz2, du, dz1, dq, dk, dv, part_ln2, part_ln1; };
-  std::vector<SideSet> ws_side;
+  SideSet side_set;
+  size_t side_bytes = 0, ws_side = 0;   // of one micro-batch's set; where the sets begin
   size_t workspace_bytes = 0;   // of one micro-batch's task
   // Micro-batches whose tasks may go out as one set of launches (see stage_run_schedule); the workspace holds that
   // many: ws_stride bytes per lane
@@ -161,6 +163,24 @@ int group_limit(const stage_config& c) {
   while (g > 1 && c.dtype == STAGE_DTYPE_BF16 && g * widest * 2 > 0x7fffffffL - 4096) --g;
   return (int)g;
 }
+
+double layer_flops(const stage_config& c, int n) {   // a layer's forward over n micro-batches
+  const double T = (double)n * c.micro_batch * c.seq, H = c.hidden, F = c.ffn;
+  return 8.0 * T * H * H + 4.0 * T * H * F;
+}
+// Whether the weight gradients of tasks over n micro-batches stay on the task's own stream (units: compute units the
+// stream may use), by the matrix flops of a layer's forward; else they go to the side stream.  Below 6 GFLOP an event
+// per hand-over costs the host 2-5 us and the streams' kernels a wait, more than the overlap gives on launches of a few
+// us: 256-wide stage, 0.8 GFLOP, 470 us with streams, 330 without; 1024-wide, 3 GFLOP, 1133 / 1111, 13 GFLOP 1219 /
+// 1235.  (fp32 products take eight times as long.)  From 150 GFLOP on every bf16 product fills the chip, and two at a
+// time only take the caches from each other: 1024-wide, 103 GFLOP, 25.2 ms with the side stream, 25.7 without; 206
+// GFLOP 11.07 / 10.87; 2048-wide, 824 GFLOP, 20.7 / 18.9.
+bool small_tasks(const stage_config& c, int n) { return layer_flops(c, n) < (c.dtype == STAGE_DTYPE_BF16 ? 6e9 : 7.5e8); }
+bool full_tasks(const stage_config& c, int n, int units) {
+  return c.dtype == STAGE_DTYPE_BF16 && layer_flops(c, n) >= 1.5e11 * units / 256;
+}
+// the same for certain, whatever stream the stage is given
+bool one_stream(const stage_config& c, int n) { return (c.flags & STAGE_FLAG_ONE_STREAM) != 0 || full_tasks(c, n, 256); }
 
 void build_layout(const stage_config& c, Layout& L) {
   const size_t H = c.hidden, F = c.ffn, T = (size_t)c.micro_batch * c.seq, E = c.dtype == STAGE_DTYPE_BF16 ? 2 : 4;
@@ -234,11 +254,18 @@ void build_layout(const stage_config& c, Layout& L) {
     if (c.dtype == STAGE_DTYPE_BF16 && c.has_embedding)
       for (int fs = 0; fs < (L.recompute ? 2 : 1); ++fs) L.ws_x0f[fs] = wtake(T * H * 4);
     const size_t ln_part = ((T + 7) / 8) * 3 * H * 4;
-    L.ws_side.resize(c.n_layers);
-    for (auto& ss : L.ws_side) {
-      ss.dz2 = wtake(U); ss.du = wtake(T * F * E); ss.dz1 = wtake(U);
-      ss.dq = wtake(U); ss.dk = wtake(U); ss.dv = wtake(U);
-      ss.part_ln2 = wtake(ln_part); ss.part_ln1 = wtake(ln_part);
+    {
+      size_t so = 0;
+      auto take1 = [&](size_t bytes) { size_t o = so; so += align_up(bytes); return o; };
+      auto& ss = L.side_set;
+      ss.dz2 = take1(U); ss.du = take1(T * F * E); ss.dz1 = take1(U);
+      ss.dq = take1(U); ss.dk = take1(U); ss.dv = take1(U);
+      ss.part_ln2 = take1(ln_part); ss.part_ln1 = take1(ln_part);
+      L.side_bytes = so;
+      size_t sets = 0;
+      for (int n = 1; n <= (int)G; ++n) sets = std::max(sets, (size_t)n * (one_stream(c, n) ? 1 : c.n_layers));
+      L.ws_side = wo;
+      wo += so * sets;
     }
     if (c.has_mlm_head) {
       const size_t NP = L.NP, VP = L.VP;
@@ -329,18 +356,8 @@ struct dapple_stage {
   template <typename Fn>
   int run(int cls, double flops, Fn&& fn) { return run_on(cur, cls, flops, fn); }
 
-  // Whether the weight gradients of tasks over n micro-batches go to the side stream, by the matrix flops of a layer's
-  // forward.  Below 6 GFLOP an event per hand-over costs the host 2-5 us and the streams' kernels a wait, more than
-  // the overlap gives on launches of a few us: 256-wide stage, 0.8 GFLOP, 470 us with streams, 330 without; 1024-wide,
-  // 3 GFLOP, 1133 / 1111, 13 GFLOP 1219 / 1235.  (fp32 products take eight times as long.)  From 150 GFLOP on every
-  // bf16 product fills the chip, and two at a time only take the caches from each other: 1024-wide, 103 GFLOP, 25.2
-  // ms with the side stream, 25.7 without; 206 GFLOP 11.07 / 10.87; 2048-wide, 824 GFLOP, 20.7 / 18.9.
-  bool small_tasks(int n) const { return layer_flops(n) < (dt == DT_BF16 ? 6e9 : 7.5e8); }
-  bool full_tasks(int n) const { return dt == DT_BF16 && layer_flops(n) >= 1.5e11 * (units ? units : 256) / 256; }
-  double layer_flops(int n) const {
-    const double T = (double)n * cfg.micro_batch * cfg.seq, H = cfg.hidden, F = cfg.ffn;
-    return 8.0 * T * H * H + 4.0 * T * H * F;
-  }
+  bool small_tasks(int n) const { return ::small_tasks(cfg, n); }
+  bool full_tasks(int n) const { return ::full_tasks(cfg, n, units ? units : 256); }
   // main -> side: the side stream may start once the main stream has passed this point
   int fork(int layer, int which) {
     if (dry || side == cur) return STAGE_OK;
@@ -644,9 +661,12 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
   for (int l = cfg.n_layers - 1; l >= 0; --l) {
     const LayerParams& p = L.lp[l];
     const LayerStash& a = L.ls[l];
-    const Layout::SideSet& ss = L.ws_side[l];  // this layer's buffers that the side stream reads
-    char *dz2 = ws(ss.dz2), *du = ws(ss.du), *dz1 = ws(ss.dz1), *dq = ws(ss.dq), *dk = ws(ss.dk), *dv = ws(ss.dv);
-    float *part_ln2 = (float*)ws(ss.part_ln2), *part_ln1 = (float*)ws(ss.part_ln1);
+    // what the weight gradients read: one set for all layers where they are on this stream too
+    const Layout::SideSet& ss = L.side_set;
+    char* const set = ws(L.ws_side) + (side == cur ? 0 : (size_t)l) * n * L.side_bytes;
+    char *dz2 = set + n * ss.dz2, *du = set + n * ss.du, *dz1 = set + n * ss.dz1, *dq = set + n * ss.dq, *dk = set + n * ss.dk,
+         *dv = set + n * ss.dv;
+    float *part_ln2 = (float*)(set + n * ss.part_ln2), *part_ln1 = (float*)(set + n * ss.part_ln1);
     const char* xl = l == 0 ? sl(L.slot_x0) : sl(L.ls[l - 1].y);
     char *ctx = sl(a.ctx), *z1 = sl(a.z1), *y1 = sl(a.y1), *gp = sl(a.gp), *g = sl(a.g), *z2 = sl(a.z2);
     float *lse = (float*)sl(a.lse), *st1 = (float*)sl(a.st1), *st2 = (float*)sl(a.st2);
@@ -746,7 +766,7 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
         GemmArgs ga{};
         ga.A = dq + r; ga.lda = H; ga.B = w(p.Wq); ga.ldb = H; ga.aux = dz1 + r; ga.ldaux = H;
         ga.C = out; ga.ldc = H; ga.M = c * T1; ga.N = H; ga.K = 3 * H; ga.kseg_len = H;
-        ga.segA = (long)((ss.dk - ss.dq) / E()); ga.segB = (long)pstride; ga.epi = EPI_ADD;
+        ga.segA = (long)((dk - dq) / (long)E()); ga.segB = (long)pstride; ga.epi = EPI_ADD;
         return gemm(KC_GEMM_DGRAD, ga);
       };
       if (l == 0 && !cfg.has_embedding) {   // to the caller's buffers
