@@ -162,21 +162,21 @@ int stage_schedule_ops(int M, int K, int order, int32_t* ops_out, int capacity);
  * order EXPLICIT takes explicit_ops/n_ops in the encoding above; the list is
  * validated (each F before its B, every micro-batch once, at most K resident)
  * before anything is enqueued.
- * The early-backward order is executed as the dependence graph that defines it
- * (the control edges B_m -> F_{m+K} of section V-C plus F_m -> B_m, forwards in
- * list order): forward tasks go to the library's forward stream, backward tasks
- * alternate between the caller's stream and a second backward stream (each with
- * its own workspace), and every gradient-accumulator update of every backward task
- * goes to the one side stream in list order, which fixes the order of every sum.
- * In both built-in orders neighbouring tasks of one kind go out together where their slots lie side by side: one set of
- * launches over the rows of several micro-batches (as many as divide the resident count and make up to 8192 rows);
- * at most K micro-batches are resident as before, and every accumulator gets each micro-batch's sum on its own, in
- * list order.  Buffers of consecutive micro-batches that lie one behind the other (xs[m+1] = xs[m] + b*s*H, likewise
- * ys, dys, dxs, auxs) save a few launches at the ends of the stage.
- * The GPipe order alternates its backward tasks the same way but starts none before
- * the last forward listed before it has finished; an explicit list keeps one backward
- * stream and the same rule.  Results do not depend on the overlap: they are the same
- * bits as with STAGE_FLAG_ONE_STREAM. */
+ * Both built-in orders are executed as the dependence graphs that define them (F_m -> B_m, the control edges
+ * B_m -> F_{m+K} of section V-C, forwards in list order, backwards in list order): neighbouring tasks of one kind go
+ * out together as one set of launches over the rows of several micro-batches (up to 8192 rows and at most eight
+ * micro-batches; the K resident ones are cut into runs of that many slots and a shorter one).  At most K micro-batches
+ * are resident as before, and every accumulator gets each micro-batch's sum on its own, in list order.  Buffers of
+ * consecutive micro-batches that lie one behind the other (xs[m+1] = xs[m] + b*s*H, likewise ys, dys, dxs, auxs) save a
+ * few launches at the ends of the stage.  Weight gradients go to the library's side stream where that pays (between 6
+ * and 150 GFLOP a layer and task).  An explicit list is run task by task, as listed.
+ * Under STAGE_FLAG_RECOMPUTE a task is one micro-batch, and tasks overlap instead: forward tasks go to the library's
+ * forward stream, backward tasks alternate between the caller's stream and a second backward stream (each with its own
+ * workspace), and every gradient-accumulator update goes to the side stream in list order.  The GPipe order starts no
+ * backward before the last forward listed before it has finished; an explicit list keeps one backward stream and the
+ * same rule.
+ * Results do not depend on groups or overlap: they are the same bits task by task (stage_fwd, stage_bwd) and with
+ * STAGE_FLAG_ONE_STREAM. */
 int stage_run_schedule(stage_handle h, int M, int K, int order,
                        const void* const* xs, const void* const* dys,
                        void* const* ys, void* const* dxs, const void* const* auxs,

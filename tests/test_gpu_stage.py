@@ -457,6 +457,16 @@ def test_groups_of_micro_batches_change_no_bit(kind, M, K, order):
     groups_against_tasks(cfg, M, K, B.ORDER_GPIPE if order == "gpipe" else B.ORDER_EARLY_BACKWARD)
 
 
+@pytest.mark.parametrize("kind", ["middle", "first", "last", "f32"])
+@pytest.mark.parametrize("M,K,order", [(20, 9, "early"), (23, 11, "early"), (11, 11, "gpipe")])
+def test_uneven_groups_change_no_bit(kind, M, K, order):
+    """More resident micro-batches than a group takes (eight), in runs of slots of different length: 8 + 1 and 8 + 3, a
+    short last group."""
+    cfg = I.StageConfig(1, 128, 2, 256, 20, 2, M, K, "f32" if kind == "f32" else "bf16", has_embedding=kind == "first",
+                        has_mlm_head=kind == "last", vocab=200, max_pos=64)
+    groups_against_tasks(cfg, M, K, B.ORDER_GPIPE if order == "gpipe" else B.ORDER_EARLY_BACKWARD)
+
+
 @pytest.mark.parametrize("H,dtype", [(384, "bf16"), (512, "bf16"), (1024, "bf16"), (1024, "f32")])
 def test_weight_gradients_over_three_micro_batches(H, dtype):
     """The weight gradients of a group in one launch, at the widths that take each of its tile shapes: every

@@ -186,6 +186,29 @@ def test_peak_is_K_for_early_backward_and_M_for_gpipe(M, K):
         B.stage_destroy(h)
 
 
+@pytest.mark.parametrize("M,K,order,groups", [
+    (10, 5, "early", 4), (14, 7, "early", 4), (9, 3, "early", 3), (8, 4, "early", 2), (11, 5, "early", 5),
+    (4, 5, "early", 1), (9, 9, "gpipe", 3), (7, 1, "early", 7),
+])
+def test_resident_counts_that_a_group_does_not_divide(M, K, order, groups):
+    """2048 tokens a micro-batch, four of them to a group: any resident count is served by full groups and a smaller
+    one, K micro-batches resident at most and every one forward and backward once."""
+    cfg = dry(max(M, K), n_layers=1, hidden=1024, n_heads=16, ffn=4096, seq=512, micro_batch=4, dtype=B.DTYPE_BF16)
+    h = B.stage_init(cfg, None, None, 0)
+    try:
+        B.stage_reset_stats(h)
+        B.stage_run_schedule(h, 1, 1, B.ORDER_EARLY_BACKWARD)
+        one = B.stage_stats(h).kernel_launches
+        B.stage_reset_stats(h)
+        B.stage_run_schedule(h, M, K, B.ORDER_GPIPE if order == "gpipe" else B.ORDER_EARLY_BACKWARD)
+        st = B.stage_stats(h)
+        assert st.kernel_launches == groups * one
+        assert st.peak_live_slots == (M if order == "gpipe" else min(K, M))
+        assert st.fwd_tasks == M and st.bwd_tasks == M and st.live_slots == 0
+    finally:
+        B.stage_destroy(h)
+
+
 def test_run_schedule_rejects_bad_orders_before_running_anything():
     h = B.stage_init(dry(2), None, None, 0)
     try:
