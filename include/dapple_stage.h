@@ -170,6 +170,9 @@ int stage_schedule_ops(int M, int K, int order, int32_t* ops_out, int capacity);
  * consecutive micro-batches that lie one behind the other (xs[m+1] = xs[m] + b*s*H, likewise ys, dys, dxs, auxs) save a
  * few launches at the ends of the stage.  Weight gradients go to the library's side stream where that pays (between 6
  * and 150 GFLOP a layer and task).  An explicit list is run task by task, as listed.
+ * Buffers of different tasks may overlap (ys[m] as xs[m+1], a ring of ys): every task then finds what the tasks listed
+ * before it left, and a call whose groups would show is run task by task.  (Not so between a forward and the backward of
+ * another micro-batch under STAGE_FLAG_RECOMPUTE, where the two may overlap in time.)
  * Under STAGE_FLAG_RECOMPUTE a task is one micro-batch, and tasks overlap instead: forward tasks go to the library's
  * forward stream, backward tasks alternate between the caller's stream and a second backward stream (each with its own
  * workspace), and every gradient-accumulator update goes to the side stream in list order.  The GPipe order starts no

@@ -1094,6 +1094,27 @@ static int make_groups(int M, int R, int order, int g, std::vector<TaskGroup>& o
   return STAGE_OK;
 }
 
+// A caller's buffer, used by the task at place `task` of the list
+struct Span {
+  const char *begin, *end;
+  int task;
+  bool write;
+};
+// Whether the groups leave every task the values that the list in its own order would: buffers of different tasks may
+// overlap (the output of F_m the input of F_{m+1}, say).  A group reads all its micro-batches' inputs before it writes
+// the first output, and moves tasks against those of the other kind.  group_of[task]: place of the group.
+static bool groups_keep_order(std::vector<Span>& spans, const std::vector<int>& group_of) {
+  std::sort(spans.begin(), spans.end(), [](const Span& a, const Span& b) { return a.begin < b.begin; });
+  for (size_t i = 0; i < spans.size(); ++i)
+    for (size_t j = i + 1; j < spans.size() && spans[j].begin < spans[i].end; ++j) {
+      const Span &p = spans[i].task < spans[j].task ? spans[i] : spans[j], &q = &p == &spans[i] ? spans[j] : spans[i];
+      if (p.task == q.task || !(p.write || q.write)) continue;
+      const int gp = group_of[p.task], gq = group_of[q.task];
+      if (gp > gq || (gp == gq && p.write && !q.write)) return false;
+    }
+  return true;
+}
+
 static int ensure_lanes(stage_handle h) {
   if (h->fwd) return STAGE_OK;
   hipError_t e = make_lane(h->st, &h->fwd);
@@ -1132,11 +1153,29 @@ int stage_run_schedule(stage_handle h, int M, int K, int order, const void* cons
   // Groups.  The micro-batches of a call are all given at its start, so neighbouring tasks of one kind whose slots lie
   // side by side go out as ONE set of launches over all their rows.  The dependences are the lists': F_m before B_m,
   // B_m before the forward that reuses its slot, forwards in order, backwards in order; an accumulator gets every
-  // micro-batch's sum on its own, in list order, so no bit depends on the groups.  An explicit list is run task by task.
+  // micro-batch's sum on its own, in list order, so no bit depends on the groups.  An explicit list is run task by task,
+  // and so is a call whose buffers overlap in a way that groups would show.
   std::vector<TaskGroup> groups;
   if (order != STAGE_ORDER_EXPLICIT && h->L.group > 1) {
     TRY(make_groups(M, limit, order, h->L.group, groups));
-  } else {
+    std::vector<int> group_of(ops.size()), fwd_at(M), bwd_at(M);
+    for (size_t i = 0; i < ops.size(); ++i) (ops[i] > 0 ? fwd_at[ops[i] - 1] : bwd_at[-ops[i] - 1]) = (int)i;
+    for (size_t g = 0; g < groups.size(); ++g)
+      for (int m = groups[g].m0; m < groups[g].m0 + groups[g].n; ++m) group_of[(groups[g].kind == 0 ? fwd_at : bwd_at)[m]] = (int)g;
+    const size_t T = (size_t)h->cfg.micro_batch * h->cfg.seq, act = T * h->cfg.hidden * h->E();
+    std::vector<Span> spans;
+    spans.reserve(5 * (size_t)M);
+    auto add = [&](const void* const* p, const std::vector<int>& at, size_t bytes, bool write) {
+      for (int m = 0; p && m < M; ++m) spans.push_back(Span{(const char*)p[m], (const char*)p[m] + bytes, at[m], write});
+    };
+    add(xs, fwd_at, h->cfg.has_embedding ? T * 4 : act, false);
+    add(ys, fwd_at, h->cfg.has_mlm_head ? 4 : act, true);
+    if (h->cfg.has_mlm_head) add(auxs, fwd_at, T * 4, false);
+    else add(dys, bwd_at, act, false);
+    if (!h->cfg.has_embedding) add(dxs, bwd_at, act, true);
+    if (!groups_keep_order(spans, group_of)) groups.clear();
+  }
+  if (groups.empty()) {
     for (int32_t op : ops) groups.push_back(TaskGroup{op > 0 ? 0 : 1, (op > 0 ? op : -op) - 1, 1, -1});
   }
   int G = 1;   // the largest

@@ -467,6 +467,37 @@ def test_uneven_groups_change_no_bit(kind, M, K, order):
     groups_against_tasks(cfg, M, K, B.ORDER_GPIPE if order == "gpipe" else B.ORDER_EARLY_BACKWARD)
 
 
+@pytest.mark.parametrize("order", [B.ORDER_EARLY_BACKWARD, B.ORDER_GPIPE])
+def test_outputs_that_are_the_next_inputs(order):
+    """ys[m] is xs[m+1] and dxs[m] is dys[m+1]: the same numbers as task by task, the tasks called one after the other."""
+    M, K = 4, 4
+    cfg = I.StageConfig(1, 128, 2, 256, 60, 2, M, K, "bf16")
+    theta, mbs = make_inputs(cfg, SEED, 1)
+    T, H = cfg.tokens, cfg.hidden
+    out = []
+    for driven in (False, True):
+        r = B.StageRunner(c_config(cfg, K), theta)
+        try:
+            x, d = (torch.zeros(M + 1, T, H, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+            x[0], d[0] = r.to_dev(mbs[0]["x"].reshape(T, H)), r.to_dev(mbs[0]["dy"].reshape(T, H))
+            torch.cuda.synchronize()
+            p = lambda t: [t[m].data_ptr() for m in range(M + 1)]
+            if driven:
+                for kind, m in B.stage_schedule_ops(M, K, order):
+                    if kind == "F":
+                        B.stage_fwd(r.h, m, p(x)[m], p(x)[m + 1])
+                    else:
+                        B.stage_bwd(r.h, m, p(d)[m], p(d)[m + 1])
+            else:
+                B.stage_run_schedule(r.h, M, K, order, p(x)[:M], p(d)[:M], p(x)[1:], p(d)[1:])
+            B.stage_sync(r.h)
+            out.append((to_np(x), to_np(d), r.grads.cpu().numpy().copy()))
+        finally:
+            r.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
+    assert np.linalg.norm(out[0][0][M]) > 0
+
+
 @pytest.mark.parametrize("H,dtype", [(384, "bf16"), (512, "bf16"), (1024, "bf16"), (1024, "f32")])
 def test_weight_gradients_over_three_micro_batches(H, dtype):
     """The weight gradients of a group in one launch, at the widths that take each of its tile shapes: every

@@ -209,6 +209,41 @@ def test_resident_counts_that_a_group_does_not_divide(M, K, order, groups):
         B.stage_destroy(h)
 
 
+def _launches_with_buffers(M, K, xs, dys, ys, dxs, order=B.ORDER_EARLY_BACKWARD):
+    """Launches of an iteration whose buffers lie at the given places of one address range (a dry run: no buffer is
+    touched), 2048 x 1024 bf16 a micro-batch, four micro-batches to a group."""
+    cfg = dry(max(M, K), n_layers=1, hidden=1024, n_heads=16, ffn=4096, seq=512, micro_batch=4, dtype=B.DTYPE_BF16)
+    at = lambda places: [(1 << 40) + int(p * 2048 * 1024 * 2) for p in places]
+    h = B.stage_init(cfg, None, None, 0)
+    try:
+        B.stage_reset_stats(h)
+        B.stage_run_schedule(h, M, K, order, at(xs), at(dys), at(ys), at(dxs))
+        return B.stage_stats(h).kernel_launches
+    finally:
+        B.stage_destroy(h)
+
+
+def test_overlapping_buffers_are_not_grouped_across_a_dependence():
+    M, K = 8, 4
+    n = lambda first: list(range(first, first + M))
+    base = dict(xs=n(0), dys=n(10), ys=n(20), dxs=n(30))
+    one = _launches_with_buffers(1, 1, [0], [10], [20], [30])
+    run = lambda **kw: _launches_with_buffers(M, K, **{**base, **kw}) // one
+    assert run() == 2                                        # two groups of four
+    # the output of a forward is the input of the next one; of a backward, of the next one; partly
+    assert run(ys=n(1)) == M and run(dxs=n(11)) == M and run(ys=[v + 0.75 for v in n(0)]) == M
+    # what groups cannot show: in place, all outputs in one buffer, all inputs in one buffer, the output as its own
+    # gradient, a ring of K outputs, an output that replaces an input read before it
+    assert run(ys=n(0)) == 2 and run(dxs=n(10)) == 2 and run(ys=[20] * M, dxs=[30] * M) == 2 and run(xs=[0] * M) == 2
+    assert run(ys=n(10)) == 2 and run(ys=[10 + m % K for m in range(M)], dys=[10 + m % K for m in range(M)]) == 2
+    assert run(ys=[v - 1 for v in n(0)]) == 2
+    # F_5 is listed before B_2 and overwrites what that one reads: grouped, it would come after
+    assert run(ys=n(20)[:4] + [11] + n(20)[5:]) == M
+    # the GPipe order has no such pair, but the chain of forwards
+    gp = lambda **kw: _launches_with_buffers(M, K, **{**base, **kw}, order=B.ORDER_GPIPE) // one
+    assert gp() == 2 and gp(ys=n(1)) == M and gp(ys=n(20)[:4] + [11] + n(20)[5:]) == 2
+
+
 def test_run_schedule_rejects_bad_orders_before_running_anything():
     h = B.stage_init(dry(2), None, None, 0)
     try:
