@@ -123,10 +123,11 @@ __global__ void attn_bwd_plain(AttnArgs a, float scale2, float scale, int which)
 // D: width of a head's block in LDS and registers (32, 64 or 128; a head of d <= D columns is padded with zeros).
 // RAG: some edge is ragged -- s is no multiple of 64 or d is smaller than D: rows and columns outside are read as
 //      zeros, their probabilities are zero, and nothing outside is stored.
-// HL:  the probabilities and dS enter their products as a sum of two bf16 values (high and low half), so that they
-//      count with 16 significant bits; otherwise they are rounded to bf16 once.  (D = 64 with s % 64 == 0 rounds
-//      once; every other shape was served by fp32 arithmetic before it had MFMA kernels and keeps that accuracy.
-//      The extra MFMAs ride in the shadow of the exponentials: the matrix pipe is busy 13% of these kernels.)
+// P32: the probabilities and dS enter their products as a sum of three bf16 values, which holds all 24 bits of an fp32
+//      one; otherwise they are rounded to bf16 once.  (D = 64 with s % 64 == 0 rounds once; every other shape was served
+//      by fp32 arithmetic before it had MFMA kernels and keeps it, the library's exp2f with its denormal results too.
+//      Against two bf16 values, 16 bits, it costs 1-3% of an iteration: 4 layers of 768, 3 x 200 tokens, 6 micro-batches
+//      1.94 -> 1.99 ms, 2 layers of 1024 with heads of 128, 2 x 256 tokens, 4 micro-batches 0.666 -> 0.673.)
 
 // A 64 x D bf16 block sits in LDS as 64 rows of D/8 16-byte chunks, the chunks of row r XOR-swizzled by aswz(r).
 // The same block is read two ways -- 128-bit reads along a row (16 lanes = 16 rows at a time) and transpose reads
@@ -282,12 +283,14 @@ __device__ __forceinline__ bf16x8 acc_to_operand(const float (&p)[16], int ks) {
   for (int e = 0; e < 8; ++e) f[e] = (bf16)p[8 * ks + e];
   return f;
 }
-// what rounding to bf16 left of them
-__device__ __forceinline__ bf16x8 acc_to_operand_low(const float (&p)[16], bf16x8 hi, int ks) {
-  bf16x8 f;
+// what rounding to bf16 left of them, as two more bf16 values (both differences are exact)
+__device__ __forceinline__ void acc_to_operand_rest(const float (&p)[16], bf16x8 hi, int ks, bf16x8& mid, bf16x8& lo) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) f[e] = (bf16)(p[8 * ks + e] - (float)hi[e]);
-  return f;
+  for (int e = 0; e < 8; ++e) {
+    const float r = p[8 * ks + e] - (float)hi[e];
+    mid[e] = (bf16)r;
+    lo[e] = (bf16)(r - (float)mid[e]);
+  }
 }
 
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0)
@@ -306,9 +309,35 @@ __device__ __forceinline__ float delta_at(const AttnArgs& a, int bi, int hh, int
   return a.delta[((long)bi * a.A + hh) * a.s + qi];
 }
 
-// 2^x for x <= 0 as the bare v_exp_f32: the library exp2f wraps it in three more instructions that
-// rescale denormal results, and a probability below 2^-126 may as well be zero
-__device__ __forceinline__ float exp2_neg(float x) { return __builtin_amdgcn_exp2f(x); }
+// 2^x of every element.  Where a probability is rounded to bf16 anyway (P32 unset) the bare v_exp_f32: one below 2^-126
+// may as well be zero there.  Otherwise the library's exp2f, which wraps it in four more instructions that scale denormal
+// results -- and gives its bits where there are none, so they are spent only where an element of the wave needs them
+// (2 layers of 768, heads of 32, 4 x 256 tokens, 4 micro-batches: 0.865 ms with exp2f always, 0.841 so).
+// CHECK unset: spent always, where the check's registers would spill (the backward of 64-wide heads).
+template <bool P32, bool CHECK, int N>
+__device__ __forceinline__ void exp2_all(float (&x)[N]) {
+  if constexpr (P32 && !CHECK) {
+#pragma unroll
+    for (int v = 0; v < N; ++v) x[v] = exp2f(x[v]);
+    return;
+  }
+  if constexpr (P32) {
+    float least = x[0];
+#pragma unroll
+    for (int v = 1; v < N; ++v) least = fminf(least, x[v]);
+    if (__builtin_amdgcn_ballot_w64(least < -126.f)) {
+#pragma unroll
+      for (int v = 0; v < N; ++v) x[v] = exp2f(x[v]);
+      return;
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < N; ++v) x[v] = __builtin_amdgcn_exp2f(x[v]);
+}
+template <bool P32>
+__device__ __forceinline__ float exp2_of(float x) {
+  return P32 ? exp2f(x) : __builtin_amdgcn_exp2f(x);
+}
 
 // max / sum of the two half waves' values (a row's 64 keys sit in lanes l and l + 32), in both; v_permlane32_swap is an
 // ordinary vector instruction where a shuffle is a trip through the LDS crossbar
@@ -329,7 +358,7 @@ __device__ __forceinline__ f32x16 zero16() {
 }
 
 // NW: waves per workgroup (4, or 2 where the grid is small), each with 32 query rows
-template <int D, bool RAG, bool HL, int NW>
+template <int D, bool RAG, bool P32, int NW>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnArgs a, float scale2) {
   constexpr int NKK = D / 16, NDB = D / 32;
   typedef Ring<D, NW, D == 128 ? 2 : 3, false> R;
@@ -403,15 +432,16 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
     }
     // the maximum is taken over the raw products (the scale is positive): one multiply-add per logit, not two steps
     const float mn = fmaxf(m, halves_max(mx) * scale2);
-    const float alpha = exp2_neg(m - mn);
+    const float alpha = exp2_of<P32>(m - mn);
     float rs = 0.f;
 #pragma unroll
-    for (int kb2 = 0; kb2 < 2; ++kb2)
+    for (int kb2 = 0; kb2 < 2; ++kb2) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        p[kb2][v] = exp2_neg(fmaf(p[kb2][v], scale2, -mn));
-        rs += p[kb2][v];
-      }
+      for (int v = 0; v < 16; ++v) p[kb2][v] = fmaf(p[kb2][v], scale2, -mn);
+      exp2_all<P32, true>(p[kb2]);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) rs += p[kb2][v];
+    }
     l = l * alpha + halves_sum(rs);
     m = mn;
     // the running maximum of most rows settles after the first key blocks: skip the rescale of
@@ -431,8 +461,11 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
       }
 #pragma unroll
       for (int db = 0; db < NDB; ++db) o[db] = MFMA(vf[ks][db], pf, o[db]);
-      if (HL) {
-        const bf16x8 pl = acc_to_operand_low(p[ks >> 1], pf, ks & 1);
+      if (P32) {
+        bf16x8 pm, pl;
+        acc_to_operand_rest(p[ks >> 1], pf, ks & 1, pm, pl);
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) o[db] = MFMA(vf[ks][db], pm, o[db]);
 #pragma unroll
         for (int db = 0; db < NDB; ++db) o[db] = MFMA(vf[ks][db], pl, o[db]);
       }
@@ -462,7 +495,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
 
 // dk, dv: the wave owns 32 key rows; query blocks of 64 stream through LDS with their lse and delta (the two blocks
 // of 32 columns a head of 64 has are added where they are read)
-template <int D, bool RAG, bool HL, int NW, typename R>
+template <int D, bool RAG, bool P32, int NW, typename R>
 __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, float scale, const unsigned char* sm) {
   constexpr int NKK = D / 16, NDB = D / 32;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
@@ -544,14 +577,16 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
       float p[16], ds[16];
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk) {
-        float4 L4 = L4s[blk], D4 = D4s[blk];
-        float Lv[4] = {L4.x, L4.y, L4.z, L4.w}, Dv[4] = {D4.x, D4.y, D4.z, D4.w};
+        const float Lv[4] = {L4s[blk].x, L4s[blk].y, L4s[blk].z, L4s[blk].w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float pv = exp2_neg(fmaf(sa[4 * blk + e], scale2, -Lv[e]));
-          p[4 * blk + e] = pv;
-          ds[4 * blk + e] = pv * (dp[4 * blk + e] - Dv[e]);
-        }
+        for (int e = 0; e < 4; ++e) p[4 * blk + e] = fmaf(sa[4 * blk + e], scale2, -Lv[e]);
+      }
+      exp2_all<P32, D != 64>(p);
+#pragma unroll
+      for (int blk = 0; blk < 4; ++blk) {
+        const float Dv[4] = {D4s[blk].x, D4s[blk].y, D4s[blk].z, D4s[blk].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ds[4 * blk + e] = p[4 * blk + e] * (dp[4 * blk + e] - Dv[e]);
       }
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
@@ -561,8 +596,15 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
           dv[db] = MFMA(gc[ks][db], pf, dv[db]);
           dk[db] = MFMA(qc[ks][db], dsf, dk[db]);
         }
-        if (HL) {
-          const bf16x8 pl = acc_to_operand_low(p, pf, ks), dsl = acc_to_operand_low(ds, dsf, ks);
+        if (P32) {
+          bf16x8 pm, pl, dsm, dsl;
+          acc_to_operand_rest(p, pf, ks, pm, pl);
+          acc_to_operand_rest(ds, dsf, ks, dsm, dsl);
+#pragma unroll
+          for (int db = 0; db < NDB; ++db) {
+            dv[db] = MFMA(gc[ks][db], pm, dv[db]);
+            dk[db] = MFMA(qc[ks][db], dsm, dk[db]);
+          }
 #pragma unroll
           for (int db = 0; db < NDB; ++db) {
             dv[db] = MFMA(gc[ks][db], pl, dv[db]);
@@ -595,7 +637,7 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
 }
 
 // dq: the wave owns 32 query rows; key blocks of 64 stream through LDS
-template <int D, bool RAG, bool HL, int NW, typename R>
+template <int D, bool RAG, bool P32, int NW, typename R>
 __device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, float scale, const unsigned char* sm) {
   constexpr int NKK = D / 16, NDB = D / 32;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
@@ -655,8 +697,11 @@ __device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, fl
       __builtin_amdgcn_sched_barrier(0);
       float ds[16];
 #pragma unroll
+      for (int v = 0; v < 16; ++v) ds[v] = fmaf(sa[v], scale2, -Lq);
+      exp2_all<P32, D != 64>(ds);
+#pragma unroll
       for (int v = 0; v < 16; ++v) {
-        ds[v] = exp2_neg(fmaf(sa[v], scale2, -Lq)) * (dp[v] - Dq);
+        ds[v] *= dp[v] - Dq;
         // a key beyond the last: its logit 0 may lie far above the row's logsumexp, so it is masked, not multiplied away
         if (RAG && kb * 64 + kb2 * 32 + 8 * (v >> 2) + 4 * h + (v & 3) >= a.s) ds[v] = 0.f;
       }
@@ -665,8 +710,11 @@ __device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, fl
         bf16x8 dsf = acc_to_operand(ds, ks);
 #pragma unroll
         for (int db = 0; db < NDB; ++db) dq[db] = MFMA(kc[ks][db], dsf, dq[db]);
-        if (HL) {
-          const bf16x8 dsl = acc_to_operand_low(ds, dsf, ks);
+        if (P32) {
+          bf16x8 dsm, dsl;
+          acc_to_operand_rest(ds, dsf, ks, dsm, dsl);
+#pragma unroll
+          for (int db = 0; db < NDB; ++db) dq[db] = MFMA(kc[ks][db], dsm, dq[db]);
 #pragma unroll
           for (int db = 0; db < NDB; ++db) dq[db] = MFMA(kc[ks][db], dsl, dq[db]);
         }
@@ -726,12 +774,12 @@ template <int D, int NW>
 struct BwdRing {
   typedef Ring<D, NW, D == 128 ? 2 : 3, true> R;
 };
-template <int D, bool RAG, bool HL, int NW>
+template <int D, bool RAG, bool P32, int NW>
 __global__ __launch_bounds__(64 * NW, D <= 64 ? 2 : 1) void attn_bwd_mfma(AttnArgs a, float scale2, float scale) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char asm_[];
   typedef typename BwdRing<D, NW>::R R;
-  if (blockIdx.z == 0) attn_dq_body<D, RAG, HL, NW, R>(a, scale2, scale, asm_);
-  else attn_dkdv_body<D, RAG, HL, NW, R>(a, scale2, scale, asm_);
+  if (blockIdx.z == 0) attn_dq_body<D, RAG, P32, NW, R>(a, scale2, scale, asm_);
+  else attn_dkdv_body<D, RAG, P32, NW, R>(a, scale2, scale, asm_);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -746,7 +794,7 @@ bool attn_takes_delta_blocks(Dtype dt, const AttnArgs& a) {
   return attn_uses_mfma(dt, a) && (a.d == 32 || a.d == 64);
 }
 
-// f(D, RAG, HL, NW) as constants for the shape: the narrowest block that holds a head; workgroups of four waves (128
+// f(D, RAG, P32, NW) as constants for the shape: the narrowest block that holds a head; workgroups of four waves (128
 // rows), or of two where four would leave a quarter of the 256 units without one (one sample of 512 tokens, 16 heads:
 // 64 workgroups of four); roles: workgroups per block of rows (the backward has two)
 template <typename F>
@@ -754,9 +802,9 @@ static void pick_variant(const AttnArgs& a, int roles, F&& f) {
   typedef std::true_type T;
   typedef std::false_type N;
   const bool rag = a.s % 64 != 0;
-  auto waves = [&](auto D, auto RAG, auto HL) {
-    if ((long)((a.s + 127) / 128) * a.b * a.A * roles < 192) f(D, RAG, HL, std::integral_constant<int, 2>{});
-    else f(D, RAG, HL, std::integral_constant<int, 4>{});
+  auto waves = [&](auto D, auto RAG, auto P32) {
+    if ((long)((a.s + 127) / 128) * a.b * a.A * roles < 192) f(D, RAG, P32, std::integral_constant<int, 2>{});
+    else f(D, RAG, P32, std::integral_constant<int, 4>{});
   };
   if (a.d <= 32) {
     if (rag || a.d != 32) waves(std::integral_constant<int, 32>{}, T{}, T{});
@@ -774,9 +822,9 @@ hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
   float scale2 = LOG2E / sqrtf((float)a.d);
   if (attn_uses_mfma(dt, a)) {
     hipError_t e = hipSuccess;
-    pick_variant(a, 1, [&](auto D, auto RAG, auto HL, auto NW) {
+    pick_variant(a, 1, [&](auto D, auto RAG, auto P32, auto NW) {
       constexpr int d = decltype(D)::value, nw = decltype(NW)::value, lds = Ring<d, nw, d == 128 ? 2 : 3, false>::BYTES;
-      auto kern = attn_fwd_mfma<d, decltype(RAG)::value, decltype(HL)::value, nw>;
+      auto kern = attn_fwd_mfma<d, decltype(RAG)::value, decltype(P32)::value, nw>;
       static const hipError_t rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
       if ((e = rc) != hipSuccess) return;
       hipLaunchKernelGGL(kern, dim3((a.s + 32 * nw - 1) / (32 * nw), a.b * a.A), dim3(64 * nw), lds, st, a, scale2);
@@ -807,9 +855,9 @@ hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
-    pick_variant(a, 2, [&](auto D, auto RAG, auto HL, auto NW) {
+    pick_variant(a, 2, [&](auto D, auto RAG, auto P32, auto NW) {
       constexpr int d = decltype(D)::value, nw = decltype(NW)::value, lds = BwdRing<d, nw>::R::BYTES;
-      auto kern = attn_bwd_mfma<d, decltype(RAG)::value, decltype(HL)::value, nw>;
+      auto kern = attn_bwd_mfma<d, decltype(RAG)::value, decltype(P32)::value, nw>;
       static const hipError_t rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
       if ((e = rc) != hipSuccess) return;
       hipLaunchKernelGGL(kern, dim3((a.s + 32 * nw - 1) / (32 * nw), a.b * a.A, 2), dim3(64 * nw), lds, st, a, scale2, scale);

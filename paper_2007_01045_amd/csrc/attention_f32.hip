@@ -64,7 +64,6 @@ __device__ __forceinline__ void own_row(const float* row, bool ok, int d, int la
     if (ok && k < d) f[kk] = *(const f32x4*)(row + k);
   }
 }
-__device__ __forceinline__ float exp2_neg(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float over_groups_sum(float v) {   // the four lanes of one owned row, pairs first
   v += __shfl_xor(v, 16, 64);
   return v + __shfl_xor(v, 32, 64);
@@ -118,13 +117,13 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(AttnArgs a, float scale2) {
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float mn = fmaxf(m, mx), alpha = exp2_neg(m - mn);
+    const float mn = fmaxf(m, mx), alpha = exp2f(m - mn);
     float rs = 0.f;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        p[t][e] = exp2_neg(p[t][e] - mn);
+        p[t][e] = exp2f(p[t][e] - mn);
         rs += p[t][e];
       }
     l = l * alpha + over_groups_sum(rs);
@@ -205,7 +204,7 @@ __device__ __forceinline__ void dq_f32(const AttnArgs& a, float scale2, float sc
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        float ds = exp2_neg(s[e] * scale2 - Lq) * (dp[e] - Dq);
+        float ds = exp2f(s[e] * scale2 - Lq) * (dp[e] - Dq);
         if (k0 + 16 * t + 4 * g4 + e >= a.s) ds = 0.f;
 #pragma unroll
         for (int i = 0; i < NK; ++i) dq[i] = MFMA4(fcol<D>(Ks, 16 * i, 16 * t, e, lane), ds, dq[i]);
@@ -280,7 +279,7 @@ __device__ __forceinline__ void dkdv_f32(const AttnArgs& a, float scale2, float 
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         // a query beyond the last: zero rows, lse 0, delta 0 -- probability 1 times a zero row, dS = 0
-        const float p = exp2_neg(s[e] * scale2 - L4[e]), ds = p * (dp[e] - D4[e]);
+        const float p = exp2f(s[e] * scale2 - L4[e]), ds = p * (dp[e] - D4[e]);
 #pragma unroll
         for (int i = 0; i < NK; ++i) {
           dv[i] = MFMA4(fcol<D>(Gs, 16 * i, 16 * t, e, lane), p, dv[i]);

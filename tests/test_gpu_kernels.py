@@ -264,6 +264,96 @@ def test_attention_fp32_head_widths_and_ragged_lengths(d, s):
     attention_case(B.DTYPE_F32, 2, s, 3, d)
 
 
+def _bf16_parts(x):
+    """x as a sum of two bf16 values and what they leave."""
+    hi = I.round_to_bf16(np.float32(x).reshape(1)).astype(np.float64)[0]
+    lo = I.round_to_bf16(np.float32(x - hi).reshape(1)).astype(np.float64)[0]
+    return hi, lo, x - hi - lo
+
+
+@pytest.mark.parametrize("s,d", [(4, 8), (4, 32), (4, 64), (4, 128), (64, 32), (64, 128)])
+def test_attention_probabilities_keep_their_24_bits(s, d):
+    """Where the probabilities and dS are not rounded to bf16, outputs that cancel to what two bf16 values leave of one
+    of them must come out: ctx = p - hi - lo, dv and dk likewise.  Bound: 3 units of 2^-24, for the roundings of the
+    exponent, its exponential and the row's logsumexp in fp32; cut to 16 bits the outputs are off by 5 to 20 of them."""
+    ulp, L2E = 2.0 ** -24, 1.0 / math.log(2.0)
+    A = 8                                                    # heads: eight probabilities
+    H = A * d
+    z = lambda: np.zeros((1, s, A, d))
+    def fwd(q, k, v):
+        t = [dev(x.reshape(1, s, H), torch.bfloat16) for x in (q, k, v)]
+        ctx, lse = torch.empty(s, H, dtype=torch.bfloat16, device="cuda"), torch.empty(1, A, s, dtype=torch.float32, device="cuda")
+        B.dapple_attention_fwd(B.DTYPE_BF16, *(x.data_ptr() for x in t), ctx.data_ptr(), lse.data_ptr(), 1, s, A, H)
+        torch.cuda.synchronize()
+        return t, ctx, lse
+    scale = 1.0 / math.sqrt(d)
+    x = np.array([I.round_to_bf16(np.float32([0.31 + 0.13 * h]))[0] for h in range(A)], dtype=np.float64) * 2  # logit / scale
+    # forward: query 0 sees logit 0 at keys 0 and 2, -x scale at key 1, far below at the others
+    q, k, v, parts = z(), z(), z(), []
+    q[0, 0, :, 0] = 1.0
+    k[0, 1, :, 0] = -x
+    k[0, 3:, :, 0] = -60000.0
+    for h in range(A):
+        e = math.exp(-x[h] * scale)
+        hi, lo, rest = _bf16_parts(e)
+        v[0, 0, h, 0], v[0, 2, h, 0], v[0, 1, h, 0] = hi, lo, -1.0
+        parts.append(-rest / (2.0 + e))
+    _, ctx, _ = fwd(q, k, v)
+    got = to_np(ctx).reshape(s, A, d)[0, :, 0]
+    off = [np.abs(got - parts).max() / ulp]
+    # backward: query 0 sees logit 0 at keys 0, 2 and 3, -x scale at key 1; queries 1 and 2 see 1 / s everywhere.  v: +1
+    # at key 1, -1 at key 0, so that those two have delta 0 and dS = 1 / s at key 1.  Column 1 is not in the logits.
+    q, k, v, g = z(), z(), z(), z()
+    q[0, 0, :, 0] = 1.0
+    k[0, 1, :, 0] = -x
+    k[0, 4:, :, 0] = -60000.0
+    v[0, 1, :, 0], v[0, 0, :, 0] = 1.0, -1.0
+    _, ctx, lse = fwd(q, k, v)
+    c = to_np(ctx).reshape(s, A, d)
+    g[0, :3, :, 0] = 1.0
+    dv_ref, dk_ref = [], []
+    for h in range(A):
+        e = math.exp(-x[h] * scale)
+        P = e / (3.0 + e)
+        dS = P * (1.0 - c[0, h, 0])
+        hi, lo, rest = _bf16_parts(P)                        # dv of key 1, column 2
+        g[0, 0, h, 2], g[0, 1, h, 2], g[0, 2, h, 2] = -1.0, s * hi, s * lo
+        dv_ref.append(-rest)
+        hi, lo, rest = _bf16_parts(dS)                       # dk of key 1, column 1
+        q[0, 0, h, 1], q[0, 1, h, 1], q[0, 2, h, 1] = -1.0, s * hi, s * lo
+        dk_ref.append(-rest)
+    (tq, tk, tv), ctx, lse = fwd(q, k, v)
+    tg = dev(g.reshape(1, s, H), torch.bfloat16)
+    gq, gk, gv = (torch.empty(s, H, dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    delta = torch.empty(1, A, s, dtype=torch.float32, device="cuda")
+    B.dapple_attention_bwd(B.DTYPE_BF16, tq.data_ptr(), tk.data_ptr(), tv.data_ptr(), ctx.data_ptr(), lse.data_ptr(),
+                           tg.data_ptr(), gq.data_ptr(), gk.data_ptr(), gv.data_ptr(), delta.data_ptr(), 1, s, A, H)
+    torch.cuda.synchronize()
+    got_v, got_k = to_np(gv).reshape(s, A, d)[1, :, 2], to_np(gk).reshape(s, A, d)[1, :, 1]
+    off += [np.abs(got_v - dv_ref).max() / ulp, np.abs(got_k / scale - dk_ref).max() / ulp]
+    print(f"s={s} d={d}: ctx, dv, dk off by {off} of 2^-24")
+    assert min(np.abs(r).max() for r in (parts, dv_ref, dk_ref)) > 5 * ulp     # what 16 bits would miss
+    assert max(off) <= 3, off
+
+
+@pytest.mark.parametrize("dtype,s,d", [(B.DTYPE_F32, 5, 16), (B.DTYPE_F32, 64, 64), (B.DTYPE_BF16, 5, 64), (B.DTYPE_BF16, 64, 128)])
+def test_attention_keeps_denormal_probabilities(dtype, s, d):
+    # key 1 lies 130 powers of two below key 0: its probability, 2^-130, times a value of 2^126
+    q, k, v = (np.zeros((1, s, d)) for _ in range(3))
+    scale2 = 1.0 / (math.log(2.0) * math.sqrt(d))
+    q[0, :, 0], k[0, :, 0], k[0, 0, 0], k[0, 1, 0] = 1.0, -400.0 / scale2, 0.0, -130.0 / scale2
+    v[0, 1, 0] = 2.0 ** 126
+    fix = (lambda a: I.round_to_bf16(a.astype(np.float32)).astype(np.float64)) if dtype == B.DTYPE_BF16 else (lambda a: a.astype(np.float32).astype(np.float64))
+    k = fix(k)
+    t = [dev(x, TD[dtype]) for x in (q, k, v)]
+    ctx, lse = torch.empty(s, d, dtype=TD[dtype], device="cuda"), torch.empty(1, 1, s, dtype=torch.float32, device="cuda")
+    B.dapple_attention_fwd(dtype, *(x.data_ptr() for x in t), ctx.data_ptr(), lse.data_ptr(), 1, s, 1, d)
+    torch.cuda.synchronize()
+    ref = 2.0 ** (k[0, 1, 0] * scale2 + 126)
+    # a denormal fp32 has 19 bits at 2^-130, its bf16 part 3
+    assert np.abs(to_np(ctx)[:, 0] / ref - 1).max() < (0.1 if dtype == B.DTYPE_BF16 else 1e-4)
+
+
 @pytest.mark.parametrize("dtype", [B.DTYPE_F32, B.DTYPE_BF16])
 def test_attention_plain(dtype):
     attention_case(dtype, 2, 16, 4, 16)
