@@ -365,7 +365,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
   extern __shared__ __attribute__((aligned(1024))) unsigned char asm_[];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int bi = blockIdx.y / a.A, hh = blockIdx.y % a.A;
+  const AttnPlace at = attn_place(a);
+  if (!at.ok) return;
+  const int bi = at.seq, hh = at.head;
   const int d = RAG ? a.d : D;
   const long hb = (long)bi * a.s * a.H + hh * d;
   const bf16 *Q = (const bf16*)a.q + hb, *K = (const bf16*)a.k + hb, *V = (const bf16*)a.v + hb;
@@ -496,11 +498,11 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
 // dk, dv: the wave owns 32 key rows; query blocks of 64 stream through LDS with their lse and delta (the two blocks
 // of 32 columns a head of 64 has are added where they are read)
 template <int D, bool RAG, bool P32, int NW, typename R>
-__device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, float scale, const unsigned char* sm) {
+__device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, const AttnPlace& at, float scale2, float scale, const unsigned char* sm) {
   constexpr int NKK = D / 16, NDB = D / 32;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int bi = blockIdx.y / a.A, hh = blockIdx.y % a.A;
+  const int bi = at.seq, hh = at.head;
   const int d = RAG ? a.d : D;
   const long hb = (long)bi * a.s * a.H + hh * d;
   const bf16 *Q = (const bf16*)a.q + hb, *K = (const bf16*)a.k + hb, *V = (const bf16*)a.v + hb,
@@ -638,11 +640,11 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
 
 // dq: the wave owns 32 query rows; key blocks of 64 stream through LDS
 template <int D, bool RAG, bool P32, int NW, typename R>
-__device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, float scale, const unsigned char* sm) {
+__device__ __forceinline__ void attn_dq_body(const AttnArgs& a, const AttnPlace& at, float scale2, float scale, const unsigned char* sm) {
   constexpr int NKK = D / 16, NDB = D / 32;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int bi = blockIdx.y / a.A, hh = blockIdx.y % a.A;
+  const int bi = at.seq, hh = at.head;
   const int d = RAG ? a.d : D;
   const long hb = (long)bi * a.s * a.H + hh * d;
   const bf16 *Q = (const bf16*)a.q + hb, *K = (const bf16*)a.k + hb, *V = (const bf16*)a.v + hb,
@@ -768,7 +770,7 @@ __global__ __launch_bounds__(256) void attn_delta_rows(AttnArgs a) {
   }
 }
 
-// both roles in one launch: grid.z = 0 the dq workgroups, 1 the dk/dv workgroups.  At most 256 registers per lane up
+// both roles in one launch: 0 the dq workgroups, 1 the dk/dv workgroups.  At most 256 registers per lane up
 // to D = 64, so that a workgroup of each role shares a compute unit; D = 128 keeps twice the accumulators.
 template <int D, int NW>
 struct BwdRing {
@@ -778,8 +780,10 @@ template <int D, bool RAG, bool P32, int NW>
 __global__ __launch_bounds__(64 * NW, D <= 64 ? 2 : 1) void attn_bwd_mfma(AttnArgs a, float scale2, float scale) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char asm_[];
   typedef typename BwdRing<D, NW>::R R;
-  if (blockIdx.z == 0) attn_dq_body<D, RAG, P32, NW, R>(a, scale2, scale, asm_);
-  else attn_dkdv_body<D, RAG, P32, NW, R>(a, scale2, scale, asm_);
+  const AttnPlace at = attn_place(a, 2);
+  if (!at.ok) return;
+  if (at.role == 0) attn_dq_body<D, RAG, P32, NW, R>(a, at, scale2, scale, asm_);
+  else attn_dkdv_body<D, RAG, P32, NW, R>(a, at, scale2, scale, asm_);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -827,7 +831,7 @@ hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
       auto kern = attn_fwd_mfma<d, decltype(RAG)::value, decltype(P32)::value, nw>;
       static const hipError_t rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
       if ((e = rc) != hipSuccess) return;
-      hipLaunchKernelGGL(kern, dim3((a.s + 32 * nw - 1) / (32 * nw), a.b * a.A), dim3(64 * nw), lds, st, a, scale2);
+      hipLaunchKernelGGL(kern, attn_grid(a, 32 * nw), dim3(64 * nw), lds, st, a, scale2);
       e = hipGetLastError();
     });
     return e;
@@ -860,7 +864,7 @@ hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
       auto kern = attn_bwd_mfma<d, decltype(RAG)::value, decltype(P32)::value, nw>;
       static const hipError_t rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
       if ((e = rc) != hipSuccess) return;
-      hipLaunchKernelGGL(kern, dim3((a.s + 32 * nw - 1) / (32 * nw), a.b * a.A, 2), dim3(64 * nw), lds, st, a, scale2, scale);
+      hipLaunchKernelGGL(kern, attn_grid(a, 32 * nw, 2), dim3(64 * nw), lds, st, a, scale2, scale);
       e = hipGetLastError();
     });
     return e;

@@ -128,6 +128,20 @@ struct AttnArgs {
   const float* delta_blocks;
   int b, s, A, d, H;
 };
+// Grid of an attention kernel: x = blocks of rows, (y, z) = heads of all sequences, `roles` workgroups each.  y and z end
+// at 65535, which short sequences in a large batch exceed: beyond it z counts runs of 32768 heads.
+inline dim3 attn_grid(const AttnArgs& a, int rows, int roles = 1) {
+  const int heads = a.b * a.A, run = heads <= 65535 ? heads : 32768;
+  return dim3((a.s + rows - 1) / rows, run, roles * ((heads + run - 1) / run));
+}
+struct AttnPlace {
+  int seq, head, role;
+  bool ok;   // the last run may have fewer heads
+};
+__device__ __forceinline__ AttnPlace attn_place(const AttnArgs& a, int roles = 1) {
+  const int i = (int)(blockIdx.z / roles * gridDim.y + blockIdx.y);
+  return AttnPlace{i / a.A, i % a.A, (int)(blockIdx.z % roles), i < a.b * a.A};
+}
 hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st);
 hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& a, hipStream_t st);
 bool attn_uses_mfma(Dtype dt, const AttnArgs& a);

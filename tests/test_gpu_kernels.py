@@ -354,6 +354,12 @@ def test_attention_keeps_denormal_probabilities(dtype, s, d):
     assert np.abs(to_np(ctx)[:, 0] / ref - 1).max() < (0.1 if dtype == B.DTYPE_BF16 else 1e-4)
 
 
+@pytest.mark.parametrize("dtype,d", [(B.DTYPE_F32, 4), (B.DTYPE_BF16, 8), (B.DTYPE_BF16, 64)])
+def test_attention_of_more_heads_than_a_grid_dimension_holds(dtype, d):
+    attention_case(dtype, 8200, 3, 8, d)     # 65600 heads: 65535 end the y dimension; a last run that is nearly empty
+    attention_case(dtype, 65535 // 5, 2, 5, d)
+
+
 @pytest.mark.parametrize("dtype", [B.DTYPE_F32, B.DTYPE_BF16])
 def test_attention_plain(dtype):
     attention_case(dtype, 2, 16, 4, 16)
