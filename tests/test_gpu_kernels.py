@@ -364,6 +364,9 @@ def test_attention_of_more_heads_than_a_grid_dimension_holds(dtype, d):
 def test_attention_plain(dtype):
     attention_case(dtype, 2, 16, 4, 16)
     attention_case(dtype, 1, 37, 3, 8)
+    # widths that only the kernels with one thread per output element take
+    attention_case(dtype, 2, 19, 3, 6)
+    attention_case(dtype, 1, 70, 2, 136)
 
 
 @pytest.mark.parametrize("dtype,H", [(B.DTYPE_F32, 64), (B.DTYPE_F32, 1000), (B.DTYPE_BF16, 1024),

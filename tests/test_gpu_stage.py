@@ -49,7 +49,7 @@ def test_tiny_fp32_config():
 
 
 def test_fp32_ragged_shapes():
-    # sizes that are not multiples of the kernels' tiles: plain kernels, several blocks
+    # sizes that are not multiples of the kernels' tiles, several blocks
     cfg = I.StageConfig(2, 72, 6, 100, 19, 3, 3, 2, "f32", ln_eps=1e-5)
     check_config(cfg, 3, 2, TOL_F32)
 
@@ -62,7 +62,7 @@ def test_bf16_mfma_path_small():
 
 
 def test_bf16_plain_fallback_shapes():
-    # head dim 32 and odd sequence: plain attention kernels, MFMA GEMMs where they apply
+    # head dim 32 and a sequence that is no multiple of a block
     cfg = I.StageConfig(1, 64, 2, 128, 24, 2, 2, 1, "bf16")
     check_config(cfg, 2, 1, TOL_BF16)
 
@@ -304,7 +304,7 @@ def test_two_chained_stages_bf16_follow_the_oracle():
 
 @pytest.mark.parametrize("M,K", [(1, 1), (2, 1), (3, 2), (5, 3), (7, 2), (4, 4), (6, 8)])
 def test_lanes_do_not_change_a_bit_for_any_depth(M, K):
-    # forward lane, two backward lanes and the side lane against the strictly serial GPipe order
+    # (tasks this small stay on one stream: test_streams_change_no_bit has those that do not)
     cfg = I.StageConfig(2, 128, 2, 256, 64, 2, M, K, "bf16")
     theta, mbs = make_inputs(cfg, SEED, M)
     a = run_gpu(cfg, theta, mbs, M, K, B.ORDER_EARLY_BACKWARD)
@@ -392,10 +392,31 @@ def test_one_stream_flag_changes_no_bit():
         assert np.array_equal(a["ys"][m], b["ys"][m]) and np.array_equal(a["dxs"][m], b["dxs"][m])
 
 
-@pytest.mark.parametrize("kind", ["recompute", "first_stage", "last_stage", "gpipe_order"])
+@pytest.mark.parametrize("M,K", [(1, 1), (5, 3), (4, 4)])
+@pytest.mark.parametrize("kind", ["bf16", "f32", "first", "last"])
+def test_streams_change_no_bit(kind, M, K):
+    """Tasks that go to several streams (a layer's forward between 6 and 150 GFLOP; fp32 from 0.75 on): the side stream
+    with the weight gradients' list cut in two, and under re-computation the forward lane and two backward lanes,
+    against the same stage on one stream."""
+    shape = (2, 256, 4, 1024, 128, 4) if kind == "f32" else (2, 1024, 16, 4096, 256, 2)
+    cfg = I.StageConfig(*shape, M, K, "f32" if kind == "f32" else "bf16", has_embedding=kind == "first",
+                        has_mlm_head=kind == "last", vocab=500, max_pos=256)
+    T, H, F = cfg.tokens, cfg.hidden, cfg.ffn
+    gflop = (8 * H * H + 4 * H * F) * T * 1e-9
+    assert gflop >= 0.75 if kind == "f32" else 6 <= gflop and gflop * min(M, K, 8192 // T) < 150
+    theta, mbs = make_inputs(cfg, SEED, M)
+    ref = _bits(run_gpu(cfg, theta, mbs, M, K, B.ORDER_EARLY_BACKWARD, flags=B.FLAG_ONE_STREAM))
+    ops = B.stage_schedule_ops(M, K, B.ORDER_EARLY_BACKWARD)
+    for flags in (0, B.FLAG_RECOMPUTE, B.FLAG_RECOMPUTE | B.FLAG_ONE_STREAM):
+        for kw in (dict(order=B.ORDER_EARLY_BACKWARD), dict(order=B.ORDER_GPIPE), dict(order=B.ORDER_EXPLICIT, explicit_ops=ops)):
+            got = _bits(run_gpu(cfg, theta, mbs, M, K, flags=flags, **kw))
+            assert all(np.array_equal(x, y) for x, y in zip(ref, got)), (flags, kw)
+
+
+@pytest.mark.parametrize("kind", ["recompute", "first_stage", "last_stage", "gpipe_order", "side_stream", "recompute_lanes"])
 def test_graph_replays_of_the_other_stage_kinds(kind):
-    """A captured iteration of a re-computing stage, a first stage (token ids in), a last stage (losses out) and of
-    the GPipe order: two replays with an eager iteration between them, each equal to the eager result bit for bit."""
+    """A captured iteration of a re-computing stage, a first stage (token ids in), a last stage (losses out), of
+    the GPipe order, and of stages large enough for a side stream and for the lanes: two replays with an eager iteration between them, each equal to the eager result bit for bit."""
     import torch
     flags, order = 0, B.ORDER_EARLY_BACKWARD
     if kind == "first_stage":
@@ -404,7 +425,9 @@ def test_graph_replays_of_the_other_stage_kinds(kind):
         cfg = I.StageConfig(2, 128, 2, 256, 64, 2, 4, 2, "bf16", has_mlm_head=True, vocab=520)
     else:
         cfg = I.StageConfig(3, 256, 4, 512, 128, 2, 4, 2, "bf16")
-        flags = B.FLAG_RECOMPUTE if kind == "recompute" else 0
+        if kind in ("side_stream", "recompute_lanes"):   # 6.4 GFLOP a layer and micro-batch
+            cfg = I.StageConfig(2, 1024, 16, 4096, 256, 1, 4, 2, "bf16")
+        flags = B.FLAG_RECOMPUTE if kind.startswith("recompute") else 0
         order = B.ORDER_GPIPE if kind == "gpipe_order" else order
     M, K = 4, 2
     slots = M if order == B.ORDER_GPIPE else K
