@@ -31,13 +31,13 @@ PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 
-# HBM-side bytes per gemm_mfma_kernel launch (average over the 528 launches of a step), from the
+# HBM-side bytes per product launch (average over those of a step, weight gradients included), from the
 # rocprofv3 FETCH_SIZE / WRITE_SIZE passes summarised in profiles/gemm_mfma_bert_large_pmc_traffic.md,
 # each counter scaled by what it reads for the library's copy kernel of known size.  Counters cannot
 # be read from inside this process, so the figure is carried here per workload, with the commit of
 # the library it was measured on: it is a record of that build, not a live measurement.
-GEMM_TRAFFIC = {"bert_large": {"bytes_per_launch": 66187701,
-                               "source": "profiles/gemm_mfma_bert_large_pmc_traffic.md", "library_commit": "e1f1768"}}
+GEMM_TRAFFIC = {"bert_large": {"bytes_per_launch": 250254060,
+                               "source": "profiles/gemm_mfma_bert_large_pmc_traffic.md", "library_commit": "b05b7da"}}
 
 
 def stage_flops(cfg, M):
@@ -190,15 +190,17 @@ def time_iteration(cfg, theta, mbs, order, slots, flags, steps, warmup, synced=0
     return mean, med, peak, None
 
 
-def algorithmic_bytes(cls, cfg):
-    """HBM bytes one launch of an HBM-bound kernel class has to move (unit = T*H elements)."""
+def algorithmic_bytes(cls, cfg, launches_per_step):
+    """HBM bytes one launch of an HBM-bound kernel class has to move, on average (a launch covers the rows of the
+    micro-batches that share it: a step's rows over its launches).  Two LayerNorms per layer and micro-batch."""
     T, H = cfg.tokens, cfg.hidden
     e = 2 if cfg.dtype == "bf16" else 4
-    u = T * H
-    if cls == "ln_fwd":     # reads the fp32 pre-LN sum, writes y (and its fp32 copy for the next residual add) + stats
-        return u * (4 + e + 4) + 8 * T if cfg.dtype == "bf16" else u * 8 + 8 * T
-    if cls == "ln_bwd":     # reads dy and the pre-LN sum, writes dz and one partial-sum triple per block of 8 rows
-        return u * (e + 4 + e) + ((T + 7) // 8) * 3 * H * 4 if cfg.dtype == "bf16" else u * 12 + ((T + 7) // 8) * 3 * H * 4
+    rows = 2 * cfg.n_layers * cfg.M * T / launches_per_step
+    if cls == "ln_fwd":     # reads the fp32 pre-LN sum, writes y and a row's two statistics
+        return rows * (H * (4 + e) + 8)
+    if cls == "ln_bwd":     # reads dy, the pre-LN sum and the statistics, writes dz and three partial sums a column per block
+        block = 16 if T >= 1024 else 8
+        return rows * (H * (e + 4 + e) + 8) + rows / block * 3 * H * 4
     return None
 
 
@@ -232,7 +234,7 @@ def serial_kernel_table(cfg, theta, mbs, steps):
             row.update(gflop_per_launch=fl / n / 1e9, tflops=fl / (ms * 1e-3) / 1e12,
                        frac_of_mfma_peak=fl / (ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS)
         else:
-            by = algorithmic_bytes(cls, cfg)
+            by = algorithmic_bytes(cls, cfg, n / steps)
             if by:
                 row.update(mbytes_per_launch=by / 1e6, gbs=by / (us * 1e-6) / 1e9,
                            frac_of_hbm_peak=by / (us * 1e-6) / 1e9 / PEAK_HBM_GBS)
@@ -363,12 +365,13 @@ def main():
         "tflops_algorithmic": flops / sec / 1e12,
         "mfma_peak_frac_algorithmic": flops / sec / 1e12 / PEAK_BF16_TFLOPS,
         "gpipe_order": {"samples_per_s": samples / sec_gp, "ms_per_step": sec_gp * 1e3,
-                        "note": "the same tasks, all forwards listed before all backwards: no backward may start "
-                                "before the last forward has finished, so forwards never run beside backwards; the "
-                                "difference to the early-backward figure is this executor's overlap, not a property "
-                                "of the schedules (on one stage both do the same work)"},
+                        "note": "the same tasks, all forwards listed before all backwards: on one stage both orders do "
+                                "the same work, and groups of micro-batches of the same size take the same time"},
         "peak_activation_bytes": {"early_backward_K_slots": peak_eb, "gpipe_M_slots": peak_gp,
                                   "ratio": peak_eb / peak_gp},
+        # all device memory of the stage: accumulators, slots and the workspace of a group of micro-batches
+        "arena_bytes": {"early_backward_K_slots": int(B.stage_query_sizes(B.config_for(cfg, K)).arena_bytes),
+                        "gpipe_M_slots": int(B.stage_query_sizes(B.config_for(cfg, M)).arena_bytes)},
         "roofline": {"bound": "mfma", "kernel": "gemm_mfma_kernel (all linear-layer products: fwd, dgrad, wgrad)",
                      "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_BF16_TFLOPS,
@@ -378,7 +381,7 @@ def main():
                      "launches_per_step": serial["gemm"]["launches_per_step"],
                      "avg_launch_us": serial["gemm"]["avg_launch_us"],
                      "timed": "HIP events around every launch of the iteration run on ONE stream (no kernel of "
-                              "another stream on the compute units); `value` is the four-stream iteration"},
+                              "another stream on the compute units); `value` is the iteration without events"},
         "recompute": {"samples_per_s": samples / sec_rc, "ms_per_step": sec_rc * 1e3,
                       "peak_activation_bytes": peak_rc, "throughput_vs_stored": sec / sec_rc,
                       "memory_vs_stored": peak_rc / peak_eb, "memory_vs_gpipe_order": peak_rc / peak_gp},
