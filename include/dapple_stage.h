@@ -31,9 +31,9 @@
  *   - all device work is ordered in the HIP stream given to stage_init; no call
  *     synchronises the stream except stage_sync.  (The library owns up to three more
  *     streams: one for the gradient-accumulator kernels of every backward task, and,
- *     inside stage_run_schedule, one for the forward tasks and one for every second
- *     backward task.  All are forked from and joined back into the caller's stream
- *     inside the call, so the caller's stream order still covers everything.)
+ *     inside stage_run_schedule under STAGE_FLAG_RECOMPUTE, one for the forward tasks and
+ *     one for every second backward task.  All are forked from and joined back into the
+ *     caller's stream inside the call, so the caller's stream order still covers everything.)
  *     Buffers passed to a call must stay valid until the stream has passed that call.
  *   - every call returns 0 on success or a negative STAGE_E_* code; nothing throws
  *     or aborts.  stage_last_error() gives a message for the last failure of the
@@ -113,8 +113,9 @@ typedef struct {
   uint64_t grad_bytes;      /* fp32 accumulators */
   uint64_t slot_bytes;      /* activations one resident micro-batch keeps from F to B */
   uint64_t workspace_bytes; /* transient buffers of one micro-batch's task */
-  uint64_t arena_bytes;     /* grad_bytes + max_slots * slot_bytes + copies * group * workspace_bytes (+ alignment, +
-                               the forward tasks' activation buffer under STAGE_FLAG_RECOMPUTE); copies = 2 under
+  uint64_t arena_bytes;     /* grad_bytes + max_slots * slot_bytes + at most copies * group * workspace_bytes (+
+                               alignment, + the forward tasks' activation buffer under STAGE_FLAG_RECOMPUTE; less where
+                               a group's weight gradients need no buffers of their own per layer); copies = 2 under
                                STAGE_FLAG_RECOMPUTE (one workspace per backward lane), else, and under
                                STAGE_FLAG_ONE_STREAM, 1; group = the micro-batches
                                one set of launches may cover (up to 8192 token rows, at most 8, no more than

@@ -110,6 +110,8 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 // units each, 36.7 -> 32.2 ms per iteration.  Where another stream's products run beside this one (GemmArgs::shared: the
 // data gradients beside the weight gradients) the tile with the whole LDS keeps them off its unit: 12 layers of 1024
 // with 4096 rows take 28.4 ms with the five-stage ring and 27.3 with two stages, though alone it is the faster one.
+// (The lines between those points -- K >= 2048, N <= 1024, three quarters of the units -- were read off widths of 256,
+// 1024 and 2048 and 512 to 8192 rows.)
 // No bit of a result depends on the choice: an output element is one wave's sum in ascending k whatever the tile.
 static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   auto tiles = [&](long m, long n) { return ((g.M + m - 1) / m) * ((g.N + n - 1) / n) * g.batch; };

@@ -1,4 +1,4 @@
-// Products with A k-strided and B k-contiguous (gemm_mfma.h).
+// Products with A k-strided and B k-contiguous (gemm_mfma.h): no product of the stage, dapple_gemm alone has them.
 #include "gemm_mfma.h"
 
 namespace dapple {

@@ -319,10 +319,11 @@ struct dapple_stage {
   char* arena;
   float* grads;
   hipStream_t st;         // the caller's stream: the critical path (forward; backward data gradients)
-  // library-owned: weight / bias / LayerNorm gradient work of every backward task, in task order
+  // library-owned: weight / bias / LayerNorm gradient work of the backward tasks that do not keep it (small_tasks,
+  // full_tasks), in task order
   hipStream_t side = nullptr;
-  hipStream_t fwd = nullptr;   // library-owned: forward tasks inside stage_run_schedule
-  hipStream_t bwd2 = nullptr;  // library-owned: every second backward task inside stage_run_schedule
+  // library-owned, under STAGE_FLAG_RECOMPUTE: forward tasks, and every second backward task, of stage_run_schedule
+  hipStream_t fwd = nullptr, bwd2 = nullptr;
   hipEvent_t ev_b2done = nullptr;
   hipGraph_t graph = nullptr;          // a captured iteration (stage_graph_capture)
   hipGraphExec_t graph_exec = nullptr;
@@ -588,7 +589,7 @@ int dapple_stage::forward(const Act& sl, int fs, int n, const void* const* xs, v
 }
 
 int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* const* dxs) {
-  // Two streams.  The caller's stream runs the chain that produces dx (LayerNorm backward,
+  // Two streams (one where small_tasks or full_tasks say so: `side` is then the caller's).  The caller's stream runs the chain that produces dx (LayerNorm backward,
   // data-gradient products, attention backward): it is the critical path.  Everything that only
   // feeds the gradient accumulators (weight-gradient products, bias column sums, LayerNorm
   // parameter sums) goes to the side stream as soon as its inputs exist, so those kernels fill
