@@ -126,8 +126,9 @@ __global__ void attn_bwd_plain(AttnArgs a, float scale2, float scale, int which)
 // P32: the probabilities and dS enter their products as a sum of three bf16 values, which holds all 24 bits of an fp32
 //      one; otherwise they are rounded to bf16 once.  (D = 64 with s % 64 == 0 rounds once; every other shape was served
 //      by fp32 arithmetic before it had MFMA kernels and keeps it, the library's exp2f with its denormal results too.
-//      Against two bf16 values, 16 bits, it costs 1-3% of an iteration: 4 layers of 768, 3 x 200 tokens, 6 micro-batches
-//      1.94 -> 1.99 ms, 2 layers of 1024 with heads of 128, 2 x 256 tokens, 4 micro-batches 0.666 -> 0.673.)
+//      Against two bf16 values, 16 bits, and the bare v_exp_f32 it costs 1-6% of an iteration, most where attention is
+//      most of it: 4 layers of 768, 3 x 200 tokens, 6 micro-batches 1.97 -> 2.02 ms; 2 layers of 1024 with heads of 128,
+//      2 x 256 tokens, 4 micro-batches 0.70 -> 0.71; 3 layers of 320, 444 tokens, 4 micro-batches 0.625 -> 0.670.)
 
 // A 64 x D bf16 block sits in LDS as 64 rows of D/8 16-byte chunks, the chunks of row r XOR-swizzled by aswz(r).
 // The same block is read two ways -- 128-bit reads along a row (16 lanes = 16 rows at a time) and transpose reads
@@ -313,7 +314,7 @@ __device__ __forceinline__ float delta_at(const AttnArgs& a, int bi, int hh, int
 // may as well be zero there.  Otherwise the library's exp2f, which wraps it in four more instructions that scale denormal
 // results -- and gives its bits where there are none, so they are spent only where an element of the wave needs them
 // (2 layers of 768, heads of 32, 4 x 256 tokens, 4 micro-batches: 0.865 ms with exp2f always, 0.841 so).
-// CHECK unset: spent always, where the check's registers would spill (the backward of 64-wide heads).
+// CHECK unset: spent always, where the check's registers would spill (dk and dv of 64-wide heads).
 template <bool P32, bool CHECK, int N>
 __device__ __forceinline__ void exp2_all(float (&x)[N]) {
   if constexpr (P32 && !CHECK) {
@@ -419,12 +420,19 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
 #pragma unroll
       for (int kk = 0; kk < NKK; ++kk) sa = MFMA(kf[kb2][kk], qf[kk], sa);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        p[kb2][v] = sa[v];
-        if (RAG && kb * 64 + kb2 * 32 + 8 * (v >> 2) + 4 * h + (v & 3) >= a.s) p[kb2][v] = -INFINITY;
-        mx = fmaxf(mx, p[kb2][v]);
-      }
+      for (int v = 0; v < 16; ++v) p[kb2][v] = sa[v];
     }
+    if (RAG && kb + 1 == nkb) {   // keys beyond the last
+#pragma unroll
+      for (int kb2 = 0; kb2 < 2; ++kb2)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (kb * 64 + kb2 * 32 + 8 * (v >> 2) + 4 * h + (v & 3) >= a.s) p[kb2][v] = -INFINITY;
+    }
+#pragma unroll
+    for (int kb2 = 0; kb2 < 2; ++kb2)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) mx = fmaxf(mx, p[kb2][v]);
     if (ALL) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks)
@@ -700,12 +708,14 @@ __device__ __forceinline__ void attn_dq_body(const AttnArgs& a, const AttnPlace&
       float ds[16];
 #pragma unroll
       for (int v = 0; v < 16; ++v) ds[v] = fmaf(sa[v], scale2, -Lq);
-      exp2_all<P32, D != 64>(ds);
+      exp2_all<P32, true>(ds);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        ds[v] *= dp[v] - Dq;
-        // a key beyond the last: its logit 0 may lie far above the row's logsumexp, so it is masked, not multiplied away
-        if (RAG && kb * 64 + kb2 * 32 + 8 * (v >> 2) + 4 * h + (v & 3) >= a.s) ds[v] = 0.f;
+      for (int v = 0; v < 16; ++v) ds[v] *= dp[v] - Dq;
+      // a key beyond the last: its logit 0 may lie far above the row's logsumexp, so it is masked, not multiplied away
+      if (RAG && kb + 1 == nkb) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (kb * 64 + kb2 * 32 + 8 * (v >> 2) + 4 * h + (v & 3) >= a.s) ds[v] = 0.f;
       }
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
