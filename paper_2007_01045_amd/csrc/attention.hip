@@ -314,7 +314,8 @@ __device__ __forceinline__ float delta_at(const AttnArgs& a, int bi, int hh, int
 // may as well be zero there.  Otherwise the library's exp2f, which wraps it in four more instructions that scale denormal
 // results -- and gives its bits where there are none, so they are spent only where an element of the wave needs them
 // (2 layers of 768, heads of 32, 4 x 256 tokens, 4 micro-batches: 0.865 ms with exp2f always, 0.841 so).
-// CHECK unset: spent always, where the check's registers would spill (dk and dv of 64-wide heads).
+// CHECK unset: spent always, where the check's registers would spill (dk and dv of 64-wide heads in workgroups of two
+// waves; more registers per wave there are slower still).
 template <bool P32, bool CHECK, int N>
 __device__ __forceinline__ void exp2_all(float (&x)[N]) {
   if constexpr (P32 && !CHECK) {
@@ -584,20 +585,19 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, const AttnPlac
           qc[ks][db] = frag_cols<D>(Qs, db * 32, qb2 * 32 + ks * 16, lane);
         }
       __builtin_amdgcn_sched_barrier(0);
-      float p[16], ds[16];
+      float p[16], ds[16];   // (dP - delta first: its registers are free again before the exponentials)
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk) {
-        const float Lv[4] = {L4s[blk].x, L4s[blk].y, L4s[blk].z, L4s[blk].w};
+        const float Lv[4] = {L4s[blk].x, L4s[blk].y, L4s[blk].z, L4s[blk].w}, Dv[4] = {D4s[blk].x, D4s[blk].y, D4s[blk].z, D4s[blk].w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) p[4 * blk + e] = fmaf(sa[4 * blk + e], scale2, -Lv[e]);
+        for (int e = 0; e < 4; ++e) {
+          p[4 * blk + e] = fmaf(sa[4 * blk + e], scale2, -Lv[e]);
+          ds[4 * blk + e] = dp[4 * blk + e] - Dv[e];
+        }
       }
-      exp2_all<P32, D != 64>(p);
+      exp2_all<P32, D != 64 || NW == 4>(p);
 #pragma unroll
-      for (int blk = 0; blk < 4; ++blk) {
-        const float Dv[4] = {D4s[blk].x, D4s[blk].y, D4s[blk].z, D4s[blk].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) ds[4 * blk + e] = p[4 * blk + e] * (dp[4 * blk + e] - Dv[e]);
-      }
+      for (int v = 0; v < 16; ++v) ds[v] *= p[v];
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         bf16x8 pf = acc_to_operand(p, ks), dsf = acc_to_operand(ds, ks);
@@ -832,7 +832,9 @@ static void pick_variant(const AttnArgs& a, int roles, F&& f) {
   }
 }
 
-hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
+hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& args, hipStream_t st) {
+  AttnArgs a = args;
+  a.run = attn_run(a);
   float scale2 = LOG2E / sqrtf((float)a.d);
   if (attn_uses_mfma(dt, a)) {
     hipError_t e = hipSuccess;
@@ -854,7 +856,9 @@ hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
+hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& args, hipStream_t st) {
+  AttnArgs a = args;
+  a.run = attn_run(a);
   float scale = 1.0f / sqrtf((float)a.d), scale2 = LOG2E * scale;
   const long nd = (long)a.b * a.s * a.A;
   const dim3 gd((unsigned)((nd + 255) / 256));

@@ -127,19 +127,21 @@ struct AttnArgs {
   float* delta;
   const float* delta_blocks;
   int b, s, A, d, H;
+  int run;   // set by the launchers (attn_run)
 };
 // Grid of an attention kernel: x = blocks of rows, (y, z) = heads of all sequences, `roles` workgroups each.  y and z end
-// at 65535, which short sequences in a large batch exceed: beyond it z counts runs of 32768 heads.
+// at 65535, which short sequences in a large batch exceed: beyond it z counts runs of 32768 heads.  (The run's length is
+// a kernel argument: the grid's size would be one more trip to memory at a kernel's start.)
+inline int attn_run(const AttnArgs& a) { return a.b * a.A <= 65535 ? a.b * a.A : 32768; }
 inline dim3 attn_grid(const AttnArgs& a, int rows, int roles = 1) {
-  const int heads = a.b * a.A, run = heads <= 65535 ? heads : 32768;
-  return dim3((a.s + rows - 1) / rows, run, roles * ((heads + run - 1) / run));
+  return dim3((a.s + rows - 1) / rows, a.run, roles * ((a.b * a.A + a.run - 1) / a.run));
 }
 struct AttnPlace {
   int seq, head, role;
   bool ok;   // the last run may have fewer heads
 };
 __device__ __forceinline__ AttnPlace attn_place(const AttnArgs& a, int roles = 1) {
-  const int i = (int)(blockIdx.z / roles * gridDim.y + blockIdx.y);
+  const int i = (int)(blockIdx.z / roles) * a.run + (int)blockIdx.y;
   return AttnPlace{i / a.A, i % a.A, (int)(blockIdx.z % roles), i < a.b * a.A};
 }
 hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st);
