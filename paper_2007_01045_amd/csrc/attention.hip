@@ -126,9 +126,9 @@ __global__ void attn_bwd_plain(AttnArgs a, float scale2, float scale, int which)
 // P32: the probabilities and dS enter their products as a sum of three bf16 values, which holds all 24 bits of an fp32
 //      one; otherwise they are rounded to bf16 once.  (D = 64 with s % 64 == 0 rounds once; every other shape was served
 //      by fp32 arithmetic before it had MFMA kernels and keeps it, the library's exp2f with its denormal results too.
-//      Against two bf16 values, 16 bits, and the bare v_exp_f32 it costs 1-6% of an iteration, most where attention is
-//      most of it: 4 layers of 768, 3 x 200 tokens, 6 micro-batches 1.97 -> 2.02 ms; 2 layers of 1024 with heads of 128,
-//      2 x 256 tokens, 4 micro-batches 0.70 -> 0.71; 3 layers of 320, 444 tokens, 4 micro-batches 0.625 -> 0.670.)
+//      Against two bf16 values, 16 bits, and the bare v_exp_f32 it costs 1-5% of an iteration, most where attention is
+//      most of it: 4 layers of 768, 3 x 200 tokens, 6 micro-batches 2.00 -> 2.01 ms; 2 layers of 1024 with heads of 128,
+//      2 x 256 tokens, 4 micro-batches 0.704 -> 0.714; 3 layers of 320, 444 tokens, 4 micro-batches 0.628 -> 0.661.)
 
 // A 64 x D bf16 block sits in LDS as 64 rows of D/8 16-byte chunks, the chunks of row r XOR-swizzled by aswz(r).
 // The same block is read two ways -- 128-bit reads along a row (16 lanes = 16 rows at a time) and transpose reads
@@ -284,14 +284,29 @@ __device__ __forceinline__ bf16x8 acc_to_operand(const float (&p)[16], int ks) {
   for (int e = 0; e < 8; ++e) f[e] = (bf16)p[8 * ks + e];
   return f;
 }
-// what rounding to bf16 left of them, as two more bf16 values (both differences are exact)
-__device__ __forceinline__ void acc_to_operand_rest(const float (&p)[16], bf16x8 hi, int ks, bf16x8& mid, bf16x8& lo) {
+// two fp32 values as bf16 in one register, and what rounding left of them (the differences are exact)
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+__device__ __forceinline__ unsigned take_bf16(float& a, float& b) {
+  const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
+  a -= __builtin_bit_cast(float, u << 16);
+  b -= __builtin_bit_cast(float, u & 0xffff0000u);
+  return u;
+}
+// accumulator rows 16 ks .. 16 ks + 15 as a sum of three such operands.  (Pair by pair in whole registers: element by
+// element the compiler converts every value once to pack it and once more to subtract it: the last of the stages above 0.673 ms.)
+__device__ __forceinline__ void acc_to_operands(const float (&p)[16], int ks, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
+  typedef unsigned u32x4 __attribute__((__vector_size__(4 * sizeof(unsigned))));
+  u32x4 h, m, l;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float r = p[8 * ks + e] - (float)hi[e];
-    mid[e] = (bf16)r;
-    lo[e] = (bf16)(r - (float)mid[e]);
+  for (int e = 0; e < 4; ++e) {
+    float a = p[8 * ks + 2 * e], b = p[8 * ks + 2 * e + 1];
+    h[e] = take_bf16(a, b);
+    m[e] = take_bf16(a, b);
+    l[e] = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
   }
+  hi = __builtin_bit_cast(bf16x8, h);
+  mid = __builtin_bit_cast(bf16x8, m);
+  lo = __builtin_bit_cast(bf16x8, l);
 }
 
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0)
@@ -465,7 +480,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
     }
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      bf16x8 pf = acc_to_operand(p[ks >> 1], ks & 1);
+      bf16x8 pf, pm, pl;
+      if (P32) acc_to_operands(p[ks >> 1], ks & 1, pf, pm, pl);
+      else pf = acc_to_operand(p[ks >> 1], ks & 1);
       if (!ALL) {
 #pragma unroll
         for (int db = 0; db < NDB; ++db) vf[ks][db] = frag_cols<D>(Vs, db * 32, ks * 16, lane);
@@ -473,8 +490,6 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
 #pragma unroll
       for (int db = 0; db < NDB; ++db) o[db] = MFMA(vf[ks][db], pf, o[db]);
       if (P32) {
-        bf16x8 pm, pl;
-        acc_to_operand_rest(p[ks >> 1], pf, ks & 1, pm, pl);
 #pragma unroll
         for (int db = 0; db < NDB; ++db) o[db] = MFMA(vf[ks][db], pm, o[db]);
 #pragma unroll
@@ -600,16 +615,20 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, const AttnPlac
       for (int v = 0; v < 16; ++v) ds[v] *= p[v];
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        bf16x8 pf = acc_to_operand(p, ks), dsf = acc_to_operand(ds, ks);
+        bf16x8 pf, pm, pl, dsf, dsm, dsl;
+        if (P32) {
+          acc_to_operands(p, ks, pf, pm, pl);
+          acc_to_operands(ds, ks, dsf, dsm, dsl);
+        } else {
+          pf = acc_to_operand(p, ks);
+          dsf = acc_to_operand(ds, ks);
+        }
 #pragma unroll
         for (int db = 0; db < NDB; ++db) {
           dv[db] = MFMA(gc[ks][db], pf, dv[db]);
           dk[db] = MFMA(qc[ks][db], dsf, dk[db]);
         }
         if (P32) {
-          bf16x8 pm, pl, dsm, dsl;
-          acc_to_operand_rest(p, pf, ks, pm, pl);
-          acc_to_operand_rest(ds, dsf, ks, dsm, dsl);
 #pragma unroll
           for (int db = 0; db < NDB; ++db) {
             dv[db] = MFMA(gc[ks][db], pm, dv[db]);
@@ -719,12 +738,12 @@ __device__ __forceinline__ void attn_dq_body(const AttnArgs& a, const AttnPlace&
       }
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        bf16x8 dsf = acc_to_operand(ds, ks);
+        bf16x8 dsf, dsm, dsl;
+        if (P32) acc_to_operands(ds, ks, dsf, dsm, dsl);
+        else dsf = acc_to_operand(ds, ks);
 #pragma unroll
         for (int db = 0; db < NDB; ++db) dq[db] = MFMA(kc[ks][db], dsf, dq[db]);
         if (P32) {
-          bf16x8 dsm, dsl;
-          acc_to_operand_rest(ds, dsf, ks, dsm, dsl);
 #pragma unroll
           for (int db = 0; db < NDB; ++db) dq[db] = MFMA(kc[ks][db], dsm, dq[db]);
 #pragma unroll
