@@ -382,9 +382,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
   extern __shared__ __attribute__((aligned(1024))) unsigned char asm_[];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const AttnPlace at = attn_place(a);
-  if (!at.ok) return;
-  const int bi = at.seq, hh = at.head;
+  const int bi = (a.head0 + blockIdx.y) / a.A, hh = (a.head0 + blockIdx.y) % a.A;
   const int d = RAG ? a.d : D;
   const long hb = (long)bi * a.s * a.H + hh * d;
   const bf16 *Q = (const bf16*)a.q + hb, *K = (const bf16*)a.k + hb, *V = (const bf16*)a.v + hb;
@@ -436,19 +434,21 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
 #pragma unroll
       for (int kk = 0; kk < NKK; ++kk) sa = MFMA(kf[kb2][kk], qf[kk], sa);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) p[kb2][v] = sa[v];
+      for (int v = 0; v < 16; ++v) {
+        p[kb2][v] = sa[v];
+        mx = fmaxf(mx, sa[v]);
+      }
     }
-    if (RAG && kb + 1 == nkb) {   // keys beyond the last
+    if (RAG && kb + 1 == nkb) {   // without the keys beyond the last
+      mx = -INFINITY;
 #pragma unroll
       for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
+        for (int v = 0; v < 16; ++v) {
           if (kb * 64 + kb2 * 32 + 8 * (v >> 2) + 4 * h + (v & 3) >= a.s) p[kb2][v] = -INFINITY;
+          mx = fmaxf(mx, p[kb2][v]);
+        }
     }
-#pragma unroll
-    for (int kb2 = 0; kb2 < 2; ++kb2)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) mx = fmaxf(mx, p[kb2][v]);
     if (ALL) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks)
@@ -462,11 +462,16 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
     float rs = 0.f;
 #pragma unroll
     for (int kb2 = 0; kb2 < 2; ++kb2) {
+      if (P32) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) p[kb2][v] = fmaf(p[kb2][v], scale2, -mn);
-      exp2_all<P32, true>(p[kb2]);
+        for (int v = 0; v < 16; ++v) p[kb2][v] = fmaf(p[kb2][v], scale2, -mn);
+        exp2_all<true, true>(p[kb2]);
+      }
 #pragma unroll
-      for (int v = 0; v < 16; ++v) rs += p[kb2][v];
+      for (int v = 0; v < 16; ++v) {
+        if (!P32) p[kb2][v] = __builtin_amdgcn_exp2f(fmaf(p[kb2][v], scale2, -mn));
+        rs += p[kb2][v];
+      }
     }
     l = l * alpha + halves_sum(rs);
     m = mn;
@@ -522,11 +527,11 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
 // dk, dv: the wave owns 32 key rows; query blocks of 64 stream through LDS with their lse and delta (the two blocks
 // of 32 columns a head of 64 has are added where they are read)
 template <int D, bool RAG, bool P32, int NW, typename R>
-__device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, const AttnPlace& at, float scale2, float scale, const unsigned char* sm) {
+__device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, float scale, const unsigned char* sm) {
   constexpr int NKK = D / 16, NDB = D / 32;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int bi = at.seq, hh = at.head;
+  const int bi = (a.head0 + blockIdx.y) / a.A, hh = (a.head0 + blockIdx.y) % a.A;
   const int d = RAG ? a.d : D;
   const long hb = (long)bi * a.s * a.H + hh * d;
   const bf16 *Q = (const bf16*)a.q + hb, *K = (const bf16*)a.k + hb, *V = (const bf16*)a.v + hb,
@@ -667,11 +672,11 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, const AttnPlac
 
 // dq: the wave owns 32 query rows; key blocks of 64 stream through LDS
 template <int D, bool RAG, bool P32, int NW, typename R>
-__device__ __forceinline__ void attn_dq_body(const AttnArgs& a, const AttnPlace& at, float scale2, float scale, const unsigned char* sm) {
+__device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, float scale, const unsigned char* sm) {
   constexpr int NKK = D / 16, NDB = D / 32;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int bi = at.seq, hh = at.head;
+  const int bi = (a.head0 + blockIdx.y) / a.A, hh = (a.head0 + blockIdx.y) % a.A;
   const int d = RAG ? a.d : D;
   const long hb = (long)bi * a.s * a.H + hh * d;
   const bf16 *Q = (const bf16*)a.q + hb, *K = (const bf16*)a.k + hb, *V = (const bf16*)a.v + hb,
@@ -799,7 +804,7 @@ __global__ __launch_bounds__(256) void attn_delta_rows(AttnArgs a) {
   }
 }
 
-// both roles in one launch: 0 the dq workgroups, 1 the dk/dv workgroups.  At most 256 registers per lane up
+// both roles in one launch: grid.z = 0 the dq workgroups, 1 the dk/dv workgroups.  At most 256 registers per lane up
 // to D = 64, so that a workgroup of each role shares a compute unit; D = 128 keeps twice the accumulators.
 template <int D, int NW>
 struct BwdRing {
@@ -809,10 +814,8 @@ template <int D, bool RAG, bool P32, int NW>
 __global__ __launch_bounds__(64 * NW, D <= 64 ? 2 : 1) void attn_bwd_mfma(AttnArgs a, float scale2, float scale) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char asm_[];
   typedef typename BwdRing<D, NW>::R R;
-  const AttnPlace at = attn_place(a, 2);
-  if (!at.ok) return;
-  if (at.role == 0) attn_dq_body<D, RAG, P32, NW, R>(a, at, scale2, scale, asm_);
-  else attn_dkdv_body<D, RAG, P32, NW, R>(a, at, scale2, scale, asm_);
+  if (blockIdx.z == 0) attn_dq_body<D, RAG, P32, NW, R>(a, scale2, scale, asm_);
+  else attn_dkdv_body<D, RAG, P32, NW, R>(a, scale2, scale, asm_);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -851,9 +854,7 @@ static void pick_variant(const AttnArgs& a, int roles, F&& f) {
   }
 }
 
-hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& args, hipStream_t st) {
-  AttnArgs a = args;
-  a.run = attn_run(a);
+hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
   float scale2 = LOG2E / sqrtf((float)a.d);
   if (attn_uses_mfma(dt, a)) {
     hipError_t e = hipSuccess;
@@ -862,8 +863,10 @@ hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& args, hipStream_t st) {
       auto kern = attn_fwd_mfma<d, decltype(RAG)::value, decltype(P32)::value, nw>;
       static const hipError_t rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
       if ((e = rc) != hipSuccess) return;
-      hipLaunchKernelGGL(kern, attn_grid(a, 32 * nw), dim3(64 * nw), lds, st, a, scale2);
-      e = hipGetLastError();
+      e = attn_launches(a, [&](const AttnArgs& l, int heads) {
+        hipLaunchKernelGGL(kern, dim3((a.s + 32 * nw - 1) / (32 * nw), heads), dim3(64 * nw), lds, st, l, scale2);
+        return hipGetLastError();
+      });
     });
     return e;
   }
@@ -875,9 +878,7 @@ hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& args, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& args, hipStream_t st) {
-  AttnArgs a = args;
-  a.run = attn_run(a);
+hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
   float scale = 1.0f / sqrtf((float)a.d), scale2 = LOG2E * scale;
   const long nd = (long)a.b * a.s * a.A;
   const dim3 gd((unsigned)((nd + 255) / 256));
@@ -897,8 +898,10 @@ hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& args, hipStream_t st) {
       auto kern = attn_bwd_mfma<d, decltype(RAG)::value, decltype(P32)::value, nw>;
       static const hipError_t rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
       if ((e = rc) != hipSuccess) return;
-      hipLaunchKernelGGL(kern, attn_grid(a, 32 * nw, 2), dim3(64 * nw), lds, st, a, scale2, scale);
-      e = hipGetLastError();
+      e = attn_launches(a, [&](const AttnArgs& l, int heads) {
+        hipLaunchKernelGGL(kern, dim3((a.s + 32 * nw - 1) / (32 * nw), heads, 2), dim3(64 * nw), lds, st, l, scale2, scale);
+        return hipGetLastError();
+      });
     });
     return e;
   }

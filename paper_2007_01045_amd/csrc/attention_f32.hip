@@ -75,9 +75,7 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(AttnArgs a, float scale2) {
   __shared__ __attribute__((aligned(16))) float Ks[BR * (D + 8)];
   __shared__ __attribute__((aligned(16))) float Vs[BR * (D + 8)];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g4 = lane >> 4;
-  const AttnPlace at = attn_place(a);
-  if (!at.ok) return;
-  const int bi = at.seq, hh = at.head;
+  const int bi = (a.head0 + blockIdx.y) / a.A, hh = (a.head0 + blockIdx.y) % a.A;
   const long hb = (long)bi * a.s * a.H + hh * a.d;
   const float *Q = (const float*)a.q + hb, *K = (const float*)a.k + hb, *V = (const float*)a.v + hb;
   const int qrow = blockIdx.x * 64 + wave * 16 + (lane & 15);
@@ -154,10 +152,10 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(AttnArgs a, float scale2) {
 }
 
 template <int D>
-__device__ __forceinline__ void dq_f32(const AttnArgs& a, const AttnPlace& at, float scale2, float scale, float* Ks, float* Vs) {
+__device__ __forceinline__ void dq_f32(const AttnArgs& a, float scale2, float scale, float* Ks, float* Vs) {
   constexpr int NK = D / 16;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g4 = lane >> 4;
-  const int bi = at.seq, hh = at.head;
+  const int bi = (a.head0 + blockIdx.y) / a.A, hh = (a.head0 + blockIdx.y) % a.A;
   const long hb = (long)bi * a.s * a.H + hh * a.d;
   const float *K = (const float*)a.k + hb, *V = (const float*)a.v + hb;
   const int qrow = blockIdx.x * 64 + wave * 16 + (lane & 15);
@@ -223,12 +221,12 @@ __device__ __forceinline__ void dq_f32(const AttnArgs& a, const AttnPlace& at, f
 }
 
 template <int D>
-__device__ __forceinline__ void dkdv_f32(const AttnArgs& a, const AttnPlace& at, float scale2, float scale, float* Qs, float* Gs, float* Ls,
+__device__ __forceinline__ void dkdv_f32(const AttnArgs& a, float scale2, float scale, float* Qs, float* Gs, float* Ls,
                                          float* Ds) {
   constexpr int NK = D / 16;
   typedef F32Block<D> Blk;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g4 = lane >> 4;
-  const int bi = at.seq, hh = at.head;
+  const int bi = (a.head0 + blockIdx.y) / a.A, hh = (a.head0 + blockIdx.y) % a.A;
   const long hb = (long)bi * a.s * a.H + hh * a.d;
   const float *Q = (const float*)a.q + hb, *G = (const float*)a.dctx + hb, *O = (const float*)a.ctx + hb;
   const float* lse = a.lse + ((long)bi * a.A + hh) * a.s;
@@ -302,17 +300,15 @@ __device__ __forceinline__ void dkdv_f32(const AttnArgs& a, const AttnPlace& at,
   }
 }
 
-// role 0: dq, 1: dk and dv
+// grid.z = 0: dq, 1: dk and dv
 template <int D>
 __global__ __launch_bounds__(256) void attn_bwd_f32(AttnArgs a, float scale2, float scale) {
   __shared__ __attribute__((aligned(16))) float X[BR * (D + 8)];
   __shared__ __attribute__((aligned(16))) float Y[BR * (D + 8)];
   __shared__ __attribute__((aligned(16))) float Ls[BR];
   __shared__ __attribute__((aligned(16))) float Ds[BR];
-  const AttnPlace at = attn_place(a, 2);
-  if (!at.ok) return;
-  if (at.role == 0) dq_f32<D>(a, at, scale2, scale, X, Y);
-  else dkdv_f32<D>(a, at, scale2, scale, X, Y, Ls, Ds);
+  if (blockIdx.z == 0) dq_f32<D>(a, scale2, scale, X, Y);
+  else dkdv_f32<D>(a, scale2, scale, X, Y, Ls, Ds);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -333,16 +329,20 @@ static void pick_width(int d, F&& f) {
 
 hipError_t launch_attn_fwd_f32(const AttnArgs& a, hipStream_t st) {
   const float scale2 = LOG2E / sqrtf((float)a.d);
-  const dim3 grid = attn_grid(a, 64);
-  pick_width(a.d, [&](auto D) { hipLaunchKernelGGL(attn_fwd_f32<decltype(D)::value>, grid, dim3(256), 0, st, a, scale2); });
-  return hipGetLastError();
+  return attn_launches(a, [&](const AttnArgs& l, int heads) {
+    const dim3 grid((a.s + 63) / 64, heads);
+    pick_width(a.d, [&](auto D) { hipLaunchKernelGGL(attn_fwd_f32<decltype(D)::value>, grid, dim3(256), 0, st, l, scale2); });
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_attn_bwd_f32(const AttnArgs& a, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)a.d), scale2 = LOG2E * scale;
-  const dim3 grid = attn_grid(a, 64, 2);
-  pick_width(a.d, [&](auto D) { hipLaunchKernelGGL(attn_bwd_f32<decltype(D)::value>, grid, dim3(256), 0, st, a, scale2, scale); });
-  return hipGetLastError();
+  return attn_launches(a, [&](const AttnArgs& l, int heads) {
+    const dim3 grid((a.s + 63) / 64, heads, 2);
+    pick_width(a.d, [&](auto D) { hipLaunchKernelGGL(attn_bwd_f32<decltype(D)::value>, grid, dim3(256), 0, st, l, scale2, scale); });
+    return hipGetLastError();
+  });
 }
 
 }  // namespace dapple

@@ -127,22 +127,20 @@ struct AttnArgs {
   float* delta;
   const float* delta_blocks;
   int b, s, A, d, H;
-  int run;   // set by the launchers (attn_run)
+  int head0;   // first head of the launch, counted over all sequences (attn_launches)
 };
-// Grid of an attention kernel: x = blocks of rows, (y, z) = heads of all sequences, `roles` workgroups each.  y and z end
-// at 65535, which short sequences in a large batch exceed: beyond it z counts runs of 32768 heads.  (The run's length is
-// a kernel argument: the grid's size would be one more trip to memory at a kernel's start.)
-inline int attn_run(const AttnArgs& a) { return a.b * a.A <= 65535 ? a.b * a.A : 32768; }
-inline dim3 attn_grid(const AttnArgs& a, int rows, int roles = 1) {
-  return dim3((a.s + rows - 1) / rows, a.run, roles * ((a.b * a.A + a.run - 1) / a.run));
-}
-struct AttnPlace {
-  int seq, head, role;
-  bool ok;   // the last run may have fewer heads
-};
-__device__ __forceinline__ AttnPlace attn_place(const AttnArgs& a, int roles = 1) {
-  const int i = (int)(blockIdx.z / roles) * a.run + (int)blockIdx.y;
-  return AttnPlace{i / a.A, i % a.A, (int)(blockIdx.z % roles), i < a.b * a.A};
+// f(args, heads) for each launch of an attention kernel: its grid's y dimension counts the heads of all sequences and ends
+// at 65535, which short sequences in a large batch exceed.  (Runs of heads in the z dimension instead, and an exit for
+// those past the last, cost every launch half a microsecond: the kernel's pointers are fetched behind that branch.)
+template <typename F>
+hipError_t attn_launches(const AttnArgs& a, F&& f) {
+  AttnArgs b = a;
+  for (b.head0 = 0; b.head0 < a.b * a.A; b.head0 += 65535) {
+    const int left = a.b * a.A - b.head0;
+    const hipError_t e = f(b, left < 65535 ? left : 65535);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st);
 hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& a, hipStream_t st);
