@@ -36,8 +36,8 @@ PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 # each counter scaled by what it reads for the library's copy kernel of known size.  Counters cannot
 # be read from inside this process, so the figure is carried here per workload, with the commit of
 # the library it was measured on: it is a record of that build, not a live measurement.
-GEMM_TRAFFIC = {"bert_large": {"bytes_per_launch": 250254060,
-                               "source": "profiles/gemm_mfma_bert_large_pmc_traffic.md", "library_commit": "b05b7da"}}
+GEMM_TRAFFIC = {"bert_large": {"bytes_per_launch": 250233813,
+                               "source": "profiles/gemm_mfma_bert_large_pmc_traffic.md", "library_commit": "a25fabf"}}
 
 
 def stage_flops(cfg, M):
@@ -387,7 +387,7 @@ def main():
                       "memory_vs_stored": peak_rc / peak_eb, "memory_vs_gpipe_order": peak_rc / peak_gp},
         "hip_graph_replay": None if sec_graph is None else
         {"samples_per_s": samples / sec_graph, "ms_per_step": sec_graph * 1e3,
-         "note": "one hipGraphLaunch per iteration (one backward lane inside the graph)"},
+         "note": "one hipGraphLaunch per iteration"},
         "apply_adam": {"ms": apply_ms, "params": n_params, "bytes": int(apply_bytes),
                        "GB/s": apply_bytes / (apply_ms * 1e-3) / 1e9, "hbm_peak_frac": apply_bytes / (apply_ms * 1e-3) / 8e12},
         "one_stream": {"ms_per_step": serial["ms_per_step_one_stream"], "kernel_classes": classes,
