@@ -119,6 +119,7 @@ static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   const bool bsum = (g.epi & EPI_BSUM) != 0;   // (offered for the weight-gradient layout only)
   int tile = g.tile;   // GemmArgs::tile names a configuration instead (tests, timing)
   if (tile == 5 && !tt) tile = 3;
+  if (tile == 8 && g.a_kstrided) tile = tt ? 5 : 3;   // (products whose rows are activations only)
   if (bsum && (tile == 1 || tile == 2 || tile == 6)) tile = 0;
   if (short_k) return tile == 3 || (tile != 4 && t128 >= most) ? 3 : 4;
   if (g.epi & EPI_SEGACC) tile = 0;
@@ -132,7 +133,7 @@ static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   if (tiles(256, 256) >= most && !(g.epi & (EPI_ADD | EPI_AUX32))) return 1;
   if (t256 >= most && t256 <= U && (g.K >= 2048 || !second || g.N <= 1024)) return 2;
   if (t128 > U) return 3;
-  if (t128 >= most) return g.K >= 2048 ? (g.shared ? 3 : 6) : 4;
+  if (t128 >= most) return g.K >= 2048 && !g.shared ? 6 : 8;
   return g.K >= 2048 && tiles(64, 64) > U ? 4 : 7;
 }
 

@@ -112,12 +112,6 @@ struct OperandTile {
   // one group (G0 = its first chunk) of the k-tile's requests
   template <int LDS_OFF, int G0>
   __device__ __forceinline__ void load_group(int4v rs, int wave_off) const {
-    // uniform already; this only tells the compiler so (no instruction when it is in SGPRs)
-    rs[0] = __builtin_amdgcn_readfirstlane(rs[0]);
-    rs[1] = __builtin_amdgcn_readfirstlane(rs[1]);
-    rs[2] = __builtin_amdgcn_readfirstlane(rs[2]);
-    rs[3] = (int)BUF_RSRC_FLAGS;
-    wave_off = __builtin_amdgcn_readfirstlane(wave_off);
     // Two hazards the hardware does not interlock and the compiler cannot see inside an asm
     // block (CDNA3 ISA guide, manually inserted wait states): a scalar write of the resource
     // registers needs 5 wait states before a vector-memory instruction reads them (the compiler
@@ -157,6 +151,66 @@ struct OperandTile {
     static_for<NGROUPS>([&](auto G) { load_group<LDS_OFF, decltype(G)::value * GROUP>(rs, wave_off); });
   }
 };
+
+// One k-tile's requests of both operands in one block: the wait states before the first one serve both.
+constexpr bool has_load_pair(int na, int nb) { return (na == nb && (na == 1 || na == 2 || na == 4)) || (na == 4 && nb == 2); }
+template <int A_OFF, int B_OFF, typename TA, typename TB>
+__device__ __forceinline__ void load_pair(const TA& a, const TB& b, int4v ars, int4v brs, int wave_off_a, int wave_off_b) {
+  constexpr int NA = TA::NI, NB = TB::NI;
+  if constexpr (NA == 1 && NB == 1) {
+    asm volatile(
+        "s_nop 4\n\ts_add_u32 m0, %0, %2\n\ts_nop 0\n\t"
+        "buffer_load_dwordx4 %6, %4, 0 offen lds\n\t"
+        "s_add_u32 m0, %1, %3\n\ts_nop 0\n\t"
+        "buffer_load_dwordx4 %7, %5, 0 offen lds"
+        :
+        : "s"(wave_off_a), "s"(wave_off_b), "i"(A_OFF), "i"(B_OFF), "s"(ars), "s"(brs), "v"(a.voff[0]), "v"(b.voff[0])
+        : "memory", "m0", "scc");
+  } else if constexpr (NA == 2 && NB == 2) {
+    asm volatile(
+        "s_nop 4\n\ts_add_u32 m0, %0, %2\n\ts_nop 0\n\t"
+        "buffer_load_dwordx4 %6, %4, 0 offen lds\n\t"
+        "buffer_load_dwordx4 %7, %4, 0 offen offset:1024 lds\n\t"
+        "s_add_u32 m0, %1, %3\n\ts_nop 0\n\t"
+        "buffer_load_dwordx4 %8, %5, 0 offen lds\n\t"
+        "buffer_load_dwordx4 %9, %5, 0 offen offset:1024 lds"
+        :
+        : "s"(wave_off_a), "s"(wave_off_b), "i"(A_OFF), "i"(B_OFF), "s"(ars), "s"(brs), "v"(a.voff[0]), "v"(a.voff[1]),
+          "v"(b.voff[0]), "v"(b.voff[1])
+        : "memory", "m0", "scc");
+  } else if constexpr (NA == 4 && NB == 4) {
+    asm volatile(
+        "s_nop 4\n\ts_add_u32 m0, %0, %2\n\ts_nop 0\n\t"
+        "buffer_load_dwordx4 %6, %4, 0 offen lds\n\t"
+        "buffer_load_dwordx4 %7, %4, 0 offen offset:1024 lds\n\t"
+        "buffer_load_dwordx4 %8, %4, 0 offen offset:2048 lds\n\t"
+        "buffer_load_dwordx4 %9, %4, 0 offen offset:3072 lds\n\t"
+        "s_add_u32 m0, %1, %3\n\ts_nop 0\n\t"
+        "buffer_load_dwordx4 %10, %5, 0 offen lds\n\t"
+        "buffer_load_dwordx4 %11, %5, 0 offen offset:1024 lds\n\t"
+        "buffer_load_dwordx4 %12, %5, 0 offen offset:2048 lds\n\t"
+        "buffer_load_dwordx4 %13, %5, 0 offen offset:3072 lds"
+        :
+        : "s"(wave_off_a), "s"(wave_off_b), "i"(A_OFF), "i"(B_OFF), "s"(ars), "s"(brs), "v"(a.voff[0]), "v"(a.voff[1]),
+          "v"(a.voff[2]), "v"(a.voff[3]), "v"(b.voff[0]), "v"(b.voff[1]), "v"(b.voff[2]), "v"(b.voff[3])
+        : "memory", "m0", "scc");
+  } else {
+    static_assert(NA == 4 && NB == 2, "see has_load_pair");
+    asm volatile(
+        "s_nop 4\n\ts_add_u32 m0, %0, %2\n\ts_nop 0\n\t"
+        "buffer_load_dwordx4 %6, %4, 0 offen lds\n\t"
+        "buffer_load_dwordx4 %7, %4, 0 offen offset:1024 lds\n\t"
+        "buffer_load_dwordx4 %8, %4, 0 offen offset:2048 lds\n\t"
+        "buffer_load_dwordx4 %9, %4, 0 offen offset:3072 lds\n\t"
+        "s_add_u32 m0, %1, %3\n\ts_nop 0\n\t"
+        "buffer_load_dwordx4 %10, %5, 0 offen lds\n\t"
+        "buffer_load_dwordx4 %11, %5, 0 offen offset:1024 lds"
+        :
+        : "s"(wave_off_a), "s"(wave_off_b), "i"(A_OFF), "i"(B_OFF), "s"(ars), "s"(brs), "v"(a.voff[0]), "v"(a.voff[1]),
+          "v"(a.voff[2]), "v"(a.voff[3]), "v"(b.voff[0]), "v"(b.voff[1])
+        : "memory", "m0", "scc");
+  }
+}
 
 // LDS byte addresses of a lane's MFMA fragments, relative to the operand's tile:
 // rows w0 + 32*blk + (lane & 31), k = kk*16 + 8*(lane>>5) + 0..7.  Everything that depends
@@ -218,8 +272,13 @@ struct GemmTile {
   static constexpr int LOADS_PER_TILE = TA::NI + TB::NI;  // per wave
   static constexpr size_t EPI_BYTES = (size_t)NW * 32 * EPI_LD * sizeof(float);
   static constexpr size_t LDS_BYTES = MAIN_BYTES > EPI_BYTES ? MAIN_BYTES : EPI_BYTES;
-  // waves per SIMD the registers must allow: two workgroups of eight waves where LDS has room for them
-  static constexpr int MIN_WAVES = !SEG && NW == 8 && LDS_BYTES <= 80 * 1024 ? 4 : (SEG ? 2 : 1);
+  // Fragments are read from LDS a whole k-tile ahead of their MFMAs (two sets of them) instead of one k-step: where a
+  // wave's k-step is one or two MFMAs (32 or 64 clocks) and no other wave shares its SIMD, an LDS round trip per k-step
+  // is what such a loop takes.
+  static constexpr bool AHEAD = NW == 4 && MI * NI <= 2 && NS % 2 == 0;
+  // waves per SIMD the registers must allow: two workgroups where LDS has room for them
+  static constexpr bool TWO = LDS_BYTES <= 80 * 1024;
+  static constexpr int MIN_WAVES = !SEG && NW == 8 && TWO ? 4 : (SEG || (NW == 4 && TWO) ? 2 : 1);
 };
 
 // CS: the variant that can also sum B over k (EPI_BSUM); KT: the variant for K segments that are no multiple of 64
@@ -251,10 +310,9 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
 
   const bf16 *Ab = (const bf16*)g.A + z * g.sA, *Bb = (const bf16*)g.B + z * g.sB;
   void* const Cb = g.C;
-  // (SEG: whole turns of the ring each; the k-tiles beyond a segment's end read nothing)
+  // (whole turns of the ring per segment; the k-tiles beyond a segment's end read nothing)
   const int seg_tiles = (g.kseg_len + BK - 1) / BK;
-  const int tiles_per_seg = !SEG ? seg_tiles : (seg_tiles + NS - 1) / NS * NS;
-  const int nk = g.K / g.kseg_len * tiles_per_seg;
+  const int turns = (seg_tiles + NS - 1) / NS;   // of the ring, per segment
   const int k_rows = g.K > g.kseg_len ? g.kseg_len : g.k_valid;   // rows of one segment of a k-strided operand
   // bytes of one segment of each operand that may be read (beyond: zero)
   const long a_ext =
@@ -264,63 +322,83 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
 
   TA ta;
   TB tb;
-  const int last_chunks = (g.kseg_len - (tiles_per_seg - 1) * BK) / 8;   // 16-byte chunks of a segment's last k-tile
+  const int last_chunks = (g.kseg_len - (seg_tiles - 1) * BK) / 8;   // 16-byte chunks of a segment's last k-tile
   ta.init(g.lda, m0, wave, lane, last_chunks);
   tb.init(g.ldb, n0, wave, lane, last_chunks);
-  ta.set_short(tiles_per_seg == 1);
-  tb.set_short(tiles_per_seg == 1);
+  ta.set_short(seg_tiles == 1);
+  tb.set_short(seg_tiles == 1);
   FragAddr<BM, AKS, MI, BK> fa;
   FragAddr<BN, BKS, NI, BK> fb;
   fa.init(wm0, lane);
   fb.init(wn0, lane);
-  const int wave_off_a = wave * TA::NI * 1024, wave_off_b = wave * TB::NI * 1024;
+  int wave_off_a = wave * TA::NI * 1024, wave_off_b = wave * TB::NI * 1024;
 
   // Global cursors, all in scalar registers: one buffer resource per operand whose base is
   // the first element of the next k-step's slab and whose num_records is what may still be
   // read from there.  A k-step forward is base += step, records -= step; at the end of a
   // K segment the base jumps to the next segment and the records start over.
+  // A wave issues an instruction every few clocks, and the small tiles' loop is bound by that: segments are whole turns of
+  // the ring, so that only the turn's first slot, which requests the last tile of a turn, looks for a segment's end.
   const int a_step = AKS ? BK * g.lda * 2 : BK * 2, b_step = BKS ? BK * g.ldb * 2 : BK * 2;
-  const long a_jump = g.segA * 2 - (long)(tiles_per_seg - 1) * a_step;
-  const long b_jump = g.segB * 2 - (long)(tiles_per_seg - 1) * b_step;
   int4v ars, brs;
   auto set_base = [](int4v& rs, uint64_t p) {
     rs[0] = (int)(uint32_t)p;
     rs[1] = (int)(uint32_t)(p >> 32);  // a device address has no bits above 47: stride and swizzle fields stay 0
   };
   auto get_base = [](const int4v& rs) { return ((uint64_t)(uint32_t)rs[1] << 32) | (uint32_t)rs[0]; };
-  set_base(ars, (uint64_t)Ab - TA::BIAS);
-  set_base(brs, (uint64_t)Bb - TB::BIAS);
-  ars[0] = __builtin_amdgcn_readfirstlane(ars[0]);
-  ars[1] = __builtin_amdgcn_readfirstlane(ars[1]);
-  brs[0] = __builtin_amdgcn_readfirstlane(brs[0]);
-  brs[1] = __builtin_amdgcn_readfirstlane(brs[1]);
+  uint64_t a_seg = (uint64_t)Ab - TA::BIAS, b_seg = (uint64_t)Bb - TB::BIAS;   // of the segment being requested
+  set_base(ars, a_seg);
+  set_base(brs, b_seg);
   // record counts carry the operand tiles' BIAS (see OperandTile); BIAS alone = nothing readable
   const int a_rec0 = (int)a_ext + TA::BIAS, b_rec0 = (int)b_ext + TB::BIAS;
-  ars[2] = __builtin_amdgcn_readfirstlane(a_rec0);
-  brs[2] = __builtin_amdgcn_readfirstlane(b_rec0);
+  ars[2] = a_rec0;
+  brs[2] = b_rec0;
   ars[3] = brs[3] = (int)BUF_RSRC_FLAGS;
+  // (uniform, and kept in scalar registers: the resources are read by inline assembly)
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    ars[i] = __builtin_amdgcn_readfirstlane(ars[i]);
+    brs[i] = __builtin_amdgcn_readfirstlane(brs[i]);
+  }
+  wave_off_a = __builtin_amdgcn_readfirstlane(wave_off_a);
+  wave_off_b = __builtin_amdgcn_readfirstlane(wave_off_b);
   // Branch-free on purpose: with control flow inside the k-loop the accumulators get
   // copied between register files at every merge point.
-  int seg_left = tiles_per_seg, tiles_left = nk;
-  auto advance = [&]() {
-    --seg_left;
+  int tiles_left = seg_tiles, turns_left = turns, segs_left = g.K / g.kseg_len;   // still to be requested
+  auto advance = [&](auto S) __attribute__((always_inline)) {
     --tiles_left;
-    const bool cross = seg_left == 0, more = tiles_left > 0;
-    set_base(ars, get_base(ars) + (uint64_t)(cross ? a_jump : (long)a_step));
-    set_base(brs, get_base(brs) + (uint64_t)(cross ? b_jump : (long)b_step));
-    // past the last k-tile the cursor reads nothing: such a request fills its slot with zeros
-    ars[2] = more ? (cross ? a_rec0 : max(ars[2] - a_step, (int)TA::BIAS)) : (int)TA::BIAS;
-    brs[2] = more ? (cross ? b_rec0 : max(brs[2] - b_step, (int)TB::BIAS)) : (int)TB::BIAS;
-    seg_left = cross ? tiles_per_seg : seg_left;
-    ta.set_short(seg_left == 1);
-    tb.set_short(seg_left == 1);
+    set_base(ars, get_base(ars) + (uint32_t)a_step);
+    set_base(brs, get_base(brs) + (uint32_t)b_step);
+    int ar = max(ars[2] - a_step, (int)TA::BIAS), br = max(brs[2] - b_step, (int)TB::BIAS);
+    if constexpr (decltype(S)::value == 0) {   // the request before was the last of its turn
+      const bool cross = --turns_left == 0;
+      segs_left -= cross;
+      a_seg += cross ? (uint64_t)(g.segA * 2) : 0;
+      b_seg += cross ? (uint64_t)(g.segB * 2) : 0;
+      set_base(ars, cross ? a_seg : get_base(ars));
+      set_base(brs, cross ? b_seg : get_base(brs));
+      ar = cross ? a_rec0 : ar;
+      br = cross ? b_rec0 : br;
+      tiles_left = cross ? (segs_left > 0 ? seg_tiles : 0) : tiles_left;
+      turns_left = cross ? turns : turns_left;
+    }
+    // past a segment's last k-tile the cursor reads nothing: such a request fills its slot with zeros
+    ars[2] = tiles_left > 0 ? ar : (int)TA::BIAS;
+    brs[2] = tiles_left > 0 ? br : (int)TB::BIAS;
+    ta.set_short(tiles_left == 1);
+    tb.set_short(tiles_left == 1);
   };
+  constexpr bool PAIR = has_load_pair(TA::NI, TB::NI);   // one block requests a tile's part of both operands
   // request the next k-tile into ring slot S
   auto issue_loads = [&](auto S) {
     constexpr int off = decltype(S)::value * CFG::STAGE_ELEMS * 2;
-    ta.template load<off>(ars, wave_off_a);
-    tb.template load<off + TA::LDS_BYTES>(brs, wave_off_b);
-    advance();
+    if constexpr (PAIR) {
+      load_pair<off, off + TA::LDS_BYTES>(ta, tb, ars, brs, wave_off_a, wave_off_b);
+    } else {
+      ta.template load<off>(ars, wave_off_a);
+      tb.template load<off + TA::LDS_BYTES>(brs, wave_off_b);
+    }
+    advance(std::integral_constant<int, NS == 1 ? 0 : (decltype(S)::value + 1) % NS>{});
   };
 
   // The epilogue's reads.  A wave's vector-memory requests complete in the order they were issued, stores among them:
@@ -469,7 +547,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   Frags f0, f1;
   static_for<MI>([&](auto I) { f1.a[decltype(I)::value] = bf16x8{}; });
   static_for<NI>([&](auto J) { f1.b[decltype(J)::value] = bf16x8{}; });
-  constexpr int GA = TA::NGROUPS, GB = TB::NGROUPS, EXTRA = GA + GB + 1;  // request groups of A, of B, the cursor step
+  constexpr int GA = TA::NGROUPS, GB = PAIR ? 0 : TB::NGROUPS, EXTRA = GA + GB + 1;  // request groups of A, of B, the cursor step
   constexpr int NFRAG = MI + NI, NM = MI * NI;
   // step J of tile S: the MFMAs of `use`; between them the reads of `fill` (the fragments of k-step J of tile S,
   // in the order the next step's MFMAs need them: a0, b0 .. b_NI-1, a1 ..) and this step's share of the requests
@@ -508,15 +586,51 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
           fill.a[p - NI] = fa.template get<off, p - NI, j>(smem);
         } else {
           constexpr int e = e0 + (p - NFRAG);
-          if constexpr (e < GA) ta.template load_group<offn, e * TA::GROUP>(ars, wave_off_a);
+          if constexpr (PAIR && e == 0) load_pair<offn, offn + TA::LDS_BYTES>(ta, tb, ars, brs, wave_off_a, wave_off_b);
+          else if constexpr (e < GA) ta.template load_group<offn, e * TA::GROUP>(ars, wave_off_a);
           else if constexpr (e < GA + GB) tb.template load_group<offn + TA::LDS_BYTES, (e - GA) * TB::GROUP>(brs, wave_off_b);
-          else advance();
+          else advance(S);
         }
       });
       if constexpr (p1 > p0) __builtin_amdgcn_sched_barrier(0);
     });
   };
-  const int turns = !SEG ? (nk + NS - 1) / NS : tiles_per_seg / NS;   // per segment
+  // AHEAD: a whole tile at once.  The MFMAs of tile t - 1, whose fragments were read during the tile before, and between
+  // them -- the reads first, they are what the next barrier waits for -- the reads of tile t's fragments and the requests.
+  constexpr bool AHEAD = CFG::AHEAD;
+  Frags fs[AHEAD ? 2 : 1][AHEAD ? KSTEPS : 1];
+  auto clear_frags = [&](auto& f) __attribute__((always_inline)) {
+    static_for<MI>([&](auto I) { f.a[decltype(I)::value] = bf16x8{}; });
+    static_for<NI>([&](auto J) { f.b[decltype(J)::value] = bf16x8{}; });
+  };
+  auto tile_step = [&](auto& use, auto& fill, auto S, auto SN, auto WCS) __attribute__((always_inline)) {
+    constexpr int off = decltype(S)::value * CFG::STAGE_ELEMS * 2, offn = decltype(SN)::value * CFG::STAGE_ELEMS * 2;
+    constexpr int NMT = NM * KSTEPS, READS = NFRAG * KSTEPS, P = READS + EXTRA, RATE = (P + NMT - 2) / (NMT - 1);
+    static_for<NMT>([&](auto Q) {
+      constexpr int q = decltype(Q)::value, kk = q / NM, mi = q % NM / NI, ni = q % NI;
+      acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(use[kk].b[ni], use[kk].a[mi], acc[mi][ni], 0, 0, 0);
+      if constexpr (decltype(WCS)::value && mi == 0) add_cols(csum[ni], use[kk].b[ni]);
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr int p0 = q * RATE < P ? q * RATE : P, p1 = (q + 1) * RATE < P ? (q + 1) * RATE : P;
+      static_for<p1 - p0>([&](auto D) {
+        constexpr int p = p0 + decltype(D)::value;
+        if constexpr (p < READS) {
+          constexpr int k = p / NFRAG, f = p % NFRAG;   // in the order the MFMAs need them
+          if constexpr (f == 0) fill[k].a[0] = fa.template get<off, 0, k>(smem);
+          else if constexpr (f <= NI) fill[k].b[f - 1] = fb.template get<off + TA::LDS_BYTES, f - 1, k>(smem);
+          else fill[k].a[f - NI] = fa.template get<off, f - NI, k>(smem);
+        } else {
+          constexpr int e = p - READS;
+          if constexpr (PAIR && e == 0) load_pair<offn, offn + TA::LDS_BYTES>(ta, tb, ars, brs, wave_off_a, wave_off_b);
+          else if constexpr (e < GA) ta.template load_group<offn, e * TA::GROUP>(ars, wave_off_a);
+          else if constexpr (e < GA + GB) tb.template load_group<offn + TA::LDS_BYTES, (e - GA) * TB::GROUP>(brs, wave_off_b);
+          else advance(S);
+        }
+      });
+      if constexpr (p1 > p0) __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  if constexpr (AHEAD) static_for<KSTEPS>([&](auto K) { clear_frags(fs[1][decltype(K)::value]); });
   // one turn of the ring; EXTRA_IN: requests in flight besides those for tiles, issued right before it
   auto turn = [&](auto WCS, auto EXTRA_IN) __attribute__((always_inline)) {
     static_for<NS>([&](auto S) {
@@ -526,19 +640,23 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
       __builtin_amdgcn_s_waitcnt(wait_tile(inflight));
       __builtin_amdgcn_s_barrier();  // every wave's part of this tile is in LDS; the previous tile's slot is free
       asm volatile("" ::: "memory");  // ... and no LDS read of this tile may be hoisted above it
-      static_for<KSTEPS / 2>([&](auto H) {
+      if constexpr (AHEAD) tile_step(fs[(decltype(S)::value + 1) & 1], fs[decltype(S)::value & 1], S, SN{}, WCS);
+      else static_for<KSTEPS / 2>([&](auto H) {
         constexpr int kk = 2 * decltype(H)::value;
         step(f1, f0, S, SN{}, std::integral_constant<int, kk>{}, WCS);      // MFMAs of k-step kk - 1 (the previous tile's last when kk == 0)
         step(f0, f1, S, SN{}, std::integral_constant<int, kk + 1>{}, WCS);
       });
     });
   };
-  // the last k-step of the last tile
+  // what the last tile left: its last k-step (AHEAD: all of it)
   auto last_step = [&](auto WCS) __attribute__((always_inline)) {
-    static_for<NM>([&](auto Q) {
-      constexpr int q = decltype(Q)::value, mi = q / NI, ni = q % NI;
-      acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1.b[ni], f1.a[mi], acc[mi][ni], 0, 0, 0);
-      if constexpr (decltype(WCS)::value && mi == 0) add_cols(csum[ni], f1.b[ni]);
+    static_for<AHEAD ? KSTEPS : 1>([&](auto K) {
+      const Frags& f = AHEAD ? fs[AHEAD ? (NS - 1) & 1 : 0][decltype(K)::value] : f1;
+      static_for<NM>([&](auto Q) {
+        constexpr int q = decltype(Q)::value, mi = q / NI, ni = q % NI;
+        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[ni], f.a[mi], acc[mi][ni], 0, 0, 0);
+        if constexpr (decltype(WCS)::value && mi == 0) add_cols(csum[ni], f.b[ni]);
+      });
     });
   };
   constexpr std::integral_constant<int, 0> none{};
@@ -573,8 +691,8 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
 #pragma unroll
         for (int j = 0; j < NI; ++j) tot[i][j] += acc[i][j];
       clear();
-      static_for<MI>([&](auto I) { f1.a[decltype(I)::value] = bf16x8{}; });
-      static_for<NI>([&](auto J) { f1.b[decltype(J)::value] = bf16x8{}; });
+      if constexpr (AHEAD) static_for<KSTEPS>([&](auto K) { clear_frags(fs[1][decltype(K)::value]); });
+      else clear_frags(f1);
     }
     if constexpr (decltype(WCS)::value) {
       // the two half waves hold the sums over different k
@@ -596,7 +714,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
         end_segment(WCS);
       }
     } else {
-      for (int t = 0; t < turns; ++t) turn(WCS, none);
+      for (int t = g.K / g.kseg_len * turns; t > 0; --t) turn(WCS, none);
       end_segment(WCS);
     }
   };
