@@ -159,15 +159,16 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 template <int D, int NW, int NS_, bool STATS>
 struct Ring {
   static constexpr int NS = NS_, IPM = D / 8, PER = 2 * IPM / NW;          // instructions per matrix and block; per wave
-  static constexpr int Y_OFF = 64 * D * 2, S_OFF = 2 * Y_OFF;              // X, Y, then four rows of 64 fp32 (STATS)
-  static constexpr int STAGE = S_OFF + (STATS ? 1024 : 0), BYTES = NS * STAGE;
-  static constexpr int SPW = STATS ? 4 / NW : 0;   // rows of the statistics per wave
+  static constexpr int Y_OFF = 64 * D * 2, S_OFF = 2 * Y_OFF;              // X, Y, then rows of 64 fp32 (STATS)
+  static constexpr int SROWS = NW > 4 ? NW : 4, STAGE = S_OFF + (STATS ? SROWS * 256 : 0), BYTES = NS * STAGE;
+  static constexpr int SPW = STATS ? SROWS / NW : 0;   // rows of the statistics per wave
   static constexpr int BIAS = 3072, LOADS = PER + SPW;
   static_assert(PER <= IPM && (PER == 2 || PER % 4 == 0), "a wave's share lies in one matrix");
   static_assert((NS - 2) * LOADS < 64, "vmcnt is a 6-bit counter");
   int voff[PER];
   i32x4 rs, st[SPW ? SPW : 1];   // buffer resources: the wave's matrix; its rows of the statistics
-  int step, left, sleft[SPW ? SPW : 1], m0w, m0s;
+  int step, left, left0, sleft[SPW ? SPW : 1], m0w, m0s;
+  uint64_t base0, stat0[SPW ? SPW : 1];
   // g: the wave's matrix (head's first column of row 0); ld in elements; stat(r): row r of the statistics, fp32 per row
   // of X and Y, or NULL (reads zero)
   template <typename F>
@@ -179,11 +180,13 @@ struct Ring {
     }
     set(rs, (uint64_t)g - BIAS);
     step = 64 * ld * 2;
-    left = ((s - 1) * ld + d) * 2;
+    left = left0 = ((s - 1) * ld + d) * 2;
+    base0 = (uint64_t)g - BIAS;
     m0w = __builtin_amdgcn_readfirstlane(wave * PER * 1024);
 #pragma unroll
     for (int i = 0; i < SPW; ++i) {
       const float* p = stat(wave + NW * i);
+      stat0[i] = (uint64_t)p;
       set(st[i], (uint64_t)p);
       sleft[i] = p ? s * 4 : 0;
     }
@@ -238,9 +241,28 @@ struct Ring {
     set(rs, (((uint64_t)(uint32_t)rs[1] << 32) | (uint32_t)rs[0]) + (uint64_t)step);
     left -= step;
   }
-  // every wave's part of the oldest block is in LDS, and every wave is done with the block before it
+  // the next block requested is the first one again
+  __device__ __forceinline__ void rewind(int s) {
+    set(rs, base0);
+    left = left0;
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) {
+      set(st[i], stat0[i]);
+      sleft[i] = stat0[i] ? s * 4 : 0;
+    }
+  }
+  // what is requested from here on reads nothing
+  __device__ __forceinline__ void stop() {
+    left = 0;
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) sleft[i] = 0;
+  }
+  // every wave's part of the oldest block is in LDS, and every wave is done with the block before it.  MORE: requests of
+  // this wave's besides the ring's, issued since the one that is waited for
+  template <int MORE = 0>
   static __device__ __forceinline__ void wait() {
-    constexpr int N = (NS - 2) * LOADS;
+    constexpr int N = (NS - 2) * LOADS + MORE;
+    static_assert(N < 64, "vmcnt is a 6-bit counter");
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);   // vmcnt(N), lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
@@ -818,6 +840,217 @@ __global__ __launch_bounds__(64 * NW, D <= 64 ? 2 : 1) void attn_bwd_mfma(AttnAr
   else attn_dkdv_body<D, RAG, P32, NW, R>(a, scale2, scale, asm_);
 }
 
+// The backward with S and dP computed once (heads of 64, whole blocks of 64, 256 to 512 rows).  One workgroup of eight
+// waves per head.  Waves 0-3 own 32 keys each, 128 in all, keep their dK and dV in registers while the queries stream
+// past in blocks of 64, and leave dS in LDS; waves 4-7, a block behind, own 32 queries x 32 columns of every block and
+// add dS K to their part of dQ, which they hold for the whole sequence (128 registers).  Then the next 128 keys.
+// The two kinds of workgroups of attn_bwd_mfma do seven products where these do five, and every exponential twice: 16 x
+// 512 rows, 16 heads 85 -> 74 us in an iteration.  Bound by the first kind's chain of products, exponentials and products
+// with one wave of each kind per SIMD (matrix pipes 25%, vector units 25%, LDS 30% busy); dV and dK (or dV alone) on the
+// second kind of waves, P through LDS too, measured 3-8 us more.  Every sum is the same chain of MFMAs: the same bits.
+constexpr int ONCE_NS = 3;
+typedef Ring<64, 8, ONCE_NS, true> OnceRing;
+typedef Ring<64, 4, 2, false> OnceKeys;   // stage i: rows 64 i .. 64 i + 63 of the group's keys and values
+constexpr int ONCE_X = 128 * 64 * 2;      // dS of a block of queries: [128 keys][64 queries], chunks swizzled by aswz
+constexpr int ONCE_BYTES = OnceKeys::BYTES + OnceRing::BYTES + 2 * ONCE_X;
+
+__global__ __launch_bounds__(512, 2) void attn_bwd_once(AttnArgs a, float scale2, float scale) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char asm_[];
+  constexpr int D = 64, NKK = 4, NDB = 2, MAXQ = 8;
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int bi = (a.head0 + blockIdx.y) / a.A, hh = (a.head0 + blockIdx.y) % a.A;
+  const long hb = (long)bi * a.s * a.H + hh * D;
+  const bf16 *Q = (const bf16*)a.q + hb, *K = (const bf16*)a.k + hb, *V = (const bf16*)a.v + hb, *G = (const bf16*)a.dctx + hb;
+  const int nq = a.s / 64, nkg = (a.s + 127) / 128, steps = nkg * nq;   // blocks of queries, groups of keys
+  unsigned char *const kv = asm_, *const rg = asm_ + OnceKeys::BYTES, *const xs = rg + OnceRing::BYTES;
+  OnceRing ring;
+  {
+    const float* lse = a.lse + ((long)bi * a.A + hh) * a.s;
+    const long T = (long)a.b * a.s;
+    const float *d0 = a.delta + ((long)bi * a.A + hh) * a.s, *d1 = nullptr;
+    if (a.delta_blocks) {
+      d0 = a.delta_blocks + (long)(2 * hh) * T + (long)bi * a.s;
+      d1 = d0 + T;
+    }
+    ring.init(wave < 4 ? Q : G, a.H, a.s, D, wave, lane, [&](int r) { return r == 0 ? lse : (r == 1 ? d0 : (r == 2 ? d1 : nullptr)); });
+    ring.m0w += OnceKeys::BYTES;
+    ring.m0s += OnceKeys::BYTES;
+  }
+  // the block of step n + 2, after barrier n (every wave asks for its part of the same blocks, in the same order)
+  int asked = 0, asked_q = 0, slot = 0;
+  auto ask = [&]() __attribute__((always_inline)) {
+    if (asked_q == nq) {
+      ring.rewind(a.s);
+      asked_q = 0;
+    }
+    if (asked >= steps) ring.stop();   // past the last one: reads nothing
+    ring.request(slot, lane);
+    slot = slot + 1 == ONCE_NS ? 0 : slot + 1;
+    ++asked;
+    ++asked_q;
+  };
+  // Both kinds of waves pass steps + 1 barriers: step n lies between barriers n and n + 1 for waves 0-3, between n + 1
+  // and n + 2 for the others.  KV_LOADS, STORES: requests behind the ring's that a barrier need not wait for.
+  constexpr int KV_LOADS = 2 * OnceKeys::PER, STORES = 16;
+  if (wave < 4) {
+    for (int i = 0; i < ONCE_NS - 1; ++i) ask();
+    int stage = 0, x = 0;
+    const int r = 32 * wave + (lane & 31), xr = r * 64 + 4 * h, xsw = aswz<D>(r);   // the lane's key in the group
+    for (int g = 0; g < nkg; ++g) {
+      const bool live = 128 * g + 32 * wave < a.s;   // (s is a multiple of 64: a wave's keys exist or do not)
+      bf16x8 kf[NKK], vf[NKK];
+      f32x16 dv[NDB], dk[NDB];  // rows d, column = the lane's key
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) dv[db] = dk[db] = zero16();
+      for (int qb = 0; qb < nq; ++qb) {
+        if (g > 0 && qb < 2) OnceRing::wait<STORES>();
+        else OnceRing::wait();
+        ask();
+        if (qb == 0) {
+          const bf16* Ks = (const bf16*)(kv + (wave >> 1) * OnceKeys::STAGE);
+#pragma unroll
+          for (int kk = 0; kk < NKK; ++kk) {
+            kf[kk] = frag_rows<D>(Ks, (wave & 1) * 32, kk, lane);
+            vf[kk] = frag_rows<D>(Ks + OnceKeys::Y_OFF / 2, (wave & 1) * 32, kk, lane);
+          }
+        }
+        const bf16 *Qs = (const bf16*)(rg + stage * OnceRing::STAGE), *Gs = (const bf16*)((const unsigned char*)Qs + OnceRing::Y_OFF);
+        const float *Ls = (const float*)((const unsigned char*)Qs + OnceRing::S_OFF), *Ds = Ls + 64;
+        bf16* const X = (bf16*)(xs + x * ONCE_X);
+        stage = stage + 1 == ONCE_NS ? 0 : stage + 1;
+        x ^= 1;
+        if (!live) continue;   // (nothing reads these rows of X)
+#pragma unroll
+        for (int qb2 = 0; qb2 < 2; ++qb2) {
+          // every LDS read of a phase before its first MFMA (see attn_fwd_mfma)
+          bf16x8 qf[NKK], gf[NKK], gc[2][NDB], qc[2][NDB];
+          f32x4 L4[4], D4[4];
+#pragma unroll
+          for (int kk = 0; kk < NKK; ++kk) {
+            qf[kk] = frag_rows<D>(Qs, qb2 * 32, kk, lane);
+            gf[kk] = frag_rows<D>(Gs, qb2 * 32, kk, lane);
+          }
+#pragma unroll
+          for (int blk = 0; blk < 4; ++blk) {
+            const int q = qb2 * 32 + 8 * blk + 4 * h;
+            L4[blk] = *(const f32x4*)(Ls + q);
+            D4[blk] = *(const f32x4*)(Ds + q) + *(const f32x4*)(Ds + 64 + q);   // (the second block is zero where delta comes whole)
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          f32x16 sa = zero16(), dp = zero16();  // rows: query 32 qb2 + 8 blk + 4 h + e, column: key
+#pragma unroll
+          for (int kk = 0; kk < NKK; ++kk) {
+            sa = MFMA(qf[kk], kf[kk], sa);
+            dp = MFMA(gf[kk], vf[kk], dp);
+          }
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int db = 0; db < NDB; ++db) {
+              gc[ks][db] = frag_cols<D>(Gs, db * 32, qb2 * 32 + ks * 16, lane);
+              qc[ks][db] = frag_cols<D>(Qs, db * 32, qb2 * 32 + ks * 16, lane);
+            }
+          __builtin_amdgcn_sched_barrier(0);
+          float p[16], ds[16];
+#pragma unroll
+          for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              p[4 * blk + e] = __builtin_amdgcn_exp2f(fmaf(sa[4 * blk + e], scale2, -L4[blk][e]));
+              ds[4 * blk + e] = (dp[4 * blk + e] - D4[blk][e]) * p[4 * blk + e];
+            }
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks) {
+            const bf16x8 pf = acc_to_operand(p, ks), dsf = acc_to_operand(ds, ks);
+            *(bf16x4*)(X + xr + (((4 * qb2 + 2 * ks) ^ xsw) << 3)) = __builtin_shufflevector(dsf, dsf, 0, 1, 2, 3);
+            *(bf16x4*)(X + xr + (((4 * qb2 + 2 * ks + 1) ^ xsw) << 3)) = __builtin_shufflevector(dsf, dsf, 4, 5, 6, 7);
+#pragma unroll
+            for (int db = 0; db < NDB; ++db) {
+              dv[db] = MFMA(gc[ks][db], pf, dv[db]);
+              dk[db] = MFMA(qc[ks][db], dsf, dk[db]);
+            }
+          }
+        }
+      }
+      if (g + 1 == nkg) OnceRing::wait();   // (the other waves' last step, not behind these stores)
+      if (live) {
+        const long at = hb + (long)(128 * g + r) * a.H + 4 * h;
+        bf16 *const DK = (bf16*)a.dk + at, *const DV = (bf16*)a.dv + at;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int blk = 0; blk < 4; ++blk) {
+            bf16x4 o1, o2;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              o1[e] = (bf16)(dk[db][4 * blk + e] * scale);
+              o2[e] = (bf16)dv[db][4 * blk + e];
+            }
+            *(bf16x4*)(DK + db * 32 + 8 * blk) = o1;
+            *(bf16x4*)(DV + db * 32 + 8 * blk) = o2;
+          }
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // the last requests (they read nothing) before the wave may end
+    return;
+  }
+  const int w = wave - 4, qt = w & 1, dh = w >> 1;
+  OnceKeys keys;
+  keys.init(w < 2 ? K : V, a.H, a.s, D, w, lane, [](int) { return (const float*)nullptr; });
+  keys.request(0, lane);
+  keys.request(1, lane);
+  for (int i = 0; i < ONCE_NS - 1; ++i) ask();
+  f32x16 dq[MAXQ];   // rows: column 32 dh + 8 blk + 4 h + e of the head, column: query 64 i + 32 qt + (lane & 31)
+#pragma unroll
+  for (int i = 0; i < MAXQ; ++i) dq[i] = zero16();
+  OnceRing::wait();
+  ask();
+  int x = 0;
+  for (int g = 0; g < nkg; ++g) {
+    const bool full = 128 * g + 64 < a.s;   // all 128 keys (else the first 64)
+    bf16x8 kc[8];
+#pragma unroll
+    for (int i = 0; i < MAXQ; ++i) {
+      if (i < nq) {
+        if (i == 2) OnceRing::wait<KV_LOADS>();
+        else OnceRing::wait();
+        ask();
+        if (i == 0) {
+#pragma unroll
+          for (int p = 0; p < 8; ++p) kc[p] = frag_cols<D>((const bf16*)(kv + p / 4 * OnceKeys::STAGE), dh * 32, p % 4 * 16, lane);
+        }
+        if (i == 1) {   // every wave has its part of these keys: the next ones (nq >= 4: here before they are needed)
+          keys.request(0, lane);
+          keys.request(1, lane);
+        }
+        const bf16* X = (const bf16*)(xs + x * ONCE_X);
+        x ^= 1;
+        bf16x8 ds[8];
+#pragma unroll
+        for (int p = 0; p < 8; ++p) ds[p] = frag_cols<D>(X, qt * 32, p * 16, lane);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int p = 0; p < 8; ++p)
+          if (p < 4 || full) dq[i] = MFMA(kc[p], ds[p], dq[i]);
+      }
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+#pragma unroll
+  for (int i = 0; i < MAXQ; ++i)
+    if (i < nq) {
+      bf16* DQ = (bf16*)a.dq + hb + (long)(64 * i + 32 * qt + (lane & 31)) * a.H + 32 * dh + 4 * h;
+#pragma unroll
+      for (int blk = 0; blk < 4; ++blk) {
+        bf16x4 ov;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ov[e] = (bf16)(dq[i][4 * blk + e] * scale);
+        *(bf16x4*)(DQ + 8 * blk) = ov;
+      }
+    }
+}
+
 // ------------------------------------------------------------------ launchers
 static bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
@@ -878,6 +1111,14 @@ hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// One workgroup per head, one to a unit, for about three quarters of the time of attn_bwd_mfma's on a full chip (with
+// the delta kernel, 512 rows: 256 heads 102 -> 81 us, 192 80 -> 72, 128 53 -> 65; 512 heads of 256 rows 70 -> 57): where
+// the turns of the units are three quarters full.  No bit depends on it.
+static bool bwd_once_takes(const AttnArgs& a) {
+  const long U = a.units > 0 ? a.units : 256, heads = (long)a.b * a.A;
+  return a.d == 64 && a.s % 64 == 0 && a.s >= 256 && a.s <= 512 && 4 * heads >= 3 * U * ((heads + U - 1) / U);
+}
+
 hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
   float scale = 1.0f / sqrtf((float)a.d), scale2 = LOG2E * scale;
   const long nd = (long)a.b * a.s * a.A;
@@ -892,6 +1133,14 @@ hipError_t launch_attn_bwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
       else hipLaunchKernelGGL(attn_delta_kernel<bf16>, gd, dim3(256), 0, st, a);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
+    }
+    if (bwd_once_takes(a)) {
+      static const hipError_t rc = hipFuncSetAttribute((const void*)attn_bwd_once, hipFuncAttributeMaxDynamicSharedMemorySize, ONCE_BYTES);
+      if (rc != hipSuccess) return rc;
+      return attn_launches(a, [&](const AttnArgs& l, int heads) {
+        hipLaunchKernelGGL(attn_bwd_once, dim3(1, heads), dim3(512), ONCE_BYTES, st, l, scale2, scale);
+        return hipGetLastError();
+      });
     }
     pick_variant(a, 2, [&](auto D, auto RAG, auto P32, auto NW) {
       constexpr int d = decltype(D)::value, nw = decltype(NW)::value, lds = BwdRing<d, nw>::R::BYTES;

@@ -105,7 +105,9 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 //   5: 128x128, four stages of 32      weight gradients: both operands k-strided, so a 32-deep tile still reads whole
 //                                      256-byte rows, and three tiles are in flight in the LDS of two of 64
 //   6: 128x128, five stages of 64      one workgroup per unit: T=4096 N=1024 K=4096 67 -> 45
-//   7: 64x64, four stages of 64        T=512 N=1024 K=4096 24 (128x64) -> 17, K=1024 10.5 -> 7.6; T=1024 25 -> 19
+//   7: 64x64, four stages of 64        T=512 N=1024 K=4096 23 (128x64) -> 16, K=1024 9.6 -> 6.9; T=1024 23 -> 17
+//   8: 128x128, four waves, four       two workgroups per unit: T=4096 N=1024 K=1024 17 (128x64: 19), and beside another
+//      stages of 32                    stream K=4096 38 (the five-stage ring 35, two stages of 64 47)
 // A stream restricted to part of the units (GemmArgs::units) moves the lines with it: four stages of 2048 rows on 64
 // units each, 36.7 -> 32.2 ms per iteration.  Where another stream's products run beside this one (GemmArgs::shared: the
 // data gradients beside the weight gradients) the tile with the whole LDS keeps them off its unit: 12 layers of 1024

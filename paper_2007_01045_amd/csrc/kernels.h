@@ -58,7 +58,7 @@ struct GemmArgs {
   int k_valid;  // k-strided operands: rows k >= k_valid read as zero (K itself is padded)
   int m_valid, n_valid;  // rows of A / B that exist in memory (0 = M / N); rows beyond read as zero
   int epi;
-  int tile;  // 0 = automatic choice; 1..7 = a specific tile shape / ring depth (see launch_gemm)
+  int tile;  // 0 = automatic choice; 1..8 = a specific tile shape / ring depth (see launch_gemm)
   // for the automatic choice: compute units the stream may use (0 = all 256); shared: another stream's products run
   // beside this one, so a workgroup should leave room on its unit
   int units;
@@ -128,6 +128,7 @@ struct AttnArgs {
   const float* delta_blocks;
   int b, s, A, d, H;
   int head0;   // first head of the launch, counted over all sequences (attn_launches)
+  int units;   // as in GemmArgs
 };
 // f(args, heads) for each launch of an attention kernel: its grid's y dimension counts the heads of all sequences and ends
 // at 65535, which short sequences in a large batch exceed.  (Runs of heads in the z dimension instead, and an exit for

@@ -723,7 +723,7 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
     AttnArgs aa{};
     aa.q = sl(a.q); aa.k = sl(a.k); aa.v = sl(a.v); aa.ctx = ctx; aa.lse = lse; aa.dctx = dctx;
     aa.ctx32 = dt == DT_BF16 ? (float*)sl(a.ctx32) : nullptr;
-    aa.dq = dq; aa.dk = dk; aa.dv = dv; aa.delta = delta;
+    aa.dq = dq; aa.dk = dk; aa.dv = dv; aa.delta = delta; aa.units = units;
     aa.b = n * cfg.micro_batch; aa.s = cfg.seq; aa.A = cfg.n_heads; aa.d = H / cfg.n_heads; aa.H = H;
     {  // dctx = dz1 Wo^T; where the MFMA kernels run, its epilogue also leaves rowsum(dctx o ctx) per block of
        // 32 columns, the delta of the attention backward

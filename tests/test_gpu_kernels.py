@@ -100,7 +100,7 @@ def gemm_case(dtype, M, N, K, akS, bkS, epi, batch=1, nseg=1, expect_mfma=None, 
         assert np.abs(g - w).max() < (3e-2 if bf else 1e-4) * max(np.abs(w).max(), 1.0)
 
 
-@pytest.mark.parametrize("tile", [1, 2, 3, 4, 5, 6])
+@pytest.mark.parametrize("tile", [1, 2, 3, 4, 5, 6, 8])
 def test_gemm_mfma_every_tile_shape_and_ring_depth(tile):
     # K = 64 * (1, 2, 3, 5, 7, 8): shorter than the ring, a multiple of no ring depth, and longer;
     # ragged M and N; both operand layouts; a segmented K
@@ -131,7 +131,7 @@ def test_gemm_mfma_64_wide_tile():
     gemm_case(B.DTYPE_BF16, 328, 200, 192, False, False, B.EPI_ROWDOT | B.EPI_AUX32, expect_mfma=True, tile=7)
 
 
-@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 6])
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 6, 8])
 def test_gemm_row_sums_of_output_times_second_operand(tile):
     # ragged M and N (N not a multiple of 32: the last block is short), bf16 and fp32 second operand
     gemm_case(B.DTYPE_BF16, 328, 200, 192, False, False, B.EPI_ROWDOT | B.EPI_AUX32, expect_mfma=True, tile=tile)
@@ -250,6 +250,30 @@ def attention_case(dtype, b, s, A, d):
 def test_attention_mfma():
     attention_case(B.DTYPE_BF16, 2, 192, 3, 64)      # ragged: 192 = 128 + 64 rows
     attention_case(B.DTYPE_BF16, 1, 512, 2, 64)
+
+
+@pytest.mark.parametrize("s", [256, 320, 448, 512])
+def test_attention_backward_with_a_workgroup_per_head(s):
+    # enough heads for the kernel that computes S and dP once (its last group of 128 keys whole or half), against the
+    # oracle where that is half, and everywhere the bits of the kernel that a single sequence's heads take
+    b, A, d = 12, 16, 64
+    H = A * d
+    if s == 320:
+        attention_case(B.DTYPE_BF16, b, s, A, d)
+    q, k, v, g = (dev(rnd(t, (b, s, H), bf16=True), torch.bfloat16) for t in ("q", "k", "v", "dctx"))
+    bf = lambda: torch.empty(b, s, H, dtype=torch.bfloat16, device="cuda")
+    ctx, lse, delta = bf(), torch.empty(b, A, s, device="cuda"), torch.empty(b, A, s, device="cuda")
+    B.dapple_attention_fwd(B.DTYPE_BF16, *(t.data_ptr() for t in (q, k, v, ctx, lse)), b, s, A, H)
+    outs = []
+    for n in (b, 1):
+        out = [bf() for _ in range(3)]
+        for i in range(0, b, n):
+            ptr = lambda *ts: (t[i].data_ptr() for t in ts)
+            B.dapple_attention_bwd(B.DTYPE_BF16, *ptr(q, k, v, ctx, lse, g, *out, delta), n, s, A, H)
+        outs.append(out)
+    torch.cuda.synchronize()
+    for x, y in zip(*outs):
+        assert torch.equal(x, y)
 
 
 @pytest.mark.parametrize("d", [8, 32, 40, 64, 96, 128])
