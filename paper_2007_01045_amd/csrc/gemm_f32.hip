@@ -8,7 +8,8 @@
 //    in LDS (2 x 37 KB: two workgroups per unit), the next tile's global loads in flight behind the MFMAs;
 //  * gemm_f32_small<TW>: 16 TW square tiles, one per workgroup whose four waves take every fourth 16-wide piece of K
 //    straight from global memory and add their partial tiles in wave order through LDS: for products with so few
-//    tiles that the length of one wave's MFMA chain is the time;
+//    tiles that the length of one wave's MFMA chain, or the launch's memory latencies, are the time (32 x 64 x 64 with
+//    both operands' loads unmasked and a wave's pieces of K counted in scalar registers: 4.6 -> 2.9 us);
 //  * gemm_f32_quad: the sums of gemm_f32_small in the 64-wide tiles of gemm_f32_kernel, every wave with four sets of
 //    accumulators: for a group of micro-batches of which one alone takes the small kernel.
 // Measured before -> after: 2 layers of 1024 x 4096, 2 x 512 tokens, 2 micro-batches: 412 -> 3.3 ms per iteration
@@ -223,7 +224,8 @@ __device__ __forceinline__ void f32_small_tile(GemmArgs g, int tiles_n, const in
   constexpr int BT = 16 * TW, LD = BT + 4;
   __shared__ __attribute__((aligned(16))) float part[NSG][4][BT * LD];
   __shared__ float cpart[NSG][4][BT];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l15 = lane & 15, q4 = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, q4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (uniform: a wave's pieces of K are counted in scalar registers)
   const int tm = bid / tiles_n, tn = bid % tiles_n;
   const int m0 = tm * BT, n0 = tn * BT;
   const float *A = (const float*)g.A + z * g.sA, *B = (const float*)g.B + z * g.sB;
@@ -253,40 +255,61 @@ __device__ __forceinline__ void f32_small_tile(GemmArgs g, int tiles_n, const in
 #pragma unroll
         for (int j = 0; j < TW; ++j) acc[s][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
-    // rows l15 of the 16-row block at r0, k = k0 + 4 q4 + 0..3
-    auto fetch = [&](const float* X, int ld, bool ks, int r, int rows, int k0) {
-      const int k = k0 + 4 * q4;
-      f32x4 v{0.f, 0.f, 0.f, 0.f};
-      if (r < rows) {
-        if (!ks) {
-          if (k < klen) v = *(const f32x4*)(X + (long)r * ld + k);   // klen is a multiple of 4 here
-        } else {
+    // rows l15 of the 16-row block at r0, k = k0 + 4 q4 + 0..3.  No branch: what lies outside re-reads the last row or k,
+    // and is zeroed before it is used (a launch this small is latencies in a row, a masked load a branch of its own).
+    auto fetch = [&](const float* X, int ld, bool ks, int r, int rows, int k0) __attribute__((always_inline)) {
+      const int k = k0 + 4 * q4, rr = min(r, rows - 1);
+      if (!ks) return *(const f32x4*)(X + (long)rr * ld + min(k, (klen - 1) & ~3));
+      f32x4 v;
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (k + e < klen) v[e] = X[(long)(k + e) * ld + r];
-        }
-      }
+      for (int e = 0; e < 4; ++e) v[e] = X[(long)min(k + e, klen - 1) * ld + rr];
       return v;
+    };
+    auto inside = [&](f32x4& v, bool ks, int r, int rows, int k0) __attribute__((always_inline)) {
+      const int k = k0 + 4 * q4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = r < rows && (ks ? k + e : k) < klen ? v[e] : 0.f;
+    };
+    // segment and first k of piece c
+    auto piece = [&](int c, int& seg, int& k0) __attribute__((always_inline)) {
+      seg = 0;
+      k0 = 16 * c;
+      if (NSG == 1 && !segacc && nseg > 1) {   // (an integer division: only where there are segments)
+        seg = c / per_seg;
+        k0 -= seg * per_seg * 16;
+      }
     };
     constexpr int U = (TW == 1 ? 8 : 4) / NSG;   // 16-wide pieces of K (of each segment) whose loads are in flight together
     for (int c0 = wave; c0 < nc; c0 += 4 * U) {
       f32x4 a[NSG][U][TW], b[NSG][U][TW];
 #pragma unroll
-      for (int s = 0; s < NSG; ++s)
+      for (int u = 0; u < U; ++u) {
+        const int c = c0 + 4 * u;
+        if (c >= nc) break;
+        int seg, k0;
+        piece(c, seg, k0);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int c = c0 + 4 * u, seg = NSG > 1 ? s : c / per_seg, k0 = c < nc ? (c - (NSG > 1 ? 0 : seg * per_seg)) * 16 : klen;
-          const float *As = A + (c < nc ? seg : 0) * g.segA, *Bs = B + (c < nc ? seg : 0) * g.segB;
+        for (int s = 0; s < NSG; ++s) {
+          const float *As = A + (NSG > 1 ? s : seg) * g.segA, *Bs = B + (NSG > 1 ? s : seg) * g.segB;
 #pragma unroll
           for (int i = 0; i < TW; ++i) {
             a[s][u][i] = fetch(As, g.lda, AKS, m0 + 16 * i + l15, g.m_valid, k0);
             b[s][u][i] = fetch(Bs, g.ldb, BKS, n0 + 16 * i + l15, g.n_valid, k0);
           }
         }
+      }
 #pragma unroll
       for (int s = 0; s < NSG; ++s)
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+          if (c0 + 4 * u >= nc) break;
+          int seg, k0;
+          piece(c0 + 4 * u, seg, k0);
+#pragma unroll
+          for (int i = 0; i < TW; ++i) {
+            inside(a[s][u][i], AKS, m0 + 16 * i + l15, g.m_valid, k0);
+            inside(b[s][u][i], BKS, n0 + 16 * i + l15, g.n_valid, k0);
+          }
 #pragma unroll
           for (int e = 0; e < 4; ++e)
 #pragma unroll
