@@ -20,6 +20,7 @@
 #include "device_common.h"
 #include "gemm_epilogue.h"
 #include "kernels.h"
+#include "reduce_jobs.h"
 
 namespace dapple {
 
@@ -473,6 +474,12 @@ struct F32Tiles {
 };
 template <int BT, int NSG>
 __global__ __launch_bounds__(256, 2) void wgrad_group_f32(WgradGroup w, F32Tiles t) {
+  if ((int)blockIdx.x >= t.first[w.n]) {   // behind the products' tiles: the sums
+    __shared__ float red[4][64];
+    const int b = blockIdx.x - t.first[w.n], per = (w.jobs.j[0].cols + 63) / 64;
+    reduce_columns(w.jobs.j[b / per], w.jobs.nmb, w.jobs.mb_stride, b % per, 1, red);
+    return;
+  }
   int i = 0;
 #pragma unroll
   for (int k = 1; k < WgradGroup::MAX; ++k) i += k < w.n && (int)blockIdx.x >= t.first[k];
@@ -572,7 +579,7 @@ static hipError_t launch_group_of(const WgradGroup& w, hipStream_t st) {
   }
   F32Tiles t{};
   for (int i = 0; i < w.n; ++i) t.first[i + 1] = t.first[i] + ((w.p[i].M + BT - 1) / BT) * ((w.p[i].N + BT - 1) / BT);
-  hipLaunchKernelGGL(kern, dim3(t.first[w.n]), dim3(256), lds, st, w, t);
+  hipLaunchKernelGGL(kern, dim3(t.first[w.n] + w.job_blocks()), dim3(256), lds, st, w, t);
   return hipGetLastError();
 }
 

@@ -6,6 +6,7 @@
 // tiles two workgroups of four waves (64x64 each: 2/3 of the peak) share a unit and hide each other's ends:
 // K = 4096 (two micro-batches of 2048 rows) 135 -> 102 us, K = 2048 77 -> 57 us.
 #include "gemm_mfma.h"
+#include "reduce_jobs.h"
 
 namespace dapple {
 
@@ -15,6 +16,12 @@ struct TileTable {
 
 template <int BM, int BN, int WGM, int WGN, int NS, int BK, bool SEG>
 __global__ __launch_bounds__(64 * WGM * WGN, SEG ? 2 : 1) void wgrad_group_kernel(WgradGroup w, TileTable t) {
+  if ((int)blockIdx.x >= t.first[w.n]) {   // behind the products' tiles: the sums
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int b = blockIdx.x - t.first[w.n], per = (w.jobs.j[0].cols + 63) / 64;
+    reduce_columns(w.jobs.j[b / per], w.jobs.nmb, w.jobs.mb_stride, b % per, WGM * WGN / 4, (float(*)[64])smem);
+    return;
+  }
   int i = 0;
 #pragma unroll
   for (int k = 1; k < WgradGroup::MAX; ++k) i += k < w.n && (int)blockIdx.x >= t.first[k];
@@ -46,7 +53,7 @@ static hipError_t launch(const WgradGroup& w, hipStream_t st) {
   TileTable t{};
   for (int i = 0; i < w.n; ++i)
     t.first[i + 1] = t.first[i] + ((w.p[i].M + BM - 1) / BM) * ((w.p[i].N + BN - 1) / BN);
-  hipLaunchKernelGGL(kern, dim3(t.first[w.n]), dim3(CFG::NT), CFG::LDS_BYTES, st, w, t);
+  hipLaunchKernelGGL(kern, dim3(t.first[w.n] + w.job_blocks()), dim3(CFG::NT), CFG::LDS_BYTES, st, w, t);
   return hipGetLastError();
 }
 

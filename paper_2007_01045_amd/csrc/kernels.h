@@ -75,6 +75,21 @@ hipError_t launch_mfma_nn(int tile, bool short_k, const GemmArgs& g, hipStream_t
 hipError_t launch_mfma_nt(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
 hipError_t launch_mfma_tn(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
 hipError_t launch_mfma_tt(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
+// out[c] += sum over blk (ascending, in the order of launch_partial_reduce) of partial[blk*stride + c], c < cols,
+// for up to 12 such jobs in one launch.  nmb > 1: the same for partial + mb_stride, partial + 2 mb_stride, ..., one
+// micro-batch's sum after the other
+struct ReduceJob {
+  const float* partial;
+  float* out;
+  int nblk, cols;
+  long stride;
+};
+struct ReduceJobs {
+  ReduceJob j[12];
+  int n;
+  int nmb;          // 0 counts as 1
+  long mb_stride;
+};
 // Several weight-gradient products over the same rows in one launch: for each problem C += sum over the micro-batches'
 // rows of A^T B, both operands [rows][...] with the rows of the micro-batches one behind the other; K = rows in all,
 // kseg = rows of a micro-batch; each one's sum is added to C -- and its column sums of B to bsum, if given -- on its
@@ -92,6 +107,10 @@ struct WgradGroup {
   // fp32: 64x64 tiles of the whole list that this one is part of (0 = of this one): the order of the sums follows from
   // them, and must not change where a caller cuts its list in two
   long list_tiles64;
+  // sums that go out with the products, as workgroups behind theirs (the LayerNorm parameter gradients of the layer): a
+  // launch of their own is 3 to 8 us of waiting for memory with most of the chip idle, here they fill a tail.  nmb >= 1
+  ReduceJobs jobs;
+  int job_blocks() const { return jobs.n > 0 ? jobs.n * ((jobs.j[0].cols + 63) / 64) : 0; }   // (all of one width)
 };
 // the same as one accumulating product
 GemmArgs wgrad_args(const WgradGroup& w, int i);
@@ -178,21 +197,7 @@ hipError_t launch_colsum(Dtype dt, const void* X, int rows, int cols, int ld, fl
 // first stage of launch_colsum alone: partial[(z*nblk + blk)*PS + c], blk < *nblk = ceil(rows/64) blocks of 64 rows
 hipError_t launch_colsum_partials(Dtype dt, const void* X, int rows, int cols, int ld, float* partial, int nb, long zs_x,
                                   int* nblk, int* PS_out, hipStream_t st);
-// out[c] += sum over blk (ascending, in the order of launch_partial_reduce) of partial[blk*stride + c], c < cols,
-// for up to 12 such jobs in one launch.  nmb > 1: the same for partial + mb_stride, partial + 2 mb_stride, ..., one
-// micro-batch's sum after the other
-struct ReduceJob {
-  const float* partial;
-  float* out;
-  int nblk, cols;
-  long stride;
-};
-struct ReduceJobs {
-  ReduceJob j[12];
-  int n;
-  int nmb;          // 0 counts as 1
-  long mb_stride;
-};
+// (see ReduceJobs)
 hipError_t launch_reduce_jobs(const ReduceJobs& J, hipStream_t st);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t st);
 hipError_t launch_zero(void* dst, size_t bytes, hipStream_t st);

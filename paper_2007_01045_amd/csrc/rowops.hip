@@ -5,6 +5,7 @@
 // blocks) so that results do not depend on timing.
 #include "device_common.h"
 #include "kernels.h"
+#include "reduce_jobs.h"
 
 namespace dapple {
 
@@ -278,53 +279,10 @@ __global__ __launch_bounds__(256) void partial_reduce_kernel(const float* __rest
   }
 }
 
-// Several partial_reduce jobs in one launch (blockIdx.y = job): the summation of a job is that of
-// partial_reduce_kernel, addition for addition, and with several micro-batches each one's sum is added to the output
-// on its own, in order.  Four waves per micro-batch, up to four micro-batches at a time.
+// Several partial_reduce jobs in one launch (blockIdx.y = job)
 __global__ __launch_bounds__(1024) void reduce_jobs_kernel(ReduceJobs J) {
   __shared__ float red[16][64];
-  const ReduceJob& job = J.j[blockIdx.y];
-  const int lane = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3, grp = threadIdx.x >> 8, ngrp = blockDim.x >> 8;
-  const int c = blockIdx.x * 64 + lane;
-  if (blockIdx.x * 64 >= job.cols) return;   // the whole workgroup: no barrier is skipped by part of it
-  for (int i0 = 0; i0 < J.nmb; i0 += ngrp) {
-    float t = 0.f;
-    if (c < job.cols && i0 + grp < J.nmb) {
-      const float* p = job.partial + (i0 + grp) * J.mb_stride + c;
-      const long stride = job.stride;
-      const int nblk = job.nblk;
-      int b = w;
-      // 32 loads in flight per wave: the launch is a hundred workgroups waiting for memory
-      for (; b + 124 < nblk; b += 128) {
-        float x[32];
-#pragma unroll
-        for (int u = 0; u < 32; ++u) x[u] = p[(long)(b + 4 * u) * stride];
-#pragma unroll
-        for (int u = 0; u < 32; ++u) t += x[u];
-      }
-      for (; b + 28 < nblk; b += 32) {
-        float x[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = p[(long)(b + 4 * u) * stride];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) t += x[u];
-      }
-      for (; b < nblk; b += 4) t += p[(long)b * stride];
-    }
-    red[grp * 4 + w][lane] = t;
-    __syncthreads();
-    if (threadIdx.x < 64 && c < job.cols) {
-      float o = job.out[c];
-      for (int q = 0; q < ngrp && i0 + q < J.nmb; ++q) {
-        float r = red[4 * q][lane] + red[4 * q + 1][lane];
-        r += red[4 * q + 2][lane];
-        r += red[4 * q + 3][lane];
-        o += r;
-      }
-      job.out[c] = o;
-    }
-    __syncthreads();
-  }
+  reduce_columns(J.j[blockIdx.y], J.nmb, J.mb_stride, blockIdx.x, blockDim.x >> 8, red);
 }
 
 // ------------------------------------------------------------------ column sums

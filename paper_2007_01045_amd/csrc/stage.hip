@@ -427,6 +427,7 @@ struct dapple_stage {
       const GemmArgs g = wgrad_args(w, k);
       TRY(run_on(side, cls, 2.0 * g.M * g.N * (double)g.K, [&](hipStream_t s) { return launch_gemm(dt, g, s); }, &g));
     }
+    if (w.jobs.n) TRY(run_on(side, KC_REDUCE, 0, [&](hipStream_t s) { return launch_reduce_jobs(w.jobs, s); }));
     return STAGE_OK;
   }
   // n micro-batches in consecutive slots as one task: every product sees n T rows, every row-wise kernel n T rows,
@@ -688,10 +689,6 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
         });
       }));
     }
-    // One side stream: the layer's bias and LayerNorm-parameter reductions wait and go out as ONE
-    // launch after the last weight-gradient product (the side stream is the longest chain of a
-    // step, and a small kernel costs it a dispatch of ~15 us when the GPU is full).  Each
-    // reduction adds in the same order as the stand-alone kernels.
     {  // du = (dz2 W2^T) o GELU'(u)
       GemmArgs ga{};
       ga.A = dz2; ga.lda = H; ga.B = w(p.W2); ga.ldb = H; ga.aux = gp; ga.ldaux = F;
@@ -749,17 +746,21 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
     wg.p[wg.n++] = WgradProblem{xl, dk, gr(p.Wk), gr(p.bk), H, H, H, H, H};
     wg.p[wg.n++] = WgradProblem{xl, dv, gr(p.Wv), gr(p.bv), H, H, H, H, H};
     wg.p[wg.n++] = WgradProblem{ctx, dz1, gr(p.Wo), nullptr, H, H, H, H, H};  // dWo += ctx^T dz1
-    TRY(wgrad(KC_GEMM_WGRAD, wg, n, T1));
+    // The sums of both LayerNorms' block partials go out with them (tiny fp32 stage 229 -> 220 us, 6 layers of 8192 rows
+    // 10.70 -> 10.55 ms, 4 of 1800 on a side stream 1925 -> 1916 us) -- on their own beside another stream's large
+    // tiles, whose LDS their workgroups would hold (12 layers of 4096 rows 24.79 ms, 24.92 with the products).
+    ReduceJobs late{};
     {
-      ReduceJobs J{};
+      ReduceJobs& J = side != cur && T >= 4096 ? late : wg.jobs;
       J.nmb = n; J.mb_stride = (long)nblk * 3 * H;
       auto add = [&](const float* partial, float* out) { J.j[J.n++] = ReduceJob{partial, out, nblk, H, 3L * H}; };
       float* o2[3] = {gr(p.ln2g), gr(p.ln2b), gr(p.b2)};
       float* o1[3] = {gr(p.ln1g), gr(p.ln1b), gr(p.bo)};
       for (int v = 0; v < 3; ++v) add(part_ln2 + (size_t)v * H, o2[v]);
       for (int v = 0; v < 3; ++v) add(part_ln1 + (size_t)v * H, o1[v]);
-      TRY(run_on(side, KC_REDUCE, 0, [&](hipStream_t q) { return launch_reduce_jobs(J, q); }));
     }
+    TRY(wgrad(KC_GEMM_WGRAD, wg, n, T1));
+    if (late.n) TRY(run_on(side, KC_REDUCE, 0, [&](hipStream_t q) { return launch_reduce_jobs(late, q); }));
     TRY(side_done(l));
     {  // dx = dq Wq^T + dk Wk^T + dv Wv^T + dz1 (residual branch): one product over K = 3H
       auto dx_gemm = [&](char* out, int i, int c) {
