@@ -5,7 +5,7 @@
 // below their rates, and the kernels are bound by the matrix pipe once every SIMD has a wave.  What decides the time
 // is therefore how many SIMDs a product reaches:
 //  * gemm_f32_kernel<128> / <64>: a square tile per workgroup of 2x2 waves, 32-wide k-tiles through a double buffer
-//    in LDS (2 x 37 KB: two workgroups per unit), the next tile's global loads in flight behind the MFMAs;
+//    in LDS (2 x 37 KB: two workgroups per unit), the next two tiles' global loads in flight behind the MFMAs;
 //  * gemm_f32_small<TW>: 16 TW square tiles, one per workgroup whose four waves take every fourth 16-wide piece of K
 //    straight from global memory and add their partial tiles in wave order through LDS: for products with so few
 //    tiles that the length of one wave's MFMA chain, or the launch's memory latencies, are the time (32 x 64 x 64 with
@@ -40,15 +40,13 @@ struct F32Tile {
   static constexpr int N = R * BK / 4 / 256;   // float4 per thread
   f32x4 v[N];
   unsigned off[N], off_tail[N];   // bytes from the tile's first element; of a segment's last tile
-  const char* next;               // first element of the next tile
   bool tail;                      // v holds a segment's last tile
   int tail_k;                     // ... which has this many k entries
   unsigned live;                  // bit i: piece i lies inside the operand's rows
   static __device__ __forceinline__ int row_of(int pos) { return KS ? pos % (R / 4) * 4 : pos / (BK / 4); }
   static __device__ __forceinline__ int k_of(int pos) { return KS ? pos / (R / 4) : pos % (BK / 4) * 4; }
-  // X: the operand's row r0, with `rows` valid rows from there on
-  __device__ __forceinline__ void init(const float* X, int ld, int rows, int tk, int tid) {
-    next = (const char*)X;
+  // rows: valid rows from the tile's first one on
+  __device__ __forceinline__ void init(int ld, int rows, int tk, int tid) {
     tail_k = tk;
     live = 0;
 #pragma unroll
@@ -60,7 +58,8 @@ struct F32Tile {
       off_tail[i] = 4u * (unsigned)(KS ? kt * ld + r : r * ld + kt);
     }
   }
-  __device__ __forceinline__ void load(bool is_tail) {
+  // next: first element of the tile
+  __device__ __forceinline__ void load(const char* next, bool is_tail) {
     tail = is_tail;
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] = *(const f32x4*)(next + (is_tail ? off_tail[i] : off[i]));
@@ -88,6 +87,65 @@ struct F32Tile {
   static __device__ __forceinline__ f32x4 frag16(const float* S, int r, int piece, int q4) { return frag(S, r, 2 * piece, q4); }
 };
 
+// The tiles of both operands, in order: two sets of registers, so that a tile is requested two k-tiles before it is used.
+// (With one set it was a k-tile's time, about what memory takes: 2048 x 1024 x 4096 in 64-wide tiles 184 -> 146 us, the
+// 128-wide tile 3%.)
+template <bool AKS, bool BKS, typename TA, typename TB, int BK>
+struct F32Feed {
+  struct Set {
+    TA a;
+    TB b;
+  };
+  static constexpr int STAGE = TA::FLOATS + TB::FLOATS;
+  Set s0, s1;
+  const char *a_next, *b_next;   // first elements of the next tile
+  long a_step, b_step, a_jump, b_jump;
+  int per_seg, kt, left;         // tiles per segment; the next one's place in its segment; tiles not yet requested
+  __device__ __forceinline__ void init(const GemmArgs& g, int z, int m0, int n0, int klen, int tid) {
+    per_seg = (klen + BK - 1) / BK;
+    left = g.K / g.kseg_len * per_seg;
+    kt = 0;
+    const int tail_k = klen - (per_seg - 1) * BK;
+    s0.a.init(g.lda, g.m_valid - m0, tail_k, tid);
+    s0.b.init(g.ldb, g.n_valid - n0, tail_k, tid);
+    s1 = s0;
+    a_next = (const char*)((const float*)g.A + z * g.sA + (AKS ? (long)m0 : (long)m0 * g.lda));
+    b_next = (const char*)((const float*)g.B + z * g.sB + (BKS ? (long)n0 : (long)n0 * g.ldb));
+    a_step = 4L * BK * (AKS ? g.lda : 1);
+    b_step = 4L * BK * (BKS ? g.ldb : 1);
+    a_jump = 4L * g.segA - (per_seg - 1) * a_step;
+    b_jump = 4L * g.segB - (per_seg - 1) * b_step;
+  }
+  __device__ __forceinline__ void load(Set& s) {   // the next tile; past the last one that one again
+    s.a.load(a_next, kt == per_seg - 1);
+    s.b.load(b_next, kt == per_seg - 1);
+    --left;
+    const bool last = kt == per_seg - 1, more = left > 0;
+    a_next += more ? (last ? a_jump : a_step) : 0;
+    b_next += more ? (last ? b_jump : b_step) : 0;
+    kt = more ? (last ? 0 : kt + 1) : kt;
+  }
+  static __device__ __forceinline__ void store(const Set& s, float* S, int tid) {
+    s.a.store(S, tid);
+    s.b.store(S + TA::FLOATS, tid);
+  }
+  // f(now, then) for every k-tile: its operands are in LDS, `now` is to take the tile after the next one, `then` holds
+  // the next one
+  template <typename F>
+  __device__ __forceinline__ void each(int tiles, F&& f) {
+    for (; tiles > 1; tiles -= 2) {
+      f(s0, s1);
+      f(s1, s0);
+    }
+    if (tiles) {
+      f(s0, s1);
+      const Set x = s0;   // the sets change places
+      s0 = s1;
+      s1 = x;
+    }
+  }
+};
+
 // CS: the variant that can also sum B over k (EPI_BSUM).  The k-loop holds no branch: one had the accumulators copied
 // between the register files in every k-tile (2048 x 1024 x 4096: 190 us with it).
 template <int BT, bool AKS, bool BKS, bool CS>
@@ -104,7 +162,6 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& g, int tiles_m, int til
   const bool do_cs = bs != nullptr && tm == 0 && wm0 == 0;
   const int klen = g.K > g.kseg_len ? g.kseg_len : min(g.K, g.k_valid);
   const int per_seg = (klen + FBK - 1) / FBK, nseg = g.K / g.kseg_len;
-  const int tail_k = klen - (per_seg - 1) * FBK;
   f32x16 acc[NB][NB];
   float cs[NB];
   auto clear = [&]() __attribute__((always_inline)) {
@@ -118,26 +175,12 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& g, int tiles_m, int til
     }
   };
   clear();
-  TA ta;
-  TB tb;
-  ta.init((const float*)g.A + z * g.sA + (AKS ? (long)m0 : (long)m0 * g.lda), g.lda, g.m_valid - m0, tail_k, tid);
-  tb.init((const float*)g.B + z * g.sB + (BKS ? (long)n0 : (long)n0 * g.ldb), g.ldb, g.n_valid - n0, tail_k, tid);
-  const long a_step = 4L * FBK * (AKS ? g.lda : 1), b_step = 4L * FBK * (BKS ? g.ldb : 1);
-  const long a_jump = 4L * g.segA - (per_seg - 1) * a_step, b_jump = 4L * g.segB - (per_seg - 1) * b_step;
-  int kt = 0, left = nseg * per_seg;   // tile inside its segment, and tiles not yet loaded
-  auto load = [&]() __attribute__((always_inline)) {   // the next tile; past the last one that one again
-    ta.load(kt == per_seg - 1);
-    tb.load(kt == per_seg - 1);
-    --left;
-    const bool last = kt == per_seg - 1, more = left > 0;
-    ta.next += more ? (last ? a_jump : a_step) : 0;
-    tb.next += more ? (last ? b_jump : b_step) : 0;
-    kt = more ? (last ? 0 : kt + 1) : kt;
-  };
-  constexpr int STAGE = TA::FLOATS + TB::FLOATS;
-  load();
-  ta.store(fsm, tid);
-  tb.store(fsm + TA::FLOATS, tid);
+  typedef F32Feed<AKS, BKS, TA, TB, FBK> Feed;
+  Feed feed;
+  feed.init(g, z, m0, n0, klen, tid);
+  feed.load(feed.s0);
+  feed.load(feed.s1);
+  Feed::store(feed.s0, fsm, tid);
   __syncthreads();
   const long zc = z * g.sC, zb = z * g.sBias;
   auto finish = [&]() __attribute__((always_inline)) {   // add the column sums and store the tile
@@ -173,35 +216,35 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& g, int tiles_m, int til
     }
   };
   int buf = 0;
-  auto k_loop = [&](int tiles, auto WCS) __attribute__((always_inline)) {
-    for (int t = 0; t < tiles; ++t) {
-      const float *SA = fsm + buf * STAGE, *SB = SA + TA::FLOATS;
-      load();
-      __builtin_amdgcn_sched_barrier(0);   // (the loads would sink to their use, behind the products that cover them)
+  auto k_tile = [&](typename Feed::Set& now, const typename Feed::Set& then, auto WCS) __attribute__((always_inline)) {
+    const float *SA = fsm + buf * Feed::STAGE, *SB = SA + TA::FLOATS;
+    feed.load(now);
+    __builtin_amdgcn_sched_barrier(0);   // (the loads would sink to their use, behind the products that cover them)
 #pragma unroll
-      for (int kk = 0; kk < FBK / 8; ++kk) {
-        f32x4 a[NB], b[NB];
+    for (int kk = 0; kk < FBK / 8; ++kk) {
+      f32x4 a[NB], b[NB];
 #pragma unroll
-        for (int i = 0; i < NB; ++i) a[i] = TA::frag(SA, wm0 + 32 * i + l31, kk, h);
+      for (int i = 0; i < NB; ++i) a[i] = TA::frag(SA, wm0 + 32 * i + l31, kk, h);
 #pragma unroll
-        for (int j = 0; j < NB; ++j) b[j] = TB::frag(SB, wn0 + 32 * j + l31, kk, h);
+      for (int j = 0; j < NB; ++j) b[j] = TB::frag(SB, wn0 + 32 * j + l31, kk, h);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
+      for (int e = 0; e < 4; ++e)
 #pragma unroll
-          for (int i = 0; i < NB; ++i)
+        for (int i = 0; i < NB; ++i)
 #pragma unroll
-            for (int j = 0; j < NB; ++j)   // B first: a lane then owns 4 consecutive columns of one row
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][e], a[i][e], acc[i][j], 0, 0, 0);
-        if constexpr (decltype(WCS)::value) {
+          for (int j = 0; j < NB; ++j)   // B first: a lane then owns 4 consecutive columns of one row
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][e], a[i][e], acc[i][j], 0, 0, 0);
+      if constexpr (decltype(WCS)::value) {
 #pragma unroll
-          for (int j = 0; j < NB; ++j) cs[j] += (b[j][0] + b[j][1]) + (b[j][2] + b[j][3]);
-        }
+        for (int j = 0; j < NB; ++j) cs[j] += (b[j][0] + b[j][1]) + (b[j][2] + b[j][3]);
       }
-      buf ^= 1;
-      ta.store(fsm + buf * STAGE, tid);
-      tb.store(fsm + buf * STAGE + TA::FLOATS, tid);
-      __syncthreads();
     }
+    buf ^= 1;
+    Feed::store(then, fsm + buf * Feed::STAGE, tid);
+    __syncthreads();
+  };
+  auto k_loop = [&](int tiles, auto WCS) __attribute__((always_inline)) {
+    feed.each(tiles, [&](typename Feed::Set& now, const typename Feed::Set& then) __attribute__((always_inline)) { k_tile(now, then, WCS); });
   };
   // EPI_SEGACC: a segment's sum goes to C on its own
   const bool segacc = (g.epi & EPI_SEGACC) != 0;
@@ -380,7 +423,6 @@ __device__ __forceinline__ void f32_quad_tile(const GemmArgs& g, int tiles_m, in
   tile_of(bid, tiles_m, tiles_n, 64, 64, tm, tn);
   const int m0 = tm * 64, n0 = tn * 64, wm0 = (wave >> 1) * 32, wn0 = (wave & 1) * 32;
   const int klen = g.K > g.kseg_len ? g.kseg_len : min(g.K, g.k_valid);
-  const int per_seg = (klen + BK - 1) / BK, left0 = g.K / g.kseg_len * per_seg;
   f32x4 acc[4][2][2];
 #pragma unroll
   for (int c = 0; c < 4; ++c)
@@ -388,31 +430,18 @@ __device__ __forceinline__ void f32_quad_tile(const GemmArgs& g, int tiles_m, in
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[c][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  TA ta;
-  TB tb;
-  ta.init((const float*)g.A + z * g.sA + (long)m0 * g.lda, g.lda, g.m_valid - m0, klen - (per_seg - 1) * BK, tid);
-  tb.init((const float*)g.B + z * g.sB + (BKS ? (long)n0 : (long)n0 * g.ldb), g.ldb, g.n_valid - n0, klen - (per_seg - 1) * BK, tid);
-  const long a_step = 4L * BK, b_step = 4L * BK * (BKS ? g.ldb : 1);
-  const long a_jump = 4L * g.segA - (per_seg - 1) * a_step, b_jump = 4L * g.segB - (per_seg - 1) * b_step;
-  int kt = 0, left = left0;
-  auto load = [&]() __attribute__((always_inline)) {   // the next tile; past the last one that one again
-    ta.load(kt == per_seg - 1);
-    tb.load(kt == per_seg - 1);
-    --left;
-    const bool last = kt == per_seg - 1, more = left > 0;
-    ta.next += more ? (last ? a_jump : a_step) : 0;
-    tb.next += more ? (last ? b_jump : b_step) : 0;
-    kt = more ? (last ? 0 : kt + 1) : kt;
-  };
-  constexpr int STAGE = TA::FLOATS + TB::FLOATS;
-  load();
-  ta.store(fsm, tid);
-  tb.store(fsm + TA::FLOATS, tid);
+  typedef F32Feed<false, BKS, TA, TB, BK> Feed;
+  Feed feed;
+  feed.init(g, z, m0, n0, klen, tid);
+  const int tiles = feed.left;
+  feed.load(feed.s0);
+  feed.load(feed.s1);
+  Feed::store(feed.s0, fsm, tid);
   __syncthreads();
   int buf = 0;
-  for (int t = 0; t < left0; ++t) {
-    const float *SA = fsm + buf * STAGE, *SB = SA + TA::FLOATS;
-    load();
+  feed.each(tiles, [&](typename Feed::Set& now, const typename Feed::Set& then) __attribute__((always_inline)) {
+    const float *SA = fsm + buf * Feed::STAGE, *SB = SA + TA::FLOATS;
+    feed.load(now);
     __builtin_amdgcn_sched_barrier(0);   // (see f32_tile)
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -430,10 +459,9 @@ __device__ __forceinline__ void f32_quad_tile(const GemmArgs& g, int tiles_m, in
             acc[c][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][e], a[i][e], acc[c][i][j], 0, 0, 0);
     }
     buf ^= 1;
-    ta.store(fsm + buf * STAGE, tid);
-    tb.store(fsm + buf * STAGE + TA::FLOATS, tid);
+    Feed::store(then, fsm + buf * Feed::STAGE, tid);
     __syncthreads();
-  }
+  });
   const long zc = z * g.sC, zb = z * g.sBias;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -550,6 +578,13 @@ static hipError_t launch_small(const GemmArgs& g, hipStream_t st) {
   return hipGetLastError();
 }
 
+// 128-wide tiles rather than 64-wide ones: where they reach most of the units and the fullest unit has no more work than
+// with the 64-wide ones' finer split (three products of 2048 x 1024 x 1024, 384 tiles: 143 -> 112 us)
+static bool large_tiles(long t128, long t64, int units) {
+  const long U = units > 0 ? units : 256;
+  return t128 >= 192 && 40 * ((t128 + U - 1) / U) <= 11 * ((t64 + U - 1) / U);
+}
+
 template <bool AKS, bool BKS>
 static hipError_t launch_layout(const GemmArgs& g, hipStream_t st) {
   auto tiles_of = [&](long rows, long t) { return ((rows + t - 1) / t) * ((g.N + t - 1) / t) * g.batch; };
@@ -560,7 +595,7 @@ static hipError_t launch_layout(const GemmArgs& g, hipStream_t st) {
   // with K split over the waves: a 16-wide one has a quarter of the MFMA chain but reads every operand element twice as
   // often.
   const bool chain = tiles_of(g.rows1 > 0 ? g.rows1 : g.M, 64) >= 160;
-  if (chain) return tiles(128) >= 192 ? launch_tile<128, AKS, BKS>(g, st) : launch_tile<64, AKS, BKS>(g, st);
+  if (chain) return large_tiles(tiles(128), tiles(64), g.units) ? launch_tile<128, AKS, BKS>(g, st) : launch_tile<64, AKS, BKS>(g, st);
   if constexpr (!AKS)
     if (tiles(64) >= 160 && !(g.epi & EPI_SEGACC) && (g.K == g.kseg_len || g.kseg_len % 64 == 0)) return launch_quad<BKS>(g, st);
   if (tiles(32) >= 160) return launch_small<2, AKS, BKS>(g, st);
@@ -597,7 +632,7 @@ hipError_t launch_wgrad_group_f32(const WgradGroup& w, hipStream_t st) {
     return n;
   };
   if ((w.list_tiles64 > 0 ? w.list_tiles64 : tiles(64)) >= 160)   // the lines of launch_layout
-    return tiles(128) >= 192 ? launch_group<128>(w, st) : launch_group<64>(w, st);
+    return large_tiles(tiles(128), tiles(64), w.units) ? launch_group<128>(w, st) : launch_group<64>(w, st);
   if (tiles(32) >= 160) return launch_group<32>(w, st);
   return launch_group<16>(w, st);
 }

@@ -217,6 +217,18 @@ def test_gemm_fp32_tiles(M, N, K):
         gemm_case(B.DTYPE_F32, M, N, K + 3, True, True, B.EPI_ACC32 | B.EPI_BSUM)
 
 
+@pytest.mark.parametrize("M,N", [(648, 1032), (1160, 2056), (40, 72)])
+@pytest.mark.parametrize("K", [4, 32, 36, 64, 96, 100])
+def test_gemm_fp32_few_and_odd_numbers_of_k_tiles(M, N, K):
+    # 64-wide tiles, 128-wide ones and the kernel that splits K over its waves: two k-tiles are on their way ahead of the
+    # one in use, so one, two, three and four of them; as three segments, where an odd number changes the sets' places
+    # (M and N: enough tiles for each kernel, ragged against its tile)
+    for akS, bkS in ((False, True), (False, False), (True, True)):
+        gemm_case(B.DTYPE_F32, M, N, K, akS, bkS, B.EPI_BIAS)
+        gemm_case(B.DTYPE_F32, M, N, 3 * K, akS, bkS, B.EPI_ADD, nseg=3)
+    gemm_case(B.DTYPE_F32, M, N, K + 3, True, True, B.EPI_ACC32 | B.EPI_BSUM)
+
+
 def attention_case(dtype, b, s, A, d):
     bf = dtype == B.DTYPE_BF16
     td = TD[dtype]
