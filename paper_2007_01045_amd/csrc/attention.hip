@@ -396,6 +396,38 @@ __device__ __forceinline__ f32x16 zero16() {
   return z;
 }
 
+// A wave's 32 rows x 32 NDB columns of an output (t: rows = columns of the head, column = the lane's row) times f, through a
+// piece of LDS of the wave's own into whole rows: straight from the accumulators a store is 16 bytes (32 of an fp32 copy)
+// of each of 32 rows, and the L2 takes every line in eight pieces.  rows: valid rows; d: columns of the head.
+// C32 (may be NULL): an fp32 copy.
+template <int NDB>
+struct OutTile {
+  static constexpr int W = 32 * NDB, LD = W + 4, BYTES = 32 * LD * 4;
+  static __device__ __forceinline__ void store(float* S, const f32x16* t, float f, bf16* C, float* C32, long ld, int rows, int d, int lane) {
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int blk = 0; blk < 4; ++blk)
+        *(f32x4*)(S + (lane & 31) * LD + db * 32 + 8 * blk + 4 * (lane >> 5)) =
+            f32x4{t[db][4 * blk], t[db][4 * blk + 1], t[db][4 * blk + 2], t[db][4 * blk + 3]} * f;
+    __builtin_amdgcn_wave_barrier();   // (private to the wave, whose LDS accesses execute in order)
+    constexpr int RS = 64 / (W / 4);   // rows per instruction
+    const int r = lane / (W / 4), c = lane % (W / 4) * 4;
+#pragma unroll
+    for (int i = 0; i < 32; i += RS) {
+      const f32x4 v = *(const f32x4*)(S + (i + r) * LD + c);
+      if (i + r < rows && c < d) {
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (bf16)v[e];
+        *(bf16x4*)(C + (i + r) * ld + c) = o;
+        if (C32) *(f32x4*)(C32 + (i + r) * ld + c) = v;
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+};
+
 // NW: waves per workgroup (4, or 2 where the grid is small), each with 32 query rows
 template <int D, bool RAG, bool P32, int NW>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnArgs a, float scale2) {
@@ -525,8 +557,15 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);   // the ring's last requests (they read nothing) before the wave may end
-  if (qok) {
-    float inv = 1.0f / l;
+  const float inv = 1.0f / l;
+  if constexpr (D <= 64) {
+    typedef OutTile<NDB> Out;
+    static_assert(NW * Out::BYTES <= R::BYTES, "the output's staging lies where the ring was");
+    __syncthreads();   // every wave is done with the ring, and its requests
+    const int row0 = blockIdx.x * (32 * NW) + wave * 32;
+    const long o0 = hb + (long)row0 * a.H;
+    Out::store((float*)(asm_ + wave * Out::BYTES), o, inv, (bf16*)a.ctx + o0, a.ctx32 ? a.ctx32 + o0 : nullptr, a.H, a.s - row0, d, lane);
+  } else if (qok) {
     bf16* C = (bf16*)a.ctx + hb + (long)qrow * a.H;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
@@ -542,14 +581,14 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
           *(float4*)(a.ctx32 + hb + (long)qrow * a.H + col) =
               make_float4(o[db][4 * blk] * inv, o[db][4 * blk + 1] * inv, o[db][4 * blk + 2] * inv, o[db][4 * blk + 3] * inv);
       }
-    if (h == 0) a.lse[((long)bi * a.A + hh) * a.s + qrow] = m + log2f(l);
   }
+  if (qok && h == 0) a.lse[((long)bi * a.A + hh) * a.s + qrow] = m + log2f(l);
 }
 
 // dk, dv: the wave owns 32 key rows; query blocks of 64 stream through LDS with their lse and delta (the two blocks
 // of 32 columns a head of 64 has are added where they are read)
 template <int D, bool RAG, bool P32, int NW, typename R>
-__device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, float scale, const unsigned char* sm) {
+__device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, float scale, unsigned char* sm) {
   constexpr int NKK = D / 16, NDB = D / 32;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -671,7 +710,16 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);
-  if (kok) {
+  if constexpr (D <= 64) {   // (as in attn_fwd_mfma)
+    typedef OutTile<NDB> Out;
+    static_assert(NW * Out::BYTES <= R::BYTES, "the output's staging lies where the ring was");
+    __syncthreads();
+    const int row0 = blockIdx.x * (32 * NW) + wave * 32;
+    const long o0 = hb + (long)row0 * a.H;
+    float* const S = (float*)(sm + wave * Out::BYTES);
+    Out::store(S, dk, scale, (bf16*)a.dk + o0, nullptr, a.H, a.s - row0, d, lane);
+    Out::store(S, dv, 1.f, (bf16*)a.dv + o0, nullptr, a.H, a.s - row0, d, lane);
+  } else if (kok) {
     bf16* DK = (bf16*)a.dk + hb + (long)krow * a.H;
     bf16* DV = (bf16*)a.dv + hb + (long)krow * a.H;
 #pragma unroll
@@ -694,7 +742,7 @@ __device__ __forceinline__ void attn_dkdv_body(const AttnArgs& a, float scale2, 
 
 // dq: the wave owns 32 query rows; key blocks of 64 stream through LDS
 template <int D, bool RAG, bool P32, int NW, typename R>
-__device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, float scale, const unsigned char* sm) {
+__device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, float scale, unsigned char* sm) {
   constexpr int NKK = D / 16, NDB = D / 32;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -780,7 +828,12 @@ __device__ __forceinline__ void attn_dq_body(const AttnArgs& a, float scale2, fl
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);
-  if (qok) {
+  if constexpr (D <= 64) {   // (as in attn_fwd_mfma)
+    typedef OutTile<NDB> Out;
+    __syncthreads();
+    const int row0 = blockIdx.x * (32 * NW) + wave * 32;
+    Out::store((float*)(sm + wave * Out::BYTES), dq, scale, (bf16*)a.dq + hb + (long)row0 * a.H, nullptr, a.H, a.s - row0, d, lane);
+  } else if (qok) {
     bf16* DQ = (bf16*)a.dq + hb + (long)qrow * a.H;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
@@ -852,7 +905,7 @@ constexpr int ONCE_NS = 3;
 typedef Ring<64, 8, ONCE_NS, true> OnceRing;
 typedef Ring<64, 4, 2, false> OnceKeys;   // stage i: rows 64 i .. 64 i + 63 of the group's keys and values
 constexpr int ONCE_X = 128 * 64 * 2;      // dS of a block of queries: [128 keys][64 queries], chunks swizzled by aswz
-constexpr int ONCE_BYTES = OnceKeys::BYTES + OnceRing::BYTES + 2 * ONCE_X;
+constexpr int ONCE_BYTES = OnceKeys::BYTES + OnceRing::BYTES + 2 * ONCE_X + 4 * 32 * 68 * 4;   // ... and outputs' staging
 
 __global__ __launch_bounds__(512, 2) void attn_bwd_once(AttnArgs a, float scale2, float scale) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char asm_[];
@@ -975,21 +1028,12 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_once(AttnArgs a, float scale2
       }
       if (g + 1 == nkg) OnceRing::wait();   // (the other waves' last step, not behind these stores)
       if (live) {
-        const long at = hb + (long)(128 * g + r) * a.H + 4 * h;
-        bf16 *const DK = (bf16*)a.dk + at, *const DV = (bf16*)a.dv + at;
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-#pragma unroll
-          for (int blk = 0; blk < 4; ++blk) {
-            bf16x4 o1, o2;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              o1[e] = (bf16)(dk[db][4 * blk + e] * scale);
-              o2[e] = (bf16)dv[db][4 * blk + e];
-            }
-            *(bf16x4*)(DK + db * 32 + 8 * blk) = o1;
-            *(bf16x4*)(DV + db * 32 + 8 * blk) = o2;
-          }
+        const long o0 = hb + (128L * g + 32 * wave) * a.H;
+        float* const S = (float*)(xs + 2 * ONCE_X + wave * OutTile<NDB>::BYTES);
+        int at = lane;
+        asm volatile("" : "+v"(at));   // (addresses made of it are not kept through the loop)
+        OutTile<NDB>::store(S, dk, scale, (bf16*)a.dk + o0, nullptr, a.H, 32, D, at);
+        OutTile<NDB>::store(S, dv, 1.f, (bf16*)a.dv + o0, nullptr, a.H, 32, D, at);
       }
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);   // the last requests (they read nothing) before the wave may end
@@ -1037,18 +1081,15 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_once(AttnArgs a, float scale2
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);
+  // (where the keys were: these waves read them last, barriers ago)
+  int at = lane;
+  asm volatile("" : "+v"(at));   // (addresses made of it are not kept through the loop)
+  static_assert(4 * OutTile<1>::BYTES <= OnceKeys::BYTES, "staging of four waves");
 #pragma unroll
   for (int i = 0; i < MAXQ; ++i)
-    if (i < nq) {
-      bf16* DQ = (bf16*)a.dq + hb + (long)(64 * i + 32 * qt + (lane & 31)) * a.H + 32 * dh + 4 * h;
-#pragma unroll
-      for (int blk = 0; blk < 4; ++blk) {
-        bf16x4 ov;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) ov[e] = (bf16)(dq[i][4 * blk + e] * scale);
-        *(bf16x4*)(DQ + 8 * blk) = ov;
-      }
-    }
+    if (i < nq)
+      OutTile<1>::store((float*)(kv + w * OutTile<1>::BYTES), &dq[i], scale, (bf16*)a.dq + hb + (64L * i + 32 * qt) * a.H + 32 * dh, nullptr,
+                        a.H, 32, 32, at);
 }
 
 // ------------------------------------------------------------------ launchers
