@@ -399,8 +399,8 @@ __device__ __forceinline__ f32x16 zero16() {
 // A wave's 32 rows x 32 NDB columns of an output (t: rows = columns of the head, column = the lane's row) times f, through a
 // piece of LDS of the wave's own into whole rows: straight from the accumulators a store is 16 bytes (32 of an fp32 copy)
 // of each of 32 rows, and the L2 takes every line in eight pieces.  rows: valid rows; d: columns of the head.
-// C32 (may be NULL): an fp32 copy.
-template <int NDB>
+// C32 (may be NULL): an fp32 copy; FAR: it is not read again soon enough to be kept in a cache (see store_c in gemm_mfma.h).
+template <int NDB, bool FAR = false>
 struct OutTile {
   static constexpr int W = 32 * NDB, LD = W + 4, BYTES = 32 * LD * 4;
   static __device__ __forceinline__ void store(float* S, const f32x16* t, float f, bf16* C, float* C32, long ld, int rows, int d, int lane) {
@@ -421,7 +421,10 @@ struct OutTile {
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = (bf16)v[e];
         *(bf16x4*)(C + (i + r) * ld + c) = o;
-        if (C32) *(f32x4*)(C32 + (i + r) * ld + c) = v;
+        if (C32) {
+          if (FAR) __builtin_nontemporal_store(v, (f32x4*)(C32 + (i + r) * ld + c));
+          else *(f32x4*)(C32 + (i + r) * ld + c) = v;
+        }
       }
     }
     __builtin_amdgcn_wave_barrier();
@@ -559,7 +562,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void attn_fwd_mfma(AttnA
   __builtin_amdgcn_s_waitcnt(0x0F70);   // the ring's last requests (they read nothing) before the wave may end
   const float inv = 1.0f / l;
   if constexpr (D <= 64) {
-    typedef OutTile<NDB> Out;
+    typedef OutTile<NDB, NW == 4> Out;
     static_assert(NW * Out::BYTES <= R::BYTES, "the output's staging lies where the ring was");
     __syncthreads();   // every wave is done with the ring, and its requests
     const int row0 = blockIdx.x * (32 * NW) + wave * 32;

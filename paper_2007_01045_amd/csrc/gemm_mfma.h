@@ -247,16 +247,22 @@ struct FragAddr {
   }
 };
 
-// A lane's 8 or 16 bytes of C.  THROUGH: written through to memory.  What a launch leaves dirty in the eight L2s (32 MB) is
-// written back when it ends, with nothing beside it; the large tiles, whose launches write that much and more, send it on
-// while other tiles still multiply (6 layers of 1024: 8192 rows 10.66 -> 10.52 ms, with re-computation 28.0 -> 27.7;
-// small launches only lose what the next kernel would have found in its L2: one sample 1216 -> 1240 us with all tiles).
+// A lane's 8 or 16 bytes of an output.
+// Through: written through to memory.  What a launch leaves dirty in the eight L2s (32 MB) is written back when it ends,
+// with nothing beside it; the large tiles, whose launches write that much and more, send it on while other tiles still
+// multiply (6 layers of 1024: 8192 rows 10.66 -> 10.52 ms, with re-computation 28.0 -> 27.7; small launches only lose what
+// the next kernel would have found in its L2: one sample 1216 -> 1240 us with all tiles).
+// Far: not kept in the caches.  What only the backward task reads again -- GELU', the attention's fp32 output -- is out of
+// them by then and takes the place of what the next kernels read (12 layers of 4096 rows 24.93 -> 24.62 ms, 6 of 8192 10.43
+// -> 10.38; with smaller tiles too one sample 1214 -> 1219 us, 2 layers of 2048 rows 680 -> 684: what they write is still there).
 // (Wait states: a store of more than 8 bytes reads its data after issue, and the compiler does not see one in here.)
-template <bool THROUGH, typename V>
+enum class Store { Plain, Through, Far };
+template <Store S, typename V>
 __device__ __forceinline__ void store_c(void* p, V v) {
   typedef float fv __attribute__((__vector_size__(sizeof(V))));
   const fv x = __builtin_bit_cast(fv, v);
-  if constexpr (!THROUGH) *(fv*)p = x;
+  if constexpr (S == Store::Plain) *(fv*)p = x;
+  else if constexpr (S == Store::Far) __builtin_nontemporal_store(x, (fv*)p);
   else if constexpr (sizeof(V) == 8) asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(p), "v"(x) : "memory");
   else asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(x) : "memory");
 }
@@ -428,7 +434,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   constexpr int NIT = 32 * C4 / 64;           // float4 per lane per 32-row block
   static_assert(64 % C4 == 0, "a lane stores the same columns of every row");
   constexpr int HB = MI > 2 ? (NIT > 4 ? 4 : NIT) : (NIT > 8 ? 8 : NIT);   // processed HB at a time
-  constexpr bool THROUGH = BM == 256;
+  constexpr Store THROUGH = BM == 256 ? Store::Through : Store::Plain, FAR = BM == 256 ? Store::Far : Store::Plain;
   constexpr bool PRE = !CS && !SEG && MI * NIT <= 16;   // (the column-sum variant serves accumulating products only)
   const int epi = g.epi;
   const int lane_col = n0 + wn0 + lane % C4 * 4;   // the lane's four columns
@@ -876,7 +882,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
           }
           if (ok[u]) {
             store_c<THROUGH>(at(Cb, g.ldc, c_off4 >> 1, i, hb + u, 2), gv);
-            store_c<THROUGH>(at(g.C2, g.ldc, c_off4 >> 1, i, hb + u, 2), gp);
+            store_c<FAR>(at(g.C2, g.ldc, c_off4 >> 1, i, hb + u, 2), gp);
           }
         }
       } else {
