@@ -255,6 +255,8 @@ struct FragAddr {
 // Far: not kept in the caches.  What only the backward task reads again -- GELU', the attention's fp32 output -- is out of
 // them by then and takes the place of what the next kernels read (12 layers of 4096 rows 24.93 -> 24.62 ms, 6 of 8192 10.43
 // -> 10.38; with smaller tiles too one sample 1214 -> 1219 us, 2 layers of 2048 rows 680 -> 684: what they write is still there).
+// Weight gradients summed over several micro-batches likewise: read and written once per group (2 layers of 2048 rows
+// 682 -> 676 us, 12 of 4096 24.44 -> 24.31 ms; with non-temporal loads of C too 24.54).
 // (Wait states: a store of more than 8 bytes reads its data after issue, and the compiler does not see one in here.)
 enum class Store { Plain, Through, Far };
 template <Store S, typename V>
@@ -855,7 +857,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
       if (SEG || (epi & EPI_OUT32)) {   // (SEG: C is in the sum already)
 #pragma unroll
         for (int u = 0; u < HB; ++u)
-          if (ok[u]) store_c<THROUGH>(at(Cb, g.ldc, c_off4, i, hb + u, 4), f32x4{t[u].x, t[u].y, t[u].z, t[u].w});
+          if (ok[u]) store_c<SEG ? Store::Far : THROUGH>(at(Cb, g.ldc, c_off4, i, hb + u, 4), f32x4{t[u].x, t[u].y, t[u].z, t[u].w});
       } else if (mode == ACCF || (mode == ANY && has_acc)) {
         float4 cv[HB];
 #pragma unroll
