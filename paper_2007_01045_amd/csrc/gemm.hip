@@ -108,6 +108,13 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 //   7: 64x64, four stages of 64        T=512 N=1024 K=4096 23 (128x64) -> 16, K=1024 9.6 -> 6.9; T=1024 23 -> 17
 //   8: 128x128, four waves, four       two workgroups per unit: T=4096 N=1024 K=1024 17 (128x64: 19), and beside another
 //      stages of 32                    stream K=4096 38 (the five-stage ring 35, two stages of 64 47)
+//   9: 32x64, two waves, four          where 64x64 tiles leave half of the units without work: what a unit requests bounds
+//      stages of 64                    them, and these request three quarters of it.  T=512 N=1024 K=4096 forward 16.2 ->
+//                                      14.3, gradient 15.1 -> 13.5, K=1024 7.0 -> 6.4; T=512 N=256 K=256 4.8 -> 3.9 (not
+//                                      two to a unit: T=1024 N=1024 K=4096 17 -> 21.  Six stages: that gradient 11.9, but
+//                                      beside the weight gradients' stream all of a layer's backward 1.5% slower)
+//  10: 32x32, one wave, four stages    half of it.  T=256 N=1024 K=4096 14.6 -> 12.8, 14.9 -> 12.3 (32x64: 12.9, 13.1);
+//      of 64                           T=256 N=256 K=512 5.7 -> 4.1 (4.4)
 // A stream restricted to part of the units (GemmArgs::units) moves the lines with it: four stages of 2048 rows on 64
 // units each, 36.7 -> 32.2 ms per iteration.  Where another stream's products run beside this one (GemmArgs::shared: the
 // data gradients beside the weight gradients) the tile with the whole LDS keeps them off its unit: 12 layers of 1024
@@ -122,6 +129,7 @@ static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   int tile = g.tile;   // GemmArgs::tile names a configuration instead (tests, timing)
   if (tile == 5 && !tt) tile = 3;
   if (tile == 8 && g.a_kstrided) tile = tt ? 5 : 3;   // (products whose rows are activations only)
+  if (tile >= 9 && g.a_kstrided) tile = 7;
   if (bsum && (tile == 1 || tile == 2 || tile == 6)) tile = 0;
   if (short_k) return tile == 3 || (tile != 4 && t128 >= most) ? 3 : 4;
   if (g.epi & EPI_SEGACC) tile = 0;
@@ -136,6 +144,7 @@ static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   if (t256 >= most && t256 <= U && (g.K >= 2048 || !second || g.N <= 1024)) return 2;
   if (t128 > U) return 3;
   if (t128 >= most) return g.K >= 2048 && !g.shared ? 6 : 8;
+  if (tiles(32, 64) <= U && !g.a_kstrided) return tiles(32, 32) <= U ? 10 : 9;
   return g.K >= 2048 && tiles(64, 64) > U ? 4 : 7;
 }
 

@@ -66,8 +66,8 @@ struct OperandTile {
   static __device__ __forceinline__ int rswz(int row) { return BK == 64 ? (row >> 1) & 7 : (row >> 2) & 3; }
 
   // chunk swizzle of k row k of a k-strided tile: rows of 256 B or more rotate by 64 B per
-  // row (4 rows cover 256 B); rows of 128 B alternate halves every second row
-  static __device__ __forceinline__ int kswz(int k) { return R >= 128 ? (k & 3) << 2 : ((k >> 1) & 1) << 2; }
+  // row (4 rows cover 256 B); rows of 128 B alternate halves every second row; four rows of 64 B are 256 B as they are
+  static __device__ __forceinline__ int kswz(int k) { return R >= 128 ? (k & 3) << 2 : R == 64 ? ((k >> 1) & 1) << 2 : 0; }
 
   // A wave loads NI consecutive 1 KiB chunks of the tile.  The instruction's immediate offset is
   // added to the global AND to the LDS address, so the loads of a group of up to four chunks share
@@ -153,7 +153,7 @@ struct OperandTile {
 };
 
 // One k-tile's requests of both operands in one block: the wait states before the first one serve both.
-constexpr bool has_load_pair(int na, int nb) { return (na == nb && (na == 1 || na == 2 || na == 4)) || (na == 4 && nb == 2); }
+constexpr bool has_load_pair(int na, int nb) { return (na == nb && (na == 1 || na == 2 || na == 4)) || (na == 4 && nb == 2) || (na == 2 && nb == 4); }
 template <int A_OFF, int B_OFF, typename TA, typename TB>
 __device__ __forceinline__ void load_pair(const TA& a, const TB& b, int4v ars, int4v brs, int wave_off_a, int wave_off_b) {
   constexpr int NA = TA::NI, NB = TB::NI;
@@ -193,6 +193,20 @@ __device__ __forceinline__ void load_pair(const TA& a, const TB& b, int4v ars, i
         :
         : "s"(wave_off_a), "s"(wave_off_b), "i"(A_OFF), "i"(B_OFF), "s"(ars), "s"(brs), "v"(a.voff[0]), "v"(a.voff[1]),
           "v"(a.voff[2]), "v"(a.voff[3]), "v"(b.voff[0]), "v"(b.voff[1]), "v"(b.voff[2]), "v"(b.voff[3])
+        : "memory", "m0", "scc");
+  } else if constexpr (NA == 2 && NB == 4) {
+    asm volatile(
+        "s_nop 4\n\ts_add_u32 m0, %0, %2\n\ts_nop 0\n\t"
+        "buffer_load_dwordx4 %6, %4, 0 offen lds\n\t"
+        "buffer_load_dwordx4 %7, %4, 0 offen offset:1024 lds\n\t"
+        "s_add_u32 m0, %1, %3\n\ts_nop 0\n\t"
+        "buffer_load_dwordx4 %8, %5, 0 offen lds\n\t"
+        "buffer_load_dwordx4 %9, %5, 0 offen offset:1024 lds\n\t"
+        "buffer_load_dwordx4 %10, %5, 0 offen offset:2048 lds\n\t"
+        "buffer_load_dwordx4 %11, %5, 0 offen offset:3072 lds"
+        :
+        : "s"(wave_off_a), "s"(wave_off_b), "i"(A_OFF), "i"(B_OFF), "s"(ars), "s"(brs), "v"(a.voff[0]), "v"(a.voff[1]),
+          "v"(b.voff[0]), "v"(b.voff[1]), "v"(b.voff[2]), "v"(b.voff[3])
         : "memory", "m0", "scc");
   } else {
     static_assert(NA == 4 && NB == 2, "see has_load_pair");
@@ -297,7 +311,7 @@ struct GemmTile {
   // Fragments are read from LDS a whole k-tile ahead of their MFMAs (two sets of them) instead of one k-step: where a
   // wave's k-step is one or two MFMAs (32 or 64 clocks) and no other wave shares its SIMD, an LDS round trip per k-step
   // is what such a loop takes.
-  static constexpr bool AHEAD = NW == 4 && MI * NI <= 2 && NS % 2 == 0;
+  static constexpr bool AHEAD = NW <= 4 && MI * NI <= 2 && NS % 2 == 0;
   // waves per SIMD the registers must allow: two workgroups where LDS has room for them
   static constexpr bool TWO = LDS_BYTES <= 80 * 1024;
   static constexpr int MIN_WAVES = !SEG && NW == 8 && TWO ? 4 : (SEG || (NW == 4 && TWO) ? 2 : 1);
@@ -324,7 +338,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   const int m0 = tm * BM, n0 = tn * BN;
   // (the small tiles: every argument the prologue and the first requests need in one go of scalar loads, not a round trip
   // per branch that uses some)
-  constexpr bool EARLY = CFG::NW == 4 && MI * (CFG::WN / 8) <= 8;
+  constexpr bool EARLY = CFG::NW <= 4 && MI * (CFG::WN / 8) <= 8;
   if constexpr (EARLY)
     asm volatile("" ::"s"(g.A), "s"(g.B), "s"(g.C), "s"(g.bias), "s"(g.aux), "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.lda), "s"(g.ldb),
                  "s"(g.ldc), "s"(g.ldaux), "s"(g.kseg_len), "s"(g.segA), "s"(g.segB), "s"(g.ln_stats), "s"(g.ln_gamma),

@@ -14,6 +14,8 @@ hipError_t launch_mfma_nt(int tile, bool short_k, const GemmArgs& g, hipStream_t
     case 4: return launch_mfma<128, 64, 2, 2, 3, false, true, 64>(g, st);
     case 6: return launch_mfma<128, 128, 2, 4, 5, false, true, 64>(g, st);
     case 8: return launch_mfma<128, 128, 2, 2, 4, false, true, 32>(g, st);
+    case 9: return launch_mfma<32, 64, 1, 2, 4, false, true, 64>(g, st);
+    case 10: return launch_mfma<32, 32, 1, 1, 4, false, true, 64>(g, st);
     default: return launch_mfma<64, 64, 2, 2, 4, false, true, 64>(g, st);
   }
 }

@@ -131,6 +131,20 @@ def test_gemm_mfma_64_wide_tile():
     gemm_case(B.DTYPE_BF16, 328, 200, 192, False, False, B.EPI_ROWDOT | B.EPI_AUX32, expect_mfma=True, tile=7)
 
 
+@pytest.mark.parametrize("tile", [9, 10])
+def test_gemm_mfma_32_row_tiles(tile):
+    # K shorter than the ring, no multiple of it, longer; ragged edges; both layouts; segments; the other layouts get the
+    # 64x64 tile
+    for K in (64, 128, 320, 448, 1536):
+        gemm_case(B.DTYPE_BF16, 72, 136, K, False, True, B.EPI_BIAS | B.EPI_GELU, expect_mfma=True, tile=tile)
+        gemm_case(B.DTYPE_BF16, 40, 72, K, False, False, B.EPI_MUL, expect_mfma=True, tile=tile)
+    gemm_case(B.DTYPE_BF16, 72, 136, 192, False, True, B.EPI_BIAS, batch=3, expect_mfma=True, tile=tile)
+    gemm_case(B.DTYPE_BF16, 200, 264, 3 * 192, False, False, B.EPI_ADD, nseg=3, expect_mfma=True, tile=tile)
+    gemm_case(B.DTYPE_BF16, 328, 200, 192, False, False, B.EPI_ROWDOT | B.EPI_AUX32, expect_mfma=True, tile=tile)
+    gemm_case(B.DTYPE_BF16, 136, 264, 320, True, False, 0, expect_mfma=True, tile=tile)
+    gemm_case(B.DTYPE_BF16, 64, 64, 320, True, True, B.EPI_ACC32 | B.EPI_BSUM, expect_mfma=True, tile=tile)
+
+
 @pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 6, 8])
 def test_gemm_row_sums_of_output_times_second_operand(tile):
     # ragged M and N (N not a multiple of 32: the last block is short), bf16 and fp32 second operand
