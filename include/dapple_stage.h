@@ -169,8 +169,8 @@ int stage_schedule_ops(int M, int K, int order, int32_t* ops_out, int capacity);
  * micro-batches; the K resident ones are cut into runs of that many slots and a shorter one).  At most K micro-batches
  * are resident as before, and every accumulator gets each micro-batch's sum on its own, in list order.  Buffers of
  * consecutive micro-batches that lie one behind the other (xs[m+1] = xs[m] + b*s*H, likewise ys, dys, dxs, auxs) save a
- * few launches at the ends of the stage.  Weight gradients go to the library's side stream where that pays (between 6
- * and 150 GFLOP a layer and task).  An explicit list is run task by task, as listed.
+ * few launches at the ends of the stage.  Weight gradients go to the library's side stream where that pays (between 12,
+ * narrow layers 20, and 150 GFLOP a layer and task; from 6 under re-computation).  An explicit list is run task by task, as listed.
  * Buffers of different tasks may overlap (ys[m] as xs[m+1], a ring of ys): every task then finds what the tasks listed
  * before it left, and a call whose groups would show is run task by task.  (Not so between a forward and the backward of
  * another micro-batch under STAGE_FLAG_RECOMPUTE, where the two may overlap in time.)

@@ -169,13 +169,22 @@ double layer_flops(const stage_config& c, int n) {   // a layer's forward over n
   return 8.0 * T * H * H + 4.0 * T * H * F;
 }
 // Whether the weight gradients of tasks over n micro-batches stay on the task's own stream (units: compute units the
-// stream may use), by the matrix flops of a layer's forward; else they go to the side stream.  Below 6 GFLOP an event
-// per hand-over costs the host 2-5 us and the streams' kernels a wait, more than the overlap gives on launches of a few
-// us: 256-wide stage, 0.8 GFLOP, 470 us with streams, 330 without; 1024-wide, 3 GFLOP, 1133 / 1111, 13 GFLOP 1219 /
-// 1235.  (fp32 products take eight times as long.)  From 150 GFLOP on every bf16 product fills the chip, and two at a
-// time only take the caches from each other: 1024-wide, 103 GFLOP, 25.2 ms with the side stream, 25.7 without; 206
-// GFLOP 11.07 / 10.87; 2048-wide, 824 GFLOP, 20.7 / 18.9.
-bool small_tasks(const stage_config& c, int n) { return layer_flops(c, n) < (c.dtype == STAGE_DTYPE_BF16 ? 6e9 : 7.5e8); }
+// stream may use), by the matrix flops of a layer's forward; else they go to the side stream.  Below 12 GFLOP -- 20 where a
+// weight of the FFN makes fewer 128x128 tiles than there are units -- an event per hand-over costs the host 2-5 us and the
+// streams' kernels a wait, and the gradients' large tiles hold units that the small ones of the main chain are short of:
+// more than the overlap gives.  Us with the side stream / without: 512 wide, 6.4 GFLOP 892 / 791, 12.9 950 / 913, 19.3
+// 422 / 388; 768 wide, 8.5 GFLOP 3684 / 3372, 12.7 1290 / 1253, 17 2282 / 2226, 21.7 2547 / 2616, 25.5 1889 / 1943; 1024
+// wide, 6.4 GFLOP 1047 / 987, 12.9 1187 / 1184, 10097 / 10240 and 9268 / 9305.  (fp32 products take eight times as long:
+// 1024 wide, 52 GFLOP 3.08 / 3.15 ms, 256 wide 575 / 583 us.)  From 150 GFLOP on every bf16 product fills the chip, and
+// two at a time only take the caches from each other: 1024-wide, 103 GFLOP, 24.1 ms with the side stream, 24.7 without;
+// 206 GFLOP 11.07 / 10.87; 2048-wide, 824 GFLOP, 20.7 / 18.9.
+// With re-computation tasks overlap each other on lanes instead, and the line is 6 GFLOP (12.9: 4.67 ms with lanes and side
+// stream, 5.83 without).
+bool small_tasks(const stage_config& c, int n) {
+  const bool wide = (long)((c.hidden + 127) / 128) * ((c.ffn + 127) / 128) >= 256;
+  const double line = c.dtype != STAGE_DTYPE_BF16 ? 7.5e8 : c.flags & STAGE_FLAG_RECOMPUTE ? 6e9 : wide ? 1.2e10 : 2e10;
+  return layer_flops(c, n) < line;
+}
 bool full_tasks(const stage_config& c, int n, int units) {
   return c.dtype == STAGE_DTYPE_BF16 && layer_flops(c, n) >= 1.5e11 * units / 256;
 }

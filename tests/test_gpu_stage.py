@@ -395,7 +395,7 @@ def test_one_stream_flag_changes_no_bit():
 @pytest.mark.parametrize("M,K", [(1, 1), (5, 3), (4, 4)])
 @pytest.mark.parametrize("kind", ["bf16", "f32", "first", "last"])
 def test_streams_change_no_bit(kind, M, K):
-    """Tasks that go to several streams (a layer's forward between 6 and 150 GFLOP; fp32 from 0.75 on): the side stream
+    """Tasks that go to several streams (a layer's forward between 12 and 150 GFLOP; fp32 from 0.75 on): the side stream
     with the weight gradients' list cut in two, and under re-computation the forward lane and two backward lanes,
     against the same stage on one stream."""
     shape = (2, 256, 4, 1024, 128, 4) if kind == "f32" else (2, 1024, 16, 4096, 256, 2)
@@ -403,7 +403,7 @@ def test_streams_change_no_bit(kind, M, K):
                         has_mlm_head=kind == "last", vocab=500, max_pos=256)
     T, H, F = cfg.tokens, cfg.hidden, cfg.ffn
     gflop = (8 * H * H + 4 * H * F) * T * 1e-9
-    assert gflop >= 0.75 if kind == "f32" else 6 <= gflop and gflop * min(M, K, 8192 // T) < 150
+    assert gflop >= 0.75 if kind == "f32" else 12 <= gflop and gflop * min(M, K, 8192 // T) < 150
     theta, mbs = make_inputs(cfg, SEED, M)
     ref = _bits(run_gpu(cfg, theta, mbs, M, K, B.ORDER_EARLY_BACKWARD, flags=B.FLAG_ONE_STREAM))
     ops = B.stage_schedule_ops(M, K, B.ORDER_EARLY_BACKWARD)
@@ -411,6 +411,21 @@ def test_streams_change_no_bit(kind, M, K):
         for kw in (dict(order=B.ORDER_EARLY_BACKWARD), dict(order=B.ORDER_GPIPE), dict(order=B.ORDER_EXPLICIT, explicit_ops=ops)):
             got = _bits(run_gpu(cfg, theta, mbs, M, K, flags=flags, **kw))
             assert all(np.array_equal(x, y) for x, y in zip(ref, got)), (flags, kw)
+
+
+@pytest.mark.parametrize("shape", [(2, 512, 8, 2048, 512, 4), (2, 768, 12, 3072, 200, 3)])
+def test_narrow_stages_on_either_side_of_the_side_streams_line(shape):
+    # a layer's forward of 12.9 and 8.5 GFLOP for one micro-batch (its tasks keep the weight gradients) and more than 20 for
+    # three (the side stream takes them); 6 GFLOP is the line under re-computation
+    cfg = I.StageConfig(*shape, 4, 3, "bf16")
+    T, H, F = cfg.tokens, cfg.hidden, cfg.ffn
+    gflop = (8 * H * H + 4 * H * F) * T * 1e-9
+    assert 6 <= gflop < 20 <= 3 * gflop and -(-H // 128) * -(-F // 128) < 256
+    theta, mbs = make_inputs(cfg, SEED, 4)
+    ref = _bits(run_gpu(cfg, theta, mbs, 4, 3, B.ORDER_EARLY_BACKWARD, flags=B.FLAG_ONE_STREAM))
+    for K, flags in ((3, 0), (1, 0), (3, B.FLAG_RECOMPUTE)):
+        got = _bits(run_gpu(cfg, theta, mbs, 4, K, B.ORDER_EARLY_BACKWARD, flags=flags))
+        assert all(np.array_equal(x, y) for x, y in zip(ref, got)), (K, flags)
 
 
 @pytest.mark.parametrize("kind", ["recompute", "first_stage", "last_stage", "gpipe_order", "side_stream", "recompute_lanes"])
