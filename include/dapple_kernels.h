@@ -73,6 +73,10 @@ typedef struct {
 
 /* Returns 1 if the bf16 MFMA kernel takes this problem, 0 if the plain kernel does. */
 int dapple_gemm(int dtype, const dapple_gemm_desc* d, void* stream);
+/* What dapple_gemm would launch (host only; nothing is enqueued).  Returns as dapple_gemm does; with 1, plan_out[0..3] are
+ * the rows and columns of a workgroup's tile, the depth of a k-tile, and the k-tiles each workgroup runs (a ring is filled
+ * in whole turns: k-tiles of zeros are among them). */
+int dapple_gemm_plan(int dtype, const dapple_gemm_desc* d, int32_t* plan_out);
 
 /* Attention of one layer.  q,k,v,ctx,dctx,dq,dk,dv: [b*s, H], head h in columns
  * [h*d, (h+1)*d), d = H / A.  lse [b,A,s] fp32: log2-domain logsumexp of the scaled

@@ -93,6 +93,7 @@ SYMBOLS = {
     "pipeline_sync": (_i, [_vp]),
     "pipeline_timeline": (_i, [_vp, C.POINTER(C.c_double), C.POINTER(C.c_double), _i]),
     "dapple_gemm": (_i, [_i, C.POINTER(dapple_gemm_desc), _vp]),
+    "dapple_gemm_plan": (_i, [_i, C.POINTER(dapple_gemm_desc), C.POINTER(C.c_int32)]),
     "dapple_attention_fwd": (_i, [_i, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _vp]),
     "dapple_attention_bwd": (_i, [_i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _vp]),
     "dapple_layernorm_fwd": (_i, [_i, _vp, _vp, _vp, _vp, _vp, _i, _i, _f, _vp]),
@@ -365,6 +366,15 @@ def dapple_gemm(dtype, desc: dapple_gemm_desc, stream_ptr=None) -> int:
     if rc < 0:
         raise StageError(rc, "dapple_gemm rejected its arguments")
     return rc
+
+
+def dapple_gemm_plan(dtype, desc: dapple_gemm_desc):
+    """(rows, columns, depth, k-tiles) of the MFMA launch that dapple_gemm would make, None if another kernel takes it."""
+    out = (C.c_int32 * 4)()
+    rc = load().dapple_gemm_plan(dtype, C.byref(desc), out)
+    if rc < 0:
+        raise StageError(rc, "dapple_gemm_plan rejected its arguments")
+    return tuple(out) if rc == 1 else None
 
 
 def _kcheck(rc, name):

@@ -10,7 +10,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdapple_stage.so")
-SOURCES = ["gemm_wgrad.hip", "gemm_tt.hip", "gemm_nt.hip", "gemm_nn.hip", "gemm_tn.hip", "gemm.hip", "gemm_f32.hip", "attention.hip", "attention_f32.hip",
+SOURCES = ["gemm_nn.hip", "gemm_nt.hip", "gemm_nn_pack.hip", "gemm_nt_pack.hip", "gemm_tn.hip", "gemm_tn_pack.hip", "gemm_tt.hip",
+           "gemm_tt_pack.hip", "gemm_wgrad.hip", "gemm.hip", "gemm_f32.hip", "attention.hip", "attention_f32.hip",
            "rowops.hip", "embed_head.hip", "optimizer.hip", "stage.hip", "pipeline.hip", "kernel_api.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-result", "-Wno-inline-asm",
          # keep the compiler from forming packed-fp32 instructions

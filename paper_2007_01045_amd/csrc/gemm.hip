@@ -172,7 +172,7 @@ hipError_t launch_wgrad_group(Dtype dt, const WgradGroup& w, hipStream_t st) {
   return dt == DT_BF16 ? launch_wgrad_group_mfma(w, st) : launch_wgrad_group_f32(w, st);
 }
 
-hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st) {
+hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st, GemmPlan* plan) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
   const bool mfma = gemm_uses_mfma(dt, g);
   if ((g.epi & EPI_ROWDOT) && !mfma) return hipErrorInvalidValue;  // only the MFMA kernel's epilogue has it
@@ -180,10 +180,12 @@ hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st) {
     const bool tt = g.a_kstrided && g.b_kstrided;   // the weight-gradient layout
     const bool short_k = g.kseg_len % 64 != 0 && !tt;
     const int tile = choose_tile(g, tt, short_k);
-    if (tt) return launch_mfma_tt(tile, short_k, g, st);
-    if (g.a_kstrided) return launch_mfma_tn(tile, short_k, g, st);
-    return g.b_kstrided ? launch_mfma_nt(tile, short_k, g, st) : launch_mfma_nn(tile, short_k, g, st);
+    const GemmLaunch l{tile, short_k, st, plan};
+    if (tt) return launch_mfma_tt(g, l);
+    if (g.a_kstrided) return launch_mfma_tn(g, l);
+    return g.b_kstrided ? launch_mfma_nt(g, l) : launch_mfma_nn(g, l);
   }
+  if (plan) return hipErrorInvalidValue;
   if (dt == DT_F32 && gemm_f32_takes(g)) return launch_gemm_f32(g, st);
   dim3 blk(32, 8);
   dim3 grid((g.N + 31) / 32, (g.M + 7) / 8, g.batch);

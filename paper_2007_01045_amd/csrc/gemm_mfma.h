@@ -320,8 +320,9 @@ struct GemmTile {
 // CS: the variant that can also sum B over k (EPI_BSUM); KT: the variant for K segments that are no multiple of 64
 // when an operand is k-contiguous (see OperandTile); SEG: an accumulating product over several K segments, each one's
 // sum added to C on its own, in order (EPI_SEGACC): a second set of accumulators holds C and takes the sums of the
-// segments as they are complete, so C is read and written once whatever their number
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false, bool SEG = false>
+// segments as they are complete, so C is read and written once whatever their number; PACK: the k-tiles of several
+// segments follow each other without a gap (see packs)
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false, bool SEG = false, bool PACK = false>
 __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, int tiles_n, const int bid, const int z) {
   typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, SEG> CFG;
   typedef typename CFG::TA TA;
@@ -346,9 +347,9 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
 
   const bf16 *Ab = (const bf16*)g.A + z * g.sA, *Bb = (const bf16*)g.B + z * g.sB;
   void* const Cb = g.C;
-  // (whole turns of the ring per segment; the k-tiles beyond a segment's end read nothing)
-  const int seg_tiles = (g.kseg_len + BK - 1) / BK;
-  const int turns = (seg_tiles + NS - 1) / NS;   // of the ring, per segment
+  // (whole turns of the ring per segment, PACK: in all; the k-tiles beyond the end read nothing)
+  const int nseg = g.K / g.kseg_len, seg_tiles = (g.kseg_len + BK - 1) / BK;
+  const int turns = ((PACK ? nseg * seg_tiles : seg_tiles) + NS - 1) / NS;   // of the ring, per segment (PACK: in all)
   const int k_rows = g.K > g.kseg_len ? g.kseg_len : g.k_valid;   // rows of one segment of a k-strided operand
   // bytes of one segment of each operand that may be read (beyond: zero)
   const long a_ext =
@@ -375,7 +376,9 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   // K segment the base jumps to the next segment and the records start over.
   // A wave issues an instruction every few clocks, and the small tiles' loop is bound by that: segments are whole turns of
   // the ring, so that only the turn's first slot, which requests the last tile of a turn, looks for a segment's end.
+  // (PACK: every slot does.)
   const int a_step = AKS ? BK * g.lda * 2 : BK * 2, b_step = BKS ? BK * g.ldb * 2 : BK * 2;
+  const long a_jump = g.segA * 2 - (long)(seg_tiles - 1) * a_step, b_jump = g.segB * 2 - (long)(seg_tiles - 1) * b_step;
   int4v ars, brs;
   auto set_base = [](int4v& rs, uint64_t p) {
     rs[0] = (int)(uint32_t)p;
@@ -400,9 +403,21 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   wave_off_b = __builtin_amdgcn_readfirstlane(wave_off_b);
   // Branch-free on purpose: with control flow inside the k-loop the accumulators get
   // copied between register files at every merge point.
-  int tiles_left = seg_tiles, turns_left = turns, segs_left = g.K / g.kseg_len;   // still to be requested
+  // still to be requested (tiles_left: of the segment, PACK: in all)
+  int tiles_left = PACK ? nseg * seg_tiles : seg_tiles, turns_left = turns, segs_left = nseg, seg_left = seg_tiles;
   auto advance = [&](auto S) __attribute__((always_inline)) {
     --tiles_left;
+    if constexpr (PACK) {
+      const bool cross = --seg_left == 0, more = tiles_left > 0;
+      set_base(ars, get_base(ars) + (uint64_t)(cross ? a_jump : (long)a_step));
+      set_base(brs, get_base(brs) + (uint64_t)(cross ? b_jump : (long)b_step));
+      ars[2] = more ? (cross ? a_rec0 : max(ars[2] - a_step, (int)TA::BIAS)) : (int)TA::BIAS;
+      brs[2] = more ? (cross ? b_rec0 : max(brs[2] - b_step, (int)TB::BIAS)) : (int)TB::BIAS;
+      seg_left = cross ? seg_tiles : seg_left;
+      ta.set_short(seg_left == 1);
+      tb.set_short(seg_left == 1);
+      return;
+    }
     set_base(ars, get_base(ars) + (uint32_t)a_step);
     set_base(brs, get_base(brs) + (uint32_t)b_step);
     int ar = max(ars[2] - a_step, (int)TA::BIAS), br = max(brs[2] - b_step, (int)TB::BIAS);
@@ -547,8 +562,8 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   constexpr int KSTEPS = BK / 16;
   static_assert(KSTEPS % 2 == 0, "the two fragment sets alternate over an even number of k-steps");
 
-  // The loop runs whole turns of the ring: K is padded to a multiple of NS k-tiles with
-  // tiles that read nothing (zeros in LDS add nothing), and every iteration requests a tile,
+  // The loop runs whole turns of the ring: each K segment (PACK: all of K) is padded to a multiple of NS k-tiles
+  // with tiles that read nothing (zeros in LDS add nothing), and every iteration requests a tile,
   // so the count of requests in flight is the same in every iteration.
   // vmcnt(N): at most N of this wave's requests still in flight; requests complete in order,
   // so N = (NS - 2) * LOADS_PER_TILE means "tile kt has landed"
@@ -746,12 +761,12 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
       request_c();
       turn(WCS, std::integral_constant<int, C_LOADS>{});
       end_segment(WCS);
-      for (int s = g.K / g.kseg_len; s > 1; --s) {
+      for (int s = nseg; s > 1; --s) {
         for (int t = 0; t < turns; ++t) turn(WCS, none);
         end_segment(WCS);
       }
     } else {
-      for (int t = g.K / g.kseg_len * turns; t > 0; --t) turn(WCS, none);
+      for (int t = PACK ? turns : nseg * turns; t > 0; --t) turn(WCS, none);
       end_segment(WCS);
     }
   };
@@ -930,15 +945,34 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   static_assert(MI <= 4, "at most four 32-row blocks per wave");
 }
 
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false, bool SEG = false>
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS, bool KT = false, bool SEG = false, bool PACK = false>
 __global__ __launch_bounds__(64 * WGM * WGN, (GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, SEG>::MIN_WAVES)) void gemm_mfma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-  gemm_mfma_tile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT, SEG>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.z);
+  gemm_mfma_tile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT, SEG, PACK>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.z);
 }
 
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool CS = false, bool KT = false, bool SEG = false>
-static hipError_t launch_mfma(const GemmArgs& g, hipStream_t st) {
+// Whether a product of several K segments takes the variant whose cursor looks for a segment's end at every k-tile: where
+// padding each segment to whole turns of a ring of ns would run more turns than padding their sum.  (The same turns: the
+// cheaper cursor.  No bit depends on it: k-tiles of zeros add nothing.)  The gradient of the attention's input, three
+// segments of the width, us with padded segments -> without: 320 wide, 4096 rows (24 k-tiles -> 16) 10.6 -> 8.8; 576, 2048
+// rows 13.7 -> 11.6; 200, 2048 rows 9.7 -> 8.4; 1024, 8192 rows (54 -> 48) 54.2 -> 52.1, 4096 rows (60 -> 50) 32.5 -> 30.3,
+// 2048 rows 22.7 -> 21.4.
+inline bool packs(const GemmArgs& g, int ns, int bk) {
+  const int seg_tiles = (g.kseg_len + bk - 1) / bk, nseg = g.K / g.kseg_len;
+  return nseg * ((seg_tiles + ns - 1) / ns) > (nseg * seg_tiles + ns - 1) / ns;
+}
+
+// packed: the same layout's launches with PACK, which are compiled on their own (NULL where these are they)
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool PACK, bool CS = false, bool KT = false, bool SEG = false>
+static hipError_t launch_mfma(const GemmArgs& g, const GemmLaunch& l, LaunchMfma packed) {
   typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, SEG> CFG;
-  auto kern = gemm_mfma_kernel<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT, SEG>;
+  if constexpr (!PACK && !SEG)   // (the sums of SEG's segments are kept apart: each one starts a turn)
+    if (packs(g, NS, BK)) return packed(g, l);
+  if (l.plan) {
+    const int seg_tiles = (g.kseg_len + BK - 1) / BK, nseg = g.K / g.kseg_len;
+    *l.plan = GemmPlan{BM, BN, BK, PACK ? (nseg * seg_tiles + NS - 1) / NS * NS : nseg * ((seg_tiles + NS - 1) / NS * NS)};
+    return hipSuccess;
+  }
+  auto kern = gemm_mfma_kernel<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT, SEG, PACK>;
   // once per instantiation, whichever host thread comes first (initialisation of a function-local static is
   // thread-safe)
   static const hipError_t attr_rc = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -946,7 +980,7 @@ static hipError_t launch_mfma(const GemmArgs& g, hipStream_t st) {
   if (attr_rc != hipSuccess) return attr_rc;
   int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   dim3 grid(tiles_m * tiles_n, 1, g.batch);
-  hipLaunchKernelGGL(kern, grid, dim3(CFG::NT), CFG::LDS_BYTES, st, g, tiles_m, tiles_n);
+  hipLaunchKernelGGL(kern, grid, dim3(CFG::NT), CFG::LDS_BYTES, l.st, g, tiles_m, tiles_n);
   return hipGetLastError();
 }
 

@@ -1,0 +1,8 @@
+// Products of several K segments with A k-strided and B k-contiguous (gemm_layouts.h).
+#include "gemm_layouts.h"
+
+namespace dapple {
+
+hipError_t launch_mfma_tn_pack(const GemmArgs& g, const GemmLaunch& l) { return launch_tn<true>(g, l, nullptr); }
+
+}  // namespace dapple

@@ -38,9 +38,8 @@ static int scratch_of_current_device(float** out) {
 static int dev_rc(hipError_t e) { return e == hipSuccess ? STAGE_OK : STAGE_E_DEVICE; }
 static bool bad_dtype(int dt) { return dt != STAGE_DTYPE_F32 && dt != STAGE_DTYPE_BF16; }
 
-extern "C" {
-
-int dapple_gemm(int dtype, const dapple_gemm_desc* d, void* stream) {
+// the launcher's arguments of a product; 1 if the MFMA kernel takes it, 0 if not, negative if the arguments are rejected
+static int gemm_args(int dtype, const dapple_gemm_desc* d, GemmArgs& g) {
   if (!d || !d->A || !d->B || !d->C) return STAGE_E_NULL;
   if (bad_dtype(dtype) || d->M < 1 || d->N < 1 || d->K < 1) return STAGE_E_CONFIG;
   if ((d->epi & DAPPLE_EPI_BIAS) && !d->bias) return STAGE_E_NULL;
@@ -55,7 +54,6 @@ int dapple_gemm(int dtype, const dapple_gemm_desc* d, void* stream) {
     if ((d->epi & (DAPPLE_EPI_ADD | DAPPLE_EPI_MUL | DAPPLE_EPI_GELU | DAPPLE_EPI_ACC32 | DAPPLE_EPI_OUT32)) || d->batch > 1)
       return STAGE_E_CONFIG;
   }
-  GemmArgs g{};
   g.A = d->A; g.B = d->B; g.C = d->C; g.C2 = d->C2; g.bias = d->bias; g.aux = d->aux;
   g.M = d->M; g.N = d->N; g.K = d->K; g.lda = d->lda; g.ldb = d->ldb; g.ldc = d->ldc; g.ldaux = d->ldaux;
   g.a_kstrided = d->a_kstrided; g.b_kstrided = d->b_kstrided;
@@ -64,12 +62,31 @@ int dapple_gemm(int dtype, const dapple_gemm_desc* d, void* stream) {
   g.k_valid = d->k_valid ? d->k_valid : d->K; g.epi = d->epi; g.tile = d->tile;
   g.m_valid = d->M; g.n_valid = d->N; g.bsum = d->bsum;
   if (g.K % g.kseg_len) return STAGE_E_CONFIG;
-  Dtype dt = dtype == STAGE_DTYPE_BF16 ? DT_BF16 : DT_F32;
   g.rowdot = d->rowdot;
-  int mfma = gemm_uses_mfma(dt, g) ? 1 : 0;
+  int mfma = gemm_uses_mfma(dtype == STAGE_DTYPE_BF16 ? DT_BF16 : DT_F32, g) ? 1 : 0;
   if ((g.epi & EPI_ROWDOT) && !mfma) return STAGE_E_CONFIG;  // the plain kernel has no such epilogue
-  hipError_t e = launch_gemm(dt, g, (hipStream_t)stream);
+  return mfma;
+}
+
+extern "C" {
+
+int dapple_gemm(int dtype, const dapple_gemm_desc* d, void* stream) {
+  GemmArgs g{};
+  const int mfma = gemm_args(dtype, d, g);
+  if (mfma < 0) return mfma;
+  hipError_t e = launch_gemm(dtype == STAGE_DTYPE_BF16 ? DT_BF16 : DT_F32, g, (hipStream_t)stream);
   return e == hipSuccess ? mfma : STAGE_E_DEVICE;
+}
+
+int dapple_gemm_plan(int dtype, const dapple_gemm_desc* d, int32_t* plan) {
+  if (!plan) return STAGE_E_NULL;
+  GemmArgs g{};
+  const int mfma = gemm_args(dtype, d, g);
+  if (mfma != 1) return mfma;
+  GemmPlan p{};
+  if (launch_gemm(DT_BF16, g, nullptr, &p) != hipSuccess) return STAGE_E_CONFIG;
+  plan[0] = p.rows; plan[1] = p.cols; plan[2] = p.depth; plan[3] = p.k_tiles;
+  return 1;
 }
 
 int dapple_attention_fwd(int dtype, const void* q, const void* k, const void* v, void* ctx, float* lse, int b,

@@ -68,13 +68,31 @@ struct GemmArgs {
   int rows1;
 };
 
-hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st);
+// a launch of the MFMA kernel: its tile, the depth of a k-tile, and the k-tiles a workgroup runs, those of zeros that fill
+// the ring's last turn among them
+struct GemmPlan {
+  int rows, cols, depth, k_tiles;
+};
+// plan: filled in instead of launching anything (MFMA kernel only)
+hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st, GemmPlan* plan = nullptr);
 // the MFMA kernel's launches per operand layout (a = A k-strided, b = B k-strided: nn, nt, tn, tt); tile: see
-// launch_gemm; short_k: K segments that are no multiple of 64
-hipError_t launch_mfma_nn(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
-hipError_t launch_mfma_nt(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
-hipError_t launch_mfma_tn(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
-hipError_t launch_mfma_tt(int tile, bool short_k, const GemmArgs& g, hipStream_t st);
+// choose_tile; short_k: K segments that are no multiple of 64
+struct GemmLaunch {
+  int tile;
+  bool short_k;
+  hipStream_t st;
+  GemmPlan* plan;   // filled in instead of launching anything, if given
+};
+typedef hipError_t (*LaunchMfma)(const GemmArgs& g, const GemmLaunch& l);
+hipError_t launch_mfma_nn(const GemmArgs& g, const GemmLaunch& l);
+hipError_t launch_mfma_nt(const GemmArgs& g, const GemmLaunch& l);
+hipError_t launch_mfma_tn(const GemmArgs& g, const GemmLaunch& l);
+hipError_t launch_mfma_tt(const GemmArgs& g, const GemmLaunch& l);
+// ... for products of several K segments that follow each other without a gap in the ring (packs, gemm_mfma.h)
+hipError_t launch_mfma_nn_pack(const GemmArgs& g, const GemmLaunch& l);
+hipError_t launch_mfma_nt_pack(const GemmArgs& g, const GemmLaunch& l);
+hipError_t launch_mfma_tn_pack(const GemmArgs& g, const GemmLaunch& l);
+hipError_t launch_mfma_tt_pack(const GemmArgs& g, const GemmLaunch& l);
 // out[c] += sum over blk (ascending, in the order of launch_partial_reduce) of partial[blk*stride + c], c < cols,
 // for up to 12 such jobs in one launch.  nmb > 1: the same for partial + mb_stride, partial + 2 mb_stride, ..., one
 // micro-batch's sum after the other

@@ -195,6 +195,30 @@ def test_gemm_mfma_segments_and_batch():
     gemm_case(B.DTYPE_BF16, 136, 128, 64, False, True, B.EPI_BIAS, batch=3, expect_mfma=True)
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10])
+def test_gemm_mfma_segments_that_are_no_whole_turns_of_the_ring(tile):
+    # one, three and five k-tiles of 64 a segment: every ring wraps inside a segment; against the oracle, and bit for bit
+    # against the same K as one segment
+    for Ks in (64, 192, 320):
+        for akS, bkS in ((False, False), (False, True), (True, False), (True, True)):
+            gemm_case(B.DTYPE_BF16, 136, 200, 3 * Ks, akS, bkS, B.EPI_ADD, nseg=3, expect_mfma=True, tile=tile)
+        gemm_case(B.DTYPE_BF16, 136, 200, 3 * Ks, True, True, B.EPI_ACC32 | B.EPI_BSUM, nseg=3, expect_mfma=True, tile=tile)
+        M, N = 264, 328
+        a, b = (torch.randn(r, 3 * Ks, generator=torch.Generator().manual_seed(r)).to("cuda", torch.bfloat16) for r in (M, N))
+        outs = []
+        for nseg in (1, 3):
+            k = 3 * Ks // nseg
+            sa, sb = (t.reshape(-1, nseg, k).transpose(0, 1).contiguous() for t in (a, b))
+            c = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+            d = B.dapple_gemm_desc()
+            d.A, d.B, d.C, d.M, d.N, d.K, d.lda, d.ldb, d.ldc = sa.data_ptr(), sb.data_ptr(), c.data_ptr(), M, N, 3 * Ks, k, k, N
+            d.kseg_len, d.segA, d.segB, d.tile = k, M * k, N * k, tile
+            assert B.dapple_gemm(B.DTYPE_BF16, d) == 1
+            outs.append(c)
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16)), (tile, Ks)
+
+
 @pytest.mark.parametrize("tile", [0, 3, 4])
 @pytest.mark.parametrize("K", [8, 56, 72, 120, 200, 600])
 def test_gemm_mfma_k_not_a_multiple_of_the_k_tile(K, tile):

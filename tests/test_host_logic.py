@@ -304,3 +304,38 @@ def test_pipeline_host_functions_follow_the_oracle():
     with pytest.raises(B.StageError):
         B.pipeline_latency_model(3, [1.0, 1.0], [1.0, 1.0], Q=2)
     assert B.pipeline_boundary_bytes(3, 4, 1000) == 2 * 2 * 4 * 1024
+
+
+def plan(M, N, Ks, nseg=1, akS=False, bkS=False, epi=0, tile=0):
+    """The launch dapple_gemm would make (host only: the pointers are never read)."""
+    d = B.dapple_gemm_desc()
+    d.A = d.B = d.C = d.aux = d.bsum = 1 << 20
+    d.M, d.N, d.K, d.kseg_len, d.segA, d.segB = M, N, Ks * nseg, Ks, 8 * M * Ks, 8 * N * Ks
+    d.lda, d.ldb, d.ldc, d.ldaux = (M if akS else Ks), (N if bkS else Ks), N, N
+    d.a_kstrided, d.b_kstrided, d.epi, d.tile = int(akS), int(bkS), epi, tile
+    return B.dapple_gemm_plan(B.DTYPE_BF16, d)
+
+
+@pytest.mark.parametrize("akS,bkS", [(False, False), (False, True), (True, False), (True, True)])
+def test_segments_of_a_product_share_the_turns_of_a_ring(akS, bkS):
+    # a workgroup runs less than one turn (five k-tiles at most) of zeros in all, whatever the length of a segment
+    for tile in range(11):
+        for Ks in [64 * n for n in range(1, 19)] + [8, 40, 200, 264]:
+            for nseg in (1, 2, 3, 4):
+                rows, cols, depth, tiles = plan(600, 320, Ks, nseg, akS, bkS, B.EPI_ADD, tile)
+                assert 0 <= tiles - nseg * -(-Ks // depth) < 5, (tile, Ks, nseg, rows, cols, depth, tiles)
+    # the data gradient of the attention's input: three segments of the hidden width
+    for H in range(64, 1088, 64):
+        for T in (256, 600, 2048, 4096, 8192):
+            _, _, depth, tiles = plan(T, H, H, 3, epi=B.EPI_ADD)
+            assert tiles - 3 * -(-H // depth) < 5, (T, H, depth, tiles)
+
+
+def test_the_plan_of_a_product_is_the_named_tile():
+    for tile, shape in {1: (256, 256, 32), 2: (256, 128, 64), 3: (128, 128, 64), 4: (128, 64, 64), 6: (128, 128, 64),
+                        7: (64, 64, 64), 8: (128, 128, 32), 9: (32, 64, 64), 10: (32, 32, 64)}.items():
+        assert plan(600, 320, 320, tile=tile)[:3] == shape
+    d = B.dapple_gemm_desc()
+    with pytest.raises(B.StageError):
+        B.dapple_gemm_plan(B.DTYPE_BF16, d)
+    assert plan(600, 322, 320) is None   # a row of C that is no multiple of 4: the plain kernel
