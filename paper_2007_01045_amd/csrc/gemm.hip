@@ -126,7 +126,7 @@ static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   auto tiles = [&](long m, long n) { return ((g.M + m - 1) / m) * ((g.N + n - 1) / n) * g.batch; };
   const long t128 = tiles(128, 128), U = g.units > 0 ? g.units : 256, most = 3 * U / 4;
   const bool bsum = (g.epi & EPI_BSUM) != 0;   // (offered for the weight-gradient layout only)
-  int tile = g.tile;   // GemmArgs::tile names a configuration instead (tests, timing)
+  int tile = g.tile < 0 || g.tile > 10 ? 7 : g.tile;   // GemmArgs::tile names a configuration instead (tests, timing)
   if (tile == 5 && !tt) tile = 3;
   if (tile == 8 && g.a_kstrided) tile = tt ? 5 : 3;   // (products whose rows are activations only)
   if (tile >= 9 && g.a_kstrided) tile = 7;
@@ -143,7 +143,9 @@ static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   if (tiles(256, 256) >= most && !(g.epi & (EPI_ADD | EPI_AUX32))) return 1;
   if (t256 >= most && t256 <= U && (g.K >= 2048 || !second || g.N <= 1024)) return 2;
   if (t128 > U) return 3;
-  if (t128 >= most) return g.K >= 2048 && !g.shared ? 6 : 8;
+  // (A k-strided has no 8, and is never beside another stream.  Us for tiles 3 / 4 / 6: 2048 x 1920 x 512 8.7 / 9.6 / 8.8,
+  // 2048 x 2048 x 1024 11.8 / 13.7 / 12.6, 1536 x 2048 x 1536 18.4 / 16.0 / 13.6, 1792 x 1792 x 1792 23.4 / 18.7 / 16.9)
+  if (t128 >= most) return g.a_kstrided ? (g.K > 1024 ? 6 : 3) : g.K >= 2048 && !g.shared ? 6 : 8;
   if (tiles(32, 64) <= U && !g.a_kstrided) return tiles(32, 32) <= U ? 10 : 9;
   return g.K >= 2048 && tiles(64, 64) > U ? 4 : 7;
 }

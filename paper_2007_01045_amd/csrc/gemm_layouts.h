@@ -4,6 +4,8 @@
 
 namespace dapple {
 
+// (A tile that a layout does not hold is an error: choose_tile names none.)
+
 // A k-contiguous: forward products (BKS) and data gradients
 template <bool BKS, bool PACK>
 static hipError_t launch_rows(const GemmArgs& g, const GemmLaunch& l, LaunchMfma packed) {
@@ -19,7 +21,8 @@ static hipError_t launch_rows(const GemmArgs& g, const GemmLaunch& l, LaunchMfma
     case 8: return launch_mfma<128, 128, 2, 2, 4, false, BKS, 32, PACK>(g, l, packed);
     case 9: return launch_mfma<32, 64, 1, 2, 4, false, BKS, 64, PACK>(g, l, packed);
     case 10: return launch_mfma<32, 32, 1, 1, 4, false, BKS, 64, PACK>(g, l, packed);
-    default: return launch_mfma<64, 64, 2, 2, 4, false, BKS, 64, PACK>(g, l, packed);
+    case 7: return launch_mfma<64, 64, 2, 2, 4, false, BKS, 64, PACK>(g, l, packed);
+    default: return hipErrorInvalidValue;
   }
 }
 
@@ -35,7 +38,8 @@ static hipError_t launch_tn(const GemmArgs& g, const GemmLaunch& l, LaunchMfma p
     case 3: return launch_mfma<128, 128, 2, 4, 2, true, false, 64, PACK>(g, l, packed);
     case 4: return launch_mfma<128, 64, 2, 2, 3, true, false, 64, PACK>(g, l, packed);
     case 6: return launch_mfma<128, 128, 2, 4, 5, true, false, 64, PACK>(g, l, packed);
-    default: return launch_mfma<64, 64, 2, 2, 4, true, false, 64, PACK>(g, l, packed);
+    case 7: return launch_mfma<64, 64, 2, 2, 4, true, false, 64, PACK>(g, l, packed);
+    default: return hipErrorInvalidValue;
   }
 }
 
@@ -52,9 +56,10 @@ static hipError_t launch_tt(const GemmArgs& g, const GemmLaunch& l, LaunchMfma p
         case 4:
           return bsum ? launch_mfma<128, 64, 2, 2, 3, true, true, 64, false, true, false, true>(g, l, packed)
                       : launch_mfma<128, 64, 2, 2, 3, true, true, 64, false, false, false, true>(g, l, packed);
-        default:
+        case 7:
           return bsum ? launch_mfma<64, 64, 2, 2, 4, true, true, 64, false, true, false, true>(g, l, packed)
                       : launch_mfma<64, 64, 2, 2, 4, true, true, 64, false, false, false, true>(g, l, packed);
+        default: return hipErrorInvalidValue;
       }
     }
   switch (l.tile) {
@@ -70,9 +75,10 @@ static hipError_t launch_tt(const GemmArgs& g, const GemmLaunch& l, LaunchMfma p
       return bsum ? launch_mfma<128, 128, 2, 4, 4, true, true, 32, PACK, true>(g, l, packed)
                   : launch_mfma<128, 128, 2, 4, 4, true, true, 32, PACK>(g, l, packed);
     case 6: return launch_mfma<128, 128, 2, 4, 5, true, true, 64, PACK>(g, l, packed);
-    default:
+    case 7:
       return bsum ? launch_mfma<64, 64, 2, 2, 4, true, true, 64, PACK, true>(g, l, packed)
                   : launch_mfma<64, 64, 2, 2, 4, true, true, 64, PACK>(g, l, packed);
+    default: return hipErrorInvalidValue;
   }
 }
 

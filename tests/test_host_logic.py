@@ -331,6 +331,23 @@ def test_segments_of_a_product_share_the_turns_of_a_ring(akS, bkS):
             assert tiles - 3 * -(-H // depth) < 5, (T, H, depth, tiles)
 
 
+def test_every_layout_has_the_tile_that_is_chosen_for_it():
+    # A k-strided, B k-contiguous: where 128x128 tiles reach three quarters of the units and fit them, they are taken
+    for M, N in ((2048, 1536), (2048, 1920), (1792, 1792), (2048, 2048)):
+        for K in (256, 512, 1024, 1536, 2048):
+            assert plan(M, N, K, akS=True)[:3] == (128, 128, 64), (M, N, K)
+    # any product and any named tile has a launch (one that is not in the list: the 64x64 tile)
+    for akS, bkS in ((False, False), (False, True), (True, False), (True, True)):
+        for tile in range(-1, 13):
+            for M, N in ((64, 64), (600, 320), (1024, 1024), (2048, 1536), (8192, 1024), (8192, 4096)):
+                for K in (200, 512, 2048):
+                    assert plan(M, N, K, akS=akS, bkS=bkS, tile=tile) is not None
+        assert plan(600, 320, 320, akS=akS, bkS=bkS, tile=11)[:3] == (64, 64, 64)
+    for epi in (B.EPI_ACC32, B.EPI_ACC32 | B.EPI_BSUM):
+        for tile in range(-1, 13):
+            assert plan(600, 320, 320, akS=True, bkS=True, epi=epi, tile=tile) is not None
+
+
 def test_the_plan_of_a_product_is_the_named_tile():
     for tile, shape in {1: (256, 256, 32), 2: (256, 128, 64), 3: (128, 128, 64), 4: (128, 64, 64), 6: (128, 128, 64),
                         7: (64, 64, 64), 8: (128, 128, 32), 9: (32, 64, 64), 10: (32, 32, 64)}.items():
