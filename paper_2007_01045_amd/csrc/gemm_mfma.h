@@ -348,8 +348,8 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   const bf16 *Ab = (const bf16*)g.A + z * g.sA, *Bb = (const bf16*)g.B + z * g.sB;
   void* const Cb = g.C;
   // (whole turns of the ring per segment, PACK: in all; the k-tiles beyond the end read nothing)
-  const int nseg = g.K / g.kseg_len, seg_tiles = (g.kseg_len + BK - 1) / BK;
-  const int turns = ((PACK ? nseg * seg_tiles : seg_tiles) + NS - 1) / NS;   // of the ring, per segment (PACK: in all)
+  const int seg_tiles = (g.kseg_len + BK - 1) / BK;
+  const int turns = (seg_tiles + NS - 1) / NS;   // of the ring, per segment
   const int k_rows = g.K > g.kseg_len ? g.kseg_len : g.k_valid;   // rows of one segment of a k-strided operand
   // bytes of one segment of each operand that may be read (beyond: zero)
   const long a_ext =
@@ -404,7 +404,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
   // Branch-free on purpose: with control flow inside the k-loop the accumulators get
   // copied between register files at every merge point.
   // still to be requested (tiles_left: of the segment, PACK: in all)
-  int tiles_left = PACK ? nseg * seg_tiles : seg_tiles, turns_left = turns, segs_left = nseg, seg_left = seg_tiles;
+  int turns_left = turns, segs_left = g.K / g.kseg_len, seg_left = seg_tiles, tiles_left = PACK ? segs_left * seg_tiles : seg_tiles;
   auto advance = [&](auto S) __attribute__((always_inline)) {
     --tiles_left;
     if constexpr (PACK) {
@@ -761,12 +761,12 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs& g, int tiles_m, i
       request_c();
       turn(WCS, std::integral_constant<int, C_LOADS>{});
       end_segment(WCS);
-      for (int s = nseg; s > 1; --s) {
+      for (int s = g.K / g.kseg_len; s > 1; --s) {
         for (int t = 0; t < turns; ++t) turn(WCS, none);
         end_segment(WCS);
       }
     } else {
-      for (int t = PACK ? turns : nseg * turns; t > 0; --t) turn(WCS, none);
+      for (int t = PACK ? (g.K / g.kseg_len * seg_tiles + NS - 1) / NS : g.K / g.kseg_len * turns; t > 0; --t) turn(WCS, none);
       end_segment(WCS);
     }
   };
@@ -953,20 +953,23 @@ __global__ __launch_bounds__(64 * WGM * WGN, (GemmTile<BM, BN, WGM, WGN, NS, AKS
 // Whether a product of several K segments takes the variant whose cursor looks for a segment's end at every k-tile: where
 // padding each segment to whole turns of a ring of ns would run more turns than padding their sum.  (The same turns: the
 // cheaper cursor.  No bit depends on it: k-tiles of zeros add nothing.)  The gradient of the attention's input, three
-// segments of the width, us with padded segments -> without: 320 wide, 4096 rows (24 k-tiles -> 16) 10.6 -> 8.8; 576, 2048
-// rows 13.7 -> 11.6; 200, 2048 rows 9.7 -> 8.4; 1024, 8192 rows (54 -> 48) 54.2 -> 52.1, 4096 rows (60 -> 50) 32.5 -> 30.3,
-// 2048 rows 22.7 -> 21.4.
+// segments of the width, us alone with padded segments -> without: 64x64 tiles 320 wide, 4096 rows (24 k-tiles -> 16) 10.3 ->
+// 8.7; 128x64 448 wide (27 -> 21) 11.9 -> 10.8; 128x128, two stages 576 wide (30 -> 28) 21.9 -> 21.3, five 1024 wide (60 ->
+// 50) 33.3 -> 30.8; 256x128 1024 wide, 8192 rows (54 -> 48) 49.6 -> 47.2.  Not the four waves of 128x128, whose k-tiles of 32
+// leave no room between their MFMAs for it (576 wide, 2048 rows, 60 -> 56: 16.5 -> 17.9).
 inline bool packs(const GemmArgs& g, int ns, int bk) {
+  if (g.K == g.kseg_len) return false;
   const int seg_tiles = (g.kseg_len + bk - 1) / bk, nseg = g.K / g.kseg_len;
   return nseg * ((seg_tiles + ns - 1) / ns) > (nseg * seg_tiles + ns - 1) / ns;
 }
 
-// packed: the same layout's launches with PACK, which are compiled on their own (NULL where these are they)
-template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool PACK, bool CS = false, bool KT = false, bool SEG = false>
-static hipError_t launch_mfma(const GemmArgs& g, const GemmLaunch& l, LaunchMfma packed) {
+// (the sums of SEG's segments are kept apart: each one starts a turn)
+template <int BM, int BK, bool SEG>
+constexpr bool can_pack = !SEG && (BK == 64 || BM == 256);
+
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool PACK, bool CS, bool KT, bool SEG>
+static hipError_t launch_kernel(const GemmArgs& g, const GemmLaunch& l) {
   typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, SEG> CFG;
-  if constexpr (!PACK && !SEG)   // (the sums of SEG's segments are kept apart: each one starts a turn)
-    if (packs(g, NS, BK)) return packed(g, l);
   if (l.plan) {
     const int seg_tiles = (g.kseg_len + BK - 1) / BK, nseg = g.K / g.kseg_len;
     *l.plan = GemmPlan{BM, BN, BK, PACK ? (nseg * seg_tiles + NS - 1) / NS * NS : nseg * ((seg_tiles + NS - 1) / NS * NS)};
@@ -982,6 +985,19 @@ static hipError_t launch_mfma(const GemmArgs& g, const GemmLaunch& l, LaunchMfma
   dim3 grid(tiles_m * tiles_n, 1, g.batch);
   hipLaunchKernelGGL(kern, grid, dim3(CFG::NT), CFG::LDS_BYTES, l.st, g, tiles_m, tiles_n);
   return hipGetLastError();
+}
+
+// packed: the same layout's launches with PACK, which are compiled on their own (NULL where these are they)
+template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool PACK, bool CS = false, bool KT = false, bool SEG = false>
+static hipError_t launch_mfma(const GemmArgs& g, const GemmLaunch& l, LaunchMfma packed) {
+  if constexpr (can_pack<BM, BK, SEG>) {
+    if (!PACK && packs(g, NS, BK)) return packed(g, l);
+    return launch_kernel<BM, BN, WGM, WGN, NS, AKS, BKS, BK, PACK, CS, KT, SEG>(g, l);
+  } else if constexpr (PACK) {
+    return hipErrorInvalidValue;   // (no launch asks for it)
+  } else {
+    return launch_kernel<BM, BN, WGM, WGN, NS, AKS, BKS, BK, PACK, CS, KT, SEG>(g, l);
+  }
 }
 
 }  // namespace dapple

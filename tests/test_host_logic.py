@@ -318,17 +318,21 @@ def plan(M, N, Ks, nseg=1, akS=False, bkS=False, epi=0, tile=0):
 
 @pytest.mark.parametrize("akS,bkS", [(False, False), (False, True), (True, False), (True, True)])
 def test_segments_of_a_product_share_the_turns_of_a_ring(akS, bkS):
-    # a workgroup runs less than one turn (five k-tiles at most) of zeros in all, whatever the length of a segment
+    def check(rows, cols, depth, tiles, Ks, nseg):
+        seg = -(-Ks // depth)
+        if (rows, cols, depth) == (128, 128, 32):   # whole turns of four k-tiles per segment: its loop has no room for the other cursor
+            assert tiles == nseg * -(-seg // 4) * 4
+        else:                                       # less than one turn (five k-tiles at most) of zeros in all
+            assert 0 <= tiles - nseg * seg < 5, (Ks, nseg, rows, cols, depth, tiles)
+
     for tile in range(11):
         for Ks in [64 * n for n in range(1, 19)] + [8, 40, 200, 264]:
             for nseg in (1, 2, 3, 4):
-                rows, cols, depth, tiles = plan(600, 320, Ks, nseg, akS, bkS, B.EPI_ADD, tile)
-                assert 0 <= tiles - nseg * -(-Ks // depth) < 5, (tile, Ks, nseg, rows, cols, depth, tiles)
+                check(*plan(600, 320, Ks, nseg, akS, bkS, B.EPI_ADD, tile), Ks, nseg)
     # the data gradient of the attention's input: three segments of the hidden width
     for H in range(64, 1088, 64):
         for T in (256, 600, 2048, 4096, 8192):
-            _, _, depth, tiles = plan(T, H, H, 3, epi=B.EPI_ADD)
-            assert tiles - 3 * -(-H // depth) < 5, (T, H, depth, tiles)
+            check(*plan(T, H, H, 3, epi=B.EPI_ADD), H, 3)
 
 
 def test_every_layout_has_the_tile_that_is_chosen_for_it():
