@@ -403,6 +403,10 @@ __device__ __forceinline__ f32x16 zero16() {
 template <int NDB, bool FAR = false>
 struct OutTile {
   static constexpr int W = 32 * NDB, LD = W + 4, BYTES = 32 * LD * 4;
+  static constexpr int RS = 64 / (W / 4);   // rows per instruction
+  // Vector stores of C by a wave whose 32 rows and W columns are all valid, C32 aside.  A caller's wait may count on as many
+  // behind an older request: one instruction per RS rows, and no way past it.
+  static constexpr int STORES = 32 / RS;
   static __device__ __forceinline__ void store(float* S, const f32x16* t, float f, bf16* C, float* C32, long ld, int rows, int d, int lane) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
@@ -411,10 +415,10 @@ struct OutTile {
         *(f32x4*)(S + (lane & 31) * LD + db * 32 + 8 * blk + 4 * (lane >> 5)) =
             f32x4{t[db][4 * blk], t[db][4 * blk + 1], t[db][4 * blk + 2], t[db][4 * blk + 3]} * f;
     __builtin_amdgcn_wave_barrier();   // (private to the wave, whose LDS accesses execute in order)
-    constexpr int RS = 64 / (W / 4);   // rows per instruction
     const int r = lane / (W / 4), c = lane % (W / 4) * 4;
 #pragma unroll
-    for (int i = 0; i < 32; i += RS) {
+    for (int u = 0; u < STORES; ++u) {
+      const int i = u * RS;
       const f32x4 v = *(const f32x4*)(S + (i + r) * LD + c);
       if (i + r < rows && c < d) {
         bf16x4 o;
@@ -908,7 +912,7 @@ constexpr int ONCE_NS = 3;
 typedef Ring<64, 8, ONCE_NS, true> OnceRing;
 typedef Ring<64, 4, 2, false> OnceKeys;   // stage i: rows 64 i .. 64 i + 63 of the group's keys and values
 constexpr int ONCE_X = 128 * 64 * 2;      // dS of a block of queries: [128 keys][64 queries], chunks swizzled by aswz
-constexpr int ONCE_BYTES = OnceKeys::BYTES + OnceRing::BYTES + 2 * ONCE_X + 4 * 32 * 68 * 4;   // ... and outputs' staging
+constexpr int ONCE_BYTES = OnceKeys::BYTES + OnceRing::BYTES + 2 * ONCE_X + 4 * OutTile<2>::BYTES;   // ... and outputs' staging
 
 __global__ __launch_bounds__(512, 2) void attn_bwd_once(AttnArgs a, float scale2, float scale) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char asm_[];
@@ -948,7 +952,8 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_once(AttnArgs a, float scale2
   };
   // Both kinds of waves pass steps + 1 barriers: step n lies between barriers n and n + 1 for waves 0-3, between n + 1
   // and n + 2 for the others.  KV_LOADS, STORES: requests behind the ring's that a barrier need not wait for.
-  constexpr int KV_LOADS = 2 * OnceKeys::PER, STORES = 16;
+  typedef OutTile<NDB> Out;
+  constexpr int KV_LOADS = 2 * OnceKeys::PER, STORES = 2 * Out::STORES;   // two of the key blocks; dk and dv
   if (wave < 4) {
     for (int i = 0; i < ONCE_NS - 1; ++i) ask();
     int stage = 0, x = 0;
@@ -1032,11 +1037,11 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_once(AttnArgs a, float scale2
       if (g + 1 == nkg) OnceRing::wait();   // (the other waves' last step, not behind these stores)
       if (live) {
         const long o0 = hb + (128L * g + 32 * wave) * a.H;
-        float* const S = (float*)(xs + 2 * ONCE_X + wave * OutTile<NDB>::BYTES);
+        float* const S = (float*)(xs + 2 * ONCE_X + wave * Out::BYTES);
         int at = lane;
         asm volatile("" : "+v"(at));   // (addresses made of it are not kept through the loop)
-        OutTile<NDB>::store(S, dk, scale, (bf16*)a.dk + o0, nullptr, a.H, 32, D, at);
-        OutTile<NDB>::store(S, dv, 1.f, (bf16*)a.dv + o0, nullptr, a.H, 32, D, at);
+        Out::store(S, dk, scale, (bf16*)a.dk + o0, nullptr, a.H, 32, D, at);
+        Out::store(S, dv, 1.f, (bf16*)a.dv + o0, nullptr, a.H, 32, D, at);
       }
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);   // the last requests (they read nothing) before the wave may end
