@@ -428,6 +428,38 @@ def test_narrow_stages_on_either_side_of_the_side_streams_line(shape):
         assert all(np.array_equal(x, y) for x, y in zip(ref, got)), (K, flags)
 
 
+@pytest.mark.parametrize("s", [256, 320])
+def test_the_attention_backward_of_a_group_has_the_bits_of_its_tasks(s):
+    """16 heads of 64, 4 sequences: the heads of four micro-batches fill the 256 units (a workgroup per head, which adds the
+    two blocks of 32 columns of delta itself), those of one do not, but fill 64 of them.  The same bits as a group, task by
+    task, and both ways on a quarter of the units."""
+    M = 4
+    cfg = I.StageConfig(1, 1024, 16, 2048, s, 4, M, M, "bf16")
+    heads = cfg.micro_batch * cfg.n_heads
+    assert heads < 192 <= M * heads and 4 * heads >= 3 * 64 and M * cfg.tokens <= 8192
+    theta, mbs = make_inputs(cfg, SEED, M)
+    ops = B.stage_schedule_ops(M, M, B.ORDER_EARLY_BACKWARD)
+    ways = (dict(order=B.ORDER_EARLY_BACKWARD), dict(order=B.ORDER_EXPLICIT, explicit_ops=ops))
+    ref, one = (_bits(run_gpu(cfg, theta, mbs, M, M, **kw)) for kw in ways)
+    assert all(np.array_equal(x, y) for x, y in zip(ref, one))
+    st = B.pipeline_partition_stream_create(0, 4)
+    try:
+        for kw in ways:
+            r = B.StageRunner(c_config(cfg, M), theta, stream_ptr=st)
+            try:
+                xs, dys = ([r.to_dev(mb[k].reshape(cfg.tokens, cfg.hidden)) for mb in mbs] for k in ("x", "dy"))
+                torch.cuda.synchronize()   # the stage runs on a stream of its own
+                ys, dxs = r.run(M, M, xs=xs, dys=dys, **kw)
+                B.stage_sync(r.h)
+                torch.cuda.synchronize()
+                got = _bits(dict(ys=[to_np(y) for y in ys], dxs=[to_np(d) for d in dxs], grads=r.grads.detach().cpu().numpy().copy()))
+                assert all(np.array_equal(x, y) for x, y in zip(ref, got)), kw
+            finally:
+                r.close()
+    finally:
+        B.pipeline_partition_stream_destroy(st)
+
+
 @pytest.mark.parametrize("kind", ["recompute", "first_stage", "last_stage", "gpipe_order", "side_stream", "recompute_lanes"])
 def test_graph_replays_of_the_other_stage_kinds(kind):
     """A captured iteration of a re-computing stage, a first stage (token ids in), a last stage (losses out), of
