@@ -952,20 +952,19 @@ __global__ __launch_bounds__(64 * WGM * WGN, (GemmTile<BM, BN, WGM, WGN, NS, AKS
 
 // Whether a product of several K segments takes the variant whose cursor looks for a segment's end at every k-tile: where
 // padding each segment to whole turns of a ring of ns would run more turns than padding their sum.  (The same turns: the
-// cheaper cursor.  No bit depends on it: k-tiles of zeros add nothing.)  The gradient of the attention's input, three
-// segments of the width, us alone with padded segments -> without: 64x64 tiles 320 wide, 4096 rows (24 k-tiles -> 16) 10.3 ->
-// 8.7; 128x64 448 wide (27 -> 21) 11.9 -> 10.8; 128x128, two stages 576 wide (30 -> 28) 21.9 -> 21.3, five 1024 wide (60 ->
-// 50) 33.3 -> 30.8; 256x128 1024 wide, 8192 rows (54 -> 48) 49.6 -> 47.2.  Not the four waves of 128x128, whose k-tiles of 32
-// leave no room between their MFMAs for it (576 wide, 2048 rows, 60 -> 56: 16.5 -> 17.9).
+// cheaper cursor.  No bit depends on it: k-tiles of zeros add nothing.)
+// Tiles of which a unit holds one workgroup only: nothing else there hides a k-tile of zeros.  The gradient of the
+// attention's input, three segments of the width, us alone with padded segments -> without: 256x128 1024 wide, 8192 rows (54
+// k-tiles -> 48) 49.6 -> 47.2, 832 wide (45 -> 39) 40.1 -> 37.0; 128x128 in five stages 1024 wide, 4096 rows (60 -> 50) 33.3
+// -> 30.8.  Whole iterations: 832 wide 6154 -> 6124, 704 wide 4861 -> 4835, 1024 wide on 64 units (five stages) 4593 -> 4578.
+// The smaller tiles gain alone (64x64, 320 wide, 4096 rows, 24 -> 16: 10.3 -> 8.7) and nothing or less in an iteration,
+// where they find the code of one more kernel cold: 320 wide, 4096 rows 1407 / 1407, 318 rows 2042 -> 2068; 128x64, 832
+// wide, 2048 rows 2241 -> 2251.
 inline bool packs(const GemmArgs& g, int ns, int bk) {
   if (g.K == g.kseg_len) return false;
   const int seg_tiles = (g.kseg_len + bk - 1) / bk, nseg = g.K / g.kseg_len;
   return nseg * ((seg_tiles + ns - 1) / ns) > (nseg * seg_tiles + ns - 1) / ns;
 }
-
-// (the sums of SEG's segments are kept apart: each one starts a turn)
-template <int BM, int BK, bool SEG>
-constexpr bool can_pack = !SEG && (BK == 64 || BM == 256);
 
 template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool PACK, bool CS, bool KT, bool SEG>
 static hipError_t launch_kernel(const GemmArgs& g, const GemmLaunch& l) {
@@ -990,7 +989,9 @@ static hipError_t launch_kernel(const GemmArgs& g, const GemmLaunch& l) {
 // packed: the same layout's launches with PACK, which are compiled on their own (NULL where these are they)
 template <int BM, int BN, int WGM, int WGN, int NS, bool AKS, bool BKS, int BK, bool PACK, bool CS = false, bool KT = false, bool SEG = false>
 static hipError_t launch_mfma(const GemmArgs& g, const GemmLaunch& l, LaunchMfma packed) {
-  if constexpr (can_pack<BM, BK, SEG>) {
+  // (the sums of SEG's segments are kept apart: each one starts a turn)
+  constexpr bool can_pack = !SEG && !GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, SEG>::TWO;
+  if constexpr (can_pack) {
     if (!PACK && packs(g, NS, BK)) return packed(g, l);
     return launch_kernel<BM, BN, WGM, WGN, NS, AKS, BKS, BK, PACK, CS, KT, SEG>(g, l);
   } else if constexpr (PACK) {

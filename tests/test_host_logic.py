@@ -318,21 +318,27 @@ def plan(M, N, Ks, nseg=1, akS=False, bkS=False, epi=0, tile=0):
 
 @pytest.mark.parametrize("akS,bkS", [(False, False), (False, True), (True, False), (True, True)])
 def test_segments_of_a_product_share_the_turns_of_a_ring(akS, bkS):
-    def check(rows, cols, depth, tiles, Ks, nseg):
-        seg = -(-Ks // depth)
-        if (rows, cols, depth) == (128, 128, 32):   # whole turns of four k-tiles per segment: its loop has no room for the other cursor
-            assert tiles == nseg * -(-seg // 4) * 4
-        else:                                       # less than one turn (five k-tiles at most) of zeros in all
-            assert 0 <= tiles - nseg * seg < 5, (Ks, nseg, rows, cols, depth, tiles)
-
-    for tile in range(11):
-        for Ks in [64 * n for n in range(1, 19)] + [8, 40, 200, 264]:
+    # tiles of which a unit holds one workgroup: less than one turn of k-tiles of zeros in all, whatever a segment's length
+    for tile, ring in ((1, 4), (2, 3), (6, 5)):
+        for Ks in range(64, 64 * 19, 64):
             for nseg in (1, 2, 3, 4):
-                check(*plan(600, 320, Ks, nseg, akS, bkS, B.EPI_ADD, tile), Ks, nseg)
-    # the data gradient of the attention's input: three segments of the hidden width
-    for H in range(64, 1088, 64):
-        for T in (256, 600, 2048, 4096, 8192):
-            check(*plan(T, H, H, 3, epi=B.EPI_ADD), H, 3)
+                rows, cols, depth, tiles = plan(600, 320, Ks, nseg, akS, bkS, B.EPI_ADD, tile)
+                assert tiles == -(-nseg * Ks // depth // ring) * ring, (tile, Ks, nseg, rows, cols, depth, tiles)
+    # the others: whole turns per segment
+    for tile, ring in ((3, 2), (4, 3), (7, 4)):
+        for Ks in range(64, 64 * 19, 64):
+            for nseg in (1, 2, 3, 4):
+                tiles = plan(600, 320, Ks, nseg, akS, bkS, B.EPI_ADD, tile)[3]
+                assert tiles == nseg * -(-Ks // 64 // ring) * ring, (tile, Ks, nseg, tiles)
+
+
+def test_the_gradient_of_the_attention_input_runs_no_more_than_a_turn_of_zeros():
+    for H in range(640, 1088, 64):   # 256x128 tiles in a ring of three
+        rows, cols, depth, tiles = plan(8192, H, H, 3, epi=B.EPI_ADD)
+        if (rows, cols, depth) == (256, 128, 64):
+            assert tiles == -(-3 * H // 64 // 3) * 3, (H, tiles)
+    assert plan(8192, 1024, 1024, 3, epi=B.EPI_ADD) == (256, 128, 64, 48)
+    assert plan(4096, 1024, 1024, 3, epi=B.EPI_ADD) == (128, 128, 64, 50)
 
 
 def test_every_layout_has_the_tile_that_is_chosen_for_it():
