@@ -97,7 +97,7 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 // Against that, a product must reach the 256 units, a k-tile must have been requested long enough ahead (about 1 us
 // from HBM: the fewer workgroups share a unit, the deeper the ring has to be), and a launch's fixed cost -- first
 // tile's latency, epilogue -- is only hidden by another workgroup on the same unit.  Eight waves (two per SIMD) beat
-// four on every tile of 128x128 and up.  Alone, in us (T rows; "->" four waves -> eight where both were measured):
+// four on every tile of 128x128 and up with k-tiles of 64.  Alone, in us (T rows; "->" four waves -> eight where both were measured):
 //   1: 256x256, four stages of 32      T=8192 N=4096 K=1024 GELU 112 -> 92, gate 90 (128x128: 101); T=4096 44 and 42
 //   2: 256x128, three stages of 64     T=8192 N=1024 K=4096 residual 77 -> 72 (128x128: 84), gradient 81 -> 65
 //   3: 128x128, two stages of 64       two workgroups per unit: T=2048 N=4096 K=1024 GELU 26, gate 23 (256x256: 36, 31)
@@ -106,8 +106,8 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 //                                      256-byte rows, and three tiles are in flight in the LDS of two of 64
 //   6: 128x128, five stages of 64      one workgroup per unit: T=4096 N=1024 K=4096 67 -> 45
 //   7: 64x64, four stages of 64        T=512 N=1024 K=4096 23 (128x64) -> 16, K=1024 9.6 -> 6.9; T=1024 23 -> 17
-//   8: 128x128, four waves, four       two workgroups per unit: T=4096 N=1024 K=1024 17 (128x64: 19), and beside another
-//      stages of 32                    stream K=4096 38 (the five-stage ring 35, two stages of 64 47)
+//   8: 128x128, four waves, four       two workgroups per unit: T=4096 N=1024 K=1024 17 (128x64: 19)
+//      stages of 32
 //   9: 32x64, two waves, four          where 64x64 tiles leave half of the units without work: what a unit requests bounds
 //      stages of 64                    them, and these request three quarters of it.  T=512 N=1024 K=4096 forward 16.2 ->
 //                                      14.3, gradient 15.1 -> 13.5, K=1024 7.0 -> 6.4; T=512 N=256 K=256 4.8 -> 3.9 (not
@@ -117,8 +117,11 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 //      of 64                           T=256 N=256 K=512 5.7 -> 4.1 (4.4)
 // A stream restricted to part of the units (GemmArgs::units) moves the lines with it: four stages of 2048 rows on 64
 // units each, 36.7 -> 32.2 ms per iteration.  Where another stream's products run beside this one (GemmArgs::shared: the
-// data gradients beside the weight gradients) the tile with the whole LDS keeps them off its unit: 12 layers of 1024
-// with 4096 rows take 28.4 ms with the five-stage ring and 27.3 with two stages, though alone it is the faster one.
+// data gradients beside the weight gradients) the tile with the whole LDS keeps them off its unit, and the four waves of tile
+// 8 get less of a unit than the eight of tile 3 where the weight gradients fill the chip: 12 layers of 1024 with 4096 rows
+// take 25.7 ms with tile 6, 24.6 with 8 and 24.3 with 3, 4 of 1536 with 2048 rows 9.19 (8) and 8.97 (3), 4 of 832 with 4096
+// rows 7.13 and 7.06.  Tile 8 in narrower layers and for the wide output of few rows: 512 wide, 6144 rows 5.10 and 5.19; 640,
+// 5120 rows 6.13 and 6.19; 768, 4096 rows 6.00 and 6.01; 1024 wide, 1024 rows 5.49 and 5.54.
 // (The lines between those points -- K >= 2048, N <= 1024, three quarters of the units -- were read off widths of 256,
 // 1024 and 2048 and 512 to 8192 rows.)
 // No bit of a result depends on the choice: an output element is one wave's sum in ascending k whatever the tile.
@@ -143,9 +146,13 @@ static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   if (tiles(256, 256) >= most && !(g.epi & (EPI_ADD | EPI_AUX32))) return 1;
   if (t256 >= most && t256 <= U && (g.K >= 2048 || !second || g.N <= 1024)) return 2;
   if (t128 > U) return 3;
-  // (A k-strided has no 8, and is never beside another stream.  Us for tiles 3 / 4 / 6: 2048 x 1920 x 512 8.7 / 9.6 / 8.8,
-  // 2048 x 2048 x 1024 11.8 / 13.7 / 12.6, 1536 x 2048 x 1536 18.4 / 16.0 / 13.6, 1792 x 1792 x 1792 23.4 / 18.7 / 16.9)
-  if (t128 >= most) return g.a_kstrided ? (g.K > 1024 ? 6 : 3) : g.K >= 2048 && !g.shared ? 6 : 8;
+  // (A k-strided, B k-contiguous has no 8, and is never beside another stream.  Us for tiles 3 / 4 / 6: 2048 x 1920 x 512 8.7 / 9.6 / 8.8,
+  // 2048 x 2048 x 1024 11.8 / 13.7 / 12.6, 1536 x 2048 x 1536 18.4 / 16.0 / 13.6)
+  if (t128 >= most) {
+    if (g.a_kstrided) return g.K > 1024 ? 6 : 3;
+    if (g.shared) return g.M >= 8 * U && g.N > 768 ? 3 : 8;
+    return g.K >= 2048 ? 6 : 8;
+  }
   if (tiles(32, 64) <= U && !g.a_kstrided) return tiles(32, 32) <= U ? 10 : 9;
   return g.K >= 2048 && tiles(64, 64) > U ? 4 : 7;
 }
