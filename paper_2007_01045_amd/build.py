@@ -17,8 +17,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
          # keep the compiler from forming packed-fp32 instructions
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          # a kernel's first arguments arrive in scalar registers with the wave, instead of by a load from memory that everything
-         # else waits for (kernels with arguments of their own, not in one structure).  Stages of short launches, us per
-         # iteration: 2 layers of 256 with 256 rows 270.4 -> 266.3, 4 of 768 with 600 rows 1880 -> 1875; large ones unchanged.
+         # else waits for: kernels with arguments of their own (LayerNorm, sums, copies), not those with one structure (products,
+         # attention).  An option of the compiler's back end; where the firmware lacks it, a kernel loads its arguments itself.
+         # Three runs each in turn, us per iteration: 2 layers of 256 with 256 rows 264.5 -> 262.5 (spread 0.1%), 6 of 1024 with
+         # 512 rows 1209 -> 1205 (0.2%), 4 of 768 with 600 rows 1904 -> 1896 (0.4%); large ones unchanged.
          "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 
 

@@ -905,7 +905,7 @@ __global__ __launch_bounds__(64 * NW, D <= 64 ? 2 : 1) void attn_bwd_mfma(AttnAr
 // past in blocks of 64, and leave dS in LDS; waves 4-7, a block behind, own 32 queries x 32 columns of every block and
 // add dS K to their part of dQ, which they hold for the whole sequence (128 registers).  Then the next 128 keys.
 // The two kinds of workgroups of attn_bwd_mfma do seven products where these do five, and every exponential twice: 16 x
-// 512 rows, 16 heads 85 -> 74 us in an iteration.  Bound by the first kind's chain of products, exponentials and products
+// 512 rows, 16 heads 87 -> 70 us in the trace of an iteration.  Bound by the first kind's chain of products, exponentials and products
 // with one wave of each kind per SIMD (matrix pipes 25%, vector units 25%, LDS 30% busy); dV and dK (or dV alone) on the
 // second kind of waves, P through LDS too, measured 3-8 us more.  Every sum is the same chain of MFMAs: the same bits.
 constexpr int ONCE_NS = 3;
@@ -1162,7 +1162,11 @@ hipError_t launch_attn_fwd(Dtype dt, const AttnArgs& a, hipStream_t st) {
 
 // One workgroup per head, one to a unit, for about three quarters of the time of attn_bwd_mfma's on a full chip (with
 // the delta kernel, 512 rows: 256 heads 102 -> 81 us, 192 80 -> 72, 128 53 -> 65; 512 heads of 256 rows 70 -> 57): where
-// the turns of the units are three quarters full.  No bit depends on it.
+// the turns of the units are three quarters full.  Beside another stream's weight gradients too, although its 152 KB of LDS
+// wait for a unit to itself (4 layers each, ms per iteration with attn_bwd_mfma -> so: 768 wide, 192 heads of 256 rows 5.23
+// -> 5.21, of 512 10.87 -> 10.86; 640 wide, 200 heads of 320 7.20 -> 7.11; 1024 wide, 256 heads of 256 7.70 -> 7.61, 240 of
+// 320 10.13 -> 9.98; 512 wide, 256 of 256 5.71 -> 5.61), and on partitions (four stages of 3 layers on 64 units each, 64
+// heads of 512 rows 27.97 -> 27.49).  No bit depends on it.
 static bool bwd_once_takes(const AttnArgs& a) {
   const long U = a.units > 0 ? a.units : 256, heads = (long)a.b * a.A;
   return a.d == 64 && a.s % 64 == 0 && a.s >= 256 && a.s <= 512 && 4 * heads >= 3 * U * ((heads + U - 1) / U);

@@ -578,8 +578,8 @@ static hipError_t launch_small(const GemmArgs& g, hipStream_t st) {
   return hipGetLastError();
 }
 
-// 128-wide tiles rather than 64-wide ones: where they reach most of the units and the fullest unit has no more work than
-// with the 64-wide ones' finer split (three products of 2048 x 1024 x 1024, 384 tiles: 143 -> 112 us)
+// 128-wide tiles rather than 64-wide ones: where there are enough for most of the 256 units (a stream with fewer of them has
+// the same line) and the fullest of its units has no more work than with the 64-wide ones' finer split (three products of 2048 x 1024 x 1024, 384 tiles: 143 -> 112 us)
 static bool large_tiles(long t128, long t64, int units) {
   const long U = units > 0 ? units : 256;
   return t128 >= 192 && 40 * ((t128 + U - 1) / U) <= 11 * ((t64 + U - 1) / U);

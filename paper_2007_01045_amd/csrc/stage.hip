@@ -168,11 +168,12 @@ double layer_flops(const stage_config& c, int n) {   // a layer's forward over n
   const double T = (double)n * c.micro_batch * c.seq, H = c.hidden, F = c.ffn;
   return 8.0 * T * H * H + 4.0 * T * H * F;
 }
-// Whether the weight gradients of tasks over n micro-batches stay on the task's own stream (units: compute units the
-// stream may use), by the matrix flops of a layer's forward; else they go to the side stream.  Below 12 GFLOP -- 20 where a
-// weight of the FFN makes fewer 128x128 tiles than there are units -- an event per hand-over costs the host 2-5 us and the
+// Whether the weight gradients of tasks over n micro-batches stay on the task's own stream, by the matrix flops of a
+// layer's forward; else they go to the side stream.  Below 12 GFLOP -- 20 where a weight of the FFN makes fewer than 256
+// 128x128 tiles, whatever part of the units the stream has (on 64 and 128 of them layers of 512 to 1024 with 13 to 19 GFLOP
+// are 0.6% faster to 5.5% slower with the side stream) -- an event per hand-over costs the host 2-5 us and the
 // streams' kernels a wait, and the gradients' large tiles hold units that the small ones of the main chain are short of:
-// more than the overlap gives.  Us with the side stream / without: 512 wide, 6.4 GFLOP 892 / 791, 12.9 950 / 913, 19.3
+// more than the overlap gives.  Us on all units with the side stream / without: 512 wide, 6.4 GFLOP 892 / 791, 12.9 950 / 913, 19.3
 // 422 / 388; 768 wide, 8.5 GFLOP 3684 / 3372, 12.7 1290 / 1253, 17 2282 / 2226, 21.7 2547 / 2616, 25.5 1889 / 1943; 1024
 // wide, 6.4 GFLOP 1047 / 987, 12.9 1187 / 1184, 10097 / 10240 and 9268 / 9305.  (fp32 products take eight times as long:
 // 1024 wide, 52 GFLOP 3.08 / 3.15 ms, 256 wide 575 / 583 us.)  From 150 GFLOP on every bf16 product fills the chip, and
@@ -185,6 +186,7 @@ bool small_tasks(const stage_config& c, int n) {
   const double line = c.dtype != STAGE_DTYPE_BF16 ? 7.5e8 : c.flags & STAGE_FLAG_RECOMPUTE ? 6e9 : wide ? 1.2e10 : 2e10;
   return layer_flops(c, n) < line;
 }
+// units: compute units the stream may use
 bool full_tasks(const stage_config& c, int n, int units) {
   return c.dtype == STAGE_DTYPE_BF16 && layer_flops(c, n) >= 1.5e11 * units / 256;
 }
@@ -755,8 +757,8 @@ int dapple_stage::backward(const Act& sl, int n, const void* const* dys, void* c
     wg.p[wg.n++] = WgradProblem{xl, dk, gr(p.Wk), gr(p.bk), H, H, H, H, H};
     wg.p[wg.n++] = WgradProblem{xl, dv, gr(p.Wv), gr(p.bv), H, H, H, H, H};
     wg.p[wg.n++] = WgradProblem{ctx, dz1, gr(p.Wo), nullptr, H, H, H, H, H};  // dWo += ctx^T dz1
-    // The sums of both LayerNorms' block partials go out with them (tiny fp32 stage 229 -> 220 us, 6 layers of 8192 rows
-    // 10.70 -> 10.55 ms, 4 of 1800 on a side stream 1925 -> 1916 us) -- on their own beside another stream's large
+    // The sums of both LayerNorms' block partials go out with them (6 layers of 8192 rows 10.70 -> 10.55 ms, 4 of 1800 on a
+    // side stream 1925 -> 1916 us) -- on their own beside another stream's large
     // tiles, whose LDS their workgroups would hold (12 layers of 4096 rows 24.79 ms, 24.92 with the products).
     ReduceJobs late{};
     {
