@@ -202,6 +202,7 @@ def test_gemm_mfma_segments_that_are_no_whole_turns_of_the_ring(tile):
     for Ks in (64, 192, 320):
         for akS, bkS in ((False, False), (False, True), (True, False), (True, True)):
             gemm_case(B.DTYPE_BF16, 136, 200, 3 * Ks, akS, bkS, B.EPI_ADD, nseg=3, expect_mfma=True, tile=tile)
+            gemm_case(B.DTYPE_BF16, 72, 136, 2 * Ks, akS, bkS, B.EPI_BIAS, batch=2, nseg=2, expect_mfma=True, tile=tile)
         gemm_case(B.DTYPE_BF16, 136, 200, 3 * Ks, True, True, B.EPI_ACC32 | B.EPI_BSUM, nseg=3, expect_mfma=True, tile=tile)
         M, N = 264, 328
         a, b = (torch.randn(r, 3 * Ks, generator=torch.Generator().manual_seed(r)).to("cuda", torch.bfloat16) for r in (M, N))
