@@ -101,7 +101,11 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 //   1: 256x256, four stages of 32      T=8192 N=4096 K=1024 GELU 112 -> 92, gate 90 (128x128: 101); T=4096 44 and 42
 //   2: 256x128, three stages of 64     T=8192 N=1024 K=4096 residual 77 -> 72 (128x128: 84), gradient 81 -> 65
 //   3: 128x128, two stages of 64       two workgroups per unit: T=2048 N=4096 K=1024 GELU 26, gate 23 (256x256: 36, 31)
-//   4: 128x64, three stages of 64      T=2048 N=1024 K=4096 27 (128x128: 46); T=4096 N=1024 K=1024 17 (20)
+//   4: 128x64, three stages of 64      T=2048 N=1024 K=4096 27 (128x128: 46); T=4096 N=1024 K=1024 17 (20); eight waves of
+//                                      32x32 where A is k-contiguous: two per SIMD wait for a k-tile's barrier and its reads
+//                                      in each other's time, which is more than the waves of 64x32 save in reads.  T=1800
+//                                      N=768 K=3072 forward 20.7 -> 19.4, gradient 20.0 -> 19.0, T=1400 N=1024 K=4096 25.4 ->
+//                                      24.5, 24.8 -> 24.1; with more tiles than units T=2560 39.9 -> 39.4, T=3000 N=768 27.5 -> 28.1
 //   5: 128x128, four stages of 32      weight gradients: both operands k-strided, so a 32-deep tile still reads whole
 //                                      256-byte rows, and three tiles are in flight in the LDS of two of 64
 //   6: 128x128, five stages of 64      one workgroup per unit: T=4096 N=1024 K=4096 67 -> 45
@@ -115,6 +119,13 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 //                                      beside the weight gradients' stream all of a layer's backward 1.5% slower)
 //  10: 32x32, one wave, four stages    half of it.  T=256 N=1024 K=4096 14.6 -> 12.8, 14.9 -> 12.3 (32x64: 12.9, 13.1);
 //      of 64                           T=256 N=256 K=512 5.7 -> 4.1 (4.4)
+//  12: 128x64, four stages of 64,      at most one workgroup for each unit.  T=2048 N=1024 K=4096 forward 25.5 (4) -> 24.0,
+//      eight waves                     gradient 24.7 -> 21.1; T=1400 24.5 -> 20.6, 24.1 -> 20.0 (with more tiles than units
+//                                      T=2560 39.4 -> 40.9, T=3000 N=768 28.1 -> 31.9).  Beside the weight gradients' stream 96 KB leave
+//                                      room for one of its workgroups instead of two halves: 4 layers of 768 with 2048 rows
+//                                      1977 us in four waves, 1990 with this tile there, 1951 with tile 4
+// (4 and 12, iterations against 4 in four waves: 4 layers of 768 with 600 rows a micro-batch 1875 -> 1831 us, 2 of 1024 with 512 and
+// heads of 128 646 -> 640, 3 of 640 with 1024 1334 -> 1312, 2 of 1024 with 510 647 -> 638.)
 // A stream restricted to part of the units (GemmArgs::units) moves the lines with it: four stages of 2048 rows on 64
 // units each, 36.7 -> 32.2 ms per iteration.  Where another stream's products run beside this one (GemmArgs::shared: the
 // data gradients beside the weight gradients) the tile with the whole LDS keeps them off its unit, and the four waves of tile
@@ -129,7 +140,7 @@ static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   auto tiles = [&](long m, long n) { return ((g.M + m - 1) / m) * ((g.N + n - 1) / n) * g.batch; };
   const long t128 = tiles(128, 128), U = g.units > 0 ? g.units : 256, most = 3 * U / 4;
   const bool bsum = (g.epi & EPI_BSUM) != 0;   // (offered for the weight-gradient layout only)
-  int tile = g.tile < 0 || g.tile > 10 ? 7 : g.tile;   // GemmArgs::tile names a configuration instead (tests, timing)
+  int tile = g.tile < 0 || g.tile == 11 || g.tile > 12 ? 7 : g.tile;   // GemmArgs::tile names a configuration instead (tests, timing)
   if (tile == 5 && !tt) tile = 3;
   if (tile == 8 && g.a_kstrided) tile = tt ? 5 : 3;   // (products whose rows are activations only)
   if (tile >= 9 && g.a_kstrided) tile = 7;
@@ -154,7 +165,8 @@ static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
     return g.K >= 2048 ? 6 : 8;
   }
   if (tiles(32, 64) <= U && !g.a_kstrided) return tiles(32, 32) <= U ? 10 : 9;
-  return g.K >= 2048 && tiles(64, 64) > U ? 4 : 7;
+  if (g.K >= 2048 && tiles(64, 64) > U) return !g.a_kstrided && !g.shared && tiles(128, 64) <= U ? 12 : 4;
+  return 7;
 }
 
 GemmArgs wgrad_args(const WgradGroup& w, int i) {

@@ -11,16 +11,17 @@ template <bool BKS, bool PACK>
 static hipError_t launch_rows(const GemmArgs& g, const GemmLaunch& l, LaunchMfma packed) {
   if (l.short_k)   // K segments that are no multiple of 64: the masked variants
     return l.tile == 3 ? launch_mfma<128, 128, 2, 4, 2, false, BKS, 64, PACK, false, true>(g, l, packed)
-                       : launch_mfma<128, 64, 2, 2, 3, false, BKS, 64, PACK, false, true>(g, l, packed);
+                       : launch_mfma<128, 64, 4, 2, 3, false, BKS, 64, PACK, false, true>(g, l, packed);
   switch (l.tile) {
     case 1: return launch_mfma<256, 256, 2, 4, 4, false, BKS, 32, PACK>(g, l, packed);
     case 2: return launch_mfma<256, 128, 4, 2, 3, false, BKS, 64, PACK>(g, l, packed);
     case 3: return launch_mfma<128, 128, 2, 4, 2, false, BKS, 64, PACK>(g, l, packed);
-    case 4: return launch_mfma<128, 64, 2, 2, 3, false, BKS, 64, PACK>(g, l, packed);
+    case 4: return launch_mfma<128, 64, 4, 2, 3, false, BKS, 64, PACK>(g, l, packed);
     case 6: return launch_mfma<128, 128, 2, 4, 5, false, BKS, 64, PACK>(g, l, packed);
     case 8: return launch_mfma<128, 128, 2, 2, 4, false, BKS, 32, PACK>(g, l, packed);
     case 9: return launch_mfma<32, 64, 1, 2, 4, false, BKS, 64, PACK>(g, l, packed);
     case 10: return launch_mfma<32, 32, 1, 1, 4, false, BKS, 64, PACK>(g, l, packed);
+    case 12: return launch_mfma<128, 64, 4, 2, 4, false, BKS, 64, PACK>(g, l, packed);
     case 7: return launch_mfma<64, 64, 2, 2, 4, false, BKS, 64, PACK>(g, l, packed);
     default: return hipErrorInvalidValue;
   }

@@ -145,6 +145,20 @@ def test_gemm_mfma_32_row_tiles(tile):
     gemm_case(B.DTYPE_BF16, 64, 64, 320, True, True, B.EPI_ACC32 | B.EPI_BSUM, expect_mfma=True, tile=tile)
 
 
+@pytest.mark.parametrize("tile", [4, 12])
+def test_gemm_mfma_128x64_tile_in_eight_waves(tile):
+    # K shorter than the ring, no multiple of it, longer, and (tile 4) short k-tiles; ragged edges; both layouts; segments,
+    # whole and padded turns; every epilogue that a forward product or a data gradient has
+    for K in (64, 192, 256, 320, 1088) + ((40, 104) if tile == 4 else ()):
+        gemm_case(B.DTYPE_BF16, 136, 72, K, False, True, B.EPI_BIAS | B.EPI_GELU, expect_mfma=True, tile=tile)
+        gemm_case(B.DTYPE_BF16, 264, 136, K, False, False, B.EPI_MUL, expect_mfma=True, tile=tile)
+        gemm_case(B.DTYPE_BF16, 128, 64, K, False, True, B.EPI_BIAS | B.EPI_ADD, expect_mfma=True, tile=tile)
+    for Ks in (64, 192, 256):
+        gemm_case(B.DTYPE_BF16, 200, 264, 3 * Ks, False, False, B.EPI_ADD, nseg=3, expect_mfma=True, tile=tile)
+    gemm_case(B.DTYPE_BF16, 328, 200, 192, False, False, B.EPI_ROWDOT | B.EPI_AUX32, expect_mfma=True, tile=tile)
+    gemm_case(B.DTYPE_BF16, 136, 264, 320, False, True, B.EPI_BIAS, batch=3, expect_mfma=True, tile=tile)
+
+
 @pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 6, 8])
 def test_gemm_row_sums_of_output_times_second_operand(tile):
     # ragged M and N (N not a multiple of 32: the last block is short), bf16 and fp32 second operand

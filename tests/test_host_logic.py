@@ -366,3 +366,13 @@ def test_the_plan_of_a_product_is_the_named_tile():
     with pytest.raises(B.StageError):
         B.dapple_gemm_plan(B.DTYPE_BF16, d)
     assert plan(600, 322, 320) is None   # a row of C that is no multiple of 4: the plain kernel
+
+
+def test_128x64_tiles_take_four_stages_where_a_unit_has_one():
+    # 65 k-tiles are 66 in a ring of three and 68 in one of four
+    K = 64 * 65
+    for M, N, want in ((2048, 1024, 68), (1296, 1024, 68), (2048 + 8, 1024, 66), (2560, 1024, 66)):
+        for bkS in (False, True):
+            assert plan(M, N, K, bkS=bkS, epi=B.EPI_ADD) == (128, 64, 64, want), (M, N, bkS)
+    assert plan(2048, 1024, K, akS=True)[:3] == (128, 64, 64)
+    assert plan(600, 320, K, tile=12) == (128, 64, 64, 68)
