@@ -126,7 +126,7 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 //                                      1977 us in four waves, 1990 with this tile there, 1951 with tile 4
 //  13: 128x64 in four waves, three     beside the weight gradients' stream where a layer's weight gradients put two workgroups on every unit
 //      stages of 64                    (1024 wide: 512 tiles of 128x128 and more): the eight waves then take from those what they gain,
-//                                      unless every unit has such a tile (2 layers with 2048 rows, heads of 128: 687 (4) and 693, the library before both 691).
+//                                      unless every unit has such a tile (2 layers with 2048 rows, heads of 128: 692 (4) and 697, each in turn with 695).
 //                                      2 layers of 1024 (F = 2048) with 1536 rows and the update, inputs changing from pass to pass,
 //                                      575 (4) -> 564, and against 4 the others of 1024 within 0.2%; narrower, 4 layers of 768
 //                                      with 600 rows a micro-batch 1828 (4) and 1842, 3 of 640 with 1024 1305 and 1316
