@@ -78,6 +78,10 @@ int dapple_gemm(int dtype, const dapple_gemm_desc* d, void* stream);
  * the rows and columns of a workgroup's tile, the depth of a k-tile, and the k-tiles each workgroup runs (a ring is filled
  * in whole turns: k-tiles of zeros are among them). */
 int dapple_gemm_plan(int dtype, const dapple_gemm_desc* d, int32_t* plan_out);
+/* What a stage would launch for this product: on a stream that may use `units` compute units (0 = all), with another
+ * stream's products beside it if `shared` is not 0 (a data gradient beside the weight gradients).  plan_out[0..3] as
+ * above, [4] the waves of a workgroup, [5] the stages of its ring. */
+int dapple_gemm_plan_beside(int dtype, const dapple_gemm_desc* d, int units, int shared, int32_t* plan_out);
 
 /* Attention of one layer.  q,k,v,ctx,dctx,dq,dk,dv: [b*s, H], head h in columns
  * [h*d, (h+1)*d), d = H / A.  lse [b,A,s] fp32: log2-domain logsumexp of the scaled

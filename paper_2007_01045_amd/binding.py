@@ -94,6 +94,7 @@ SYMBOLS = {
     "pipeline_timeline": (_i, [_vp, C.POINTER(C.c_double), C.POINTER(C.c_double), _i]),
     "dapple_gemm": (_i, [_i, C.POINTER(dapple_gemm_desc), _vp]),
     "dapple_gemm_plan": (_i, [_i, C.POINTER(dapple_gemm_desc), C.POINTER(C.c_int32)]),
+    "dapple_gemm_plan_beside": (_i, [_i, C.POINTER(dapple_gemm_desc), _i, _i, C.POINTER(C.c_int32)]),
     "dapple_attention_fwd": (_i, [_i, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _vp]),
     "dapple_attention_bwd": (_i, [_i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _vp]),
     "dapple_layernorm_fwd": (_i, [_i, _vp, _vp, _vp, _vp, _vp, _i, _i, _f, _vp]),
@@ -374,6 +375,16 @@ def dapple_gemm_plan(dtype, desc: dapple_gemm_desc):
     rc = load().dapple_gemm_plan(dtype, C.byref(desc), out)
     if rc < 0:
         raise StageError(rc, "dapple_gemm_plan rejected its arguments")
+    return tuple(out) if rc == 1 else None
+
+
+def dapple_gemm_plan_beside(dtype, desc: dapple_gemm_desc, units=0, shared=False):
+    """(rows, columns, depth, k-tiles, waves, stages) of the launch that a stage would make on a stream of `units` compute
+    units (0 = all), shared: beside another stream's products; None if another kernel takes it."""
+    out = (C.c_int32 * 6)()
+    rc = load().dapple_gemm_plan_beside(dtype, C.byref(desc), units, int(shared), out)
+    if rc < 0:
+        raise StageError(rc, "dapple_gemm_plan_beside rejected its arguments")
     return tuple(out) if rc == 1 else None
 
 

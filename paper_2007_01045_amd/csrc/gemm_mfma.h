@@ -971,7 +971,7 @@ static hipError_t launch_kernel(const GemmArgs& g, const GemmLaunch& l) {
   typedef GemmTile<BM, BN, WGM, WGN, NS, AKS, BKS, BK, KT, SEG> CFG;
   if (l.plan) {
     const int seg_tiles = (g.kseg_len + BK - 1) / BK, nseg = g.K / g.kseg_len;
-    *l.plan = GemmPlan{BM, BN, BK, PACK ? (nseg * seg_tiles + NS - 1) / NS * NS : nseg * ((seg_tiles + NS - 1) / NS * NS)};
+    *l.plan = GemmPlan{BM, BN, BK, PACK ? (nseg * seg_tiles + NS - 1) / NS * NS : nseg * ((seg_tiles + NS - 1) / NS * NS), CFG::NW, NS};
     return hipSuccess;
   }
   auto kern = gemm_mfma_kernel<BM, BN, WGM, WGN, NS, AKS, BKS, BK, CS, KT, SEG, PACK>;

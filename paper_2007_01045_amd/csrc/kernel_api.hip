@@ -78,15 +78,26 @@ int dapple_gemm(int dtype, const dapple_gemm_desc* d, void* stream) {
   return e == hipSuccess ? mfma : STAGE_E_DEVICE;
 }
 
-int dapple_gemm_plan(int dtype, const dapple_gemm_desc* d, int32_t* plan) {
+int dapple_gemm_plan_beside(int dtype, const dapple_gemm_desc* d, int units, int shared, int32_t* plan) {
   if (!plan) return STAGE_E_NULL;
+  if (units < 0) return STAGE_E_CONFIG;
   GemmArgs g{};
   const int mfma = gemm_args(dtype, d, g);
   if (mfma != 1) return mfma;
+  g.units = units; g.shared = shared != 0;
   GemmPlan p{};
   if (launch_gemm(DT_BF16, g, nullptr, &p) != hipSuccess) return STAGE_E_CONFIG;
-  plan[0] = p.rows; plan[1] = p.cols; plan[2] = p.depth; plan[3] = p.k_tiles;
+  plan[0] = p.rows; plan[1] = p.cols; plan[2] = p.depth; plan[3] = p.k_tiles; plan[4] = p.waves; plan[5] = p.stages;
   return 1;
+}
+
+int dapple_gemm_plan(int dtype, const dapple_gemm_desc* d, int32_t* plan) {
+  int32_t p[6];
+  if (!plan) return STAGE_E_NULL;
+  const int rc = dapple_gemm_plan_beside(dtype, d, 0, 0, p);
+  if (rc == 1)
+    for (int i = 0; i < 4; ++i) plan[i] = p[i];
+  return rc;
 }
 
 int dapple_attention_fwd(int dtype, const void* q, const void* k, const void* v, void* ctx, float* lse, int b,

@@ -68,10 +68,10 @@ struct GemmArgs {
   int rows1;
 };
 
-// a launch of the MFMA kernel: its tile, the depth of a k-tile, and the k-tiles a workgroup runs, those of zeros that fill
-// the ring's last turn among them
+// a launch of the MFMA kernel: its tile, the depth of a k-tile, the k-tiles a workgroup runs, those of zeros that fill
+// the ring's last turn among them, its waves and the stages of its ring
 struct GemmPlan {
-  int rows, cols, depth, k_tiles;
+  int rows, cols, depth, k_tiles, waves, stages;
 };
 // plan: filled in instead of launching anything (MFMA kernel only)
 hipError_t launch_gemm(Dtype dt, const GemmArgs& g, hipStream_t st, GemmPlan* plan = nullptr);

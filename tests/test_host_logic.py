@@ -306,14 +306,18 @@ def test_pipeline_host_functions_follow_the_oracle():
     assert B.pipeline_boundary_bytes(3, 4, 1000) == 2 * 2 * 4 * 1024
 
 
-def plan(M, N, Ks, nseg=1, akS=False, bkS=False, epi=0, tile=0):
+def plan(*a, **kw):
     """The launch dapple_gemm would make (host only: the pointers are never read)."""
+    return B.dapple_gemm_plan(B.DTYPE_BF16, gemm_desc(*a, **kw))
+
+
+def gemm_desc(M, N, Ks, nseg=1, akS=False, bkS=False, epi=0, tile=0):
     d = B.dapple_gemm_desc()
     d.A = d.B = d.C = d.aux = d.bsum = 1 << 20
     d.M, d.N, d.K, d.kseg_len, d.segA, d.segB = M, N, Ks * nseg, Ks, 8 * M * Ks, 8 * N * Ks
     d.lda, d.ldb, d.ldc, d.ldaux = (M if akS else Ks), (N if bkS else Ks), N, N
     d.a_kstrided, d.b_kstrided, d.epi, d.tile = int(akS), int(bkS), epi, tile
-    return B.dapple_gemm_plan(B.DTYPE_BF16, d)
+    return d
 
 
 @pytest.mark.parametrize("akS,bkS", [(False, False), (False, True), (True, False), (True, True)])
@@ -376,3 +380,53 @@ def test_128x64_tiles_take_four_stages_where_a_unit_has_one():
             assert plan(M, N, K, bkS=bkS, epi=B.EPI_ADD) == (128, 64, 64, want), (M, N, bkS)
     assert plan(2048, 1024, K, akS=True)[:3] == (128, 64, 64)
     assert plan(600, 320, K, tile=12) == (128, 64, 64, 68)
+
+
+def launch(M, N, K, units=0, shared=False, **kw):
+    """Rows and columns of the tile, waves and stages of the launch a stage would make."""
+    p = B.dapple_gemm_plan_beside(B.DTYPE_BF16, gemm_desc(M, N, K, **kw), units, shared)
+    return p[:2] + p[4:]
+
+
+def test_lines_of_the_128x64_tile_and_the_units_they_move_with():
+    # a data gradient and a forward product; U units, a width of 1024 on all of them
+    for bkS in (False, True):
+        for U, N, kw in ((256, 1024, {}), (256, 1024, {"units": 256}), (128, 512, {"units": 128}), (64, 512, {"units": 64})):
+            per = N // 64                          # tiles in a row of them
+            rows = lambda tiles, h: tiles // per * h   # the most rows that make so many tiles of height h
+            for K in (2048, 4096):
+                for shared in (False,):
+                    kw2 = dict(kw, bkS=bkS, shared=shared)
+                    assert launch(rows(U, 64), N, K, **kw2) == (64, 64, 4, 4)
+                    # from one tile of 64x64 more than units on: 128x64, in eight waves
+                    assert launch(rows(U, 64) + 8, N, K, **kw2)[:3] == (128, 64, 8)
+                    assert launch(rows(U, 64) + 8, N, K, **kw2)[3] == (3 if shared else 4)
+                    # four stages where a unit has at most one tile and no other stream's products run beside it
+                    assert launch(rows(U, 128) - 8, N, K, **kw2) == (128, 64, 8, 3 if shared else 4)
+                    assert launch(rows(U, 128) + 8, N, K, **kw2) == (128, 64, 8, 3)
+                    # up to three quarters of the units in 128x128 tiles
+                    t = 3 * U // 4 // (N // 128)
+                    assert launch(128 * (t - 1), N, K, **kw2) == (128, 64, 8, 3)
+                    assert launch(128 * t, N, K, **kw2)[:2] == (128, 128)
+            assert launch(rows(U, 64) + 8, N, 2048 - 64, bkS=bkS, **kw) == (64, 64, 4, 4)   # short sums
+    assert launch(1536, 1024, 4096, akS=True) == (128, 64, 4, 3)
+
+
+def test_k_segments_that_are_no_multiple_of_64_run_in_eight_waves():
+    for bkS in (False, True):
+        for shared in (False, True):
+            for M, N, K in ((64, 64, 200), (600, 768, 3000), (1536, 1024, 2040), (2560, 1024, 4008)):
+                assert launch(M, N, K, shared=shared, bkS=bkS) == (128, 64, 8, 3)
+                for tile in (4, 7, 12):
+                    assert launch(M, N, K, shared=shared, bkS=bkS, tile=tile) == (128, 64, 8, 3)
+            assert launch(3072, 1024, 4008, shared=shared, bkS=bkS) == (128, 128, 8, 2)
+
+
+def test_the_plan_beside_another_stream_checks_its_arguments():
+    d = gemm_desc(600, 320, 320)
+    for units, code in ((-1, B.STAGE_E_CONFIG),):
+        with pytest.raises(B.StageError) as e:
+            B.dapple_gemm_plan_beside(B.DTYPE_BF16, d, units)
+        assert e.value.code == code
+    assert B.dapple_gemm_plan_beside(B.DTYPE_BF16, d)[:4] == B.dapple_gemm_plan(B.DTYPE_BF16, d)
+    assert B.dapple_gemm_plan_beside(B.DTYPE_F32, d) is None
