@@ -68,8 +68,9 @@ typedef struct {
                    * 3: 128x128, two stages of 64; 4: 128x64, three stages of 64; 5: 128x128, four stages of 32
                    * (both operands k-strided; any other layout gets 3); 6: 128x128, five stages of 64; 7: 64x64,
                    * four stages of 64; 8: 128x128 in four waves, four stages of 32 (A k-contiguous; else 5 or 3);
-                   * 9: 32x64 and 10: 32x32, four stages of 64 (A k-contiguous; else 7); 12: 128x64 in four stages,
-                   * 13: tile 4 in four waves (A k-contiguous; else 7); any other number is 7 */
+                   * 9: 32x64 and 10: 32x32, four stages of 64 (A k-contiguous; else 7); 12: 128x64 in four stages
+                   * (A k-contiguous; else 7); any other number is 7.  K segments that are no multiple of 64
+                   * have 3 and 4 where an operand is k-contiguous (any other number: chosen between them) */
 } dapple_gemm_desc;
 
 /* Returns 1 if the bf16 MFMA kernel takes this problem, 0 if the plain kernel does. */

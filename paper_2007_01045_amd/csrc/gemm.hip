@@ -124,12 +124,12 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 //                                      T=2560 39.4 -> 40.9, T=3000 N=768 28.1 -> 31.9).  Beside the weight gradients' stream 96 KB leave
 //                                      room for one of its workgroups instead of two halves: 4 layers of 768 with 2048 rows
 //                                      1977 us in four waves, 1990 with this tile there, 1951 with tile 4
-//  13: 128x64 in four waves, three     beside the weight gradients' stream where a layer's weight gradients put two workgroups on every unit
-//      stages of 64                    (1024 wide: 512 tiles of 128x128 and more): the eight waves then take from those what they gain,
-//                                      unless every unit has such a tile (2 layers with 2048 rows, heads of 128: 692 (4) and 697, each in turn with 695).
-//                                      2 layers of 1024 (F = 2048) with 1536 rows and the update, inputs changing from pass to pass,
-//                                      575 (4) -> 564, and against 4 the others of 1024 within 0.2%; narrower, 4 layers of 768
-//                                      with 600 rows a micro-batch 1828 (4) and 1842, 3 of 640 with 1024 1305 and 1316
+//      (In four waves beside the weight gradients, 2 layers, a process each: 1024 wide, F = 4096, 1280 rows 542 (4) and 554,
+//      F = 2048 446 and 453, 768 wide, 6 x 600 rows 954 and 974, 640 wide 479 and 484; from 1700 rows on 1024 wide 0-1% faster
+//      (1904 rows 581 and 577; four micro-batches of 512, F = 4096, 638 and 645), 1088 to 1536 wide 0.6% faster to 1.3% slower,
+//      2048 wide 1.6% faster to 0.3% slower.  1024 wide, F = 2048, 2 x 768 rows is 2% faster with them, but not by the
+//      product: the chip clocks 2.20 GHz there with the eight waves and 2.31 with four, the kernels that are the same in both
+//      included, where 3 x 512 and 1 x 1280 rows have 2.32 with either.)
 // (4 and 12, iterations against 4 in four waves: 4 layers of 768 with 600 rows a micro-batch 1875 -> 1831 us, 2 of 1024 with 512 and
 // heads of 128 646 -> 640, 3 of 640 with 1024 1334 -> 1312, 2 of 1024 with 510 647 -> 638.)
 // A stream restricted to part of the units (GemmArgs::units) moves the lines with it: four stages of 2048 rows on 64
@@ -146,7 +146,7 @@ static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   auto tiles = [&](long m, long n) { return ((g.M + m - 1) / m) * ((g.N + n - 1) / n) * g.batch; };
   const long t128 = tiles(128, 128), U = g.units > 0 ? g.units : 256, most = 3 * U / 4;
   const bool bsum = (g.epi & EPI_BSUM) != 0;   // (offered for the weight-gradient layout only)
-  int tile = g.tile < 0 || g.tile == 11 || g.tile > 13 ? 7 : g.tile;   // GemmArgs::tile names a configuration instead (tests, timing)
+  int tile = g.tile < 0 || g.tile == 11 || g.tile > 12 ? 7 : g.tile;   // GemmArgs::tile names a configuration instead (tests, timing)
   if (tile == 5 && !tt) tile = 3;
   if (tile == 8 && g.a_kstrided) tile = tt ? 5 : 3;   // (products whose rows are activations only)
   if (tile >= 9 && g.a_kstrided) tile = 7;
@@ -171,11 +171,7 @@ static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
     return g.K >= 2048 ? 6 : 8;
   }
   if (tiles(32, 64) <= U && !g.a_kstrided) return tiles(32, 32) <= U ? 10 : 9;
-  if (g.K >= 2048 && tiles(64, 64) > U) {
-    if (g.a_kstrided) return 4;
-    if (g.shared) return g.N >= 1024 && tiles(128, 64) < U ? 13 : 4;
-    return tiles(128, 64) <= U ? 12 : 4;
-  }
+  if (g.K >= 2048 && tiles(64, 64) > U) return !g.a_kstrided && !g.shared && tiles(128, 64) <= U ? 12 : 4;
   return 7;
 }
 

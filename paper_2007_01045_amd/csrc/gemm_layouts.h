@@ -22,7 +22,6 @@ static hipError_t launch_rows(const GemmArgs& g, const GemmLaunch& l, LaunchMfma
     case 9: return launch_mfma<32, 64, 1, 2, 4, false, BKS, 64, PACK>(g, l, packed);
     case 10: return launch_mfma<32, 32, 1, 1, 4, false, BKS, 64, PACK>(g, l, packed);
     case 12: return launch_mfma<128, 64, 4, 2, 4, false, BKS, 64, PACK>(g, l, packed);
-    case 13: return launch_mfma<128, 64, 2, 2, 3, false, BKS, 64, PACK>(g, l, packed);
     case 7: return launch_mfma<64, 64, 2, 2, 4, false, BKS, 64, PACK>(g, l, packed);
     default: return hipErrorInvalidValue;
   }

@@ -58,7 +58,7 @@ struct GemmArgs {
   int k_valid;  // k-strided operands: rows k >= k_valid read as zero (K itself is padded)
   int m_valid, n_valid;  // rows of A / B that exist in memory (0 = M / N); rows beyond read as zero
   int epi;
-  int tile;  // 0 = automatic choice; 1..10, 12, 13 = a specific tile shape / ring depth (see choose_tile)
+  int tile;  // 0 = automatic choice; 1..10, 12 = a specific tile shape / ring depth (see choose_tile)
   // for the automatic choice: compute units the stream may use (0 = all 256); shared: another stream's products run
   // beside this one, so a workgroup should leave room on its unit
   int units;

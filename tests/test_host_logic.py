@@ -395,7 +395,7 @@ def test_lines_of_the_128x64_tile_and_the_units_they_move_with():
             per = N // 64                          # tiles in a row of them
             rows = lambda tiles, h: tiles // per * h   # the most rows that make so many tiles of height h
             for K in (2048, 4096):
-                for shared in (False,):
+                for shared in (False, True):
                     kw2 = dict(kw, bkS=bkS, shared=shared)
                     assert launch(rows(U, 64), N, K, **kw2) == (64, 64, 4, 4)
                     # from one tile of 64x64 more than units on: 128x64, in eight waves
