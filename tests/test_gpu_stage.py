@@ -460,6 +460,36 @@ def test_the_attention_backward_of_a_group_has_the_bits_of_its_tasks(s):
         B.pipeline_partition_stream_destroy(st)
 
 
+@pytest.mark.parametrize("s,stages", [(131, 4), (257, 3)])
+def test_the_added_layernorm_of_the_128x64_tiles_follows_the_oracle(s, stages):
+    """A stage on 64 units whose FFN products take the 128x64 tile in eight waves, in four stages and in three: the forward
+    one adds the LayerNorm of its fp32 residual; ragged rows."""
+    cfg = I.StageConfig(1, 256, 4, 2048, s, 8, 1, 1, "bf16")
+    d = B.dapple_gemm_desc()
+    d.A = d.B = d.C = d.aux = 1 << 20
+    d.M, d.N, d.K, d.lda, d.ldb, d.ldc, d.ldaux = cfg.tokens, cfg.hidden, cfg.ffn, cfg.ffn, cfg.hidden, cfg.hidden, cfg.hidden
+    d.b_kstrided, d.epi = 1, B.EPI_ADD | B.EPI_AUX32 | B.EPI_OUT32
+    assert B.dapple_gemm_plan_beside(B.DTYPE_BF16, d, 64)[:2] == (128, 64) and cfg.tokens % 128
+    assert B.dapple_gemm_plan_beside(B.DTYPE_BF16, d, 64)[4:] == (8, stages)
+    theta, mbs = make_inputs(cfg, SEED, 1)
+    st = B.pipeline_partition_stream_create(0, 4)
+    try:
+        r = B.StageRunner(c_config(cfg, 1), theta, stream_ptr=st)
+        try:
+            xs, dys = ([r.to_dev(mb[k].reshape(cfg.tokens, cfg.hidden)) for mb in mbs] for k in ("x", "dy"))
+            torch.cuda.synchronize()   # the stage runs on a stream of its own
+            ys, dxs = r.run(1, 1, B.ORDER_EARLY_BACKWARD, xs, dys)
+            B.stage_sync(r.h)
+            torch.cuda.synchronize()
+            got = dict(ys=[to_np(y) for y in ys], dxs=[to_np(d) for d in dxs], grads=r.grads.detach().cpu().numpy().copy())
+        finally:
+            r.close()
+    finally:
+        B.pipeline_partition_stream_destroy(st)
+    oracle, ref = run_oracle(cfg, theta, mbs, 1, 1)
+    compare(cfg, oracle, ref, got, TOL_BF16, 1)
+
+
 @pytest.mark.parametrize("kind", ["recompute", "first_stage", "last_stage", "gpipe_order", "side_stream", "recompute_lanes"])
 def test_graph_replays_of_the_other_stage_kinds(kind):
     """A captured iteration of a re-computing stage, a first stage (token ids in), a last stage (losses out), of

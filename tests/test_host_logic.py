@@ -323,7 +323,7 @@ def gemm_desc(M, N, Ks, nseg=1, akS=False, bkS=False, epi=0, tile=0):
 @pytest.mark.parametrize("akS,bkS", [(False, False), (False, True), (True, False), (True, True)])
 def test_segments_of_a_product_share_the_turns_of_a_ring(akS, bkS):
     # tiles of which a unit holds one workgroup: less than one turn of k-tiles of zeros in all, whatever a segment's length
-    for tile, ring in ((1, 4), (2, 3), (6, 5)):
+    for tile, ring in ((1, 4), (2, 3), (6, 5)) + (() if akS else ((12, 4),)):
         for Ks in range(64, 64 * 19, 64):
             for nseg in (1, 2, 3, 4):
                 rows, cols, depth, tiles = plan(600, 320, Ks, nseg, akS, bkS, B.EPI_ADD, tile)
@@ -352,19 +352,20 @@ def test_every_layout_has_the_tile_that_is_chosen_for_it():
             assert plan(M, N, K, akS=True)[:3] == (128, 128, 64), (M, N, K)
     # any product and any named tile has a launch (one that is not in the list: the 64x64 tile)
     for akS, bkS in ((False, False), (False, True), (True, False), (True, True)):
-        for tile in range(-1, 13):
+        for tile in range(-1, 15):
             for M, N in ((64, 64), (600, 320), (1024, 1024), (2048, 1536), (8192, 1024), (8192, 4096)):
                 for K in (200, 512, 2048):
                     assert plan(M, N, K, akS=akS, bkS=bkS, tile=tile) is not None
-        assert plan(600, 320, 320, akS=akS, bkS=bkS, tile=11)[:3] == (64, 64, 64)
+        for tile in (11, 13, 14):
+            assert plan(600, 320, 320, akS=akS, bkS=bkS, tile=tile)[:3] == (64, 64, 64)
     for epi in (B.EPI_ACC32, B.EPI_ACC32 | B.EPI_BSUM):
-        for tile in range(-1, 13):
+        for tile in range(-1, 15):
             assert plan(600, 320, 320, akS=True, bkS=True, epi=epi, tile=tile) is not None
 
 
 def test_the_plan_of_a_product_is_the_named_tile():
     for tile, shape in {1: (256, 256, 32), 2: (256, 128, 64), 3: (128, 128, 64), 4: (128, 64, 64), 6: (128, 128, 64),
-                        7: (64, 64, 64), 8: (128, 128, 32), 9: (32, 64, 64), 10: (32, 32, 64)}.items():
+                        7: (64, 64, 64), 8: (128, 128, 32), 9: (32, 64, 64), 10: (32, 32, 64), 12: (128, 64, 64)}.items():
         assert plan(600, 320, 320, tile=tile)[:3] == shape
     d = B.dapple_gemm_desc()
     with pytest.raises(B.StageError):
