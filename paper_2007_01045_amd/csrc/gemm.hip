@@ -106,6 +106,8 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 //                                      in each other's time, which is more than the waves of 64x32 save in reads.  T=1800
 //                                      N=768 K=3072 forward 20.7 -> 19.4, gradient 20.0 -> 19.0, T=1400 N=1024 K=4096 25.4 ->
 //                                      24.5, 24.8 -> 24.1; with more tiles than units T=2560 39.9 -> 39.4, T=3000 N=768 27.5 -> 28.1
+//                                      (cold weights 33.3 and 34.7), which iterations do not show: forward products in four waves
+//                                      there 0-0.3% slower 512 to 896 wide, 0.2% faster 1024 wide
 //   5: 128x128, four stages of 32      weight gradients: both operands k-strided, so a 32-deep tile still reads whole
 //                                      256-byte rows, and three tiles are in flight in the LDS of two of 64
 //   6: 128x128, five stages of 64      one workgroup per unit: T=4096 N=1024 K=4096 67 -> 45
@@ -130,6 +132,8 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 //      2048 wide 1.6% faster to 0.3% slower.  1024 wide, F = 2048, 2 x 768 rows is 2% faster with them, but not by the
 //      product: the chip clocks 2.20 GHz there with the eight waves and 2.31 with four, the kernels that are the same in both
 //      included, where 3 x 512 and 1 x 1280 rows have 2.32 with either.)
+//      (Which of 4 and 12 forward products take beside the lanes of re-computation, which are not `shared`, is all one: within 0.3%
+//      over 40 stages of 3 layers 512 to 1024 wide, 1264 to 5464 rows.)
 // (4 and 12, iterations against 4 in four waves: 4 layers of 768 with 600 rows a micro-batch 1875 -> 1831 us, 2 of 1024 with 512 and
 // heads of 128 646 -> 640, 3 of 640 with 1024 1334 -> 1312, 2 of 1024 with 510 647 -> 638.)
 // A stream restricted to part of the units (GemmArgs::units) moves the lines with it: four stages of 2048 rows on 64
@@ -141,6 +145,10 @@ bool gemm_uses_mfma(Dtype dt, const GemmArgs& g) {
 // 5120 rows 6.13 and 6.19; 768, 4096 rows 6.00 and 6.01; 1024 wide, 1024 rows 5.49 and 5.54.
 // (The lines between those points -- K >= 2048, N <= 1024, three quarters of the units -- were read off widths of 256,
 // 1024 and 2048 and 512 to 8192 rows.)
+// K segments that are no multiple of 64 have the 128x128 tile in two stages and the 128x64 one in three, both of eight waves.
+// The latter against four waves, 2 layers: 256 wide, F = 1000, 2 x 256 rows 336 and 347, 768 wide, F = 3000, 3 x 600 rows 1016 and
+// 1029, 1024 wide, F = 4008, 512 rows 887 and 896, 1536 rows 1208 and 1218; the same with other streams beside it.  (2560 rows
+// of 1024 1751 and 1727, F = 2040 1327 and 1318, F = 1000 1106 and 1111; 2600 of 896 1724 and 1727, 3096 1962 and 1956.)
 // No bit of a result depends on the choice: an output element is one wave's sum in ascending k whatever the tile.
 static int choose_tile(const GemmArgs& g, bool tt, bool short_k) {
   auto tiles = [&](long m, long n) { return ((g.M + m - 1) / m) * ((g.N + n - 1) / n) * g.batch; };

@@ -59,8 +59,8 @@ struct GemmArgs {
   int m_valid, n_valid;  // rows of A / B that exist in memory (0 = M / N); rows beyond read as zero
   int epi;
   int tile;  // 0 = automatic choice; 1..10, 12 = a specific tile shape / ring depth (see choose_tile)
-  // for the automatic choice: compute units the stream may use (0 = all 256); shared: another stream's products run
-  // beside this one, so a workgroup should leave room on its unit
+  // for the automatic choice: compute units the stream may use (0 = all 256); shared: a data gradient beside the stream of
+  // the weight gradients, so a workgroup should leave room on its unit
   int units;
   bool shared;
   // fp32: rows of one micro-batch, where M holds those of several (0 = M).  The fp32 kernels add in one of two orders,
